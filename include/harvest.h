@@ -143,7 +143,7 @@ typedef struct harvest_config {
     uint32_t gather_wg_per_cu;      /* tuning: cap the HBM-tier gather at this many workgroups per CU (they then loop
                                        over tiles, and take a request's planes one after the other); 0 = default, one workgroup
                                        per tile of gather_threads * 16 bytes */
-    uint32_t host_wgs;              /* tuning: persistent workgroups of the host-tier (PCIe) gather; 0 = default (24) */
+    uint32_t host_wgs;              /* tuning: 8 KiB of host-tier (PCIe) reads in flight per unit; 0 = default (24) */
     uint32_t shared_granule;        /* segment granule of the shared cache pool in bytes: a power of two >= 256;
                                        0 = 4096 */
     uint32_t small_fetch_cells;     /* tuning: harvest_fetch_kv takes its one-kernel form for block tables of up to this

@@ -593,6 +593,7 @@ uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t
 
 // one workgroup per tile up to here; beyond, the kernels loop.  Kept below 2^32 threads per launch dimension.
 constexpr uint32_t MAX_GRID = 0xFFFFFFFFu / WG;
+constexpr uint32_t MAX_GRID_Y = 65535;
 
 uint32_t grid_for(uint64_t n_tiles, uint32_t max_grid)
 {
@@ -714,12 +715,11 @@ hipEvent_t prof_event(harvest_ctx *ctx)
     return e;
 }
 
-// Launches the HBM-tier gather on the caller's stream and the host-tier gather on the side stream, joined back.
+// Launches the gathers of both tiers on the caller's stream.
 // max_req bounds the number of requests either list can hold; dst_base: where plane p of the working layout starts.
 // n_rep > 1 gathers n_rep consecutive layers from the same two lists (they name slots, and an object has the same slot
 // in every layer): repetition r reads layer_stride(tier) * r further into every pool and writes dst_step * r further
-// into the destination.  The host-tier gathers of all repetitions queue up behind each other on one stream, so
-// the link never waits for a join between layers.
+// into the destination.
 int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, const Lists &lists, uint64_t max_req,
                    uint64_t dst_base0, uint64_t dst_base1, const HmArgs *hm = nullptr, uint32_t n_rep = 1,
                    uint64_t dst_step = 0, int64_t layer_delta = 0, bool repeat = false)
@@ -728,12 +728,23 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     // layer strides to every pool base retargets them.  repeat: these requests have been counted for the lists' first
     // use only - add them to the running totals again.
     const ClassDev cd = class_dev(c);
+    const uint32_t planes = c.cfg.n_planes;
+    // the head-major gather runs 256 threads per workgroup, the token-major one gather_threads; a tile is 16 bytes per thread
+    const uint32_t nthr = hm ? (uint32_t)WG : ctx->gather_threads;
+    const uint32_t tpc = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16);
     GatherArgs ga{};
+    for (uint32_t p = 0; p < 2; ++p) {
+        ga.src_base[T_HOST][p] = c.host_dev[p];
+        ga.src_base[T_CACHE][p] = c.cache_base(p);
+        ga.src_base[T_LOCAL][p] = (uint64_t)c.cfg.d_local_pool[p];
+        for (int t = 0; t < 3; ++t) ga.src_base[t][p] += (uint64_t)layer_delta * cd.layer_stride[t];   // "negative" deltas wrap back
+    }
+    for (int t = 0; t < 3; ++t) ga.layer_stride[t] = cd.layer_stride[t];
+    ga.dst_base[0] = dst_base0; ga.dst_base[1] = dst_base1;
+    ga.dst_step = dst_step;
     ga.chunk_bytes = c.cfg.chunk_bytes;
-    // the head-major gather and the host tier walk 4 KiB tiles, the token-major HBM-tier gather gather_threads * 16 bytes
-    const uint32_t tile_hbm = hm ? TILE_4K : ctx->gather_threads * 16;
-    uint32_t tpc_hbm = tiles_per_chunk(c.cfg.chunk_bytes, tile_hbm);
-    uint32_t planes = c.cfg.n_planes;
+    ga.tiles_per_chunk = tpc;
+    ga.pages_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16 * HOST_LOADS);
     ga.n_planes = planes;
     // timing events cannot be recorded into a graph, and taking one from the pool may allocate
     const bool profile = ctx->profile && !ss->fixed && !is_capturing(ss->s);
@@ -741,109 +752,95 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     // one pass over both planes of each request where the cache tier keeps them side by side (see gather; not the
     // head-major gather, see gather_hm)
     const bool fold = !hm && c.cache_planes_adjacent() && !ctx->gather_grid;
-    // Grid of the HBM-tier gather: about one workgroup per tile.  The request count lives on the device, so the grid is
+    // Grid of the HBM tier: about one workgroup per tile.  The request count lives on the device, so the grid is
     // sized from what the previous gather of this class on this stream reported, never below a floor that still fills the
-    // chip, never above the bound; the kernel loops where the grid is short, so any size is correct.  The guess is
-    // biased low on purpose: surplus workgroups at the end of the grid cost time (6 % of them 1 %, 23 % of them 3.5 %),
-    // a grid 10 to 25 % short costs nothing (the first workgroups take a second tile while the rest still run).
-    uint64_t max_tiles = max_req * tpc_hbm;
+    // chip, never above the bound; the kernel loops where the grid is short, so any size is correct.  For experts, whose
+    // number changes from layer to layer, the guess is biased low on purpose: surplus workgroups at the end of the grid cost
+    // time (6 % of them 1 %, 23 % of them 3.5 %), a grid 10 to 25 % short costs less (the first workgroups take a
+    // second tile while the rest still run).  A KV table grows by a block now and then: its last count is the best guess
+    // (15 000 blocks with the planes side by side: 302.8 us on an exact grid, 307.2 us on one 1/8 short).
+    uint64_t max_tiles = max_req * tpc;
     uint64_t want = max_tiles;
-    // Which of the two gathers stays on the caller's stream: crossing to the side stream and back costs some 15 us each
-    // way, so the one that takes longer - by the same report: host bytes at PCIe rate against HBM bytes at HBM rate,
-    // about 1 : 48 per request - stays, and the short one takes the detour inside the long one's shadow.
-    // And whether there is a detour at all: when even the longer of the two is expected to be over in less time than the
-    // two crossings take (a small fetch: a few dozen blocks from the host, or some tens of MiB from HBM), both run on the
-    // caller's stream one after the other, and so they do when the class has no host tier.
-    bool host_stays = host_tier, serial = !host_tier || !ss->side;
+    bool host_stays = host_tier, serial = !host_tier;
     if (ss->feedback_valid[cls]) {
         uint64_t seen = *(volatile uint32_t *)&ss->h_feedback[cls];
         uint64_t seen_host = *(volatile uint32_t *)&ss->h_feedback[HARVEST_N_CLASSES + cls];
-        // (the head-major kernel, whose tiles cost more address arithmetic, does best on an exact grid: +0.8 %)
-        uint64_t guess = std::max<uint64_t>(1, hm ? seen : seen - seen / 8) * tpc_hbm;
+        uint64_t guess = std::max<uint64_t>(1, cls == HARVEST_KV ? seen : seen - seen / 8) * tpc;
         want = std::min(max_tiles, std::max<uint64_t>(guess, 16ull * ctx->n_cu));
+        // profiled fetches only, see below
         host_stays = host_tier && seen_host * 48 > seen;
         double bytes = (double)planes * c.cfg.chunk_bytes * n_rep;
         double us_hbm = 2.0 * seen * bytes / 6.0e6, us_host = seen_host * bytes / 57.0e3;     // at 6 TB/s and 57 GB/s
-        // ... or when the shorter one is next to nothing (a fetch served by one tier alone): waiting for the other
-        // stream costs the caller's stream more than running a few microseconds of kernel itself
         serial = serial || std::max(us_hbm, us_host) < 35.0 || std::min(us_hbm, us_host) < 8.0;
     }
-    if (!serial) {
-        HIP_TRY(hipEventRecord(ss->fork, ss->s));
-        HIP_TRY(hipStreamWaitEvent(ss->side, ss->fork, 0));
-    }
-    hipStream_t s_host = (host_stays || serial) ? ss->s : ss->side, s_hbm = (host_stays && !serial) ? ss->side : ss->s;
-    uint32_t grid = ctx->gather_grid ? grid_for(want, ctx->gather_grid) : grid_for(want, MAX_GRID);
-    for (uint32_t r = 0; r < n_rep; ++r) {
-        for (uint32_t p = 0; p < 2; ++p) {
-            const uint64_t k = (uint64_t)((int64_t)r + layer_delta);          // may be "negative": the sums wrap back
-            ga.src_base[T_HOST][p] = c.host_dev[p] + k * cd.layer_stride[T_HOST];
-            ga.src_base[T_CACHE][p] = c.cache_base(p) + k * cd.layer_stride[T_CACHE];
-            ga.src_base[T_LOCAL][p] = (uint64_t)c.cfg.d_local_pool[p] + k * cd.layer_stride[T_LOCAL];
-        }
-        ga.dst_base[0] = dst_base0 + r * dst_step;
-        ga.dst_base[1] = dst_base1 + r * dst_step;
-        // With profiling on, the events are attached to the dispatch itself and read the kernel's own begin and end.
-        hipEvent_t pa = nullptr, pb = nullptr, pc = nullptr, pd = nullptr;
-        if (profile) { pa = prof_event(ctx); pb = prof_event(ctx); }
-        if (profile && host_tier) { pc = prof_event(ctx); pd = prof_event(ctx); }
-        if (host_tier) {             // first, so that the long PCIe transfer starts before the CUs fill up
-            ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, TILE_4K);
-            const Rec *recs = (const Rec *)lists.host;
-            const uint32_t *n_req = (const uint32_t *)(lists.cnt + C_HOST_REQ);
-            uint32_t *fb = ss->d_feedback + HARVEST_N_CLASSES + cls;
-            dim3 g(ctx->host_grid);
-            if (hm) {
-                auto kernel = planes == 2 ? gather_hm_host<2> : gather_hm_host<1>;
-                if (pc)
-                    hipExtLaunchKernelGGL(kernel, g, dim3(WG), 0, s_host, pc, pd, 0, recs, n_req, ga, *hm, fb, ctx->d_lease);
-                else
-                    hipLaunchKernelGGL(kernel, g, dim3(WG), 0, s_host, recs, n_req, ga, *hm, fb, ctx->d_lease);
-            } else {
-                auto kernel = planes == 2 ? gather_host<2> : gather_host<1>;
-                if (pc)
-                    hipExtLaunchKernelGGL(kernel, g, dim3(WG), 0, s_host, pc, pd, 0, recs, n_req, ga, fb, ctx->d_lease);
-                else
-                    hipLaunchKernelGGL(kernel, g, dim3(WG), 0, s_host, recs, n_req, ga, fb, ctx->d_lease);
-            }
-            HIP_TRY(hipGetLastError());
-        }
-        ga.tiles_per_chunk = tpc_hbm;
-        const Rec *recs = (const Rec *)lists.hbm;
-        const uint32_t *n_req = (const uint32_t *)(lists.cnt + C_HBM_REQ);
+    // host_grid counts 8 KiB of loads in flight: 256 threads with 2 loads each (head-major), 128 threads with HOST_LOADS
+    const uint32_t host_wgs = !host_tier ? 0
+        : (uint32_t)std::min<uint64_t>(hm ? ctx->host_grid : std::max<uint64_t>(1, (uint64_t)ctx->host_grid * 128 / nthr), MAX_GRID / 2);
+    const uint32_t max_wgs = (MAX_GRID - host_wgs) / (fold ? 1 : planes);
+    const uint32_t hbm_wgs = grid_for(fold ? want * planes : want, ctx->gather_grid ? std::min(ctx->gather_grid, max_wgs) : max_wgs);
+    GatherBooks books{};
+    books.fb_hbm = ss->d_feedback + cls;
+    books.fb_host = ss->d_feedback + HARVEST_N_CLASSES + cls;
+    books.lease = ctx->d_lease;
+    books.totals = repeat ? ctx->d_totals + cls * C_N : nullptr;
+    auto launch = [&](uint32_t n_host, uint32_t n_hbm, hipStream_t s, hipEvent_t begin, hipEvent_t end) -> int {
+        ga.n_host = n_host;
+        ga.hbm_wgs = n_hbm;
+        const dim3 g(n_host + n_hbm * (fold ? 1 : planes), n_hbm ? ga.n_rep : 1);
+        const Rec *l_hbm = lists.hbm, *l_host = lists.host;
+        const uint32_t *cnt = lists.cnt;
         if (hm) {
-            auto kernel = gather_hm<1, true>;
-            const dim3 g(grid, planes);
-            if (pa)
-                hipExtLaunchKernelGGL(kernel, g, dim3(WG), 0, s_hbm, pa, pb, 0, recs, n_req, ga, *hm, ss->d_feedback + cls);
-            else
-                hipLaunchKernelGGL(kernel, g, dim3(WG), 0, s_hbm, recs, n_req, ga, *hm, ss->d_feedback + cls);
+            auto kernel = planes == 2 ? gather_hm<2> : gather_hm<1>;
+            if (begin) hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, l_host, cnt, ga, *hm, books);
+            else hipLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, l_hbm, l_host, cnt, ga, *hm, books);
         } else {
-            const uint32_t nthr = ctx->gather_threads;
-            auto kernel = fold ? (nthr == 64 ? gather<64, true, true> : (nthr == 128 ? gather<128, true, true> : gather<256, true, true>))
-                               : (nthr == 64 ? gather<64, true, false> : (nthr == 128 ? gather<128, true, false> : gather<256, true, false>));
-            const dim3 g = fold ? dim3(grid_for(want * planes, MAX_GRID)) : dim3(grid, planes);
-            if (pa)
-                hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s_hbm, pa, pb, 0, recs, n_req, ga, ss->d_feedback + cls);
-            else
-                hipLaunchKernelGGL(kernel, g, dim3(nthr), 0, s_hbm, recs, n_req, ga, ss->d_feedback + cls);
+            auto pick = [&](auto k64, auto k128, auto k256) { return nthr == 64 ? k64 : (nthr == 128 ? k128 : k256); };
+            auto kernel = fold ? pick(gather<64, 2, true>, gather<128, 2, true>, gather<256, 2, true>)
+                        : planes == 2 ? pick(gather<64, 2, false>, gather<128, 2, false>, gather<256, 2, false>)
+                                      : pick(gather<64, 1, false>, gather<128, 1, false>, gather<256, 1, false>);
+            if (begin) hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, l_host, cnt, ga, books);
+            else hipLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, l_hbm, l_host, cnt, ga, books);
         }
         HIP_TRY(hipGetLastError());
-        if (profile) {
-            ctx->prof.push_back({ pa, pb, 0 });
-            if (host_tier) ctx->prof.push_back({ pc, pd, 1 });
+        return HARVEST_OK;
+    };
+    int rc;
+    for (uint32_t first = 0; first < n_rep; first += ga.n_rep) {          // layers are the grid's y dimension
+        ga.n_rep = std::min(n_rep - first, MAX_GRID_Y);
+        if (first) {
+            for (int t = 0; t < 3; ++t)
+                for (uint32_t p = 0; p < 2; ++p) ga.src_base[t][p] += (uint64_t)MAX_GRID_Y * ga.layer_stride[t];
+            for (uint32_t p = 0; p < 2; ++p) ga.dst_base[p] += (uint64_t)MAX_GRID_Y * dst_step;
+            books.totals = nullptr;
+        }
+        if (!profile) {
+            if ((rc = launch(host_wgs, hbm_wgs, ss->s, nullptr, nullptr))) return rc;
+            continue;
+        }
+        // Timed by tier: the two halves as launches of their own, whose events (attached to the dispatches) read the
+        // kernels' own begin and end.  Crossing to the side stream and back costs some 15 us each way, so the one that is
+        // expected to take longer - host bytes at PCIe rate against HBM bytes at HBM rate, about 1 : 48 per request - stays on
+        // the caller's stream and the short one takes the detour inside its shadow; no detour when even the longer one is
+        // over in less than the crossings take or the shorter one is next to nothing.
+        hipStream_t s_host = (host_stays || serial) ? ss->s : ss->side, s_hbm = (host_stays && !serial) ? ss->side : ss->s;
+        if (!serial) {
+            HIP_TRY(hipEventRecord(ss->fork, ss->s));
+            HIP_TRY(hipStreamWaitEvent(ss->side, ss->fork, 0));
+        }
+        if (host_tier) {             // first, so that the long PCIe transfer starts before the CUs fill up
+            hipEvent_t a = prof_event(ctx), b = prof_event(ctx);
+            if ((rc = launch(host_wgs, 0, s_host, a, b))) return rc;
+            ctx->prof.push_back({ a, b, 1 });
+        }
+        hipEvent_t a = prof_event(ctx), b = prof_event(ctx);
+        if ((rc = launch(0, hbm_wgs, s_hbm, a, b))) return rc;
+        ctx->prof.push_back({ a, b, 0 });
+        if (!serial) {
+            HIP_TRY(hipEventRecord(ss->join, ss->side));
+            HIP_TRY(hipStreamWaitEvent(ss->s, ss->join, 0));
         }
     }
     ss->feedback_valid[cls] = true;
-    if (repeat) {                                   // off the longer gather's stream where there are two
-        hipLaunchKernelGGL(repeat_totals, dim3(1), dim3(64), 0, serial ? ss->s : ss->side, (const uint32_t *)lists.cnt,
-                           ctx->d_totals + cls * C_N);
-        HIP_TRY(hipGetLastError());
-    }
-    if (!serial) {
-        HIP_TRY(hipEventRecord(ss->join, ss->side));
-        HIP_TRY(hipStreamWaitEvent(ss->s, ss->join, 0));
-    }
     return mark_last(ctx, ss);
 }
 
@@ -862,7 +859,7 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
     HIP_TRY(hipGetDeviceProperties(&prop, cfg->device));
     ctx->n_cu = prop.multiProcessorCount;
     ctx->gather_grid = cfg->gather_wg_per_cu * ctx->n_cu;         // 0: one workgroup per tile
-    ctx->host_grid = cfg->host_wgs ? cfg->host_wgs : 24;
+    ctx->host_grid = cfg->host_wgs ? cfg->host_wgs : 24;          // 192 KiB of reads in flight, see host_tier
     ctx->gather_threads = cfg->gather_threads ? cfg->gather_threads : HBM_WG;
     ctx->ctl_grid = 8 * ctx->n_cu;                 // HBM-bound fills
     // Copies that cross PCIe outside a fetch (place, write-back): persistent workgroups with one 32 KiB tile in flight

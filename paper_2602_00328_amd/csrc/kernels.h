@@ -13,17 +13,16 @@
 //   resolve_experts          : the same for expert weights (Section 4.3: residency map) - one workgroup forms the
 //                              distinct set of routed experts and walks it in ascending order (very large batches of
 //                              routing ids are marked by many workgroups first: mark_experts).
-//   gather                   : the copy itself.  HBM tier: one wavefront per workgroup and 1 KiB tile, one 16-byte
-//                              non-temporal load and store per thread, as many workgroups as tiles; plane K before
-//                              plane V, or - where the cache tier keeps them side by side - both planes of a request
+//   gather                   : the copy itself, both tiers in one launch.  HBM tier: one wavefront per workgroup and 1 KiB
+//                              tile, one 16-byte non-temporal load and store per thread, as many workgroups as tiles; plane K
+//                              before plane V, or - where the cache tier keeps them side by side - both planes of a request
 //                              in one pass (measured on MI355X: short workgroups beat deep unrolling and persistent
 //                              grids by ~15%, one-wavefront workgroups beat four-wavefront ones by 2-5%, non-temporal
-//                              accesses are worth ~11%, 64 KiB source runs 4-5% over 32 KiB ones).
-//   gather_host              : host tier - a couple of dozen persistent workgroups with two loads in flight per
-//                              thread over 4 KiB sub-tiles: enough compute units to keep the PCIe link full, and no
-//                              more host reads in flight than the link absorbs, because the rest would only stand in
-//                              the HBM tier's way.
-//   gather_hm, gather_hm_host: the same two into a head-major working layout.
+//                              accesses are worth ~11%, 64 KiB source runs 4-5% over 32 KiB ones).  Host tier: the
+//                              launch's first workgroups, a few dozen wavefronts that stay, with four loads in
+//                              flight per thread: enough compute units to keep the PCIe link full, and no more host reads
+//                              in flight than the link absorbs, because the rest would only stand in the HBM tier's way.
+//   gather_hm                : the same into a head-major working layout.
 //   copy_items, copy_items2, fill_items, dir_write : host-built lists - placement, write-back (one source, up to two
 //                              destinations), slot poisoning after revocation, directory publication; the _hbm forms
 //                              of the first three serve copies that stay inside HBM.  The forms that cross PCIe are a
@@ -43,7 +42,7 @@ constexpr uint32_t TILE_4K = WG * 16;           // 4 KiB: one 16-byte access per
 constexpr int HBM_WG = 64;                      // the HBM-tier gather runs one wavefront per workgroup (see gather)
 constexpr int UNROLL_HOST = 8;
 constexpr uint32_t TILE_HOST = WG * 16 * UNROLL_HOST;   // 32 KiB tiles of the host-built copy lists (place, write-back)
-constexpr int HOST_LOADS = 2;                   // 16-byte loads a thread of the host-tier gather keeps in flight
+constexpr int HOST_LOADS = 4;                   // 16-byte loads a thread of the host-tier gather keeps in flight
 
 // directory entry: [1:0] tier, [31:2] slot in that tier (host slot for HOST), [63:32] generation
 constexpr uint64_t TIER_MASK = 3;
@@ -88,6 +87,21 @@ struct GatherArgs {
     uint64_t chunk_bytes;
     uint32_t tiles_per_chunk;
     uint32_t n_planes;
+    // consecutive layers gathered from the same lists (an object has the same slot in every layer): repetition r reads
+    // layer_stride[tier] * r further and writes dst_step * r further
+    uint64_t layer_stride[3];
+    uint64_t dst_step;
+    uint32_t n_rep;
+    // the launch's first n_host workgroups serve the host tier, the next hbm_wgs (per plane, unless the planes are folded)
+    // the HBM tier; either may be 0
+    uint32_t n_host, hbm_wgs;
+    uint32_t pages_per_chunk;            // of the host tier, see host_tier
+};
+// What a gather reports besides the bytes; every pointer may be null.
+struct GatherBooks {
+    uint32_t *fb_hbm, *fb_host;          // pinned words that receive the list lengths: hints for the next launch's grid
+    unsigned long long *lease;           // see link_announce
+    unsigned long long *totals;          // running totals, to which a fetch repeated from older lists adds their counters
 };
 
 __device__ inline uint32_t lane_id() { return __lane_id(); }
@@ -109,6 +123,10 @@ __device__ inline uint64_t src_base_of(const GatherArgs &a, uint32_t tier, uint3
     uint64_t k = plane ? a.src_base[T_CACHE][1] : a.src_base[T_CACHE][0];
     uint64_t l = plane ? a.src_base[T_LOCAL][1] : a.src_base[T_LOCAL][0];
     return tier == T_HOST ? h : (tier == T_CACHE ? k : l);
+}
+__device__ inline uint64_t layer_stride_of(const GatherArgs &a, uint32_t tier)
+{
+    return tier == T_HOST ? a.layer_stride[T_HOST] : (tier == T_CACHE ? a.layer_stride[T_CACHE] : a.layer_stride[T_LOCAL]);
 }
 
 // Exclusive rank of this lane among the lanes of its wavefront for which pred holds, and the wave total.
@@ -492,54 +510,6 @@ __device__ inline void copy_tile(uint64_t src, uint64_t dst, uint64_t len, uint3
     }
 }
 
-// Tiles of the chunks named by a request list whose length lives on the device.  blockIdx.y is the plane, so a
-// two-plane class is gathered plane after plane.  The grid's x size is free: with one workgroup per tile the loop body
-// runs once; a smaller grid loops.  `feedback`, when given, is a word of pinned host memory that receives the list
-// length: the host sizes the next launch from it, because workgroups that find no tile are not free (about 0.2 ns
-// each on MI355X) while a grid somewhat short of the tile count is.
-//
-// NTHR threads per workgroup, one 16-byte load and store each: a tile is NTHR * 16 bytes.  Measured on MI355X
-// (768 MiB gathered from scattered runs, read+write): one-wavefront workgroups (1 KiB tiles) move 6.29 TB/s from 32 KiB
-// runs and 6.57 TB/s from 64 KiB runs, 256-thread workgroups 6.12 and 6.40 - a wavefront that is its own workgroup
-// frees its slot the moment it is done instead of waiting for three others.
-//
-// FOLD: the planes of a request are taken in one pass - tile numbers run through plane 0, then plane 1, of each
-// request - instead of plane after plane over the whole list (blockIdx.y).  Where the cache tier keeps the planes of an
-// object next to each other this turns two 32 KiB source runs into one 64 KiB run, the length from which scattered
-// runs read as fast as a contiguous buffer (6.29 -> 6.57 TB/s in the measurement above); where the planes live in
-// pools of their own, plane after plane is the faster order (6.24 against 6.11 TB/s).
-template <int NTHR, bool NT, bool FOLD>
-__global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ recs, const uint32_t *__restrict__ n_req_ptr,
-                                               GatherArgs a, uint32_t *feedback)
-{
-    constexpr uint32_t TILE = NTHR * 16;
-    uint32_t bx = blockIdx.x, gx = gridDim.x;
-    // The first tile's list entry is fetched before the length is known, so that the two scalar loads overlap: a
-    // workgroup lives for one load and one store, and every dependent load in front of them costs bandwidth.  The
-    // host never launches more workgroups (in x) than the list has room for tiles, so the early read stays inside
-    // the list; it also guarantees capacity * tiles per request < 2^32, so tile numbers fit 32-bit division.
-    uint32_t tpc = a.tiles_per_chunk;
-    uint32_t tpr = FOLD ? tpc * a.n_planes : tpc;              // tiles per request in this grid's x dimension
-    uint64_t t = bx;
-    uint32_t idx = (uint32_t)t / tpr;
-    Rec x = recs[idx];
-    uint32_t n_req = *n_req_ptr;
-    if (feedback && bx == 0 && blockIdx.y == 0 && threadIdx.x == 0) *feedback = n_req;
-    uint64_t n_tiles = (uint64_t)n_req * tpr;
-    while (t < n_tiles) {
-        uint32_t k = (uint32_t)t - idx * tpr;
-        uint32_t plane = FOLD ? (k >= tpc ? 1u : 0u) : blockIdx.y;
-        uint64_t off = (uint64_t)(FOLD ? k - plane * tpc : k) * TILE;
-        uint64_t src = src_base_of(a, (uint32_t)(x.src & 3), plane) + (x.src & ~(uint64_t)3) + off;
-        uint64_t dst_base = plane ? a.dst_base[1] : a.dst_base[0];
-        copy_tile<NTHR, 1, NT>(src, dst_base + x.dst + off, a.chunk_bytes - off, threadIdx.x);
-        t += gx;
-        if (t >= n_tiles) break;
-        idx = (uint32_t)t / tpr;
-        x = recs[idx];
-    }
-}
-
 // Who gets the PCIe link.  A fetch that reads from the host announces, in a word of device memory, until when it
 // expects to need the link (link_announce: now + its host-tier bytes at the link's rate, on the device's constant 100 MHz
 // clock); the copies that cross the link outside a fetch - placements, write-backs - look at that word before they take
@@ -648,15 +618,133 @@ __global__ __launch_bounds__(WG) void fetch_kv_small(ClassDev c, uint32_t layer,
     }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// The gathers: both tiers of a fetch in one launch.
+// ---------------------------------------------------------------------------------------------------------
+// The first n_host workgroups read the host list over PCIe, the others copy the HBM list; both lists' lengths live on
+// the device.  One launch, because two cost more than they bring: on one stream an (often empty) host-tier launch took
+// 4.4 us in front of the HBM one, and on two streams the fork and the join cost about 15 us each.  The host-tier workgroups
+// come first in the grid, so the long PCIe transfer starts before the compute units fill up, and hold their slots
+// until it is done while the HBM tier's one-tile workgroups pass through the others.
+//
+// Host tier.  What the link needs (measured on MI355X): one compute unit sustains about 12.8 GB/s of reads from host
+// memory however many loads its threads have outstanding, so the rate is set by how many CUs take part (5 saturate the
+// 57 GB/s link) - and every host read in flight beyond what the link can absorb only queues in the memory pipeline the HBM
+// tier is using at the same time (8 x 256 threads with 16 loads per thread cost it 12 %, 24 x 256 with 2 loads 8 %).  Hence
+// HOST_LOADS loads of 16 bytes per thread in flight and host_grid * 128 threads: 192 KiB.
+//
+// Work is cut into pages of 4 loads per thread (4 KiB for one-wavefront workgroups), numbered through the whole list
+// (request * pages per chunk + position), so the bytes in flight do not depend on the chunk size.  A workgroup takes a whole
+// page - of both planes, half a page of each per step, if there are two: one-wavefront workgroups that took 1 KiB pieces in
+// turn, so that four of them shared a page of host memory, ran at 57.36 (one plane, 16 MiB chunks), 57.14 and 57.02 GB/s (two
+// planes, 32 and 16 KiB chunks), with whole pages it is 57.51, 57.45 and 57.36; half as many or twice as many
+// threads 57.1-55.3.  Each load is issued as soon as its list entry has arrived.  Lanes beyond a chunk's end re-read
+// the chunk's first bytes and store nothing: loads stay free of branches.
+template <int NTHR, int PLANES>
+__device__ inline void host_tier(const Rec *__restrict__ recs, uint32_t n_req, const GatherArgs &a, uint32_t b0)
+{
+    constexpr int L = HOST_LOADS / PLANES;                     // loads per thread, plane and step
+    const uint32_t ppc = a.pages_per_chunk;
+    const uint64_t n_pages = (uint64_t)n_req * ppc;
+    const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4), tid = threadIdx.x;
+    for (uint32_t rep = 0; rep < a.n_rep; ++rep) {
+        const uint64_t s_off = rep * a.layer_stride[T_HOST], d_off = rep * a.dst_step;
+        for (uint64_t g = b0; g < n_pages; g += a.n_host) {
+            const uint32_t idx = (uint32_t)g / ppc, j = (uint32_t)g - idx * ppc;
+            const Rec x = recs[idx];
+            const uint64_t src = (x.src & 0x0000FFFFFFFFFFFCull) + s_off, dst = x.dst + d_off;
+#pragma unroll
+            for (int s = 0; s < HOST_LOADS; s += L) {
+                const uint32_t u0 = (j * HOST_LOADS + s) * NTHR;
+                if (u0 >= chunk_units) break;
+                u32x4 v0[L], v1[L];
+                uint32_t u[L];
+#pragma unroll
+                for (int i = 0; i < L; ++i) {
+                    u[i] = u0 + i * NTHR + tid;
+                    const uint64_t at = src + (u[i] < chunk_units ? (uint64_t)u[i] * 16 : 0);
+                    v0[i] = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][0] + at));
+                    if (PLANES == 2) v1[i] = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][1] + at));
+                }
+#pragma unroll
+                for (int i = 0; i < L; ++i) {
+                    if (u[i] >= chunk_units) continue;
+                    const uint64_t d = dst + (uint64_t)u[i] * 16;
+                    st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[0] + d), v0[i]);
+                    if (PLANES == 2) st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[1] + d), v1[i]);
+                }
+            }
+        }
+    }
+}
+
+// HBM tier.  NTHR threads per workgroup, one 16-byte load and store each: a tile is NTHR * 16 bytes, and the launch has about
+// as many workgroups as tiles; a smaller grid loops.  The list length is written to a word of pinned host memory: the
+// host sizes the next launch from it, because workgroups that find no tile are not free (about 0.2 ns each on MI355X) while a
+// grid somewhat short of the tile count costs little.
+//
+// Measured on MI355X (768 MiB gathered from scattered runs, read+write): one-wavefront workgroups (1 KiB tiles) move 6.29 TB/s
+// from 32 KiB runs and 6.57 TB/s from 64 KiB runs, 256-thread workgroups 6.12 and 6.40 - a wavefront that is its own
+// workgroup frees its slot the moment it is done instead of waiting for three others.  Two or four loads per thread lose
+// (5.9 and 5.6-5.9 against 6.2-6.5 TB/s), shifts in place of the division change nothing (6.29 against 6.30): the memory
+// system's queues are full.
+//
+// FOLD: the planes of a request are taken in one pass - tile numbers run through plane 0, then plane 1, of each
+// request - instead of plane after plane over the whole list.  Where the cache tier keeps the planes of an
+// object next to each other this turns two 32 KiB source runs into one 64 KiB run, the length from which scattered
+// runs read as fast as a contiguous buffer (6.29 -> 6.57 TB/s in the measurement above); where the planes live in
+// pools of their own, plane after plane is the faster order (6.24 against 6.11 TB/s).
+template <int NTHR, int PLANES, bool FOLD>
+__global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs, const Rec *__restrict__ host_recs,
+                                               const uint32_t *__restrict__ cnt, GatherArgs a, GatherBooks books)
+{
+    constexpr uint32_t TILE = NTHR * 16;
+    if (blockIdx.x < a.n_host) {
+        if (blockIdx.y) return;                            // the host tier's workgroups walk all layers themselves
+        const uint32_t n_req = cnt[C_HOST_REQ];
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if (books.fb_host) *books.fb_host = n_req;
+            link_announce(books.lease, (uint64_t)n_req * a.chunk_bytes * PLANES * a.n_rep);
+        }
+        host_tier<NTHR, PLANES>(host_recs, n_req, a, blockIdx.x);
+        return;
+    }
+    uint32_t bx = blockIdx.x - a.n_host, plane_y = 0;
+    const uint32_t gx = a.hbm_wgs, rep = blockIdx.y;
+    if (PLANES == 2 && !FOLD && bx >= gx) { bx -= gx; plane_y = 1; }
+    // The first tile's list entry is fetched before the length is known, so that the two scalar loads overlap: a
+    // workgroup lives for one load and one store, and every dependent load in front of them costs bandwidth.  The
+    // host never launches more workgroups (per plane) than the list has room for tiles, so the early read stays inside
+    // the list; it also guarantees capacity * tiles per request < 2^32, so tile numbers fit 32-bit division.
+    uint32_t tpc = a.tiles_per_chunk;
+    uint32_t tpr = FOLD ? tpc * PLANES : tpc;              // tiles per request in this plane's tile numbers
+    uint64_t t = bx;
+    uint32_t idx = (uint32_t)t / tpr;
+    Rec x = hbm_recs[idx];
+    uint32_t n_req = cnt[C_HBM_REQ];
+    if (bx == 0 && plane_y == 0 && rep == 0) {
+        if (books.fb_hbm && threadIdx.x == 0) *books.fb_hbm = n_req;
+        if (books.totals && threadIdx.x <= C_INVALID && cnt[threadIdx.x])
+            atomicAdd(&books.totals[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
+    }
+    uint64_t n_tiles = (uint64_t)n_req * tpr;
+    while (t < n_tiles) {
+        uint32_t k = (uint32_t)t - idx * tpr;
+        uint32_t plane = FOLD ? (k >= tpc ? 1u : 0u) : plane_y;
+        uint64_t off = (uint64_t)(FOLD ? k - plane * tpc : k) * TILE;
+        uint32_t tier = (uint32_t)(x.src & 3);
+        uint64_t src = src_base_of(a, tier, plane) + rep * layer_stride_of(a, tier) + (x.src & ~(uint64_t)3) + off;
+        uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + rep * a.dst_step + x.dst + off;
+        copy_tile<NTHR, 1, true>(src, dst, a.chunk_bytes - off, threadIdx.x);
+        t += gx;
+        if (t >= n_tiles) break;
+        idx = (uint32_t)t / tpr;
+        x = hbm_recs[idx];
+    }
+}
+
 // The gather into a head-major working layout: a pool block is [token][head][head_bytes], the destination of a
-// sequence is [head][token][head_bytes].  Threads walk the block in DESTINATION order (16-byte units), so stores are
-// fully contiguous per head strip and loads come as head_bytes-long runs (256 B at the paper-shaped config: two whole
-// 128-byte lines).  No LDS: nothing is reused, the permutation is pure address arithmetic.  Staging through LDS was
-// measured on MI355X and lost: a whole 32 KiB block per workgroup (source-order loads, 8 strips of 4 KiB stored) moves
-// 5.31 TB/s against 5.81 for this kernel (12 041 scattered blocks, alone), and tiles of 4 tokens x 4 heads (every wave
-// instruction a contiguous kilobyte on both sides) 5.91 in isolation but 5.85 against 5.94 once inside the library's
-// looping, feedback-sized launch.  One-wavefront workgroups (1 KiB tiles), the token-major gather's shape, are a
-// wash here: 5.95 against 5.90 TB/s alone, 5.32 against 5.35 inside the step.
+// sequence is [head][token][head_bytes].
 struct HmArgs {
     uint32_t n_heads;
     uint32_t upr;             // 16-byte units per head row (head_bytes / 16)
@@ -664,166 +752,93 @@ struct HmArgs {
     uint32_t pad;
 };
 
-template <int UNROLL, bool NT>
-__global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ recs, const uint32_t *__restrict__ n_req_ptr,
-                                                GatherArgs a, HmArgs h, uint32_t *feedback)
+// Host tier, WG threads, one load per plane in flight and twice as many threads as host_tier's (24 workgroups: 57.5 GB/s at
+// 32 KiB chunks).  Threads walk the block in SOURCE order, so that every wave load is one contiguous kilobyte (PCIe reads of
+// 256-byte pieces reach only 22 GB/s); the stores, which go to HBM, are the ones cut into head rows.  K and V of a unit go
+// to the same place in their planes: one address computation serves both.
+template <int PLANES>
+__device__ inline void host_tier_hm(const Rec *__restrict__ recs, uint32_t n_req, const GatherArgs &a, const HmArgs &h,
+                                    uint32_t b0)
 {
-    // blockIdx.y is the plane: taking both planes of a request in one pass, as gather does for a cache tier that keeps
+    const uint32_t spc = a.tiles_per_chunk;
+    const uint64_t n_sub = (uint64_t)n_req * spc;
+    const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
+    const uint32_t row_units = h.n_heads * h.upr;              // one token: all heads
+    for (uint64_t g = b0; g < n_sub; g += a.n_host) {
+        const uint32_t idx = (uint32_t)g / spc;
+        const Rec x = recs[idx];
+        const uint32_t u = ((uint32_t)g - idx * spc) * WG + threadIdx.x, unit = u < chunk_units ? u : 0;
+        const uint64_t src = (x.src & 0x0000FFFFFFFFFFFCull) + (uint64_t)unit * 16;
+        u32x4 v0 = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][0] + src)), v1;
+        if (PLANES == 2) v1 = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][1] + src));
+        uint32_t tok = unit / row_units, rem = unit - tok * row_units;
+        uint32_t head = rem / h.upr, col = rem - head * h.upr;
+        uint64_t d = x.dst + head * ((x.src >> 48) * h.ups * 16) + (uint64_t)(tok * h.upr + col) * 16;
+        if (u < chunk_units) {
+            st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[0] + d), v0);
+            if (PLANES == 2) st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[1] + d), v1);
+        }
+    }
+}
+
+// HBM tier: threads walk the block in DESTINATION order (16-byte units), so stores are
+// fully contiguous per head strip and loads come as head_bytes-long runs (256 B at the paper-shaped config: two whole
+// 128-byte lines).  No LDS: nothing is reused, the permutation is pure address arithmetic.  Staging through LDS was
+// measured on MI355X and lost: a whole 32 KiB block per workgroup (source-order loads, 8 strips of 4 KiB stored) moves
+// 5.31 TB/s against 5.81 for this kernel (12 041 scattered blocks, alone), and tiles of 4 tokens x 4 heads (every wave
+// instruction a contiguous kilobyte on both sides) 5.91 in isolation but 5.85 against 5.94 once inside the library's
+// looping, feedback-sized launch.  One-wavefront workgroups (1 KiB tiles), the token-major gather's shape, are a
+// wash here: 5.95 against 5.90 TB/s alone, 5.32 against 5.35 inside the step.
+template <int PLANES>
+__global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs, const Rec *__restrict__ host_recs,
+                                                const uint32_t *__restrict__ cnt, GatherArgs a, HmArgs h, GatherBooks books)
+{
+    if (blockIdx.x < a.n_host) {
+        const uint32_t n_req = cnt[C_HOST_REQ];
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if (books.fb_host) *books.fb_host = n_req;
+            link_announce(books.lease, (uint64_t)n_req * a.chunk_bytes * PLANES);
+        }
+        host_tier_hm<PLANES>(host_recs, n_req, a, h, blockIdx.x);
+        return;
+    }
+    // plane after plane: taking both planes of a request in one pass, as gather does for a cache tier that keeps
     // them side by side, was measured to lose here (5.60 against 5.98 TB/s alone): the stores are 4 KiB strips, and with
     // two planes' strips interleaved they no longer follow each other
-    constexpr uint32_t UNITS = WG * UNROLL;
+    uint32_t bx = blockIdx.x - a.n_host, plane = 0;
+    const uint32_t gx = a.hbm_wgs;
+    if (PLANES == 2 && bx >= gx) { bx -= gx; plane = 1; }
     uint32_t tpr = a.tiles_per_chunk;
-    uint64_t t = blockIdx.x;
+    uint64_t t = bx;
     uint32_t idx = (uint32_t)t / tpr;
-    Rec x = recs[idx];                                   // speculative, as in gather
-    uint32_t n_req = *n_req_ptr;
-    if (feedback && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *feedback = n_req;
+    Rec x = hbm_recs[idx];                               // speculative, as in gather
+    uint32_t n_req = cnt[C_HBM_REQ];
+    if (bx == 0 && plane == 0) {
+        if (books.fb_hbm && threadIdx.x == 0) *books.fb_hbm = n_req;
+        if (books.totals && threadIdx.x <= C_INVALID && cnt[threadIdx.x])
+            atomicAdd(&books.totals[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
+    }
     uint64_t n_tiles = (uint64_t)n_req * tpr;
     uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
     while (t < n_tiles) {
         uint32_t k = (uint32_t)t - idx * tpr;
-        uint32_t plane = blockIdx.y;
         uint64_t dst_plane = plane ? a.dst_base[1] : a.dst_base[0];
-        uint32_t u0 = k * UNITS + threadIdx.x;
+        uint32_t u = k * WG + threadIdx.x;
         uint64_t cap = x.src >> 48;
         uint64_t src = src_base_of(a, (uint32_t)(x.src & 3), plane) + (x.src & 0x0000FFFFFFFFFFFCull);
         uint64_t dst = dst_plane + x.dst;
-        uint64_t head_stride = cap * h.ups * 16;
-        // unit u (in walking order) -> source unit and destination byte offset
-        auto map = [&](uint32_t u, uint32_t &s_unit, uint64_t &d_off) {
+        if (u < chunk_units) {
+            // unit u (in walking order) -> source unit and destination byte offset
             uint32_t head = u / h.ups, rem = u - head * h.ups;
             uint32_t tok = rem / h.upr, col = rem - tok * h.upr;
-            s_unit = (tok * h.n_heads + head) * h.upr + col;
-            d_off = head * head_stride + (uint64_t)rem * 16;
-        };
-        uint32_t tile_first = k * UNITS;
-        if (tile_first + UNITS <= chunk_units) {
-            // whole tile: no per-element branches, so all loads are in flight before the first store
-            u32x4 v[UNROLL];
-            uint64_t d_off[UNROLL];
-#pragma unroll
-            for (int i = 0; i < UNROLL; ++i) {
-                uint32_t s_unit;
-                map(u0 + i * WG, s_unit, d_off[i]);
-                v[i] = ld16<NT>(reinterpret_cast<const u32x4 *>(src) + s_unit);
-            }
-#pragma unroll
-            for (int i = 0; i < UNROLL; ++i) st16<true>(reinterpret_cast<u32x4 *>(dst + d_off[i]), v[i]);
-        } else {
-            for (uint32_t u = u0; u < chunk_units; u += WG) {
-                uint32_t s_unit;
-                uint64_t d_off;
-                map(u, s_unit, d_off);
-                st16<true>(reinterpret_cast<u32x4 *>(dst + d_off), ld16<NT>(reinterpret_cast<const u32x4 *>(src) + s_unit));
-            }
+            uint32_t s_unit = (tok * h.n_heads + head) * h.upr + col;
+            uint64_t d_off = head * (cap * h.ups * 16) + (uint64_t)rem * 16;
+            st16<true>(reinterpret_cast<u32x4 *>(dst + d_off), ld16<true>(reinterpret_cast<const u32x4 *>(src) + s_unit));
         }
-        t += gridDim.x;
+        t += gx;
         if (t >= n_tiles) break;
         idx = (uint32_t)t / tpr;
-        x = recs[idx];
-    }
-}
-
-// Host tier: the same request list format, read over PCIe from pinned host memory by a few persistent workgroups.
-//
-// What the link needs (measured on MI355X): one compute unit sustains about 12.8 GB/s of reads from host memory however
-// many loads its threads have outstanding, so the rate is set by how many CUs take part (5 saturate the 57 GB/s link) -
-// and every host read in flight beyond what the link can absorb (about 128 KiB) only queues in the memory pipeline the
-// HBM-tier gather is using at the same time: 8 workgroups x 16 loads per thread cost that kernel 12 %, 24 workgroups x
-// 2 loads cost it 8 % and serve the link better (57.1 against 56.8 GB/s).  Hence: HOST_LOADS = 2 loads of 16 bytes per
-// thread, a couple of dozen workgroups.
-//
-// Work is cut into 4 KiB sub-tiles numbered through the whole list (request * sub-tiles per chunk + position), so the
-// bytes in flight do not depend on the chunk size (16 KiB blocks of an fp8 KV cache and ragged sizes run at the same
-// rate as 32 KiB blocks).  A two-plane class takes one sub-tile of both planes per step, a one-plane class two
-// consecutive sub-tiles.  Each load is issued as soon as its list entry has arrived.  Lanes beyond a chunk's end
-// re-read the chunk's first bytes and store nothing: loads stay free of branches.
-struct HostSub {
-    uint64_t src;      // offset of this lane's 16 bytes inside the tier's plane pool
-    uint64_t dst;      // offset of the chunk inside the destination plane (head-major: of the sequence's region)
-    uint32_t tier;
-    uint32_t unit;     // this lane's 16-byte unit inside the chunk (0 when inactive)
-    uint64_t cap;      // head-major only: the sequence's capacity in blocks
-    bool act;
-};
-
-__device__ inline HostSub host_sub(const Rec *__restrict__ recs, uint64_t g, uint64_t n_sub, uint32_t spc,
-                                   uint32_t chunk_units, uint32_t tid)
-{
-    HostSub r;
-    bool valid = g < n_sub;
-    uint32_t idx = valid ? (uint32_t)g / spc : 0;             // a step exists only when the list is not empty
-    Rec x = recs[idx];
-    uint32_t j = valid ? (uint32_t)g - idx * spc : 0;
-    uint32_t u = j * WG + tid;
-    r.act = valid && u < chunk_units;
-    r.unit = r.act ? u : 0;
-    r.src = (x.src & 0x0000FFFFFFFFFFFCull) + (uint64_t)r.unit * 16;
-    r.dst = x.dst;
-    r.tier = (uint32_t)(x.src & 3);
-    r.cap = x.src >> 48;
-    return r;
-}
-
-template <int PLANES>
-__global__ __launch_bounds__(WG) void gather_host(const Rec *__restrict__ recs, const uint32_t *__restrict__ n_req_ptr,
-                                                  GatherArgs a, uint32_t *feedback, unsigned long long *lease)
-{
-    constexpr int U = HOST_LOADS / PLANES;                     // sub-tiles per step
-    uint32_t spc = a.tiles_per_chunk;                          // 4 KiB sub-tiles per chunk
-    uint32_t n_req = *n_req_ptr;
-    if (feedback && blockIdx.x == 0 && threadIdx.x == 0) *feedback = n_req;      // as in gather: a hint for the host
-    if (blockIdx.x == 0 && threadIdx.x == 0) link_announce(lease, (uint64_t)n_req * a.chunk_bytes * PLANES);
-    uint64_t n_sub = (uint64_t)n_req * spc;
-    uint64_t n_steps = (n_sub + U - 1) / U;
-    uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
-    uint32_t tid = threadIdx.x;
-    for (uint64_t b = blockIdx.x; b < n_steps; b += gridDim.x) {
-        HostSub q[U];
-        u32x4 v0[U], v1[U];
-#pragma unroll
-        for (int i = 0; i < U; ++i) {
-            q[i] = host_sub(recs, b * U + i, n_sub, spc, chunk_units, tid);
-            v0[i] = ld16<false>(reinterpret_cast<const u32x4 *>(src_base_of(a, q[i].tier, 0) + q[i].src));
-            if (PLANES == 2) v1[i] = ld16<false>(reinterpret_cast<const u32x4 *>(src_base_of(a, q[i].tier, 1) + q[i].src));
-        }
-#pragma unroll
-        for (int i = 0; i < U; ++i) {
-            if (!q[i].act) continue;
-            uint64_t d = q[i].dst + (uint64_t)q[i].unit * 16;
-            st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[0] + d), v0[i]);
-            if (PLANES == 2) st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[1] + d), v1[i]);
-        }
-    }
-}
-
-// The same for the head-major layout.  Unlike the HBM-tier kernel above, threads walk the block in SOURCE order, so that
-// every wave load is one contiguous kilobyte (PCIe reads of 256-byte pieces reach only 22 GB/s); the stores, which go to
-// HBM, are the ones cut into head rows.  K and V of a unit go to the same place in their planes: one address
-// computation serves both.
-template <int PLANES>
-__global__ __launch_bounds__(WG) void gather_hm_host(const Rec *__restrict__ recs, const uint32_t *__restrict__ n_req_ptr,
-                                                     GatherArgs a, HmArgs h, uint32_t *feedback, unsigned long long *lease)
-{
-    uint32_t spc = a.tiles_per_chunk;
-    uint32_t n_req = *n_req_ptr;
-    if (feedback && blockIdx.x == 0 && threadIdx.x == 0) *feedback = n_req;
-    if (blockIdx.x == 0 && threadIdx.x == 0) link_announce(lease, (uint64_t)n_req * a.chunk_bytes * PLANES);
-    uint64_t n_sub = (uint64_t)n_req * spc;
-    uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
-    uint32_t tid = threadIdx.x;
-    uint32_t row_units = h.n_heads * h.upr;                    // one token: all heads
-    for (uint64_t g = blockIdx.x; g < n_sub; g += gridDim.x) {
-        HostSub q = host_sub(recs, g, n_sub, spc, chunk_units, tid);
-        u32x4 v0 = ld16<false>(reinterpret_cast<const u32x4 *>(src_base_of(a, q.tier, 0) + q.src)), v1;
-        if (PLANES == 2) v1 = ld16<false>(reinterpret_cast<const u32x4 *>(src_base_of(a, q.tier, 1) + q.src));
-        uint32_t tok = q.unit / row_units, rem = q.unit - tok * row_units;
-        uint32_t head = rem / h.upr, col = rem - head * h.upr;
-        uint64_t d = q.dst + head * (q.cap * h.ups * 16) + (uint64_t)(tok * h.upr + col) * 16;
-        if (q.act) {
-            st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[0] + d), v0);
-            if (PLANES == 2) st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[1] + d), v1);
-        }
+        x = hbm_recs[idx];
     }
 }
 
@@ -987,13 +1002,6 @@ __global__ __launch_bounds__(WG) void dir_write(uint64_t *dir, const uint32_t *_
 {
     uint32_t i = blockIdx.x * WG + threadIdx.x;
     if (i < n) dir[ids[i]] = entries[i];
-}
-
-// A fetch repeated from the lists of the one before it serves the same requests again: they are added to the running totals.
-__global__ void repeat_totals(const uint32_t *__restrict__ cnt, unsigned long long *totals)
-{
-    uint32_t i = threadIdx.x;
-    if (i <= C_INVALID && cnt[i]) atomicAdd(&totals[i], (unsigned long long)cnt[i]);
 }
 
 // The counters of a fetch, as harvest_fetch_kv_static hands them to its caller: requests, local, cache, host, lost,

@@ -1,0 +1,96 @@
+"""The kernels of the fetch at the edges of their tiles, pages and grids, against numpy indexing of the payload.
+
+A fetch moves bytes, so the comparison is exact.  Sizes are in 16-byte units around what one workgroup takes at a time:
+1 KiB tiles, 4 KiB host pages (64 threads x 4 loads), half pages per plane.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_00328_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+class Rig:
+    """A KV class of n objects with tiers mixed by object number, and its payload [plane][layer][object][chunk] in numpy."""
+
+    def __init__(self, chunk, n, n_layers=1, n_planes=2, host_every=3, local_every=7, seed=0, **kw):
+        rng = np.random.default_rng(seed)
+        self.chunk, self.n, self.n_layers, self.n_planes = chunk, n, n_layers, n_planes
+        self.payload = rng.integers(0, 256, (n_planes, n_layers, n, chunk), dtype=np.uint8)
+        local = np.array([i for i in range(n) if local_every and i % local_every == 3], dtype=np.int64)
+        rest = np.setdiff1d(np.arange(n), local)
+        self.order = np.concatenate([rest, local])                # object number -> payload row
+        host_slots = rng.permutation(n).astype(np.int64)
+        self.h = B.Harvest(kv=B.ClassSpec(n_layers=n_layers, n_planes=n_planes, chunk_bytes=chunk, max_objects=n, n_host_slots=n,
+                                          n_cache_slots=max(1, len(rest)), n_local_slots=len(local)), **kw)
+        for p in range(n_planes):
+            self.h.host_plane(B.KV, p)[:, host_slots] = self.payload[p][:, self.order]
+        self.h.register(B.KV, len(rest), host_slots[:len(rest)])
+        if len(local):
+            self.h.register(B.KV, len(local), host_slots[len(rest):], tier=B.LOCAL)
+            for p in range(n_planes):
+                self.h.dev_plane(B.KV, B.LOCAL, p).copy_(torch.from_numpy(self.payload[p][:, local]))
+        self.on_host = np.array([bool(host_every) and i % host_every == 1 for i in range(len(rest))])
+        cached = rng.permutation(np.flatnonzero(~self.on_host))
+        if len(cached):
+            self.h.place(B.KV, cached)
+        torch.cuda.synchronize()
+
+    def tables(self, lens, width, seed=1):
+        rng = np.random.default_rng(seed)
+        t = np.full((len(lens), width), -1, dtype=np.int32)
+        for s, k in enumerate(lens):
+            t[s, :k] = rng.integers(0, self.n, k)
+        first = np.cumsum([0] + list(lens[:-1])).astype(np.int64)
+        dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+        return t, dev(t), dev(np.array(lens, dtype=np.int32)), dev(first), int(sum(lens))
+
+    def expected(self, t, lens, plane, layer):
+        ids = np.concatenate([t[s, :k] for s, k in enumerate(lens)])
+        return self.payload[plane][layer][self.order[ids]].reshape(-1)
+
+    def misses(self, t, lens):
+        return [s * t.shape[1] + j for s, k in enumerate(lens) for j in range(k)
+                if t[s, j] < len(self.on_host) and self.on_host[t[s, j]]]
+
+    def buffers(self, cap):
+        return [torch.full((self.n_layers * cap * self.chunk + 64,), 0xEE, dtype=torch.uint8, device="cuda") for _ in range(2)]
+
+
+@pytest.mark.parametrize("n_planes", [1, 2])
+@pytest.mark.parametrize("chunk", [16, 1008, 1024, 2064, 4080, 4096, 4112, 8208, 16384 + 48])
+@pytest.mark.parametrize("threads,host_wgs", [(64, 0), (64, 1), (128, 3), (256, 0)])
+def test_both_tiers_in_one_launch(n_planes, chunk, threads, host_wgs):
+    rig = Rig(chunk, 41, n_layers=3, n_planes=n_planes, flags=B.FLAG_GENERAL_FETCH, gather_threads=threads, host_wgs=host_wgs)
+    lens = [13, 1, 0, 22]
+    t, dt, dn, df, cap = rig.tables(lens, 23)
+    for _ in range(2):                                # the second call's grid is sized by the first one's report
+        k, v = rig.buffers(cap)
+        rig.h.fetch_kv_layers(0, 3, dt, dn, k, v if n_planes == 2 else None, cap * chunk, df, cap)
+        counts, miss, n_miss = rig.h.fetch_info(miss_cap=t.size)
+        assert sorted(miss.tolist()) == rig.misses(t, lens) and counts["n_host"] == n_miss
+        for p, buf in enumerate([k, v][:n_planes]):
+            got = buf.cpu().numpy()
+            for layer in range(3):
+                assert np.array_equal(got[layer * cap * chunk:(layer + 1) * cap * chunk], rig.expected(t, lens, p, layer)), (p, layer)
+            assert (got[3 * cap * chunk:] == 0xEE).all()
+    rig.h.close()
+
+
+@pytest.mark.parametrize("host_every,local_every", [(0, 0), (1, 0), (2, 5)])
+def test_again_counts_its_requests(host_every, local_every):
+    """All in the cache tier, all but one request in three on the host, and a mix: a repeated fetch adds to the totals."""
+    rig = Rig(2048, 30, n_layers=2, host_every=host_every, local_every=local_every, flags=B.FLAG_GENERAL_FETCH)
+    lens = [9, 17]
+    t, dt, dn, df, cap = rig.tables(lens, 20)
+    k, v = rig.buffers(cap)
+    rig.h.fetch_kv(0, dt, dn, k, v, df, cap)
+    once = rig.h.stats().fetch[B.KV].as_dict()
+    rig.h.fetch_kv_again(1, k, v)
+    for p, buf in enumerate([k, v]):
+        assert np.array_equal(buf.cpu().numpy()[:cap * 2048], rig.expected(t, lens, p, 1))
+    assert rig.h.stats().fetch[B.KV].as_dict() == {name: 2 * x for name, x in once.items()}
+    assert once["n_requests"] == 26 and once["n_host"] == len(rig.misses(t, lens))
+    rig.h.close()
