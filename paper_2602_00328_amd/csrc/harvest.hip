@@ -586,6 +586,7 @@ int release_after(harvest_ctx *ctx, Staging *st, hipStream_t s)
 constexpr uint64_t SMALL_FETCH_CELLS = 4096;      // block tables up to this many cells are fetched by one kernel (measured:
                                                   // it wins up to 4 096 cells and loses from 8 192 on)
 constexpr uint64_t SMALL_FETCH_TILES = 1u << 22;      // and never more workgroups than this in x
+constexpr uint64_t DEAD_TILES = 20000;                // nor with more workgroups than this (8 us) for cells that ask for nothing
 constexpr uint32_t MARKED_BATCH_IDS = 32768;      // routing-id batches beyond this take the two-kernel resolve
 constexpr uint32_t GROUPED_SCAN_ROWS = 1024;      // block tables of more than 262 144 cells take the three-kernel compaction
 
@@ -707,9 +708,12 @@ int mark_last(harvest_ctx *ctx, StreamState *ss)
     return HARVEST_OK;
 }
 
-// Launches the kernel that ends a call's work on the stream, with the stream's latest-work event as its completion signal:
-// an event recorded behind the kernel is a packet of its own, which keeps the next kernel of the stream waiting 2.9 us and
-// the host busy for 0.8; attached to the dispatch it costs 0 and 0.2 us (measured behind a 10 us kernel).
+// Launches the kernel that ends a call's work on the stream and leaves the stream's latest-work event behind it.  While the
+// work before it is still running, the event is the kernel's own completion signal: recorded behind the kernel it is a packet
+// of its own, which keeps the next kernel of the stream waiting 2.9 us and the host busy for 0.8; attached to the dispatch it
+// costs 0 and 0.2 us.  On an idle stream it is recorded: that packet is what a caller who waits for the GPU next needs anyway,
+// and waiting for a kernel's own signal takes 2.3 us longer than waiting for it (17.0 against 14.7 us from launch to the
+// end of the wait, 3 us kernel).
 template <typename... P, typename... A>
 int launch_last(harvest_ctx *ctx, StreamState *ss, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
 {
@@ -719,8 +723,13 @@ int launch_last(harvest_ctx *ctx, StreamState *ss, void (*kernel)(P...), dim3 gr
         ctx->captured_work = true;
         return HARVEST_OK;
     }
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, ss->s, nullptr, ss->last, 0, (P)args...);
+    const bool busy = ss->last_valid && hipEventQuery(ss->last) == hipErrorNotReady;
+    if (busy) {
+        (void)hipGetLastError();                    // "not ready" is an answer, not an error
+        hipExtLaunchKernelGGL(kernel, grid, block, 0, ss->s, nullptr, ss->last, 0, (P)args...);
+    } else hipLaunchKernelGGL(kernel, grid, block, 0, ss->s, (P)args...);
     HIP_TRY(hipGetLastError());
+    if (!busy) HIP_TRY(hipEventRecord(ss->last, ss->s));
     ss->last_valid = true;
     return HARVEST_OK;
 }
@@ -731,6 +740,12 @@ hipEvent_t prof_event(harvest_ctx *ctx)
     hipEvent_t e = nullptr;
     if (hipEventCreate(&e) != hipSuccess) return nullptr;
     return e;
+}
+
+// Workgroups of nthr threads with HOST_LOADS loads each in flight for the host tier: host_grid counts 8 KiB of loads.
+uint32_t host_workgroups(const harvest_ctx *ctx, uint32_t nthr)
+{
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, (uint64_t)ctx->host_grid * 128 / nthr), MAX_GRID / 2);
 }
 
 // Launches the gathers of both tiers on the caller's stream.
@@ -791,9 +806,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
         double us_hbm = 2.0 * seen * bytes / 6.0e6, us_host = seen_host * bytes / 57.0e3;     // at 6 TB/s and 57 GB/s
         serial = serial || std::max(us_hbm, us_host) < 35.0 || std::min(us_hbm, us_host) < 8.0;
     }
-    // host_grid counts 8 KiB of loads in flight: 256 threads with 2 loads each (head-major), 128 threads with HOST_LOADS
-    const uint32_t host_wgs = !host_tier ? 0
-        : (uint32_t)std::min<uint64_t>(hm ? ctx->host_grid : std::max<uint64_t>(1, (uint64_t)ctx->host_grid * 128 / nthr), MAX_GRID / 2);
+    const uint32_t host_wgs = host_tier ? host_workgroups(ctx, hm ? 128 : nthr) : 0;   // head-major: 256 threads with half the loads
     const uint32_t max_wgs = (MAX_GRID - host_wgs) / (fold ? 1 : planes);
     const uint32_t hbm_wgs = grid_for(fold ? want * planes : want, ctx->gather_grid ? std::min(ctx->gather_grid, max_wgs) : max_wgs);
     GatherBooks books{};
@@ -1478,7 +1491,8 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
                            uint32_t n_seq, uint32_t max_blocks, void *d_dst_k, void *d_dst_v,
                            const uint64_t *d_seq_dst_block, const uint32_t *d_seq_cap_blocks, uint64_t dst_capacity_blocks,
                            uint32_t n_heads, uint32_t block_tokens, void *stream, uint32_t n_layers,
-                           uint64_t dst_layer_stride, StreamState *fixed_ss = nullptr, uint32_t *miss_out = nullptr);
+                           uint64_t dst_layer_stride, StreamState *fixed_ss = nullptr, uint32_t *miss_out = nullptr,
+                           uint32_t *info = nullptr);
 
 static int fetch_kv_impl(harvest_ctx *ctx, uint32_t layer, const int32_t *d_block_table, const int32_t *d_n_blocks,
                          uint32_t n_seq, uint32_t max_blocks, void *d_dst_k, void *d_dst_v,
@@ -1495,12 +1509,13 @@ static int fetch_kv_impl(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bloc
 }
 
 // The body of every KV fetch; the context's lock is held.  fixed_ss: the stream's state when it is not one of
-// ctx->streams (harvest_fetch_kv_static); miss_out: where the miss list goes instead of the stream's own array.
+// ctx->streams (harvest_fetch_kv_static); miss_out: where the miss list goes instead of the stream's own array; info: the
+// caller's copy of the counters.
 static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_block_table, const int32_t *d_n_blocks,
                            uint32_t n_seq, uint32_t max_blocks, void *d_dst_k, void *d_dst_v,
                            const uint64_t *d_seq_dst_block, const uint32_t *d_seq_cap_blocks, uint64_t dst_capacity_blocks,
                            uint32_t n_heads, uint32_t block_tokens, void *stream, uint32_t n_layers,
-                           uint64_t dst_layer_stride, StreamState *fixed_ss, uint32_t *miss_out)
+                           uint64_t dst_layer_stride, StreamState *fixed_ss, uint32_t *miss_out, uint32_t *info)
 {
     int rc;
     ClassState &c = ctx->cls[HARVEST_KV];
@@ -1543,8 +1558,18 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     const KvWork &work = ss->work;
     uint32_t *cnt = lists.cnt;
     const uint32_t tpc = tiles_per_chunk(c.cfg.chunk_bytes, TILE_4K);
-    if (!ctx->general_fetch && !head_major && n_layers <= 65535 && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES) {
-        // a small table: the whole fetch is one kernel (no compaction, no second stream) - see fetch_kv_small
+    // A small table: the whole fetch is one kernel (no compaction) - see fetch_kv_small.  Unless most of it is padding: the
+    // one kernel has a workgroup for every tile of every cell, and one whose cell asks for nothing still costs 0.4 ns
+    // (4 096 cells, 64 of them live: 27 us), where the general path spends about 8 us more on two small kernels and none
+    // on cells that are not there.  How many are live is what the stream's last fetch reported.
+    uint64_t dead_tiles = 0;
+    if (ss->feedback_valid[HARVEST_KV]) {
+        const uint64_t live = (uint64_t)*(volatile uint32_t *)&ss->h_feedback[HARVEST_KV] +
+                              *(volatile uint32_t *)&ss->h_feedback[HARVEST_N_CLASSES + HARVEST_KV];
+        if (live < total) dead_tiles = (total - live) * tpc * c.cfg.n_planes * n_layers;
+    }
+    if (!ctx->general_fetch && !head_major && n_layers <= MAX_GRID_Y && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
+        total * tpc * n_layers <= (1ull << 31) && dead_tiles <= DEAD_TILES) {
         GatherArgs ga{};
         const ClassDev cd = class_dev(c);
         for (uint32_t p = 0; p < 2; ++p) {
@@ -1552,13 +1577,17 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
             ga.src_base[T_CACHE][p] = cd.pool[T_CACHE][p];
             ga.src_base[T_LOCAL][p] = cd.pool[T_LOCAL][p];
         }
+        for (int t = 0; t < 3; ++t) ga.layer_stride[t] = cd.layer_stride[t];
         ga.dst_base[0] = (uint64_t)d_dst_k; ga.dst_base[1] = (uint64_t)d_dst_v;
+        ga.dst_step = dst_layer_stride; ga.n_rep = n_layers;
         ga.chunk_bytes = c.cfg.chunk_bytes; ga.tiles_per_chunk = tpc; ga.n_planes = c.cfg.n_planes;
-        if ((rc = launch_last(ctx, ss, fetch_kv_small, dim3((uint32_t)(total * tpc), c.cfg.n_planes, n_layers), dim3(WG), cd,
-                              layer, d_block_table, d_n_blocks, n_seq, max_blocks, d_seq_dst_block, dst_capacity_blocks, ga,
-                              dst_layer_stride, lists.miss, cnt, ctx->d_totals + HARVEST_KV * C_N,
-                              ss->d_feedback + HARVEST_KV, ss->d_feedback + HARVEST_N_CLASSES + HARVEST_KV,
-                              c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr)))
+        ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, 128) : 0;         // WG threads with half the loads
+        SmallBooks books{ lists.miss, cnt, info, ctx->d_totals + HARVEST_KV * C_N, ss->d_feedback + HARVEST_KV,
+                          ss->d_feedback + HARVEST_N_CLASSES + HARVEST_KV, c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr };
+        const dim3 grid(ga.n_host + 1 + (uint32_t)(total * tpc), c.cfg.n_planes, n_layers);
+        if ((rc = launch_last(ctx, ss, c.cfg.n_planes == 2 ? fetch_kv_small<2> : fetch_kv_small<1>, grid, dim3(WG), cd, layer,
+                              d_block_table, d_n_blocks, (uint32_t)total, max_blocks, d_seq_dst_block, dst_capacity_blocks, ga,
+                              books)))
             return rc;
         ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
         ss->feedback_valid[HARVEST_KV] = true;
@@ -1582,7 +1611,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
                        (const uint8_t *)work.kind, (const uint32_t *)work.blk_counts, lists.hbm, lists.host,
                        lists.miss, cnt, ctx->d_totals + HARVEST_KV * C_N,
                        grouped ? (const uint32_t *)work.grp_totals : (const uint32_t *)nullptr,
-                       grouped ? (const uint32_t *)work.row_prefix : (const uint32_t *)nullptr);
+                       grouped ? (const uint32_t *)work.row_prefix : (const uint32_t *)nullptr, info);
     HIP_TRY(hipGetLastError());
     ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
     // lists recorded into a graph exist only once the graph has been replayed: nothing to use again
@@ -1650,9 +1679,9 @@ int harvest_fetch_kv_static(harvest_ctx *ctx, uint32_t layer, const int32_t *d_b
         ss->s = (hipStream_t)stream;
     }
     rc = fetch_kv_locked(ctx, layer, d_block_table, d_n_blocks, n_seq, max_blocks, d_dst_k, d_dst_v, d_seq_dst_block, nullptr,
-                         dst_capacity_blocks, 0, 0, stream, 1, 0, ss, d_miss_idx);
-    if (rc || !d_info) return rc;
-    return launch_last(ctx, ss, export_info, dim3(1), dim3(64), ss->lists[HARVEST_KV].cnt, d_info, total ? 1u : 0u);
+                         dst_capacity_blocks, 0, 0, stream, 1, 0, ss, d_miss_idx, d_info);
+    if (rc || total || !d_info) return rc;
+    return launch_last(ctx, ss, zero_info, dim3(1), dim3(64), d_info);
 }
 
 int harvest_fetch_kv(harvest_ctx *ctx, uint32_t layer, const int32_t *d_block_table, const int32_t *d_n_blocks,

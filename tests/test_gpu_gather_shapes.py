@@ -94,3 +94,52 @@ def test_again_counts_its_requests(host_every, local_every):
     assert rig.h.stats().fetch[B.KV].as_dict() == {name: 2 * x for name, x in once.items()}
     assert once["n_requests"] == 26 and once["n_host"] == len(rig.misses(t, lens))
     rig.h.close()
+
+
+@pytest.mark.parametrize("n_planes", [1, 2])
+@pytest.mark.parametrize("lens,width", [([1], 1), ([255], 255), ([256, 0], 256), ([200, 55, 257], 257), ([3, 510], 513), ([0, 0], 600),
+                                        ([1, 2, 0, 5], 1024)])
+def test_one_kernel_fetch_at_the_edges_of_its_rounds(n_planes, lens, width):
+    """Tables of one cell up to several rounds of 512, twice: the second call of a mostly empty table takes the general path."""
+    rig = Rig(4112, 37, n_layers=2, n_planes=n_planes)
+    t, dt, dn, df, cap = rig.tables(lens, width)
+    if lens[0] > 100:
+        t[0, 5], t[0, 70] = -4, rig.n                 # blocks that do not exist: invalid requests
+        dt.copy_(torch.from_numpy(t))
+    ids = np.concatenate([t[s, :k] for s, k in enumerate(lens)])
+    bad = (ids < 0) | (ids >= rig.n)
+    for _ in range(2):
+        k, v = rig.buffers(max(cap, 1))
+        rig.h.fetch_kv_layers(0, 2, dt, dn, k, v if n_planes == 2 else None, max(cap, 1) * 4112, df, max(cap, 1))
+        counts, miss, _ = rig.h.fetch_info(miss_cap=t.size)
+        assert sorted(miss.tolist()) == rig.misses(np.where(t >= 0, t, rig.n), lens)
+        assert counts["n_requests"] == cap and counts["n_invalid"] == bad.sum()
+        for p, buf in enumerate([k, v][:n_planes]):
+            for layer in range(2):
+                got = buf.cpu().numpy()[layer * max(cap, 1) * 4112:][:cap * 4112].reshape(cap, 4112)
+                want = rig.payload[p][layer][rig.order[np.where(bad, 0, ids)]]
+                want[bad] = 0xEE
+                assert np.array_equal(got, want), (p, layer)
+    rig.h.close()
+
+
+@pytest.mark.parametrize("lens,width", [([1], 1), ([300, 513], 600), ([5, 9], 4096), ([2, 1, 0], 4)])
+def test_static_fetch_hands_out_counters_and_misses_in_order(lens, width):
+    rig = Rig(2048, 50)
+    t, dt, dn, df, cap = rig.tables(lens, width)
+    for _ in range(2):
+        k, v = rig.buffers(cap)
+        info = torch.full((8,), 77, dtype=torch.int32, device="cuda")
+        miss = torch.full((t.size,), -7, dtype=torch.int32, device="cuda")
+        rig.h.fetch_kv_static(0, dt, dn, k, v, df, cap, info, miss)
+        want = rig.misses(t, lens)
+        ids = np.concatenate([t[s, :n] for s, n in enumerate(lens)])
+        n_local = int((ids >= len(rig.on_host)).sum())
+        assert info.tolist() == [cap, n_local, cap - n_local - len(want), len(want), 0, 0, len(want), 0]
+        assert miss.tolist() == want + [-7] * (t.size - len(want))
+        for p, buf in enumerate([k, v]):
+            assert np.array_equal(buf.cpu().numpy()[:cap * 2048], rig.expected(t, lens, p, 0))
+    empty = torch.zeros((0, 4), dtype=torch.int32, device="cuda")
+    rig.h.fetch_kv_static(0, empty, dn, k, v, df, cap, info, miss)
+    assert info.tolist() == [0] * 8
+    rig.h.close()
