@@ -132,19 +132,16 @@ def _np_ptr(a):
 
 
 def _dev_ptr(t):
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return vp(t)
-    return vp(t.data_ptr())
+    return t if t is None or isinstance(t, int) else t.data_ptr()
 
 
 def _stream_ptr(stream):
+    """The address of a HIP stream.  torch's current stream is asked for as an address: torch.cuda.current_stream() builds
+    a Stream object, which took 3.0 of the 9.7 us of a fetch of 8 blocks (0.1 us this way; torch initialises itself first
+    where nothing has yet)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    if isinstance(stream, int):
-        return vp(stream)
-    return vp(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 @dataclass
