@@ -287,7 +287,8 @@ struct StreamState {
     // fetch scratch
     Lists lists[HARVEST_N_CLASSES];
     KvWork work;
-    uint32_t *cnt_block = nullptr;          // the counters of both classes: one allocation
+    uint32_t *cnt_block = nullptr;          // the counters of both classes and, behind them, `next`: one allocation
+    unsigned long long *next = nullptr;     // tile counter of move_pcie, zero between launches
     uint32_t *mark = nullptr;               // [MAX_EXPERTS / 32 + 1] routed-set bitmap and invalid-id count of large batches;
                                             // zero between fetches
     int last_cls = -1;                      // class of the latest fetch enqueued on this stream, -1: none yet
@@ -444,8 +445,10 @@ int init_stream_state(StreamState *ss)
     HIP_TRY(hipStreamCreateWithFlags(&ss->side, hipStreamNonBlocking));
     for (hipEvent_t *e : { &ss->fork, &ss->join, &ss->last })
         HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
-    HIP_TRY(hipMalloc(&ss->cnt_block, HARVEST_N_CLASSES * C_N * sizeof(uint32_t)));
-    HIP_TRY(hipMemset(ss->cnt_block, 0, HARVEST_N_CLASSES * C_N * sizeof(uint32_t)));
+    const size_t cnt_bytes = HARVEST_N_CLASSES * C_N * sizeof(uint32_t);
+    HIP_TRY(hipMalloc(&ss->cnt_block, cnt_bytes + sizeof *ss->next));
+    HIP_TRY(hipMemset(ss->cnt_block, 0, cnt_bytes + sizeof *ss->next));
+    ss->next = (unsigned long long *)((char *)ss->cnt_block + cnt_bytes);
     for (int k = 0; k < HARVEST_N_CLASSES; ++k) ss->lists[k].cnt = ss->cnt_block + k * C_N;
     HIP_TRY(hipMalloc(&ss->mark, (MAX_EXPERTS / 32 + 1) * sizeof(uint32_t)));
     HIP_TRY(hipMemset(ss->mark, 0, (MAX_EXPERTS / 32 + 1) * sizeof(uint32_t)));
@@ -630,10 +633,22 @@ ClassDev class_dev(const ClassState &c)
     return d;
 }
 
+// Launches a kernel with `done` as its completion signal.  Recorded behind the kernel an event is a packet of its own, which
+// keeps the next kernel of the stream - the caller's attention, say - waiting 2.9 us and the host busy for 0.8; attached to
+// the dispatch it costs 0 and 0.2 us (behind a 10 us kernel: 14.2 against 11.3 us per iteration, 11.3 without an event).  Only
+// a caller that waits for the GPU right after the call is better off with the packet (14.7 against 17.0 us).
+template <typename... P, typename... A>
+int launch_with(hipEvent_t done, hipStream_t s, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
+{
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, nullptr, done, 0, (P)args...);
+    HIP_TRY(hipGetLastError());
+    return HARVEST_OK;
+}
+
 // Publishes the mirror entries of `ids` to the device directory with a dir_write kernel on stream `on`, ordered after
 // everything enqueued on `on` so far (for a placement: the copy that makes the new entry true) and after every earlier
-// directory edit, wherever that ran.  pre: a staging block of n * 12 bytes taken earlier, so that this step cannot fail
-// for want of one.  *committed (if given) says whether the dir_write was enqueued: from then on the device will apply
+// directory edit, wherever that ran.  Up to DIR_INLINE entries travel with the launch, more of them in a staging block - pre: one
+// of n * 12 bytes taken earlier, so that this step cannot fail for want of one.  *committed (if given) says whether the dir_write was enqueued: from then on the device will apply
 // the edit, and a failure reported by a later step no longer entitles the caller to roll its mirror back.
 int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, hipStream_t on, bool must_see,
             Staging *pre = nullptr, bool *committed = nullptr)
@@ -644,7 +659,7 @@ int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, h
     size_t bytes = n * (sizeof(uint64_t) + sizeof(uint32_t));
     Hold hold;
     Staging *st = pre;
-    if (!st) {
+    if (!st && n > DIR_INLINE) {
         int rc = acquire_staging(ctx, bytes, &st);
         if (rc) return rc;
         hold.st = st;
@@ -661,23 +676,27 @@ int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, h
     }
     if (c.edit_seq && c.edit_stream != on) DEV_TRY(hipStreamWaitEvent(on, c.edit_evt, 0));
     void *d_st = nullptr;
-    DEV_TRY(hipHostGetDevicePointer(&d_st, st->h, 0));
-    if (!ctx->no_device) {
+    if (n > DIR_INLINE) DEV_TRY(hipHostGetDevicePointer(&d_st, st->h, 0));
+    if (!ctx->no_device && n <= DIR_INLINE) {
+        DirList l;
+        for (size_t i = 0; i < n; ++i) { l.entry[i] = c.packed(ids[i]); l.id[i] = ids[i]; }
+        int rc = launch_with(c.edit_evt, on, dir_write_inline, dim3(1), dim3(DIR_INLINE), c.d_dir, (uint64_t)n, l);
+        if (rc) return rc;
+    } else if (!ctx->no_device) {
         uint64_t *ent = (uint64_t *)st->h;
         uint32_t *idv = (uint32_t *)(ent + n);
         for (size_t i = 0; i < n; ++i) { ent[i] = c.packed(ids[i]); idv[i] = ids[i]; }
         uint64_t *d_ent = (uint64_t *)d_st;
         uint32_t *d_ids = (uint32_t *)(d_ent + n);
-        hipLaunchKernelGGL(dir_write, dim3((uint32_t)((n + WG - 1) / WG)), dim3(WG), 0, on, c.d_dir, d_ids, d_ent,
-                           (uint32_t)n);
+        int rc = launch_with(c.edit_evt, on, dir_write, dim3((uint32_t)((n + WG - 1) / WG)), dim3(WG), c.d_dir, d_ids, d_ent, (uint32_t)n);
+        if (rc) return rc;
     }
     DEV_TRY(hipGetLastError());
     if (committed) *committed = true;
     c.edit_seq++;
     c.edit_stream = on;
     if (must_see) c.must_seq = c.edit_seq;
-    if (ctx->no_device) return HARVEST_OK;
-    HIP_TRY(hipEventRecord(c.edit_evt, on));
+    if (ctx->no_device || n <= DIR_INLINE) return HARVEST_OK;
     return release_after(ctx, st, on);
 }
 
@@ -708,12 +727,7 @@ int mark_last(harvest_ctx *ctx, StreamState *ss)
     return HARVEST_OK;
 }
 
-// Launches the kernel that ends a call's work on the stream and leaves the stream's latest-work event behind it.  While the
-// work before it is still running, the event is the kernel's own completion signal: recorded behind the kernel it is a packet
-// of its own, which keeps the next kernel of the stream waiting 2.9 us and the host busy for 0.8; attached to the dispatch it
-// costs 0 and 0.2 us.  On an idle stream it is recorded: that packet is what a caller who waits for the GPU next needs anyway,
-// and waiting for a kernel's own signal takes 2.3 us longer than waiting for it (17.0 against 14.7 us from launch to the
-// end of the wait, 3 us kernel).
+// Launches the kernel that ends a call's work on the stream; the stream's latest-work event is its completion signal.
 template <typename... P, typename... A>
 int launch_last(harvest_ctx *ctx, StreamState *ss, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
 {
@@ -723,15 +737,9 @@ int launch_last(harvest_ctx *ctx, StreamState *ss, void (*kernel)(P...), dim3 gr
         ctx->captured_work = true;
         return HARVEST_OK;
     }
-    const bool busy = ss->last_valid && hipEventQuery(ss->last) == hipErrorNotReady;
-    if (busy) {
-        (void)hipGetLastError();                    // "not ready" is an answer, not an error
-        hipExtLaunchKernelGGL(kernel, grid, block, 0, ss->s, nullptr, ss->last, 0, (P)args...);
-    } else hipLaunchKernelGGL(kernel, grid, block, 0, ss->s, (P)args...);
-    HIP_TRY(hipGetLastError());
-    if (!busy) HIP_TRY(hipEventRecord(ss->last, ss->s));
-    ss->last_valid = true;
-    return HARVEST_OK;
+    int rc = launch_with(ss->last, ss->s, kernel, grid, block, args...);
+    if (!rc) ss->last_valid = true;
+    return rc;
 }
 
 hipEvent_t prof_event(harvest_ctx *ctx)
@@ -875,6 +883,69 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     }
     ss->feedback_valid[cls] = true;
     return profile ? mark_last(ctx, ss) : HARVEST_OK;
+}
+
+// What a move of objects of class c has in common, from layer l0 on.
+MoveArgs move_args(const ClassState &c, uint32_t l0, uint32_t n_layers)
+{
+    const ClassDev cd = class_dev(c);
+    MoveArgs a{};
+    for (uint32_t p = 0; p < 2; ++p) {
+        a.host_base[p] = cd.pool[T_HOST][p] + l0 * cd.layer_stride[T_HOST];
+        a.cache_base[p] = cd.pool[T_CACHE][p] + l0 * cd.layer_stride[T_CACHE];
+        a.local_base[p] = cd.pool[T_LOCAL][p] + l0 * cd.layer_stride[T_LOCAL];
+    }
+    a.host_layer = cd.layer_stride[T_HOST]; a.cache_layer = cd.layer_stride[T_CACHE]; a.local_layer = cd.layer_stride[T_LOCAL];
+    a.chunk_bytes = c.cfg.chunk_bytes;
+    a.n_planes = c.cfg.n_planes;
+    a.n_layers = n_layers;
+    return a;
+}
+
+// Room for a list of n objects, for launch_move: none if it will travel with the launch.
+int reserve_move(harvest_ctx *ctx, StreamState *ss, size_t n, Hold &hold)
+{
+    if (n <= MOVE_INLINE) return HARVEST_OK;
+    int rc = ensure_ctl_cap(ctx, ss, n * sizeof(MoveRec));
+    return rc ? rc : acquire_staging(ctx, n * sizeof(MoveRec), &hold.st);
+}
+
+enum MoveWay { WITHIN_HBM, FROM_HOST, TO_HOST };
+
+// Enqueues the copies of `recs` on the stream; a device step with a roll-back (see DEV_TRY).
+int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &recs, MoveArgs a, MoveWay way, Staging *st)
+{
+    const bool in_args = recs.size() <= MOVE_INLINE;
+    MoveList list;
+    if (in_args) std::copy(recs.begin(), recs.end(), list.r);
+    else {
+        const size_t bytes = recs.size() * sizeof(MoveRec);
+        if (!ctx->no_device) memcpy(st->h, recs.data(), bytes);
+        const hipStream_t s = ss ? ss->s : nullptr;
+        DEV_TRY(hipMemcpyAsync(ss->ctl_buf, st->h, bytes, hipMemcpyHostToDevice, s));
+        if (int rc = release_after(ctx, st, s)) return rc;
+        if (!ctx->no_device) a.recs = (const MoveRec *)ss->ctl_buf;
+    }
+    if (fault_due()) return HARVEST_EHIP;
+    if (ctx->no_device) return HARVEST_OK;
+    const uint64_t items = (uint64_t)recs.size() * a.n_planes * a.n_layers;
+    const uint64_t tiles_hbm = items * tiles_per_chunk(a.chunk_bytes, 64 * 16);
+    if (way == WITHIN_HBM && tiles_hbm < (1ull << 32)) {       // a workgroup per 1 KiB tile, as in the gather
+        a.tiles_per_chunk = tiles_per_chunk(a.chunk_bytes, 64 * 16);
+        a.n_tiles = (uint32_t)tiles_hbm;
+        return launch_last(ctx, ss, in_args ? move_hbm<true> : move_hbm<false>, dim3(grid_for(tiles_hbm, MAX_GRID)), dim3(64), a, list);
+    }
+    // over PCIe (or more tiles than move_hbm counts): persistent workgroups, tiles counted out
+    const int unroll = way == TO_HOST ? 4 : 8;
+    a.tiles_per_chunk = tiles_per_chunk(a.chunk_bytes, WG * 16 * unroll);
+    const uint64_t tiles = items * a.tiles_per_chunk;
+    if (tiles >= 0xFFFFFFFFull) return HARVEST_EINVAL;         // 64 TiB
+    a.n_tiles = (uint32_t)tiles;
+    a.next = ss->next;
+    a.lease = way == WITHIN_HBM ? nullptr : ctx->d_lease;
+    const dim3 grid(grid_for(tiles, way == WITHIN_HBM ? ctx->ctl_grid : ctx->pcie_grid));
+    if (way == TO_HOST) return launch_last(ctx, ss, in_args ? move_pcie<true, 4, true> : move_pcie<false, 4, true>, grid, dim3(WG), a, list);
+    return launch_last(ctx, ss, in_args ? move_pcie<true, 8, false> : move_pcie<false, 8, false>, grid, dim3(WG), a, list);
 }
 
 int check_class(harvest_ctx *ctx, int cls)
@@ -1203,16 +1274,13 @@ static int place_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32_
     StreamState *ss = nullptr;
     if (!ctx->no_device && (rc = get_stream(ctx, stream, &ss))) return rc;
     hipStream_t s = ss ? ss->s : nullptr;
-    const size_t max_items = (size_t)n * c.cfg.n_planes * c.cfg.n_layers;
     Hold h_items, h_dir;
-    if (n) {
-        if ((rc = ensure_ctl_cap(ctx, ss, LIST_HEADER + max_items * sizeof(Item)))) return rc;
-        if ((rc = acquire_staging(ctx, LIST_HEADER + max_items * sizeof(Item), &h_items.st))) return rc;
-        if ((rc = acquire_staging(ctx, (size_t)n * (sizeof(uint64_t) + sizeof(uint32_t)), &h_dir.st))) return rc;
-    }
+    if ((rc = reserve_move(ctx, ss, n, h_items))) return rc;
+    if (n > DIR_INLINE && (rc = acquire_staging(ctx, (size_t)n * (sizeof(uint64_t) + sizeof(uint32_t)), &h_dir.st))) return rc;
     Undo undo(c);
     std::vector<uint32_t> moved;
-    std::vector<Item> items;
+    std::vector<MoveRec> recs;
+    const uint64_t slot_stride = class_dev(c).slot_stride[T_CACHE];
     std::vector<int> st_all(n, HARVEST_OK);
     for (uint32_t i = 0; i < n; ++i) {
         uint32_t id = ids[i];
@@ -1225,12 +1293,8 @@ static int place_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32_
             c.n_enospc++;
             undo.add(Undo::COUNTED_ENOSPC);
         } else {
-            for (uint32_t p = 0; p < c.cfg.n_planes; ++p)
-                for (uint32_t l = 0; l < c.cfg.n_layers; ++l) {
-                    uint64_t src = from ? from->plane[p] + ((uint64_t)l * from->stride + from->block[i]) * c.cfg.chunk_bytes
-                                        : c.addr(T_HOST, p, l, (uint64_t)c.host_slot[id]);
-                    items.push_back({ src, c.addr(T_CACHE, p, l, (uint64_t)slot) });
-                }
+            recs.push_back({ (from ? from->block[i] : (uint64_t)c.host_slot[id]) * c.cfg.chunk_bytes, NOWHERE,
+                             (uint64_t)slot * slot_stride | T_CACHE });
             const uint32_t old_gen = c.gen[id];
             c.tier[id] = T_CACHE; c.slot[id] = slot; c.gen[id] += 1;
             c.n_placed++;
@@ -1240,36 +1304,16 @@ static int place_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32_
         st_all[i] = st;
     }
     if (!moved.empty()) {
-        size_t bytes = LIST_HEADER + items.size() * sizeof(Item);
-        if (!ctx->no_device) {
-            memset(h_items.st->h, 0, LIST_HEADER);         // the copy kernel's tile counter
-            memcpy((char *)h_items.st->h + LIST_HEADER, items.data(), items.size() * sizeof(Item));
-        }
-        DEV_TRY(hipMemcpyAsync(ss->ctl_buf, h_items.st->h, bytes, hipMemcpyHostToDevice, s));
-        if ((rc = release_after(ctx, h_items.st, s))) return rc;
-        if (!ctx->no_device) {
-            const Item *d_items = (const Item *)((char *)ss->ctl_buf + LIST_HEADER);
-            const uint64_t tiles_hbm = (uint64_t)items.size() * tiles_per_chunk(c.cfg.chunk_bytes, HBM_WG * 16);
-            if (from && tiles_hbm < (1ull << 32)) {        // HBM to HBM: a workgroup per 1 KiB tile, as in the gather
-                hipLaunchKernelGGL(copy_items_hbm<HBM_WG>, dim3(grid_for(tiles_hbm, MAX_GRID)), dim3(HBM_WG), 0, s,
-                                   d_items, (uint32_t)items.size(), c.cfg.chunk_bytes,
-                                   tiles_per_chunk(c.cfg.chunk_bytes, HBM_WG * 16));
-            } else {                                       // over PCIe: a dozen persistent workgroups, tiles counted out
-                uint32_t tpc = tiles_per_chunk(c.cfg.chunk_bytes, TILE_HOST);
-                uint32_t grid = grid_for((uint64_t)items.size() * tpc, from ? ctx->ctl_grid : ctx->pcie_grid);
-                hipLaunchKernelGGL(copy_items, dim3(grid), dim3(WG), 0, s, d_items, (uint32_t)items.size(),
-                                   c.cfg.chunk_bytes, tpc, from ? (unsigned long long *)nullptr : (unsigned long long *)ss->ctl_buf,
-                                   from ? (const unsigned long long *)nullptr : (const unsigned long long *)ctx->d_lease);
-            }
-        }
-        DEV_TRY(hipGetLastError());
+        MoveArgs a = move_args(c, 0, c.cfg.n_layers);
+        for (uint32_t p = 0; p < 2; ++p) a.src_base[p] = from ? from->plane[p] : a.host_base[p];
+        a.src_layer = from ? from->stride * c.cfg.chunk_bytes : a.host_layer;
+        if ((rc = launch_move(ctx, ss, recs, a, from ? WITHIN_HBM : FROM_HOST, h_items.st))) return rc;
         // the new entries are written on the same stream, behind the copy: visible only once the bytes are in the slot,
         // and before anything enqueued on `stream` later
         bool committed = false;
         rc = publish(ctx, c, moved, s, false, h_dir.st, &committed);
         if (committed) undo.commit();
         if (rc) return rc;
-        if (!ctx->no_device && (rc = mark_last(ctx, ss))) return rc;
     }
     undo.commit();
     if (status) memcpy(status, st_all.data(), n * sizeof(int));
@@ -1362,7 +1406,7 @@ static int revoke_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32
         // what the call may have to allocate comes before any change: staging for the new entries and for the poison
         // list, one fresh event per stream that has work in flight
         Hold h_dir, h_fill;
-        if ((rc = acquire_staging(ctx, n_hit * (sizeof(uint64_t) + sizeof(uint32_t)), &h_dir.st))) return rc;
+        if (n_hit > DIR_INLINE && (rc = acquire_staging(ctx, n_hit * (sizeof(uint64_t) + sizeof(uint32_t)), &h_dir.st))) return rc;
         if (ctx->poison &&
             (rc = acquire_staging(ctx, n_hit * c.cfg.n_planes * c.cfg.n_layers * sizeof(Item), &h_fill.st)))
             return rc;
@@ -1979,16 +2023,15 @@ int harvest_evict(harvest_ctx *ctx, int cls, int layer, const harvest_obj *ids, 
     // as in harvest_place: what may have to be created or allocated comes before any change
     StreamState *ss = nullptr;
     if (!ctx->no_device && (rc = get_stream(ctx, stream, &ss))) return rc;
-    hipStream_t s = ss ? ss->s : nullptr;
+    const hipStream_t s = ss ? ss->s : nullptr;
     const uint32_t l0 = layer < 0 ? 0 : (uint32_t)layer, l1 = layer < 0 ? c.cfg.n_layers : (uint32_t)layer + 1;
-    const size_t max_items = (size_t)n * c.cfg.n_planes * (l1 - l0);
     Hold h_items, h_dir;
-    if ((rc = ensure_ctl_cap(ctx, ss, LIST_HEADER + max_items * sizeof(Item2)))) return rc;
-    if ((rc = acquire_staging(ctx, LIST_HEADER + max_items * sizeof(Item2), &h_items.st))) return rc;
-    if (n_demote && (rc = acquire_staging(ctx, n_demote * (sizeof(uint64_t) + sizeof(uint32_t)), &h_dir.st))) return rc;
-    const uint64_t src[2] = { (uint64_t)d_src0, (uint64_t)d_src1 };
-    std::vector<Item2> items;
-    items.reserve(max_items);
+    if ((rc = reserve_move(ctx, ss, n, h_items))) return rc;
+    if (n_demote > DIR_INLINE && (rc = acquire_staging(ctx, n_demote * (sizeof(uint64_t) + sizeof(uint32_t)), &h_dir.st))) return rc;
+    const ClassDev cd = class_dev(c);
+    std::vector<MoveRec> recs;
+    recs.reserve(n);
+    bool to_host = false;                       // lossy objects move between HBM pools only
     std::vector<uint32_t> demoted;
     Undo undo(c);
     // room for every lossy object that leaves local HBM, taken in request order before anything changes: all or nothing
@@ -2007,20 +2050,12 @@ int harvest_evict(harvest_ctx *ctx, int cls, int layer, const harvest_obj *ids, 
         bool demote = demote_flag && c.tier[id] == T_LOCAL;
         int64_t to_cache = -1;                  // a lossy object leaves local HBM for the cache tier: it has no host copy
         if (demote && c.host_slot[id] < 0) to_cache = room[n_room++];
-        for (uint32_t p = 0; p < c.cfg.n_planes; ++p)
-            for (uint32_t l = l0; l < l1; ++l) {
-                uint64_t li = layer < 0 ? l : 0;
-                Item2 it{};
-                it.src = src[p] + (li * src_layer_stride + src_block[i]) * c.cfg.chunk_bytes;
-                if (c.host_slot[id] >= 0) it.dst0 = c.addr(T_HOST, p, l, (uint64_t)c.host_slot[id]);
-                if (c.tier[id] == T_CACHE) it.dst1 = c.addr(T_CACHE, p, l, (uint64_t)c.slot[id]);
-                if (to_cache >= 0) it.dst1 = c.addr(T_CACHE, p, l, (uint64_t)to_cache);
-                if (c.tier[id] == T_LOCAL && !demote) {
-                    uint64_t d = c.addr(T_LOCAL, p, l, (uint64_t)c.slot[id]);
-                    if (d != it.src) it.dst1 = d;       // a source that already is the slot needs no copy
-                }
-                if (it.dst0 || it.dst1) items.push_back(it);
-            }
+        MoveRec r{ src_block[i] * c.cfg.chunk_bytes, NOWHERE, NOWHERE };
+        if (c.host_slot[id] >= 0) { r.dst0 = (uint64_t)c.host_slot[id] * c.cfg.chunk_bytes; to_host = true; }
+        const int64_t in_cache = c.tier[id] == T_CACHE ? c.slot[id] : to_cache;
+        if (in_cache >= 0) r.dst1 = (uint64_t)in_cache * cd.slot_stride[T_CACHE] | T_CACHE;
+        else if (c.tier[id] == T_LOCAL && !demote) r.dst1 = (uint64_t)c.slot[id] * c.cfg.chunk_bytes | T_LOCAL;
+        if (r.dst0 != NOWHERE || r.dst1 != NOWHERE) recs.push_back(r);
         c.n_evicted++;
         undo.add(Undo::COUNTED_EVICTED);
         if (demote) {
@@ -2035,32 +2070,11 @@ int harvest_evict(harvest_ctx *ctx, int cls, int layer, const harvest_obj *ids, 
             demoted.push_back(id);
         }
     }
-    if (!items.empty()) {
-        size_t bytes = LIST_HEADER + items.size() * sizeof(Item2);
-        if (!ctx->no_device) {
-            memset(h_items.st->h, 0, LIST_HEADER);         // the copy kernel's tile counter
-            memcpy((char *)h_items.st->h + LIST_HEADER, items.data(), items.size() * sizeof(Item2));
-        }
-        DEV_TRY(hipMemcpyAsync(ss->ctl_buf, h_items.st->h, bytes, hipMemcpyHostToDevice, s));
-        if ((rc = release_after(ctx, h_items.st, s))) return rc;
-        if (!ctx->no_device) {
-            const Item2 *d_items = (const Item2 *)((char *)ss->ctl_buf + LIST_HEADER);
-            bool to_host = false;                          // lossy objects move between HBM pools only
-            for (const Item2 &it : items) to_host |= it.dst0 != 0;
-            const uint64_t tiles_hbm = (uint64_t)items.size() * tiles_per_chunk(c.cfg.chunk_bytes, HBM_WG * 16);
-            if (!to_host && tiles_hbm < (1ull << 32)) {
-                hipLaunchKernelGGL(copy_items2_hbm<HBM_WG>, dim3(grid_for(tiles_hbm, MAX_GRID)), dim3(HBM_WG), 0, s,
-                                   d_items, (uint32_t)items.size(), c.cfg.chunk_bytes,
-                                   tiles_per_chunk(c.cfg.chunk_bytes, HBM_WG * 16));
-            } else {
-                uint32_t tpc = tiles_per_chunk(c.cfg.chunk_bytes, TILE_HOST);
-                uint32_t grid = grid_for((uint64_t)items.size() * tpc, to_host ? ctx->pcie_grid : ctx->ctl_grid);
-                hipLaunchKernelGGL(copy_items2, dim3(grid), dim3(WG), 0, s, d_items, (uint32_t)items.size(),
-                                   c.cfg.chunk_bytes, tpc, to_host ? (unsigned long long *)ss->ctl_buf : (unsigned long long *)nullptr,
-                                   to_host ? (const unsigned long long *)ctx->d_lease : (const unsigned long long *)nullptr);
-            }
-        }
-        DEV_TRY(hipGetLastError());
+    if (!recs.empty()) {
+        MoveArgs a = move_args(c, l0, l1 - l0);
+        a.src_base[0] = (uint64_t)d_src0; a.src_base[1] = (uint64_t)d_src1;
+        a.src_layer = src_layer_stride * c.cfg.chunk_bytes;
+        if ((rc = launch_move(ctx, ss, recs, a, to_host ? TO_HOST : WITHIN_HBM, h_items.st))) return rc;
     }
     // Without demotions the write-back itself is the commit point: once the copy is enqueued the bytes will change.
     bool committed = demoted.empty();
@@ -2068,7 +2082,6 @@ int harvest_evict(harvest_ctx *ctx, int cls, int layer, const harvest_obj *ids, 
     if (committed) undo.commit();
     if (rc) return rc;
     if (ctx->no_device) return HARVEST_OK;
-    if ((rc = mark_last(ctx, ss))) return rc;
     // A freed local slot may be handed out by the very next harvest_register.  Fetches enqueued through the library are
     // ordered behind the new entry, replays of recorded graphs are not: with recorded work around, the entry has to be
     // on the device before this call returns.

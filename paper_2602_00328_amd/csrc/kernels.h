@@ -24,10 +24,9 @@
 //                              flight per thread: enough compute units to keep the PCIe link full, and no more host reads
 //                              in flight than the link absorbs, because the rest would only stand in the HBM tier's way.
 //   gather_hm                : the same into a head-major working layout.
-//   copy_items, copy_items2, fill_items, dir_write : host-built lists - placement, write-back (one source, up to two
-//                              destinations), slot poisoning after revocation, directory publication; the _hbm forms
-//                              of the first three serve copies that stay inside HBM.  The forms that cross PCIe are a
-//                              dozen persistent workgroups whose tiles are counted out one at a time, and they stand
+//   move_pcie, move_hbm, fill_items, dir_write : placement, write-back (one source, up to two destinations), slot poisoning
+//                              after revocation, directory publication, from lists made on the host.  What crosses PCIe runs
+//                              as a dozen persistent workgroups whose tiles are counted out one at a time, and they stand
 //                              back while a fetch has announced that it needs the link (link_announce, yield_link).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -59,9 +58,29 @@ enum { T_HOST = 0, T_CACHE = 1, T_LOCAL = 2, T_NONE = 3 };
 //   src = byte offset of the chunk inside its tier's plane pool, tier in bits [1:0] (offsets are multiples of 16);
 //   dst = byte offset of the chunk inside the destination plane.
 struct Rec { uint64_t src, dst; };
-// Host-built lists carry absolute addresses.
+// A host-built list names chunks by absolute address (slot poisoning) ...
 struct Item { uint64_t src, dst; };
-struct Item2 { uint64_t src, dst0, dst1, pad; };
+// ... or whole objects (placement, write-back), whose chunks - every plane, every layer of the move - the kernel finds by itself:
+// byte offsets of plane 0, first layer of the move, from the bases in MoveArgs.  dst1 has its tier in bits [1:0].
+constexpr uint64_t NOWHERE = ~0ull;
+struct MoveRec { uint64_t src, dst0, dst1; };
+struct MoveArgs {
+    uint64_t src_base[2], host_base[2], cache_base[2], local_base[2];      // [plane], at the first layer of the move
+    uint64_t src_layer, host_layer, cache_layer, local_layer;              // layer strides
+    uint64_t chunk_bytes;
+    uint32_t n_planes, n_layers, tiles_per_chunk, n_tiles;
+    const MoveRec *recs;                                                   // null: the list travels with the launch (MoveList)
+    unsigned long long *next;                                              // tile counter of move_pcie
+    const unsigned long long *lease;
+};
+// Lists of up to this many objects / entries are kernel arguments; longer ones are copied to the device first.
+#ifdef HARVEST_FAULT_INJECTION
+constexpr uint32_t MOVE_INLINE = 2, DIR_INLINE = 2;      // the CPU tests' lists are short: they are to walk both ways
+#else
+constexpr uint32_t MOVE_INLINE = 80, DIR_INLINE = 128;
+#endif
+struct MoveList { MoveRec r[MOVE_INLINE]; };
+struct DirList { uint64_t entry[DIR_INLINE]; uint32_t id[DIR_INLINE]; };
 
 // per-fetch counters (uint32) and running totals (uint64) share these indices
 enum { C_REQ = 0, C_LOCAL, C_CACHE, C_HOST, C_LOST, C_INVALID, C_HBM_REQ, C_HOST_REQ, C_MISS, C_N = 16 };
@@ -937,82 +956,106 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
 // ---------------------------------------------------------------------------------------------------------
 // Host-built lists (absolute addresses).
 // ---------------------------------------------------------------------------------------------------------
-constexpr size_t LIST_HEADER = 16;       // a host-built list travels behind this many bytes, the first 8 of them the
-                                         // zeroed tile counter of the kernel that walks it
-// The tiles of a persistent copy.  next == nullptr: workgroup b takes tiles b, b + grid, b + 2 grid, ...  Otherwise the
-// tiles are counted out one at a time from *next (zero at launch): when something else is using the link as well, the
+// Placement and write-back.  The list has one record per object; which chunk a tile belongs to - object, plane, layer - is
+// worked out per tile.  Up to MOVE_INLINE records are kernel arguments: 64 objects of 32 layers and two planes were 4 096
+// addresses before, copied to the device by a memcpy of their own in front of the kernel (about 14 us on the stream).
+// A kernel argument that is indexed by a variable would be copied to scratch memory, hence the segment pointer.
+typedef const __attribute__((address_space(4))) MoveRec k_MoveRec;
+typedef const __attribute__((address_space(4))) DirList k_DirList;
+static_assert(sizeof(MoveArgs) % 8 == 0, "MoveList follows MoveArgs in the kernel's arguments");
+struct MoveChunk { uint64_t src, dst0, dst1; };         // addresses of one chunk; 0: nowhere
+template <bool INLINE>
+__device__ inline MoveChunk move_chunk(const MoveArgs &a, uint32_t item)
+{
+    const uint32_t per = a.n_planes * a.n_layers, obj = item / per, rest = item - obj * per;
+    const uint32_t plane = rest / a.n_layers, layer = rest - plane * a.n_layers;
+    MoveRec x;
+    if (INLINE) {
+        k_MoveRec *r = (k_MoveRec *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(MoveArgs));
+        x.src = r[obj].src; x.dst0 = r[obj].dst0; x.dst1 = r[obj].dst1;
+    } else x = a.recs[obj];
+    MoveChunk m;
+    m.src = (plane ? a.src_base[1] : a.src_base[0]) + layer * a.src_layer + x.src;
+    m.dst0 = x.dst0 == NOWHERE ? 0 : (plane ? a.host_base[1] : a.host_base[0]) + layer * a.host_layer + x.dst0;
+    const uint64_t base1 = (x.dst1 & 3) == T_CACHE ? (plane ? a.cache_base[1] : a.cache_base[0]) + layer * a.cache_layer
+                                                   : (plane ? a.local_base[1] : a.local_base[0]) + layer * a.local_layer;
+    m.dst1 = x.dst1 == NOWHERE ? 0 : base1 + (x.dst1 & ~(uint64_t)3);
+    if (m.dst1 == m.src) m.dst1 = 0;                    // a source that already is the slot needs no copy
+    return m;
+}
+
+// Over PCIe, either way: a few persistent workgroups (harvest_config.pcie_wgs) with U loads per thread in flight, their tiles
+// counted out one at a time from a.next: when something else is using the link as well, the
 // workgroups of one launch progress at very different rates (a 3.4-fold spread was measured), and with fixed shares
 // the launch ends with a few workgroups working off their backlog alone - a 906 MB placement beside a stream of
-// fetches took 106 ms that way.  Every thread of the workgroup gets the same tile number and leaves the loop together.
-template <typename F>
-__device__ inline void for_each_tile(unsigned long long *next, uint64_t n_tiles, const unsigned long long *lease, F body)
+// fetches took 106 ms that way.  The counter is zero at launch and again at the end: every workgroup draws one number
+// beyond the tiles, and the one that draws the last puts it back.  The next number is drawn while the tile is on its way.
+// Writes to the host are non-temporal, 16 KiB tiles: 16 MiB take 305.8 us (54.9 GB/s) against 316.7 with plain stores of
+// 32 KiB, 2 MiB 43 against 48.
+template <bool INLINE, int U, bool NT>
+__global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
 {
-    if (!next) {
-        for (uint64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) body(t);
-        return;
-    }
-    __shared__ unsigned long long s_tile;
-    for (;;) {
-        if (threadIdx.x == 0) {
-            yield_link(lease);                    // a fetch that is using the link goes first
-            s_tile = atomicAdd(next, 1ull);
-        }
-        __syncthreads();
-        const uint64_t t = s_tile;
-        __syncthreads();                          // all have read it before thread 0 writes the next one
-        if (t >= n_tiles) return;
-        body(t);
-    }
-}
-
-__global__ __launch_bounds__(WG) void copy_items(const Item *__restrict__ items, uint32_t n_items, uint64_t chunk_bytes,
-                                                 uint32_t tiles_per_chunk, unsigned long long *next,
-                                                 const unsigned long long *lease)
-{
-    for_each_tile(next, (uint64_t)n_items * tiles_per_chunk, lease, [&](uint64_t t) {
-        uint64_t it = t / tiles_per_chunk;
-        uint64_t off = (t - it * tiles_per_chunk) * TILE_HOST;
-        Item x = items[it];
-        copy_tile<WG, UNROLL_HOST, false>(x.src + off, x.dst + off, chunk_bytes - off, threadIdx.x);
-    });
-}
-
-// One source, one or two destinations (dst == 0: none): the write-back path reads each source byte once.
-__global__ __launch_bounds__(WG) void copy_items2(const Item2 *__restrict__ items, uint32_t n_items,
-                                                  uint64_t chunk_bytes, uint32_t tiles_per_chunk, unsigned long long *next,
-                                                  const unsigned long long *lease)
-{
-    constexpr uint32_t TILE = TILE_HOST;
-    for_each_tile(next, (uint64_t)n_items * tiles_per_chunk, lease, [&](uint64_t t) {
-        uint64_t it = t / tiles_per_chunk;
-        uint64_t off = (t - it * tiles_per_chunk) * TILE;
-        Item2 x = items[it];
-        uint64_t len = chunk_bytes - off;
-        if (len > TILE) len = TILE;
-        const u32x4 *s = reinterpret_cast<const u32x4 *>(x.src + off);
-        u32x4 *d0 = reinterpret_cast<u32x4 *>(x.dst0 + off);
-        u32x4 *d1 = reinterpret_cast<u32x4 *>(x.dst1 + off);
-        if (len == TILE) {                       // whole tile: all loads in flight, then the stores
-            u32x4 v[UNROLL_HOST];
+    constexpr uint32_t TILE = WG * 16 * U;
+    __shared__ unsigned long long s_tile[2];
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) { yield_link(a.lease); s_tile[0] = atomicAdd(a.next, 1ull); }
+    __syncthreads();
+    uint64_t t = s_tile[0];
+    for (uint32_t turn = 1; t < a.n_tiles; turn ^= 1) {
+        const uint32_t item = (uint32_t)t / a.tiles_per_chunk;
+        const uint64_t off = (uint64_t)((uint32_t)t - item * a.tiles_per_chunk) * TILE;
+        const MoveChunk m = move_chunk<INLINE>(a, item);
+        const u32x4 *s = reinterpret_cast<const u32x4 *>(m.src + off);
+        u32x4 *d0 = reinterpret_cast<u32x4 *>(m.dst0 + off), *d1 = reinterpret_cast<u32x4 *>(m.dst1 + off);
+        const uint64_t len = a.chunk_bytes - off;
+        if (len >= TILE) {                       // whole tile: all loads in flight, then the stores
+            u32x4 v[U];
 #pragma unroll
-            for (int i = 0; i < UNROLL_HOST; ++i) v[i] = ld16<false>(s + threadIdx.x + i * WG);
-            if (x.dst0) {
+            for (int i = 0; i < U; ++i) v[i] = ld16<false>(s + tid + i * WG);
+            if (tid == 0) { yield_link(a.lease); s_tile[turn] = atomicAdd(a.next, 1ull); }
+            if (m.dst0) {
 #pragma unroll
-                for (int i = 0; i < UNROLL_HOST; ++i) st16<false>(d0 + threadIdx.x + i * WG, v[i]);
+                for (int i = 0; i < U; ++i) st16<NT>(d0 + tid + i * WG, v[i]);
             }
-            if (x.dst1) {
+            if (m.dst1) {
 #pragma unroll
-                for (int i = 0; i < UNROLL_HOST; ++i) st16<false>(d1 + threadIdx.x + i * WG, v[i]);
+                for (int i = 0; i < U; ++i) st16<NT>(d1 + tid + i * WG, v[i]);
             }
         } else {
-            uint32_t n_vec = (uint32_t)(len >> 4);
-            for (uint32_t i = threadIdx.x; i < n_vec; i += WG) {
+            if (tid == 0) { yield_link(a.lease); s_tile[turn] = atomicAdd(a.next, 1ull); }
+            const uint32_t n_vec = (uint32_t)(len >> 4);
+            for (uint32_t i = tid; i < n_vec; i += WG) {
                 u32x4 v = ld16<false>(s + i);
-                if (x.dst0) st16<false>(d0 + i, v);
-                if (x.dst1) st16<false>(d1 + i, v);
+                if (m.dst0) st16<NT>(d0 + i, v);
+                if (m.dst1) st16<NT>(d1 + i, v);
             }
         }
-    });
+        __syncthreads();                         // two words in turn: nobody reads the one that is written next
+        t = s_tile[turn];
+    }
+    if (tid == 0 && t == (uint64_t)a.n_tiles + gridDim.x - 1) __hip_atomic_store(a.next, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Between HBM pools only (placement from a staged copy, demotion of lossy objects): the HBM-tier gather's shape - one wavefront
+// per workgroup, one 1 KiB tile each, non-temporal accesses (measured on 17 GB of staged experts: 6.30 TB/s, 4.99 TB/s in
+// the persistent form).
+template <bool INLINE>
+__global__ __launch_bounds__(64) void move_hbm(MoveArgs a, MoveList)
+{
+    constexpr uint32_t TILE = 64 * 16;
+    for (uint32_t t = blockIdx.x; t < a.n_tiles; t += gridDim.x) {
+        const uint32_t item = t / a.tiles_per_chunk;
+        const uint64_t off = (uint64_t)(t - item * a.tiles_per_chunk) * TILE;
+        const MoveChunk m = move_chunk<INLINE>(a, item);
+        const uint64_t len = a.chunk_bytes - off;
+        const uint32_t n_vec = (uint32_t)((len > TILE ? TILE : len) >> 4);
+        if (threadIdx.x < n_vec) {
+            u32x4 v = ld16<true>(reinterpret_cast<const u32x4 *>(m.src + off) + threadIdx.x);
+            if (m.dst0) st16<true>(reinterpret_cast<u32x4 *>(m.dst0 + off) + threadIdx.x, v);
+            if (m.dst1) st16<true>(reinterpret_cast<u32x4 *>(m.dst1 + off) + threadIdx.x, v);
+        }
+        if (a.n_tiles - t <= gridDim.x) break;
+    }
 }
 
 __global__ __launch_bounds__(WG) void fill_items(const Item *__restrict__ items, uint32_t n_items, uint64_t chunk_bytes,
@@ -1032,46 +1075,8 @@ __global__ __launch_bounds__(WG) void fill_items(const Item *__restrict__ items,
     }
 }
 
-// The same three between HBM pools only (placement from a staged copy, poisoning, demotion of lossy objects): nothing
-// crosses PCIe, so they take the HBM-tier gather's shape - one wavefront per workgroup, one 1 KiB tile each,
-// non-temporal accesses - instead of the few fat persistent workgroups that suit the link (measured on 17 GB of
-// staged experts: 4.99 TB/s in the persistent form).  Tile numbers are 32-bit: the host checks n_items * tiles_per_chunk.
-template <int NTHR>
-__global__ __launch_bounds__(NTHR) void copy_items_hbm(const Item *__restrict__ items, uint32_t n_items,
-                                                       uint64_t chunk_bytes, uint32_t tiles_per_chunk)
-{
-    constexpr uint32_t TILE = NTHR * 16;
-    uint32_t n_tiles = n_items * tiles_per_chunk;
-    for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        uint32_t it = t / tiles_per_chunk;
-        uint64_t off = (uint64_t)(t - it * tiles_per_chunk) * TILE;
-        Item x = items[it];
-        copy_tile<NTHR, 1, true>(x.src + off, x.dst + off, chunk_bytes - off, threadIdx.x);
-        if (n_tiles - t <= gridDim.x) break;
-    }
-}
-
-template <int NTHR>
-__global__ __launch_bounds__(NTHR) void copy_items2_hbm(const Item2 *__restrict__ items, uint32_t n_items,
-                                                        uint64_t chunk_bytes, uint32_t tiles_per_chunk)
-{
-    constexpr uint32_t TILE = NTHR * 16;
-    uint32_t n_tiles = n_items * tiles_per_chunk;
-    for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        uint32_t it = t / tiles_per_chunk;
-        uint64_t off = (uint64_t)(t - it * tiles_per_chunk) * TILE;
-        Item2 x = items[it];
-        uint64_t len = chunk_bytes - off;
-        uint32_t n_vec = (uint32_t)((len > TILE ? TILE : len) >> 4);
-        if (threadIdx.x < n_vec) {
-            u32x4 v = ld16<true>(reinterpret_cast<const u32x4 *>(x.src + off) + threadIdx.x);
-            if (x.dst0) st16<true>(reinterpret_cast<u32x4 *>(x.dst0 + off) + threadIdx.x, v);
-            if (x.dst1) st16<true>(reinterpret_cast<u32x4 *>(x.dst1 + off) + threadIdx.x, v);
-        }
-        if (n_tiles - t <= gridDim.x) break;
-    }
-}
-
+// The same with the gather's shape: one wavefront per workgroup, one 1 KiB tile each.  Tile numbers are 32-bit: the host
+// checks n_items * tiles_per_chunk.
 template <int NTHR>
 __global__ __launch_bounds__(NTHR) void fill_items_hbm(const Item *__restrict__ items, uint32_t n_items,
                                                        uint64_t chunk_bytes, uint32_t tiles_per_chunk, uint32_t pattern)
@@ -1089,11 +1094,17 @@ __global__ __launch_bounds__(NTHR) void fill_items_hbm(const Item *__restrict__ 
     }
 }
 
+// Directory edits: from a host-built list, or (up to DIR_INLINE of them) from the kernel's arguments.
 __global__ __launch_bounds__(WG) void dir_write(uint64_t *dir, const uint32_t *__restrict__ ids,
                                                 const uint64_t *__restrict__ entries, uint32_t n)
 {
     uint32_t i = blockIdx.x * WG + threadIdx.x;
     if (i < n) dir[ids[i]] = entries[i];
+}
+__global__ __launch_bounds__(DIR_INLINE) void dir_write_inline(uint64_t *dir, uint64_t n, DirList)
+{
+    k_DirList *l = (k_DirList *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + 16);
+    if (threadIdx.x < n) dir[l->id[threadIdx.x]] = l->entry[threadIdx.x];
 }
 
 // harvest_fetch_kv_static's counters for a fetch that had no table cell and ran no kernel.

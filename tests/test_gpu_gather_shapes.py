@@ -143,3 +143,48 @@ def test_static_fetch_hands_out_counters_and_misses_in_order(lens, width):
     rig.h.fetch_kv_static(0, empty, dn, k, v, df, cap, info, miss)
     assert info.tolist() == [0] * 8
     rig.h.close()
+
+
+@pytest.mark.parametrize("n_planes", [1, 2])
+@pytest.mark.parametrize("chunk", [16, 1040, 16384, 32768 + 48])
+@pytest.mark.parametrize("n", [1, 80, 81, 128, 129])
+def test_moves_with_and_without_a_list_on_the_device(n_planes, chunk, n):
+    """place, place_from and evict of as many objects as travel with a launch, and one more; tiles of 1, 16 and 32 KiB."""
+    layers, rng = 2, np.random.default_rng(n)
+    h = B.Harvest(kv=B.ClassSpec(n_layers=layers, n_planes=n_planes, chunk_bytes=chunk, max_objects=n + 3, n_host_slots=n + 3,
+                                 n_cache_slots=n, n_local_slots=3))
+    dev = lambda a: torch.from_numpy(a).cuda()
+    host_slots = rng.permutation(n + 3).astype(np.int64)
+    h.register(B.KV, n, host_slots[:n])
+    local = h.register(B.KV, 3, host_slots[n:], tier=B.LOCAL)
+    bytes_of = lambda: rng.integers(0, 256, (n_planes, layers, n + 5, chunk), dtype=np.uint8)
+    host = lambda: np.stack([h.host_plane(B.KV, p) for p in range(n_planes)])
+    pool = lambda tier: np.stack([h.dev_plane(B.KV, tier, p).cpu().numpy() for p in range(n_planes)])
+    for p in range(n_planes):
+        h.host_plane(B.KV, p)[:] = rng.integers(0, 256, (layers, n + 3, chunk), dtype=np.uint8)
+    ids, block = rng.permutation(n), rng.permutation(n + 5)[:n]
+    assert (h.place(B.KV, ids) == B.OK).all()                             # slots are handed out lowest first
+    torch.cuda.synchronize()
+    assert np.array_equal(pool(B.CACHE), host()[:, :, host_slots[ids]])
+    h.revoke(B.KV, ids)
+    src = bytes_of()
+    d = [dev(x) for x in src] + [None]
+    assert (h.place_from(B.KV, ids, d[0], d[1], block, n + 5) == B.OK).all()
+    torch.cuda.synchronize()
+    assert np.array_equal(pool(B.CACHE), src[:, :, block])
+    # write-back of all layers, then of one, for cached objects and local ones (their slots are written through as well)
+    every, where = np.concatenate([ids, local[:2]]), rng.permutation(n + 5)[:n + 2]
+    want_host, want_cache, want_local = host(), pool(B.CACHE), pool(B.LOCAL)
+    for layer in (-1, 1):
+        src = bytes_of()
+        d = [dev(x) for x in src] + [None]
+        h.evict(B.KV, layer, every, d[0], d[1], where, n + 5)
+        torch.cuda.synchronize()
+        for at in range(layers) if layer < 0 else [layer]:
+            new = src[:, at if layer < 0 else 0][:, where]
+            want_host[:, at, host_slots[np.concatenate([ids, n + np.arange(2)])]] = new
+            want_cache[:, at] = new[:, :n]
+            want_local[:, at, :2] = new[:, n:]
+        assert np.array_equal(host(), want_host)
+        assert np.array_equal(pool(B.CACHE), want_cache) and np.array_equal(pool(B.LOCAL), want_local)
+    h.close()
