@@ -899,6 +899,7 @@ MoveArgs move_args(const ClassState &c, uint32_t l0, uint32_t n_layers)
     a.chunk_bytes = c.cfg.chunk_bytes;
     a.n_planes = c.cfg.n_planes;
     a.n_layers = n_layers;
+    a.order = c.seg ? ORDER_OBJ_LAYER_PLANE : c.adjacent ? ORDER_LAYER_OBJ_PLANE : ORDER_PLANE_LAYER_OBJ;
     return a;
 }
 
@@ -916,6 +917,7 @@ enum MoveWay { WITHIN_HBM, FROM_HOST, TO_HOST };
 int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &recs, MoveArgs a, MoveWay way, Staging *st)
 {
     const bool in_args = recs.size() <= MOVE_INLINE;
+    a.n_obj = (uint32_t)recs.size();
     MoveList list;
     if (in_args) std::copy(recs.begin(), recs.end(), list.r);
     else {

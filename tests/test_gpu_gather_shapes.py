@@ -145,14 +145,14 @@ def test_static_fetch_hands_out_counters_and_misses_in_order(lens, width):
     rig.h.close()
 
 
-@pytest.mark.parametrize("n_planes", [1, 2])
+@pytest.mark.parametrize("n_planes,flags", [(1, 0), (2, 0), (2, B.FLAG_CACHE_PLANES_ADJACENT)])
 @pytest.mark.parametrize("chunk", [16, 1040, 16384, 32768 + 48])
 @pytest.mark.parametrize("n", [1, 80, 81, 128, 129])
-def test_moves_with_and_without_a_list_on_the_device(n_planes, chunk, n):
+def test_moves_with_and_without_a_list_on_the_device(n_planes, flags, chunk, n):
     """place, place_from and evict of as many objects as travel with a launch, and one more; tiles of 1, 16 and 32 KiB."""
     layers, rng = 2, np.random.default_rng(n)
     h = B.Harvest(kv=B.ClassSpec(n_layers=layers, n_planes=n_planes, chunk_bytes=chunk, max_objects=n + 3, n_host_slots=n + 3,
-                                 n_cache_slots=n, n_local_slots=3))
+                                 n_cache_slots=n, n_local_slots=3), flags=flags)
     dev = lambda a: torch.from_numpy(a).cuda()
     host_slots = rng.permutation(n + 3).astype(np.int64)
     h.register(B.KV, n, host_slots[:n])
