@@ -1614,7 +1614,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
                               *(volatile uint32_t *)&ss->h_feedback[HARVEST_N_CLASSES + HARVEST_KV];
         if (live < total) dead_tiles = (total - live) * tpc * c.cfg.n_planes * n_layers;
     }
-    if (!ctx->general_fetch && !head_major && n_layers <= MAX_GRID_Y && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
+    if (!ctx->general_fetch && !head_major && n_layers < MAX_GRID_Y && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
         total * tpc * n_layers <= (1ull << 31) && dead_tiles <= DEAD_TILES) {
         GatherArgs ga{};
         const ClassDev cd = class_dev(c);
@@ -1626,14 +1626,19 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         for (int t = 0; t < 3; ++t) ga.layer_stride[t] = cd.layer_stride[t];
         ga.dst_base[0] = (uint64_t)d_dst_k; ga.dst_base[1] = (uint64_t)d_dst_v;
         ga.dst_step = dst_layer_stride; ga.n_rep = n_layers;
-        ga.chunk_bytes = c.cfg.chunk_bytes; ga.tiles_per_chunk = tpc; ga.n_planes = c.cfg.n_planes;
-        ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, 128) : 0;         // WG threads with half the loads
+        ga.chunk_bytes = c.cfg.chunk_bytes; ga.n_planes = c.cfg.n_planes;
+        const uint32_t nthr = total <= 64 * ROUND ? 64 : WG;
+        ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16);
+        ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr / 2) : 0;                // with half of HOST_LOADS each
+        ga.hbm_wgs = (uint32_t)total * ga.tiles_per_chunk;
         SmallBooks books{ lists.miss, cnt, info, ctx->d_totals + HARVEST_KV * C_N, ss->d_feedback + HARVEST_KV,
                           ss->d_feedback + HARVEST_N_CLASSES + HARVEST_KV, c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr };
-        const dim3 grid(ga.n_host + 1 + (uint32_t)(total * tpc), c.cfg.n_planes, n_layers);
-        if ((rc = launch_last(ctx, ss, c.cfg.n_planes == 2 ? fetch_kv_small<2> : fetch_kv_small<1>, grid, dim3(WG), cd, layer,
-                              d_block_table, d_n_blocks, (uint32_t)total, max_blocks, d_seq_dst_block, dst_capacity_blocks, ga,
-                              books)))
+        const uint32_t head = ga.n_host + 1;
+        const dim3 grid(n_layers > 1 ? std::max(ga.hbm_wgs, head) : ga.hbm_wgs + head, c.cfg.n_planes, n_layers > 1 ? n_layers + 1 : 1);
+        auto kernel = c.cfg.n_planes == 2 ? (nthr == 64 ? fetch_kv_small<2, 64> : fetch_kv_small<2, WG>)
+                                          : (nthr == 64 ? fetch_kv_small<1, 64> : fetch_kv_small<1, WG>);
+        if ((rc = launch_last(ctx, ss, kernel, grid, dim3(nthr), cd, layer, d_block_table, d_n_blocks, (uint32_t)total, max_blocks,
+                              d_seq_dst_block, dst_capacity_blocks, ga, books)))
             return rc;
         ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
         ss->feedback_valid[HARVEST_KV] = true;

@@ -696,7 +696,9 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
 
 // The whole KV fetch in one kernel, for small block tables (token-major layout).  A fetch of a few blocks is made of launch
 // gaps, not of bytes.  blockIdx.y is the plane, blockIdx.z counts consecutive layers (an object has the same slot in every
-// layer): layer + z is read, dst_step * z further into the destination is written.  blockIdx.x says what a workgroup does:
+// layer): layer + z is read, dst_step * z further into the destination is written.  NTHR is 256, or 64 for tables of up to 64 *
+// ROUND cells, which a single wavefront walks at once and whose tiles are a little faster as workgroups of one (16 blocks of 32
+// layers: 14.5 us with 256, 13.1 with 64).  blockIdx.x says what a workgroup does:
 //
 //   the first n_host  walk the table, list the host's cells in LDS and read them over PCIe, all planes and layers, two loads in
 //                     flight per thread (see host_tier for why so few): 102 of 256 blocks of 2 x 32 KiB from the host take
@@ -704,7 +706,7 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
 //                     the link together: 131 us.
 //   the next one      walks the table too and keeps the books: counters, and the miss list in request order.  No atomics on
 //                     shared counters (a thousand of them on one address take longer than the copy), nothing to zero.
-//   the others        copy a 4 KiB tile each if their cell's block is in HBM: nothing is compacted, so the grid covers the padded
+//   the others        copy a tile of 16 bytes a thread if their cell's block is in HBM: nothing is compacted, so the grid covers the padded
 //                     table - which is why this is for small tables only.  Resolving the cell in every workgroup costs
 //                     little bandwidth (1 750 blocks of 2 x 16 KiB: 5.77 TB/s against 6.00 from a list, whose making
 //                     takes longer than that saves).  Non-temporal accesses: on blocks that are in no cache 1 000 take 23.4 us
@@ -722,15 +724,19 @@ struct SmallBooks {
 
 constexpr uint32_t ROUND = 2;            // cells a thread looks up at a time when a workgroup walks the table
 
-template <int PLANES>
-__global__ __launch_bounds__(WG, 8) void fetch_kv_small(ClassDev c, uint32_t layer, const int32_t *__restrict__ table,
+template <int PLANES, int NTHR>
+__global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t layer, const int32_t *__restrict__ table,
                                                         const int32_t *__restrict__ n_blocks, uint32_t total,
                                                         uint32_t max_blocks, const uint64_t *__restrict__ seq_dst_block,
                                                         uint64_t dst_cap, GatherArgs a, SmallBooks books)
 {
     const uint32_t tpc = a.tiles_per_chunk, tid = threadIdx.x;
-    if (blockIdx.x > a.n_host) {
-        const uint32_t t = blockIdx.x - a.n_host - 1, r = t / tpc, k = t - r * tpc, plane = blockIdx.y;
+    // several layers: blockIdx.z == 0 is a slice of its own for the head workgroups, not n_host + 1 idle ones in every layer
+    const bool sliced = a.n_rep > 1, head = sliced ? blockIdx.z == 0 : blockIdx.x <= a.n_host;
+    if (!head) {
+        const uint32_t t = sliced ? blockIdx.x : blockIdx.x - a.n_host - 1, z = sliced ? blockIdx.z - 1 : 0;
+        if (sliced && t >= a.hbm_wgs) return;                      // (the head slice is the wider one)
+        const uint32_t r = t / tpc, k = t - r * tpc, plane = blockIdx.y;
         const uint32_t s = r / max_blocks, j = r - s * max_blocks;
         const int32_t nb = n_blocks[s], b = table[r];              // as resolve_cell, but out at the first answer
         const uint64_t dst_chunk = seq_dst_block[s] + j;
@@ -738,25 +744,26 @@ __global__ __launch_bounds__(WG, 8) void fetch_kv_small(ClassDev c, uint32_t lay
         const uint64_t e = c.dir[b];
         const int tier = (int)entry_tier(e);
         if ((tier != T_CACHE && tier != T_LOCAL) || entry_slot(e) >= slots_of(c, tier)) return;
-        const uint64_t off = (uint64_t)k * TILE_4K;
-        const uint64_t src = src_base_of(a, (uint32_t)tier, plane) + chunk_offset(c, tier, layer + blockIdx.z, entry_slot(e)) + off;
-        const uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + blockIdx.z * a.dst_step + dst_chunk * c.chunk_bytes + off;
-        copy_tile<WG, 1, true>(src, dst, a.chunk_bytes - off, tid);
+        const uint64_t off = (uint64_t)k * (NTHR * 16);
+        const uint64_t src = src_base_of(a, (uint32_t)tier, plane) + chunk_offset(c, tier, layer + z, entry_slot(e)) + off;
+        const uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + z * a.dst_step + dst_chunk * c.chunk_bytes + off;
+        copy_tile<NTHR, 1, true>(src, dst, a.chunk_bytes - off, tid);
         return;
     }
-    if (blockIdx.y | blockIdx.z) return;
+    if (blockIdx.y || blockIdx.x > a.n_host) return;
+    constexpr uint32_t WAVES_N = NTHR / 64;
     const bool keeper = blockIdx.x == a.n_host;
     const uint32_t wave = tid >> 6;
-    __shared__ Rec s_list[WG * ROUND];               // the round's cells on the host
-    __shared__ uint32_t s_sum[ROUND * WAVES];
+    __shared__ Rec s_list[NTHR * ROUND];               // the round's cells on the host
+    __shared__ uint32_t s_sum[ROUND * WAVES_N];
     __shared__ uint32_t s_cnt[C_N];
     uint32_t n[6] = { 0, 0, 0, 0, 0, 0 };            // requests, local, cache, host, lost, invalid, of this wavefront
     uint32_t n_miss = 0;
     if (tid < C_N) s_cnt[tid] = 0;
     Ask next[ROUND];
 #pragma unroll
-    for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask_cell(table, n_blocks, max_blocks, seq_dst_block, i * WG + tid, total);
-    for (uint32_t first = 0; first < total; first += WG * ROUND) {
+    for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask_cell(table, n_blocks, max_blocks, seq_dst_block, i * NTHR + tid, total);
+    for (uint32_t first = 0; first < total; first += NTHR * ROUND) {
         int tier[ROUND];
         Rec rec[ROUND];
         Ask now[ROUND];
@@ -768,7 +775,7 @@ __global__ __launch_bounds__(WG, 8) void fetch_kv_small(ClassDev c, uint32_t lay
         }
 #pragma unroll
         for (uint32_t i = 0; i < ROUND; ++i)
-            next[i] = ask_cell(table, n_blocks, max_blocks, seq_dst_block, first + (ROUND + i) * WG + tid, total);
+            next[i] = ask_cell(table, n_blocks, max_blocks, seq_dst_block, first + (ROUND + i) * NTHR + tid, total);
         uint32_t rank[ROUND];                        // among the round's listed cells, in cell order: the host's, or the missed ones
 #pragma unroll
         for (uint32_t i = 0; i < ROUND; ++i) {
@@ -781,20 +788,20 @@ __global__ __launch_bounds__(WG, 8) void fetch_kv_small(ClassDev c, uint32_t lay
             rec[i].dst = dst_chunk * c.chunk_bytes;
             uint32_t in_wave;
             rank[i] = wave_rank(tier[i] == T_HOST || (keeper && tier[i] == T_NONE), in_wave);
-            if (lane_id() == 0) s_sum[i * WAVES + wave] = in_wave;
+            if (lane_id() == 0) s_sum[i * WAVES_N + wave] = in_wave;
         }
         __syncthreads();
         uint32_t listed = 0;
 #pragma unroll
-        for (uint32_t k = 0; k < ROUND * WAVES; ++k) {
+        for (uint32_t k = 0; k < ROUND * WAVES_N; ++k) {
             const uint32_t before = listed;
             listed += s_sum[k];
-            if ((k & (WAVES - 1)) == wave) rank[k / WAVES] += before;
+            if ((k & (WAVES_N - 1)) == wave) rank[k / WAVES_N] += before;
         }
         if (keeper) {
 #pragma unroll
             for (uint32_t i = 0; i < ROUND; ++i) {
-                if (tier[i] == T_HOST || tier[i] == T_NONE) books.miss_idx[n_miss + rank[i]] = first + i * WG + tid;
+                if (tier[i] == T_HOST || tier[i] == T_NONE) books.miss_idx[n_miss + rank[i]] = first + i * NTHR + tid;
                 const bool pred[6] = { tier[i] >= 0, tier[i] == T_LOCAL, tier[i] == T_CACHE, tier[i] == T_HOST, tier[i] == T_NONE, tier[i] == 4 };
 #pragma unroll
                 for (int k = 0; k < 6; ++k) n[k] += (uint32_t)__popcll(__ballot(pred[k]));
@@ -815,7 +822,7 @@ __global__ __launch_bounds__(WG, 8) void fetch_kv_small(ClassDev c, uint32_t lay
                     bool act[U];
 #pragma unroll
                     for (int i = 0; i < U; ++i) {    // lanes beyond a chunk's end re-read its first bytes and store nothing
-                        const uint32_t gi = g + i < n_tiles ? g + i : g, idx = gi / tpc, u = (gi - idx * tpc) * WG + tid;
+                        const uint32_t gi = g + i < n_tiles ? g + i : g, idx = gi / tpc, u = (gi - idx * tpc) * NTHR + tid;
                         const Rec x = s_list[idx];
                         act[i] = g + i < n_tiles && u < chunk_units;
                         const uint64_t off = act[i] ? (uint64_t)u * 16 : 0, at = x.src + s_off + off;

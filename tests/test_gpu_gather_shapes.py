@@ -97,7 +97,7 @@ def test_again_counts_its_requests(host_every, local_every):
 
 
 @pytest.mark.parametrize("n_planes", [1, 2])
-@pytest.mark.parametrize("lens,width", [([1], 1), ([255], 255), ([256, 0], 256), ([200, 55, 257], 257), ([3, 510], 513), ([0, 0], 600),
+@pytest.mark.parametrize("lens,width", [([1], 1), ([60, 62], 64), ([64, 0], 64), ([50, 79], 129), ([255], 255), ([256, 0], 256), ([200, 55, 257], 257), ([3, 510], 513), ([0, 0], 600),
                                         ([1, 2, 0, 5], 1024)])
 def test_one_kernel_fetch_at_the_edges_of_its_rounds(n_planes, lens, width):
     """Tables of one cell up to several rounds of 512, twice: the second call of a mostly empty table takes the general path."""
