@@ -25,6 +25,7 @@
 #include <memory>
 #include <mutex>
 #include <set>
+#include <type_traits>
 #include <unordered_set>
 #include <vector>
 
@@ -423,6 +424,11 @@ bool is_capturing(hipStream_t s)
     return st != hipStreamCaptureStatusNone;
 }
 
+// Latest-work events only ever answer whether a kernel has ended (the host waits for them before it frees slots): no
+// system-scope fence comes with them.  With it, as a gather's completion signal, the compaction in front of the gather ran 0.9 us
+// longer and the gather 2 to 4 us (caches emptied once more): 6 806 blocks in two layers 297.2 against 293.1 us.
+constexpr unsigned LATEST_WORK = hipEventDisableTiming | hipEventDisableSystemFence;
+
 // Releases what a caller stream's state owns (any part of it may be missing); the stream's work must have finished.
 void free_stream_state(StreamState *ss)
 {
@@ -443,8 +449,9 @@ void free_stream_state(StreamState *ss)
 int init_stream_state(StreamState *ss)
 {
     HIP_TRY(hipStreamCreateWithFlags(&ss->side, hipStreamNonBlocking));
-    for (hipEvent_t *e : { &ss->fork, &ss->join, &ss->last })
+    for (hipEvent_t *e : { &ss->fork, &ss->join })
         HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&ss->last, LATEST_WORK));
     const size_t cnt_bytes = HARVEST_N_CLASSES * C_N * sizeof(uint32_t);
     HIP_TRY(hipMalloc(&ss->cnt_block, cnt_bytes + sizeof *ss->next));
     HIP_TRY(hipMemset(ss->cnt_block, 0, cnt_bytes + sizeof *ss->next));
@@ -597,7 +604,7 @@ uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t
 
 // one workgroup per tile up to here; beyond, the kernels loop.  Kept below 2^32 threads per launch dimension.
 constexpr uint32_t MAX_GRID = 0xFFFFFFFFu / WG;
-constexpr uint32_t MAX_GRID_Y = 65535;
+constexpr uint32_t MAX_GRID_Z = 65535;
 
 uint32_t grid_for(uint64_t n_tiles, uint32_t max_grid)
 {
@@ -815,7 +822,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
         serial = serial || std::max(us_hbm, us_host) < 35.0 || std::min(us_hbm, us_host) < 8.0;
     }
     const uint32_t host_wgs = host_tier ? host_workgroups(ctx, hm ? 128 : nthr) : 0;   // head-major: 256 threads with half the loads
-    const uint32_t max_wgs = (MAX_GRID - host_wgs) / (fold ? 1 : planes);
+    const uint32_t max_wgs = MAX_GRID - host_wgs;
     const uint32_t hbm_wgs = grid_for(fold ? want * planes : want, ctx->gather_grid ? std::min(ctx->gather_grid, max_wgs) : max_wgs);
     GatherBooks books{};
     books.fb_hbm = ss->d_feedback + cls;
@@ -825,7 +832,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     auto launch = [&](uint32_t n_host, uint32_t n_hbm, hipStream_t s, hipEvent_t begin, hipEvent_t end) -> int {
         ga.n_host = n_host;
         ga.hbm_wgs = n_hbm;
-        const dim3 g(n_host + n_hbm * (fold ? 1 : planes), n_hbm ? ga.n_rep : 1);
+        const dim3 g(n_host + n_hbm, n_hbm && !fold ? planes : 1, n_hbm ? ga.n_rep : 1);
         const Rec *l_hbm = lists.hbm, *l_host = lists.host;
         const uint32_t *cnt = lists.cnt;
         if (hm) {
@@ -834,9 +841,13 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
             hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, l_host, cnt, ga, *hm, books);
         } else {
             auto pick = [&](auto k64, auto k128, auto k256) { return nthr == 64 ? k64 : (nthr == 128 ? k128 : k256); };
-            auto kernel = fold ? pick(gather<64, 2, true>, gather<128, 2, true>, gather<256, 2, true>)
-                        : planes == 2 ? pick(gather<64, 2, false>, gather<128, 2, false>, gather<256, 2, false>)
-                                      : pick(gather<64, 1, false>, gather<128, 1, false>, gather<256, 1, false>);
+            auto of = [&](auto multi) {
+                constexpr bool M = decltype(multi)::value;
+                return fold ? pick(gather<64, 2, true, M>, gather<128, 2, true, M>, gather<256, 2, true, M>)
+                     : planes == 2 ? pick(gather<64, 2, false, M>, gather<128, 2, false, M>, gather<256, 2, false, M>)
+                                   : pick(gather<64, 1, false, M>, gather<128, 1, false, M>, gather<256, 1, false, M>);
+            };
+            auto kernel = ga.n_rep > 1 ? of(std::true_type{}) : of(std::false_type{});
             if (!begin) return launch_last(ctx, ss, kernel, g, dim3(nthr), l_hbm, l_host, cnt, ga, books);
             hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, l_host, cnt, ga, books);
         }
@@ -844,12 +855,12 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
         return HARVEST_OK;
     };
     int rc;
-    for (uint32_t first = 0; first < n_rep; first += ga.n_rep) {          // layers are the grid's y dimension
-        ga.n_rep = std::min(n_rep - first, MAX_GRID_Y);
+    for (uint32_t first = 0; first < n_rep; first += ga.n_rep) {          // layers are the grid's z dimension
+        ga.n_rep = std::min(n_rep - first, MAX_GRID_Z);
         if (first) {
             for (int t = 0; t < 3; ++t)
-                for (uint32_t p = 0; p < 2; ++p) ga.src_base[t][p] += (uint64_t)MAX_GRID_Y * ga.layer_stride[t];
-            for (uint32_t p = 0; p < 2; ++p) ga.dst_base[p] += (uint64_t)MAX_GRID_Y * dst_step;
+                for (uint32_t p = 0; p < 2; ++p) ga.src_base[t][p] += (uint64_t)MAX_GRID_Z * ga.layer_stride[t];
+            for (uint32_t p = 0; p < 2; ++p) ga.dst_base[p] += (uint64_t)MAX_GRID_Z * dst_step;
             books.totals = nullptr;
         }
         if (!profile) {
@@ -1006,7 +1017,7 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
         if (rc) return rc;
         for (StreamState &ss : ctx->fixed_streams) {
             ss.fixed = true;
-            HIP_TRY(hipEventCreateWithFlags(&ss.last, hipEventDisableTiming));
+            HIP_TRY(hipEventCreateWithFlags(&ss.last, LATEST_WORK));
             HIP_TRY(hipHostMalloc((void **)&ss.h_feedback, 64, hipHostMallocDefault));
             memset(ss.h_feedback, 0, 64);
             HIP_TRY(hipHostGetDevicePointer((void **)&ss.d_feedback, ss.h_feedback, 0));
@@ -1423,7 +1434,7 @@ static int revoke_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32
             for (size_t i = 0; i < busy.size(); ++i) {
                 hipEvent_t e = nullptr;
                 if (!ctx->evt_pool.empty()) { e = ctx->evt_pool.back(); ctx->evt_pool.pop_back(); }
-                else HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+                else HIP_TRY(hipEventCreateWithFlags(&e, LATEST_WORK));
                 fresh.push_back(e);
             }
         // 1. invalidate
@@ -1614,7 +1625,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
                               *(volatile uint32_t *)&ss->h_feedback[HARVEST_N_CLASSES + HARVEST_KV];
         if (live < total) dead_tiles = (total - live) * tpc * c.cfg.n_planes * n_layers;
     }
-    if (!ctx->general_fetch && !head_major && n_layers < MAX_GRID_Y && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
+    if (!ctx->general_fetch && !head_major && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
         total * tpc * n_layers <= (1ull << 31) && dead_tiles <= DEAD_TILES) {
         GatherArgs ga{};
         const ClassDev cd = class_dev(c);

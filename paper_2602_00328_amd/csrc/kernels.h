@@ -353,17 +353,18 @@ __global__ __launch_bounds__(WG) void compact_kv(uint32_t total, const Rec *__re
     if (k == K_HBM) hbm_recs[b_hbm + p_hbm] = tmp[r];
     if (k == K_HOST) host_recs[b_host + p_host] = tmp[r];
     if (k == K_HOST || k == K_LOST) miss_idx[b_miss + p_miss] = r;
-    if (last && tid == 0) {
-        cnt[C_HBM_REQ] = s_pre[BC_HBM]; cnt[C_HOST_REQ] = s_pre[BC_HOST]; cnt[C_MISS] = s_pre[BC_MISS];
-        const int from[6] = { BC_REQ, BC_LOCAL, BC_CACHE, BC_HOST, BC_LOST, BC_INVALID };
-        const int to[6] = { C_REQ, C_LOCAL, C_CACHE, C_HOST, C_LOST, C_INVALID };
-        for (int i = 0; i < 6; ++i) {
-            uint32_t v = s_pre[from[i]];
-            cnt[to[i]] = v;
-            if (v) atomicAdd(&totals[to[i]], (unsigned long long)v);
-            if (info) info[to[i]] = v;
+    if (last && tid < BC_N) {                    // one counter a thread: six in turn by one thread took 1 us longer
+        const uint32_t v = s_pre[tid];
+        const int to = tid == BC_HBM ? C_HBM_REQ : tid == BC_HOST ? C_HOST_REQ : tid == BC_MISS ? C_MISS : tid == BC_REQ ? C_REQ
+                     : tid == BC_LOCAL ? C_LOCAL : tid == BC_CACHE ? C_CACHE : tid == BC_LOST ? C_LOST : C_INVALID;
+        cnt[to] = v;
+        if (tid == BC_HOST) cnt[C_HOST] = v;
+        const int total_of = tid == BC_HOST ? C_HOST : to;
+        if (total_of <= C_INVALID) {
+            if (v) atomicAdd(&totals[total_of], (unsigned long long)v);
+            if (info) info[total_of] = v;
         }
-        if (info) { info[6] = s_pre[BC_MISS]; info[7] = 0; }
+        if (info && tid == BC_MISS) { info[6] = v; info[7] = 0; }
     }
 }
 
@@ -645,13 +646,16 @@ __device__ inline void host_tier(const Rec *__restrict__ recs, uint32_t n_req, c
 // object next to each other this turns two 32 KiB source runs into one 64 KiB run, the length from which scattered
 // runs read as fast as a contiguous buffer (6.29 -> 6.57 TB/s in the measurement above); where the planes live in
 // pools of their own, plane after plane is the faster order (6.24 against 6.11 TB/s).
-template <int NTHR, int PLANES, bool FOLD>
+//
+// blockIdx.y is the plane (unless folded), blockIdx.z the layer (MULTI): what a workgroup that lives for one load and one store
+// has to work out first is kept to a division.
+template <int NTHR, int PLANES, bool FOLD, bool MULTI>
 __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs, const Rec *__restrict__ host_recs,
                                                const uint32_t *__restrict__ cnt, GatherArgs a, GatherBooks books)
 {
     constexpr uint32_t TILE = NTHR * 16;
     if (blockIdx.x < a.n_host) {
-        if (blockIdx.y) return;                            // the host tier's workgroups walk all layers themselves
+        if (blockIdx.y | blockIdx.z) return;               // the host tier's workgroups walk all planes and layers themselves
         const uint32_t n_req = cnt[C_HOST_REQ];
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             if (books.fb_host) *books.fb_host = n_req;
@@ -660,9 +664,7 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
         host_tier<NTHR, PLANES>(host_recs, n_req, a, blockIdx.x);
         return;
     }
-    uint32_t bx = blockIdx.x - a.n_host, plane_y = 0;
-    const uint32_t gx = a.hbm_wgs, rep = blockIdx.y;
-    if (PLANES == 2 && !FOLD && bx >= gx) { bx -= gx; plane_y = 1; }
+    const uint32_t bx = blockIdx.x - a.n_host, gx = a.hbm_wgs, plane_y = FOLD ? 0 : blockIdx.y, rep = MULTI ? blockIdx.z : 0;
     // The first tile's list entry is fetched before the length is known, so that the two scalar loads overlap: a
     // workgroup lives for one load and one store, and every dependent load in front of them costs bandwidth.  The
     // host never launches more workgroups (per plane) than the list has room for tiles, so the early read stays inside
@@ -684,8 +686,9 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
         uint32_t plane = FOLD ? (k >= tpc ? 1u : 0u) : plane_y;
         uint64_t off = (uint64_t)(FOLD ? k - plane * tpc : k) * TILE;
         uint32_t tier = (uint32_t)(x.src & 3);
-        uint64_t src = src_base_of(a, tier, plane) + rep * layer_stride_of(a, tier) + (x.src & ~(uint64_t)3) + off;
-        uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + rep * a.dst_step + x.dst + off;
+        uint64_t src = src_base_of(a, tier, plane) + (x.src & ~(uint64_t)3) + off;
+        uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + x.dst + off;
+        if (MULTI) { src += rep * layer_stride_of(a, tier); dst += rep * a.dst_step; }
         copy_tile<NTHR, 1, true>(src, dst, a.chunk_bytes - off, threadIdx.x);
         t += gx;
         if (t >= n_tiles) break;
@@ -917,6 +920,7 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
                                                 const uint32_t *__restrict__ cnt, GatherArgs a, HmArgs h, GatherBooks books)
 {
     if (blockIdx.x < a.n_host) {
+        if (blockIdx.y) return;
         const uint32_t n_req = cnt[C_HOST_REQ];
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             if (books.fb_host) *books.fb_host = n_req;
@@ -928,9 +932,7 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
     // plane after plane: taking both planes of a request in one pass, as gather does for a cache tier that keeps
     // them side by side, was measured to lose here (5.60 against 5.98 TB/s alone): the stores are 4 KiB strips, and with
     // two planes' strips interleaved they no longer follow each other
-    uint32_t bx = blockIdx.x - a.n_host, plane = 0;
-    const uint32_t gx = a.hbm_wgs;
-    if (PLANES == 2 && bx >= gx) { bx -= gx; plane = 1; }
+    const uint32_t bx = blockIdx.x - a.n_host, gx = a.hbm_wgs, plane = blockIdx.y;
     uint32_t tpr = a.tiles_per_chunk;
     uint64_t t = bx;
     uint32_t idx = (uint32_t)t / tpr;
