@@ -5,7 +5,7 @@ Workload (benchmark configs[1]): long-context KV decode fetch, Llama-3-8B-sh
 bf16, 16-token blocks (32 KiB K + 32 KiB V per block per layer), 4 sequences with seeded lengths in [32K, 128K] tokens,
 70% of the closed blocks in the HBM cache tier, 30% host-only.  One step = one pass of the whole hot path: resolve every
 block of every sequence through the device directory, gather one layer's K and V into the contiguous working layout
-(HBM tier on the caller's stream, host tier over PCIe on the side stream, joined), append one token per sequence, and,
+(HBM tier and, over PCIe, host tier at the same time), append one token per sequence, and,
 when a tail block fills, write it back, demote it, place it in the cache tier and open a new tail.
 
 Prints ONE JSON line on stdout; progress goes to stderr.
@@ -408,10 +408,10 @@ def bench_experts(args, embed=False):
         "objects_per_s": round(d["n_requests"] / sec), "bit_exact": None,
         "served_per_step": {k: round(v / args.steps, 2) for k, v in d.items()},
         "placed_per_step": round(placed / args.steps, 2),
-        "roofline": {"bound": "hbm", "kernel": "gather<64,true,false> (HBM-tier gather of whole experts)", "achieved": round(hbm_gbs, 1),
+        "roofline": {"bound": "hbm", "kernel": "gather<64,1,false> (HBM-tier workgroups, whole experts)", "achieved": round(hbm_gbs, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(hbm_gbs / HBM_PEAK_GBS, 4), "traffic": None,
                      "launches": int(pr.hbm_launches)},
-        "host_tier": {"bound": "pcie", "kernel": "gather_host", "achieved": round(host_gbs, 2), "unit": "GB/s",
+        "host_tier": {"bound": "pcie", "kernel": "gather (host-tier workgroups)", "achieved": round(host_gbs, 2), "unit": "GB/s",
                       "launches": int(pr.host_launches)},
         "cpu_baseline": None,
     }
@@ -1182,10 +1182,10 @@ def bench_kv(args, seed, full):
         "bit_exact": bit_exact,
         "graph_replay": graph_replay,
         "served": {k: v // args.steps for k, v in d.items()},
-        "roofline": {"bound": "hbm", "kernel": ("gather_hm<1,true>" if args.head_major else
-                                                "gather<%d,true,%s>" % (args.gather_threads or 64, "true" if args.shared_cache or
-                                                                        args.cache_layout == "adjacent" else "false"))
-                                               + " (HBM-tier gather)", "achieved": round(hbm_gbs, 1),
+        "roofline": {"bound": "hbm", "kernel": ("gather_hm<2>" if args.head_major else
+                                                "gather<%d,2,%s>" % (args.gather_threads or 64, "true" if args.shared_cache or
+                                                                     args.cache_layout == "adjacent" else "false"))
+                                               + " (HBM-tier workgroups)", "achieved": round(hbm_gbs, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(hbm_gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_source": traffic_source,
                      "launches": int(pr.hbm_launches), "avg_launch_ms": round(hbm_ms, 5),
@@ -1198,7 +1198,7 @@ def bench_kv(args, seed, full):
                      "note": "achieved / frac: the kernel inside the timed step, where the host-tier kernel reads over PCIe "
                              "beside it; alone: the same request list with every block in the cache tier (isolation.all_cache)",
                      "achieved_alone": alone, "frac_alone": round(alone / HBM_PEAK_GBS, 4) if alone else None},
-        "host_tier": {"bound": "pcie", "kernel": ("gather_hm_host<2>" if args.head_major else "gather_host<2>") + " (host-tier gather, zero-copy over PCIe)",
+        "host_tier": {"bound": "pcie", "kernel": ("gather_hm<2>" if args.head_major else "gather<64,2>") + " (host-tier workgroups, zero-copy over PCIe)",
                       "achieved": round(host_gbs, 2), "peak": round(pcie_peak_gbs, 2), "unit": "GB/s",
                       "frac": round(host_gbs / pcie_peak_gbs, 4), "launches": int(pr.host_launches),
                       "avg_launch_ms": round(host_ms, 5), "bytes_per_launch": round(host_bytes),

@@ -107,7 +107,7 @@ enum harvest_flags {
     HARVEST_FLAG_PROFILE = 4,    /* bracket the gather kernels with events; read them with harvest_profile
                                     (launches recorded into a graph are not timed) */
     HARVEST_FLAG_GENERAL_FETCH = 8, /* harvest_fetch_kv never takes its one-kernel form for small block tables (up to
-                                    4096 cells): every fetch runs resolve, compaction and the two gathers - for
+                                    4096 cells): every fetch runs resolve, compaction and the gather - for
                                     measurements and tests of that path; results are the same either way */
     HARVEST_FLAG_CACHE_PLANES_ADJACENT = 16 /* two-plane classes with cache slots of their own keep them in ONE buffer,
                                     d_cache_pool[0], laid out [layer][slot][plane][chunk_bytes] (d_cache_pool[1] is ignored):
@@ -268,8 +268,8 @@ int harvest_revoke(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32_t n
  * d_block_table[r]; its K chunk of `layer` is copied to d_dst_k + (d_seq_dst_block[s] + j) * chunk_bytes and its V
  * chunk likewise into d_dst_v.  d_dst_k / d_dst_v hold dst_capacity_blocks chunks each.  Requests naming an unknown
  * block or a destination >= dst_capacity_blocks are skipped and counted; lost blocks leave the destination
- * untouched.  HBM-tier requests run on `stream`, host-tier requests on a library-owned side stream that is joined
- * back before this call's work on `stream` ends.  EINVAL: layer out of range, class unused, n_seq * max_blocks
+ * untouched.  Both tiers are served on `stream`, in one launch (with HARVEST_FLAG_PROFILE in two, which may run on a
+ * library-owned side stream that is joined back before this call's work on `stream` ends).  EINVAL: layer out of range, class unused, n_seq * max_blocks
  * >= 2^31. */
 int harvest_fetch_kv(harvest_ctx *ctx, uint32_t layer, const int32_t *d_block_table, const int32_t *d_n_blocks,
                      uint32_t n_seq, uint32_t max_blocks, void *d_dst_k, void *d_dst_v,
@@ -278,7 +278,7 @@ int harvest_fetch_kv(harvest_ctx *ctx, uint32_t layer, const int32_t *d_block_ta
 /* The same fetch for n_layers consecutive layers in one call (Section 5.2 moves whole blocks; an engine that reloads a
  * block needs it in every layer).  The block table is resolved once - an object has the same slot in every layer -
  * and layer layer_first + r lands d_dst + r * dst_layer_stride_bytes (a multiple of 16, at least dst_capacity_blocks *
- * chunk_bytes).  The host-tier copies of all layers follow each other without a join in between.  Counts and miss
+ * chunk_bytes).  The host-tier copies of all layers follow each other without a gap.  Counts and miss
  * list are per request (block), not per layer.  Nothing can change residency inside one call, and a revocation made
  * after it returns drains all of its layers. */
 int harvest_fetch_kv_layers(harvest_ctx *ctx, uint32_t layer_first, uint32_t n_layers, const int32_t *d_block_table,
@@ -315,9 +315,8 @@ int harvest_fetch_kv_head_major(harvest_ctx *ctx, uint32_t layer, const int32_t 
  * everything it needs beyond its arguments - the arrays of the resolve, the two request lists, the counters - lives in
  * a statically allocated device array of about 3.4 MiB, which every GPU the library has created a context on holds
  * until the process ends.  The limit that follows: n_seq * max_blocks <= HARVEST_STATIC_MAX_CELLS table cells,
- * HARVEST_E2BIG (and a message on stderr, nothing enqueued) beyond.  Both gathers run on `stream` one after the other
- * (there is no side stream to overlap the host tier on), so a fetch with a large host-tier share takes the sum of the
- * two, not the longer one.  The fetch may be recorded into a HIP graph without any earlier call.
+ * HARVEST_E2BIG (and a message on stderr, nothing enqueued) beyond.  The fetch may be recorded into a HIP graph without
+ * any earlier call.
  *   d_info     (device, 8 words, may be NULL) receives: requests, local, cache, host, lost, invalid, length of the miss
  *              list, 0 - what harvest_fetch_info reports for harvest_fetch_kv;
  *   d_miss_idx (device, n_seq * max_blocks words, may be NULL) receives the miss list in request order.
@@ -363,7 +362,7 @@ int harvest_prefetch_issue(harvest_prefetcher *pf, uint32_t layer, const int32_t
 int harvest_prefetch_acquire(harvest_prefetcher *pf, void *compute_stream, void **d_staging, void ***d_expert_ptr);
 int harvest_prefetch_release(harvest_prefetcher *pf, void *compute_stream);
 
-/* Forgets a caller stream: waits for what the library has enqueued on it, then frees the scratch lists, the side stream and
+/* Forgets a caller stream: waits for what the library has enqueued on it, then frees the scratch lists, the side stream (of profiled fetches) and
  * the events the context keeps for it - or, for a stream served by harvest_fetch_kv_static, gives its fixed state back,
  * so that another stream can take it.  For applications that create and destroy streams while a context lives: call it
  * before destroying the stream (a new stream that happens to get the same handle later simply starts afresh).  The next

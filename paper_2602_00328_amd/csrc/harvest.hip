@@ -2,9 +2,10 @@
 //
 // Structure
 //   ClassState  - per object class: host mirror of the directory, slot allocators, device directory.
-//   StreamState - per caller stream: device scratch (HBM list, host list, miss list, counters), a side stream for
-//                 the host-tier gather, fork/join events and the "last operation" event the revocation drain waits on.
-//   Staging     - pinned host blocks through which host-built lists reach the device without blocking the caller.
+//   StreamState - per caller stream: device scratch (HBM list, host list, miss list, counters) and the "last operation"
+//                 event the revocation drain waits on; a side stream with fork/join events for fetches that are timed by tier.
+//   Staging     - pinned host blocks through which host-built lists too long for a launch's arguments reach the device
+//                 without blocking the caller.
 //   edit chain  - every directory edit is a dir_write kernel that waits for the edit before it, on whatever stream that
 //                 ran, so edits reach the device in the order the host made them (paper Section 3.2: revocation is
 //                 ordered).  Placements and write-backs edit on the caller's stream, right behind their copy;
