@@ -426,8 +426,8 @@ bool is_capturing(hipStream_t s)
 }
 
 // Latest-work events only ever answer whether a kernel has ended (the host waits for them before it frees slots): no
-// system-scope fence comes with them.  With it, as a gather's completion signal, the compaction in front of the gather ran 0.9 us
-// longer and the gather 2 to 4 us (caches emptied once more): 6 806 blocks in two layers 297.2 against 293.1 us.
+// system-scope fence comes with them.  Recorded behind a 10 us kernel such an event makes the next one wait 1.0 us, with the
+// fence 2.9 us.
 constexpr unsigned LATEST_WORK = hipEventDisableTiming | hipEventDisableSystemFence;
 
 // Releases what a caller stream's state owns (any part of it may be missing); the stream's work must have finished.
@@ -641,15 +641,16 @@ ClassDev class_dev(const ClassState &c)
     return d;
 }
 
-// Launches a kernel with `done` as its completion signal.  Recorded behind the kernel an event is a packet of its own, which
-// keeps the next kernel of the stream - the caller's attention, say - waiting 2.9 us and the host busy for 0.8; attached to
-// the dispatch it costs 0 and 0.2 us (behind a 10 us kernel: 14.2 against 11.3 us per iteration, 11.3 without an event).  Only
-// a caller that waits for the GPU right after the call is better off with the packet (14.7 against 17.0 us).
+// Launches a kernel and records `done` behind it.  (As the kernel's own completion signal, hipExtLaunchKernel, the event costs the
+// stream nothing at all instead of the microsecond that a record without a system-scope fence takes; but a host that had run
+// thousands of such launches ahead of the device was slow afterwards - creating a context 640 us instead of 310, placing and
+// revoking a block 75 instead of 35 - and so it is recorded.)
 template <typename... P, typename... A>
 int launch_with(hipEvent_t done, hipStream_t s, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
 {
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, s, nullptr, done, 0, (P)args...);
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, (P)args...);
     HIP_TRY(hipGetLastError());
+    HIP_TRY(hipEventRecord(done, s));
     return HARVEST_OK;
 }
 
@@ -735,7 +736,7 @@ int mark_last(harvest_ctx *ctx, StreamState *ss)
     return HARVEST_OK;
 }
 
-// Launches the kernel that ends a call's work on the stream; the stream's latest-work event is its completion signal.
+// Launches the kernel that ends a call's work on the stream, and records the stream's latest-work event.
 template <typename... P, typename... A>
 int launch_last(harvest_ctx *ctx, StreamState *ss, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
 {
