@@ -701,7 +701,7 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
 // gaps, not of bytes.  blockIdx.y is the plane, blockIdx.z counts consecutive layers (an object has the same slot in every
 // layer): layer + z is read, dst_step * z further into the destination is written.  NTHR is 256, or 64 for tables of up to 64 *
 // ROUND cells, which a single wavefront walks at once and whose tiles are a little faster as workgroups of one (16 blocks of 32
-// layers: 14.5 us with 256, 13.1 with 64).  blockIdx.x says what a workgroup does:
+// layers: 14.5 us with 256, 13.1 with 64, before a microsecond of event behind it).  blockIdx.x says what a workgroup does:
 //
 //   the first n_host  walk the table, list the host's cells in LDS and read them over PCIe, all planes and layers, two loads in
 //                     flight per thread (see host_tier for why so few): 102 of 256 blocks of 2 x 32 KiB from the host take
