@@ -583,12 +583,23 @@ int acquire_staging(harvest_ctx *ctx, size_t bytes, Staging **out)
     return HARVEST_OK;
 }
 
+// Records an event behind work that is on the stream already.  When that fails nothing will ever stand for the work, so the
+// host waits for it here: whoever would have waited for the event finds the work done, whatever older work the event names.
+int record_behind(hipEvent_t e, hipStream_t s)
+{
+    const hipError_t err = hipEventRecord(e, s);
+    if (err == hipSuccess) return HARVEST_OK;
+    fprintf(stderr, "libharvest: hipEventRecord failed: %s\n", hipGetErrorString(err));
+    (void)hipStreamSynchronize(s);
+    return HARVEST_EHIP;
+}
+
 // The device reads the block in work enqueued on `s` so far: it is free again when that work has passed.
 int release_after(harvest_ctx *ctx, Staging *st, hipStream_t s)
 {
     if (fault_due()) return HARVEST_EHIP;
     if (ctx->no_device || !st) return HARVEST_OK;
-    HIP_TRY(hipEventRecord(st->done, s));
+    if (int rc = record_behind(st->done, s)) return rc;
     st->busy = true;
     st->held = false;
     return HARVEST_OK;
@@ -641,24 +652,12 @@ ClassDev class_dev(const ClassState &c)
     return d;
 }
 
-// Launches a kernel and records `done` behind it.  (As the kernel's own completion signal, hipExtLaunchKernel, the event costs the
-// stream nothing at all instead of the microsecond that a record without a system-scope fence takes; but a host that had run
-// thousands of such launches ahead of the device was slow afterwards - creating a context 640 us instead of 310, placing and
-// revoking a block 75 instead of 35 - and so it is recorded.)
-template <typename... P, typename... A>
-int launch_with(hipEvent_t done, hipStream_t s, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
-{
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, (P)args...);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipEventRecord(done, s));
-    return HARVEST_OK;
-}
-
 // Publishes the mirror entries of `ids` to the device directory with a dir_write kernel on stream `on`, ordered after
 // everything enqueued on `on` so far (for a placement: the copy that makes the new entry true) and after every earlier
 // directory edit, wherever that ran.  Up to DIR_INLINE entries travel with the launch, more of them in a staging block - pre: one
-// of n * 12 bytes taken earlier, so that this step cannot fail for want of one.  *committed (if given) says whether the dir_write was enqueued: from then on the device will apply
-// the edit, and a failure reported by a later step no longer entitles the caller to roll its mirror back.
+// of n * 12 bytes taken earlier, so that this step cannot fail for want of one.  *committed (if given) says whether the dir_write
+// was enqueued: from then on the device will apply the edit, and a failure reported by a later step - recording an event is
+// one - no longer entitles the caller to roll its mirror back.
 int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, hipStream_t on, bool must_see,
             Staging *pre = nullptr, bool *committed = nullptr)
 {
@@ -689,24 +688,23 @@ int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, h
     if (!ctx->no_device && n <= DIR_INLINE) {
         DirList l;
         for (size_t i = 0; i < n; ++i) { l.entry[i] = c.packed(ids[i]); l.id[i] = ids[i]; }
-        int rc = launch_with(c.edit_evt, on, dir_write_inline, dim3(1), dim3(DIR_INLINE), c.d_dir, (uint64_t)n, l);
-        if (rc) return rc;
+        hipLaunchKernelGGL(dir_write_inline, dim3(1), dim3(DIR_INLINE), 0, on, c.d_dir, (uint64_t)n, l);
     } else if (!ctx->no_device) {
         uint64_t *ent = (uint64_t *)st->h;
         uint32_t *idv = (uint32_t *)(ent + n);
         for (size_t i = 0; i < n; ++i) { ent[i] = c.packed(ids[i]); idv[i] = ids[i]; }
         uint64_t *d_ent = (uint64_t *)d_st;
         uint32_t *d_ids = (uint32_t *)(d_ent + n);
-        int rc = launch_with(c.edit_evt, on, dir_write, dim3((uint32_t)((n + WG - 1) / WG)), dim3(WG), c.d_dir, d_ids, d_ent, (uint32_t)n);
-        if (rc) return rc;
+        hipLaunchKernelGGL(dir_write, dim3((uint32_t)((n + WG - 1) / WG)), dim3(WG), 0, on, c.d_dir, d_ids, d_ent, (uint32_t)n);
     }
     DEV_TRY(hipGetLastError());
     if (committed) *committed = true;
     c.edit_seq++;
     c.edit_stream = on;
     if (must_see) c.must_seq = c.edit_seq;
-    if (ctx->no_device || n <= DIR_INLINE) return HARVEST_OK;
-    return release_after(ctx, st, on);
+    if (ctx->no_device) return HARVEST_OK;
+    if (int rc = record_behind(c.edit_evt, on)) return rc;
+    return n <= DIR_INLINE ? HARVEST_OK : release_after(ctx, st, on);
 }
 
 // Orders the caller's stream after the edits of the class's directory that a fetch enqueued now has to see - every
@@ -731,24 +729,28 @@ int mark_last(harvest_ctx *ctx, StreamState *ss)
         ctx->captured_work = true;
         return HARVEST_OK;
     }
-    HIP_TRY(hipEventRecord(ss->last, ss->s));
+    if (int rc = record_behind(ss->last, ss->s)) return rc;
     ss->last_valid = true;
     return HARVEST_OK;
 }
 
-// Launches the kernel that ends a call's work on the stream, and records the stream's latest-work event.
+template <typename... P, typename... A>
+int launch(hipStream_t s, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
+{
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, (P)args...);
+    HIP_TRY(hipGetLastError());
+    return HARVEST_OK;
+}
+
+// Launches the kernel that ends a call's work on the stream, and records the stream's latest-work event behind it.  (As the
+// kernel's own completion signal, hipExtLaunchKernel, the event costs the stream nothing at all instead of the microsecond that a
+// record without a system-scope fence takes; but a host that had run thousands of such launches ahead of the device was slow
+// afterwards - creating a context 640 us instead of 310, placing and revoking a block 75 instead of 35 - and so it is recorded.)
 template <typename... P, typename... A>
 int launch_last(harvest_ctx *ctx, StreamState *ss, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
 {
-    if (is_capturing(ss->s)) {                      // see mark_last
-        hipLaunchKernelGGL(kernel, grid, block, 0, ss->s, (P)args...);
-        HIP_TRY(hipGetLastError());
-        ctx->captured_work = true;
-        return HARVEST_OK;
-    }
-    int rc = launch_with(ss->last, ss->s, kernel, grid, block, args...);
-    if (!rc) ss->last_valid = true;
-    return rc;
+    int rc = launch(ss->s, kernel, grid, block, args...);
+    return rc ? rc : mark_last(ctx, ss);
 }
 
 hipEvent_t prof_event(harvest_ctx *ctx)
@@ -926,9 +928,17 @@ int reserve_move(harvest_ctx *ctx, StreamState *ss, size_t n, Hold &hold)
 
 enum MoveWay { WITHIN_HBM, FROM_HOST, TO_HOST };
 
-// Enqueues the copies of `recs` on the stream; a device step with a roll-back (see DEV_TRY).
-int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &recs, MoveArgs a, MoveWay way, Staging *st)
+// What of a failed call is on the stream has ended when this returns: the slots the call gives back are not being written.
+void settle(harvest_ctx *ctx, hipStream_t s)
 {
+    if (!ctx->no_device) (void)hipStreamSynchronize(s);
+}
+
+// Enqueues the copies of `recs` on the stream; a device step with a roll-back (see DEV_TRY).  *launched: the copy is on the
+// stream, whatever is returned.
+int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &recs, MoveArgs a, MoveWay way, Staging *st, bool *launched)
+{
+    *launched = false;
     const bool in_args = recs.size() <= MOVE_INLINE;
     a.n_obj = (uint32_t)recs.size();
     MoveList list;
@@ -942,13 +952,19 @@ int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &r
         if (!ctx->no_device) a.recs = (const MoveRec *)ss->ctl_buf;
     }
     if (fault_due()) return HARVEST_EHIP;
-    if (ctx->no_device) return HARVEST_OK;
+    if (ctx->no_device) { *launched = true; return HARVEST_OK; }
+    auto go = [&](auto kernel, dim3 grid, dim3 block) -> int {
+        int rc = launch(ss->s, kernel, grid, block, a, list);
+        if (rc) return rc;
+        *launched = true;
+        return mark_last(ctx, ss);
+    };
     const uint64_t items = (uint64_t)recs.size() * a.n_planes * a.n_layers;
     const uint64_t tiles_hbm = items * tiles_per_chunk(a.chunk_bytes, 64 * 16);
     if (way == WITHIN_HBM && tiles_hbm < (1ull << 32)) {       // a workgroup per 1 KiB tile, as in the gather
         a.tiles_per_chunk = tiles_per_chunk(a.chunk_bytes, 64 * 16);
         a.n_tiles = (uint32_t)tiles_hbm;
-        return launch_last(ctx, ss, in_args ? move_hbm<true> : move_hbm<false>, dim3(grid_for(tiles_hbm, MAX_GRID)), dim3(64), a, list);
+        return go(in_args ? move_hbm<true> : move_hbm<false>, dim3(grid_for(tiles_hbm, MAX_GRID)), dim3(64));
     }
     // over PCIe (or more tiles than move_hbm counts): persistent workgroups, tiles counted out
     const int unroll = way == TO_HOST ? 4 : 8;
@@ -959,8 +975,8 @@ int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &r
     a.next = ss->next;
     a.lease = way == WITHIN_HBM ? nullptr : ctx->d_lease;
     const dim3 grid(grid_for(tiles, way == WITHIN_HBM ? ctx->ctl_grid : ctx->pcie_grid));
-    if (way == TO_HOST) return launch_last(ctx, ss, in_args ? move_pcie<true, 4, true> : move_pcie<false, 4, true>, grid, dim3(WG), a, list);
-    return launch_last(ctx, ss, in_args ? move_pcie<true, 8, false> : move_pcie<false, 8, false>, grid, dim3(WG), a, list);
+    if (way == TO_HOST) return go(in_args ? move_pcie<true, 4, true> : move_pcie<false, 4, true>, grid, dim3(WG));
+    return go(in_args ? move_pcie<true, 8, false> : move_pcie<false, 8, false>, grid, dim3(WG));
 }
 
 int check_class(harvest_ctx *ctx, int cls)
@@ -1322,12 +1338,13 @@ static int place_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32_
         MoveArgs a = move_args(c, 0, c.cfg.n_layers);
         for (uint32_t p = 0; p < 2; ++p) a.src_base[p] = from ? from->plane[p] : a.host_base[p];
         a.src_layer = from ? from->stride * c.cfg.chunk_bytes : a.host_layer;
-        if ((rc = launch_move(ctx, ss, recs, a, from ? WITHIN_HBM : FROM_HOST, h_items.st))) return rc;
+        bool launched, committed = false;
+        rc = launch_move(ctx, ss, recs, a, from ? WITHIN_HBM : FROM_HOST, h_items.st, &launched);
         // the new entries are written on the same stream, behind the copy: visible only once the bytes are in the slot,
         // and before anything enqueued on `stream` later
-        bool committed = false;
-        rc = publish(ctx, c, moved, s, false, h_dir.st, &committed);
+        if (!rc) rc = publish(ctx, c, moved, s, false, h_dir.st, &committed);
         if (committed) undo.commit();
+        else settle(ctx, s);
         if (rc) return rc;
     }
     undo.commit();
@@ -2090,16 +2107,18 @@ int harvest_evict(harvest_ctx *ctx, int cls, int layer, const harvest_obj *ids, 
             demoted.push_back(id);
         }
     }
+    bool launched = true;                       // nothing to copy: as good as done
     if (!recs.empty()) {
         MoveArgs a = move_args(c, l0, l1 - l0);
         a.src_base[0] = (uint64_t)d_src0; a.src_base[1] = (uint64_t)d_src1;
         a.src_layer = src_layer_stride * c.cfg.chunk_bytes;
-        if ((rc = launch_move(ctx, ss, recs, a, to_host ? TO_HOST : WITHIN_HBM, h_items.st))) return rc;
+        rc = launch_move(ctx, ss, recs, a, to_host ? TO_HOST : WITHIN_HBM, h_items.st, &launched);
     }
     // Without demotions the write-back itself is the commit point: once the copy is enqueued the bytes will change.
-    bool committed = demoted.empty();
-    if (!demoted.empty()) rc = publish(ctx, c, demoted, s, true, h_dir.st, &committed);
+    bool committed = demoted.empty() && launched;
+    if (!rc && !demoted.empty()) rc = publish(ctx, c, demoted, s, true, h_dir.st, &committed);
     if (committed) undo.commit();
+    else settle(ctx, s);
     if (rc) return rc;
     if (ctx->no_device) return HARVEST_OK;
     // A freed local slot may be handed out by the very next harvest_register.  Fetches enqueued through the library are

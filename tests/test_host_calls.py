@@ -1,0 +1,172 @@
+"""The HIP calls the library's host code makes, on a CPU: the host half of harvest.hip is linked with a runtime that writes the calls
+down and fails the one a test names (tests/fakehip/fakehip.cpp).  Kernels do not run, so these tests are about order, choice of
+path and error paths, never about payload bytes."""
+import ctypes
+import os
+import re
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2602_00328_amd import binding as B
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+POOL = 0x10000000                          # no kernel runs: pool and buffer addresses are only ever added up
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    d = tmp_path_factory.mktemp("fakehip")
+    obj, run, so = str(d / "harvest.o"), str(d / "fakehip.o"), str(d / "libharvest_fake.so")
+    flags = ["-O1", "-std=c++17", "-fPIC", "-Wno-unused-command-line-argument"]
+    subprocess.check_call(["hipcc", "--offload-arch=gfx950", "--offload-host-only", *flags, "-c", "-o", obj,
+                           os.path.join(ROOT, "paper_2602_00328_amd", "csrc", "harvest.hip")])
+    fatbin = re.search(r"\b(__hip_fatbin\w*)$", subprocess.check_output(["nm", "-u", obj], text=True), re.M).group(1)
+    subprocess.check_call(["hipcc", "-x", "hip", "--offload-arch=gfx950", "--offload-host-only", *flags, f"-DHIP_FATBIN={fatbin}", "-c", "-o", run,
+                           os.path.join(ROOT, "tests", "fakehip", "fakehip.cpp")])
+    # -Bsymbolic: in a process where torch has loaded the real runtime, these calls still stay in this library
+    subprocess.check_call(["g++", "-shared", "-Wl,-Bsymbolic", "-o", so, obj, run])
+    lib = ctypes.CDLL(so)
+    for name, (res, args) in B.SYMBOLS.items():
+        fn = getattr(lib, name)
+        fn.restype, fn.argtypes = res, args
+    lib.fake_log.restype = ctypes.c_char_p
+    lib.fake_fail.argtypes = [ctypes.c_char_p, ctypes.c_int]
+    lib.fake_capture.argtypes = lib.fake_number.argtypes = [ctypes.c_void_p]
+    lib.fake_stream.restype = lib.fake_pinned.restype = ctypes.c_void_p
+    lib.fake_pinned.argtypes = [ctypes.c_size_t, ctypes.c_size_t]
+    lib.fake_pinned_count.argtypes, lib.fake_pinned_count.restype = [ctypes.c_size_t], ctypes.c_size_t
+    return lib
+
+
+class Ctx:
+    """A context with a KV class of n objects (32 KiB chunks unless said otherwise), all on the host."""
+
+    def __init__(self, lib, n=200, n_local=0, n_layers=2, chunk=32768, flags=0, cb=None):
+        self.lib, cfg = lib, B.harvest_config()
+        cfg.flags = flags
+        kv = cfg.cls[B.KV]
+        kv.n_layers, kv.n_planes, kv.chunk_bytes, kv.max_objects = n_layers, 2, chunk, n + n_local
+        kv.n_host_slots, kv.n_cache_slots, kv.n_local_slots = n + n_local, n, max(n_local, 1)
+        for p in range(2):
+            kv.host_pool[p], kv.d_cache_pool[p], kv.d_local_pool[p] = POOL * (p + 1), POOL * (p + 3), POOL * (p + 5)
+        self.h, self.n, self.n_local = ctypes.c_void_p(), n, n_local
+        assert lib.harvest_create(ctypes.byref(cfg), ctypes.byref(self.h)) == B.OK
+        self.cb = B.REVOKE_CB(cb or (lambda *_: None))
+        slots = np.arange(n + n_local, dtype=np.int64)
+        for first, k, tier in ((0, n, B.HOST), (n, n_local, B.LOCAL)):
+            if k:
+                assert lib.harvest_register(self.h, B.KV, k, slots[first:].ctypes.data, tier, self.cb, None,
+                                            np.empty(k, dtype=np.uint32).ctypes.data) == B.OK
+        self.stream = lib.fake_stream()
+        self.number = lib.fake_number(self.stream)
+
+    def close(self):
+        assert self.lib.harvest_destroy(self.h) == B.OK
+
+    def tier(self, obj):
+        t = ctypes.c_int()
+        assert self.lib.harvest_lookup(self.h, B.KV, obj, ctypes.byref(t), None, None, None) == B.OK
+        return t.value
+
+    def stats(self):
+        s = B.harvest_stats_t()
+        assert self.lib.harvest_stats(self.h, ctypes.byref(s)) == B.OK
+        return s
+
+    def ids(self, ids):
+        a = np.asarray(ids, dtype=np.uint32)
+        return a, a.ctypes.data, a.size
+
+    def place(self, ids):
+        a, p, n = self.ids(ids)
+        return self.lib.harvest_place(self.h, B.KV, p, n, self.stream, None)
+
+    def place_from(self, ids):
+        a, p, n = self.ids(ids)
+        at = np.arange(n, dtype=np.uint64)
+        return self.lib.harvest_place_from(self.h, B.KV, p, n, POOL * 8, POOL * 9, at.ctypes.data, n, self.stream, None)
+
+    def evict(self, ids, flags=0):
+        a, p, n = self.ids(ids)
+        at = np.arange(n, dtype=np.uint64)
+        return self.lib.harvest_evict(self.h, B.KV, -1, p, n, POOL * 8, POOL * 9, at.ctypes.data, n, flags, self.stream)
+
+    def revoke(self, ids):
+        a, p, n = self.ids(ids)
+        return self.lib.harvest_revoke(self.h, B.KV, p, n)
+
+    def log(self):
+        return self.lib.fake_log().decode().splitlines()
+
+
+def launches(log, name):
+    """Where the log has a launch of the kernel that did not fail."""
+    return [i for i, line in enumerate(log) if "LaunchKernel" in line and name in line and log[i + 1:i + 2] != ["  failed"]]
+
+
+@pytest.mark.parametrize("n", [3, 81, 150])             # lists that travel with the launch; objects that do not; neither does
+@pytest.mark.parametrize("what", ["place", "place_from", "evict", "demote"])
+@pytest.mark.parametrize("failing", ["hipLaunchKernel", "hipEventRecord", "hipStreamWaitEvent", "hipHostGetDevicePointer", "hipMemcpyAsync"])
+def test_a_call_that_fails_leaves_mirror_and_device_in_step(fake, what, n, failing):
+    """Whichever HIP call fails: the mirror shows a new entry if and only if its dir_write was launched, and what was launched
+    on the stream is either stood for by an event recorded behind it or has been waited for before the call returned."""
+    reached = 0
+    for nth in range(1, 9):
+        c = Ctx(fake, n_local=150)
+        assert c.place([199]) == B.OK                     # the stream's state and an earlier edit exist
+        if what == "evict":
+            assert c.place(range(n // 2)) == B.OK
+        ids = np.arange(n) + (c.n if what == "demote" else 0)
+        call = {"place": c.place, "place_from": c.place_from, "evict": c.evict, "demote": lambda i: c.evict(i, B.EVICT_DEMOTE)}[what]
+        assert c.revoke([199]) == B.OK                    # the latest edit ran on another stream
+        before, s0 = [c.tier(i) for i in ids], c.stats()
+        c.log()
+        fake.fake_fail(failing.encode(), nth)
+        rc = call(ids)
+        hit = not fake.fake_fail_pending()
+        fake.fake_fail(b"", 0)
+        log, after, s1 = c.log(), [c.tier(i) for i in ids], c.stats()
+        if not hit:
+            assert rc == B.OK
+            c.close()
+            break
+        reached += 1
+        assert rc == B.EHIP, log
+        edited, moved = launches(log, "dir_write"), launches(log, "move_")
+        changed = [a != b for a, b in zip(after, before)]
+        if what != "evict":
+            assert all(changed) == any(changed) == bool(edited), (nth, log)
+        counted = s1.n_evicted[0] - s0.n_evicted[0] if what in ("evict", "demote") else s1.n_placed[0] - s0.n_placed[0]
+        if what == "evict":
+            assert counted == (n if moved else 0), (nth, log)
+        else:
+            assert counted == (n if edited else 0), (nth, log)
+        for at in moved + edited:
+            number = re.search(r"stream (\d+)", log[at]).group(1)
+            rest = [line for i, line in enumerate(log) if i > at and log[i + 1:i + 2] != ["  failed"]]
+            assert any(re.match(rf"(hipEventRecord|hipStreamSynchronize) stream {number}\b", line) for line in rest), (nth, log)
+        # a slot that went back to the allocator is not being written: the copy had ended before the call gave it back
+        if moved and not edited and what != "evict":
+            tail = log[moved[0]:]
+            assert any(line == f"hipStreamSynchronize stream {c.number}" for line in tail), (nth, log)
+        # and the context goes on working
+        assert call(ids) == B.OK
+        c.close()
+    assert reached or failing not in ("hipLaunchKernel", "hipEventRecord")
+
+
+def test_a_fetch_whose_event_is_not_recorded_has_ended_when_the_call_returns(fake):
+    """No event stands for it, so a revocation could not wait for it: the call does."""
+    c = Ctx(fake)
+    for how in (1, 2):                                    # the first fetch makes the stream's state
+        c.log()
+        if how == 2:
+            fake.fake_fail(b"hipEventRecord", 1)
+        rc = fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 8, POOL, POOL, POOL, 8, c.stream)
+        assert rc == (B.OK if how == 1 else B.EHIP)
+    assert c.log()[-1] == f"hipStreamSynchronize stream {c.number}"
+    c.close()
