@@ -252,8 +252,8 @@ int harvest_place_from(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32
 
 /* Revocation (Section 3.2: an explicit call whose steps come in a fixed order): for each id in the cache tier: publish (HOST, gen+1) - or
  * (NONE) for a lossy object -, wait until every fetch / evict / place enqueued so far on any stream this context
- * has seen has completed (the drain), free the slot (poison it if asked), then invoke the callback.  Ids not in the
- * cache tier are skipped.  Synchronous; ENOENT for unknown ids (nothing changed).
+ * has seen has completed and what it wrote is visible to the host and to other devices (the drain), free the slot (poison
+ * it if asked), then invoke the callback.  Ids not in the cache tier are skipped.  Synchronous; ENOENT for unknown ids (nothing changed).
  * The context is locked while the directory changes and while work is enqueued, not while the host waits for the
  * drain: other threads may meanwhile call anything on their own streams.  They see the revoked objects on the host
  * already, and the slots being revoked are handed to nobody before the wait has ended.  EHIP before the new entries

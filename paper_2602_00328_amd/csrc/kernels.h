@@ -1124,6 +1124,8 @@ __global__ __launch_bounds__(DIR_INLINE) void dir_write_inline(uint64_t *dir, ui
     if (threadIdx.x < n) dir[l->id[threadIdx.x]] = l->entry[threadIdx.x];
 }
 
+__global__ void system_fence() { __threadfence_system(); }
+
 // harvest_fetch_kv_static's counters for a fetch that had no table cell and ran no kernel.
 __global__ void zero_info(uint32_t *__restrict__ info)
 {

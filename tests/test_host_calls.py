@@ -170,3 +170,38 @@ def test_a_fetch_whose_event_is_not_recorded_has_ended_when_the_call_returns(fak
         assert rc == (B.OK if how == 1 else B.EHIP)
     assert c.log()[-1] == f"hipStreamSynchronize stream {c.number}"
     c.close()
+
+
+@pytest.mark.parametrize("recorded", [False, True])
+def test_a_revocation_hands_slots_back_behind_a_system_scope_release(fake, recorded):
+    """Between the end of the drain's waits and the callbacks there is a fence at system scope that the host has waited for: the
+    events of the drain carry none."""
+    seen = []
+    c = Ctx(fake, cb=lambda cls, obj, user: seen.append(c.log()))
+    assert c.place([3, 4]) == B.OK
+    assert fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 8, POOL, POOL, POOL, 8, c.stream) == B.OK
+    if recorded:                                          # then the drain waits for the whole device
+        fake.fake_capture(c.stream)
+        assert fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 8, POOL, POOL, POOL, 8, c.stream) == B.OK
+        fake.fake_capture(None)
+    c.log()
+    assert c.revoke([3, 4]) == B.OK
+    log = seen[0]
+    waits = [i for i, line in enumerate(log) if line.startswith("hipDeviceSynchronize" if recorded else "hipEventSynchronize")]
+    fence = launches(log, "system_fence")
+    assert len(seen) == 2 and waits and len(fence) == 1 and fence[0] > waits[-1], log
+    number = re.search(r"stream (\d+)", log[fence[0]]).group(1)
+    assert f"hipStreamSynchronize stream {number}" in log[fence[0]:], log
+    c.close()
+
+
+def test_a_drain_whose_fence_fails_keeps_the_slots(fake):
+    c = Ctx(fake, n=1)
+    assert c.place([0]) == B.OK
+    fake.fake_fail(b"hipStreamSynchronize", 1)
+    assert c.revoke([0]) == B.EHIP
+    fake.fake_fail(b"", 0)
+    st = np.zeros(1, dtype=np.int32)
+    a, p, n = c.ids([0])
+    assert fake.harvest_place(c.h, B.KV, p, n, c.stream, st.ctypes.data) == B.OK and st[0] == B.ENOSPC
+    c.close()
