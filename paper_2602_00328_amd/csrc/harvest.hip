@@ -466,11 +466,13 @@ int init_stream_state(StreamState *ss)
     HIP_TRY(hipEventCreateWithFlags(&ss->last, LATEST_WORK));
     const size_t cnt_bytes = HARVEST_N_CLASSES * C_N * sizeof(uint32_t);
     HIP_TRY(hipMalloc(&ss->cnt_block, cnt_bytes + sizeof *ss->next));
-    HIP_TRY(hipMemset(ss->cnt_block, 0, cnt_bytes + sizeof *ss->next));
+    // cleared on the stream itself: hipMemset would leave that to the null stream, which neither the host nor a stream made
+    // non-blocking waits for
+    HIP_TRY(hipMemsetAsync(ss->cnt_block, 0, cnt_bytes + sizeof *ss->next, ss->s));
     ss->next = (unsigned long long *)((char *)ss->cnt_block + cnt_bytes);
     for (int k = 0; k < HARVEST_N_CLASSES; ++k) ss->lists[k].cnt = ss->cnt_block + k * C_N;
     HIP_TRY(hipMalloc(&ss->mark, (MAX_EXPERTS / 32 + 1) * sizeof(uint32_t)));
-    HIP_TRY(hipMemset(ss->mark, 0, (MAX_EXPERTS / 32 + 1) * sizeof(uint32_t)));
+    HIP_TRY(hipMemsetAsync(ss->mark, 0, (MAX_EXPERTS / 32 + 1) * sizeof(uint32_t), ss->s));
     HIP_TRY(hipHostMalloc((void **)&ss->h_feedback, 64, hipHostMallocDefault));
     memset(ss->h_feedback, 0, 64);
     HIP_TRY(hipHostGetDevicePointer((void **)&ss->d_feedback, ss->h_feedback, 0));
@@ -489,6 +491,7 @@ int get_stream(harvest_ctx *ctx, void *stream, StreamState **out)
     auto ss = std::make_unique<StreamState>();
     ss->s = s;
     if (int rc = init_stream_state(ss.get())) {
+        (void)hipStreamSynchronize(s);
         free_stream_state(ss.get());
         return rc;
     }

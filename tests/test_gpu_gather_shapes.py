@@ -188,3 +188,21 @@ def test_moves_with_and_without_a_list_on_the_device(n_planes, flags, chunk, n):
         assert np.array_equal(host(), want_host)
         assert np.array_equal(pool(B.CACHE), want_cache) and np.array_equal(pool(B.LOCAL), want_local)
     h.close()
+
+
+def test_first_placement_on_a_stream_while_the_null_stream_is_busy():
+    n, layers, chunk, rng = 40, 4, 16384, np.random.default_rng(3)
+    h = B.Harvest(kv=B.ClassSpec(n_layers=layers, n_planes=1, chunk_bytes=chunk, max_objects=n, n_host_slots=n, n_cache_slots=n, n_local_slots=0))
+    h.host_plane(B.KV, 0)[:] = rng.integers(0, 256, (layers, n, chunk), dtype=np.uint8)
+    ids = h.register(B.KV, n, np.arange(n))
+    torch.cuda.synchronize()
+    for _ in range(6):          # a new stream's scratch each time (one that HIP maps to the null stream's hardware queue waits anyway)
+        s = torch.cuda.Stream()
+        torch.cuda._sleep(int(5e7))
+        h.place(B.KV, ids, stream=s)
+        s.synchronize()
+        assert np.array_equal(h.dev_plane(B.KV, B.CACHE, 0).cpu().numpy(), h.host_plane(B.KV, 0))
+        h.revoke(B.KV, ids)
+        h.dev_plane(B.KV, B.CACHE, 0).zero_()
+        torch.cuda.synchronize()
+    h.close()

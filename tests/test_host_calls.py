@@ -205,3 +205,19 @@ def test_a_drain_whose_fence_fails_keeps_the_slots(fake):
     a, p, n = c.ids([0])
     assert fake.harvest_place(c.h, B.KV, p, n, c.stream, st.ctypes.data) == B.OK and st[0] == B.ENOSPC
     c.close()
+
+
+def test_scratch_is_cleared_on_the_stream_that_uses_it(fake):
+    """hipMemset returns before the null stream has done it (21 us behind a null stream with 40 ms of work queued), and a stream
+    made non-blocking does not wait for the null stream: a tile counter cleared that way may still hold anything at its first
+    use, or be cleared in the middle of it."""
+    c = Ctx(fake)
+    for call in (lambda: c.place([1]), lambda: fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 8, POOL, POOL, POOL, 8, c.stream)):
+        c.stream = fake.fake_stream()
+        c.log()
+        assert call() == B.OK
+        log = c.log()
+        assert "hipMemset" not in log, log
+        cleared = [i for i, line in enumerate(log) if line == f"hipMemsetAsync stream {fake.fake_number(c.stream)}"]
+        assert len(cleared) == 2 and cleared[-1] < launches(log, "")[0], log
+    c.close()
