@@ -311,9 +311,9 @@ struct StreamState {
     // control scratch (host-built lists)
     void *ctl_buf = nullptr;
     size_t ctl_cap = 0;
-    // pinned words the HBM-tier gather reports its request count to, per class: a hint for the next grid size
-    uint32_t *h_feedback = nullptr;
-    uint32_t *d_feedback = nullptr;
+    // what the gathers of each class report, in pinned memory: hints for the next launch
+    Report *h_feedback = nullptr;
+    Report *d_feedback = nullptr;
     bool feedback_valid[HARVEST_N_CLASSES] = { false, false };
 };
 
@@ -788,7 +788,7 @@ uint32_t host_workgroups(const harvest_ctx *ctx, uint32_t nthr)
 // into the destination.
 int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, const Lists &lists, uint64_t max_req,
                    uint64_t dst_base0, uint64_t dst_base1, const HmArgs *hm = nullptr, uint32_t n_rep = 1,
-                   uint64_t dst_step = 0, int64_t layer_delta = 0, bool repeat = false)
+                   uint64_t dst_step = 0, int64_t layer_delta = 0, bool repeat = false, uint32_t n_seq = 0, uint32_t max_blocks = 0)
 {
     // layer_delta: the lists were made for another layer; an object has the same slot in every layer, so adding that many
     // layer strides to every pool base retargets them.  repeat: these requests have been counted for the lists' first
@@ -829,8 +829,8 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     uint64_t want = max_tiles;
     bool host_stays = host_tier, serial = !host_tier;
     if (ss->feedback_valid[cls]) {
-        uint64_t seen = *(volatile uint32_t *)&ss->h_feedback[cls];
-        uint64_t seen_host = *(volatile uint32_t *)&ss->h_feedback[HARVEST_N_CLASSES + cls];
+        const volatile Report &r = ss->h_feedback[cls];
+        const uint64_t seen = r.hbm, seen_host = r.host;
         uint64_t guess = std::max<uint64_t>(1, cls == HARVEST_KV ? seen : seen - seen / 8) * tpc;
         want = std::min(max_tiles, std::max<uint64_t>(guess, 16ull * ctx->n_cu));
         // profiled fetches only, see below
@@ -843,8 +843,8 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     const uint32_t max_wgs = MAX_GRID - host_wgs;
     const uint32_t hbm_wgs = grid_for(fold ? want * planes : want, ctx->gather_grid ? std::min(ctx->gather_grid, max_wgs) : max_wgs);
     GatherBooks books{};
-    books.fb_hbm = ss->d_feedback + cls;
-    books.fb_host = ss->d_feedback + HARVEST_N_CLASSES + cls;
+    books.report = ss->d_feedback + cls;
+    books.n_seq = n_seq; books.max_blocks = max_blocks;
     books.lease = ctx->d_lease;
     books.totals = repeat ? ctx->d_totals + cls * C_N : nullptr;
     auto launch = [&](uint32_t n_host, uint32_t n_hbm, hipStream_t s, hipEvent_t begin, hipEvent_t end) -> int {
@@ -1654,11 +1654,14 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     // A small table: the whole fetch is one kernel (no compaction) - see fetch_kv_small.  Unless most of it is padding: the
     // one kernel has a workgroup for every tile of every cell, and one whose cell asks for nothing still costs 0.4 ns
     // (4 096 cells, 64 of them live: 27 us), where the general path spends about 8 us more on two small kernels and none
-    // on cells that are not there.  How many are live is what the stream's last fetch reported.
+    // on cells that are not there.  How many are live is known when the latest report on this stream came from a table of these
+    // rows and columns - a step's table keeps its shape from layer to layer and mostly from step to step; of any other table
+    // (two that take turns, say) they are taken to be live, for a wrong guess costs those 8 us.  So they are for a
+    // fetch that is being recorded: its replays may meet any number of live cells.
     uint64_t dead_tiles = 0;
-    if (ss->feedback_valid[HARVEST_KV]) {
-        const uint64_t live = (uint64_t)*(volatile uint32_t *)&ss->h_feedback[HARVEST_KV] +
-                              *(volatile uint32_t *)&ss->h_feedback[HARVEST_N_CLASSES + HARVEST_KV];
+    const volatile Report &latest = ss->h_feedback[HARVEST_KV];
+    if (ss->feedback_valid[HARVEST_KV] && latest.n_seq == n_seq && latest.max_blocks == max_blocks && !is_capturing(ss->s)) {
+        const uint64_t live = (uint64_t)latest.hbm + latest.host;
         if (live < total) dead_tiles = (total - live) * tpc * c.cfg.n_planes * n_layers;
     }
     if (!ctx->general_fetch && !head_major && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
@@ -1679,7 +1682,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr / 2) : 0;                // with half of HOST_LOADS each
         ga.hbm_wgs = (uint32_t)total * ga.tiles_per_chunk;
         SmallBooks books{ lists.miss, cnt, info, ctx->d_totals + HARVEST_KV * C_N, ss->d_feedback + HARVEST_KV,
-                          ss->d_feedback + HARVEST_N_CLASSES + HARVEST_KV, c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr };
+                          c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr, n_seq };
         const uint32_t head = ga.n_host + 1;
         const dim3 grid(n_layers > 1 ? std::max(ga.hbm_wgs, head) : ga.hbm_wgs + head, c.cfg.n_planes, n_layers > 1 ? n_layers + 1 : 1);
         auto kernel = c.cfg.n_planes == 2 ? (nthr == 64 ? fetch_kv_small<2, 64> : fetch_kv_small<2, WG>)
@@ -1715,7 +1718,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     // lists recorded into a graph exist only once the graph has been replayed: nothing to use again
     remember(!is_capturing(ss->s));
     return launch_gathers(ctx, ss, c, HARVEST_KV, lists, total, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
-                          head_major ? &hm : nullptr, n_layers, dst_layer_stride);
+                          head_major ? &hm : nullptr, n_layers, dst_layer_stride, 0, false, n_seq, max_blocks);
 }
 
 int harvest_fetch_kv_again(harvest_ctx *ctx, uint32_t layer, void *d_dst_k, void *d_dst_v, void *stream)
@@ -1747,7 +1750,8 @@ int harvest_fetch_kv_again(harvest_ctx *ctx, uint32_t layer, void *d_dst_k, void
     }
     ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
     return launch_gathers(ctx, ss, c, HARVEST_KV, ss->lists[HARVEST_KV], (uint64_t)k.n_seq * k.max_blocks, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
-                          head_major ? &hm : nullptr, 1, 0, (int64_t)layer - (int64_t)k.layer, true);
+                          head_major ? &hm : nullptr, 1, 0, (int64_t)layer - (int64_t)k.layer, true,
+                          k.n_seq, k.max_blocks);
 }
 
 int harvest_fetch_kv_static(harvest_ctx *ctx, uint32_t layer, const int32_t *d_block_table, const int32_t *d_n_blocks,
@@ -1982,6 +1986,7 @@ int harvest_release_stream(harvest_ctx *ctx, void *stream)
             f.s = nullptr;
             f.last_valid = false; f.last_cls = -1; f.last_kv.valid = false;
             for (int k = 0; k < HARVEST_N_CLASSES; ++k) { f.counted[k] = false; f.feedback_valid[k] = false; f.seen_seq[k] = 0; }
+            memset(f.h_feedback, 0, 64);
             std::swap(f, ctx->fixed_streams[ctx->n_fixed_streams - 1]);
             ctx->n_fixed_streams--;
             found = true;

@@ -122,9 +122,13 @@ struct GatherArgs {
     uint32_t n_host, hbm_wgs;
     uint32_t pages_per_chunk;            // of the host tier, see host_tier
 };
+// In pinned memory, one per class and stream: requests of either tier of the latest fetch whose kernels have run - hints for the
+// next launch - and the rows and columns of the block table they were asked for with (experts: zero).
+struct Report { uint32_t hbm, host, n_seq, max_blocks; };
 // What a gather reports besides the bytes; every pointer may be null.
 struct GatherBooks {
-    uint32_t *fb_hbm, *fb_host;          // pinned words that receive the list lengths: hints for the next launch's grid
+    Report *report;
+    uint32_t n_seq, max_blocks;
     unsigned long long *lease;           // see link_announce
     unsigned long long *totals;          // running totals, to which a fetch repeated from older lists adds their counters
 };
@@ -631,7 +635,7 @@ __device__ inline void host_tier(const Rec *__restrict__ recs, uint32_t n_req, c
 }
 
 // HBM tier.  NTHR threads per workgroup, one 16-byte load and store each: a tile is NTHR * 16 bytes, and the launch has about
-// as many workgroups as tiles; a smaller grid loops.  The list length is written to a word of pinned host memory: the
+// as many workgroups as tiles; a smaller grid loops.  The list length is written to pinned host memory: the
 // host sizes the next launch from it, because workgroups that find no tile are not free (about 0.2 ns each on MI355X) while a
 // grid somewhat short of the tile count costs little.
 //
@@ -658,7 +662,7 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
         if (blockIdx.y | blockIdx.z) return;               // the host tier's workgroups walk all planes and layers themselves
         const uint32_t n_req = cnt[C_HOST_REQ];
         if (blockIdx.x == 0 && threadIdx.x == 0) {
-            if (books.fb_host) *books.fb_host = n_req;
+            if (books.report) books.report->host = n_req;
             link_announce(books.lease, (uint64_t)n_req * a.chunk_bytes * PLANES * a.n_rep);
         }
         host_tier<NTHR, PLANES>(host_recs, n_req, a, blockIdx.x);
@@ -676,7 +680,11 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
     Rec x = hbm_recs[idx];
     uint32_t n_req = cnt[C_HBM_REQ];
     if (bx == 0 && plane_y == 0 && rep == 0) {
-        if (books.fb_hbm && threadIdx.x == 0) *books.fb_hbm = n_req;
+        if (books.report && threadIdx.x == 0) {
+            books.report->hbm = n_req;
+            books.report->n_seq = books.n_seq;
+            books.report->max_blocks = books.max_blocks;
+        }
         if (books.totals && threadIdx.x <= C_INVALID && cnt[threadIdx.x])
             atomicAdd(&books.totals[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
     }
@@ -721,8 +729,9 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
 struct SmallBooks {
     uint32_t *miss_idx, *cnt, *info;     // info may be null
     unsigned long long *totals;
-    uint32_t *fb_hbm, *fb_host;          // see GatherBooks
+    Report *report;
     unsigned long long *lease;
+    uint32_t n_seq;
 };
 
 constexpr uint32_t ROUND = 2;            // cells a thread looks up at a time when a workgroup walks the table
@@ -863,8 +872,8 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
         books.cnt[C_HOST_REQ] = host;
         books.cnt[C_MISS] = n_miss;
         if (books.info) { books.info[6] = n_miss; books.info[7] = 0; }
-        *books.fb_hbm = hbm;
-        *books.fb_host = host;
+        const u32x4 r = { hbm, host, books.n_seq, max_blocks };        // one store
+        *reinterpret_cast<u32x4 *>(books.report) = r;
         link_announce(books.lease, (uint64_t)host * a.chunk_bytes * PLANES * a.n_rep);
     }
 }
@@ -923,7 +932,7 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
         if (blockIdx.y) return;
         const uint32_t n_req = cnt[C_HOST_REQ];
         if (blockIdx.x == 0 && threadIdx.x == 0) {
-            if (books.fb_host) *books.fb_host = n_req;
+            if (books.report) books.report->host = n_req;
             link_announce(books.lease, (uint64_t)n_req * a.chunk_bytes * PLANES);
         }
         host_tier_hm<PLANES>(host_recs, n_req, a, h, blockIdx.x);
@@ -939,7 +948,11 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
     Rec x = hbm_recs[idx];                               // speculative, as in gather
     uint32_t n_req = cnt[C_HBM_REQ];
     if (bx == 0 && plane == 0) {
-        if (books.fb_hbm && threadIdx.x == 0) *books.fb_hbm = n_req;
+        if (books.report && threadIdx.x == 0) {
+            books.report->hbm = n_req;
+            books.report->n_seq = books.n_seq;
+            books.report->max_blocks = books.max_blocks;
+        }
         if (books.totals && threadIdx.x <= C_INVALID && cnt[threadIdx.x])
             atomicAdd(&books.totals[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
     }

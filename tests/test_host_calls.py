@@ -221,3 +221,60 @@ def test_scratch_is_cleared_on_the_stream_that_uses_it(fake):
         cleared = [i for i, line in enumerate(log) if line == f"hipMemsetAsync stream {fake.fake_number(c.stream)}"]
         assert len(cleared) == 2 and cleared[-1] < launches(log, "")[0], log
     c.close()
+
+
+def test_a_small_table_leaves_the_one_kernel_form_only_on_a_report_about_itself(fake):
+    """The kernels report live requests (words 0 and 1: HBM and host tier) and which table they are about (words 2 and 3: rows and
+    columns).  A table that is mostly padding goes through the general path; what another table reported says nothing about it,
+    and neither does any report about the replays of a graph."""
+    c = Ctx(fake)
+
+    def path(n_seq, width, layers=1):
+        c.log()
+        assert fake.harvest_fetch_kv_layers(c.h, 0, layers, POOL, POOL, n_seq, width, POOL, POOL, 8 * 32768, POOL, 8, c.stream) == B.OK
+        log = c.log()
+        small = bool(launches(log, "fetch_kv_small"))
+        assert small != bool(launches(log, "classify_kv")), log
+        return "one kernel" if small else "general"
+
+    assert path(1, 8) == "one kernel"
+    words = (ctypes.c_uint32 * 16).from_address(fake.fake_pinned(64, fake.fake_pinned_count(64) - 1))
+
+    def report(live_hbm, live_host, n_seq, width):
+        words[:4] = [live_hbm, live_host, n_seq, width]
+
+    report(8, 0, 1, 8)                                   # an 8-block fetch has run last: 2040 * 8 * 2 tiles fewer than the next table
+    assert path(1, 2048) == "one kernel"
+    assert path(1, 2048) == "one kernel"                 # still the report of the 8-block fetch: the others have not run yet
+    assert path(2, 1024) == "one kernel"
+    assert path(1, 48, layers=2) == "one kernel"
+    report(8, 0, 1, 2048)
+    assert path(1, 2048) == "general"
+    assert path(2, 1024) == "one kernel"
+    report(1000, 1048, 1, 2048)                          # full: both tiers together
+    assert path(1, 2048) == "one kernel"
+    report(8, 0, 1, 2048)
+    fake.fake_capture(c.stream)
+    assert path(1, 2048) == "one kernel"
+    fake.fake_capture(None)
+    c.close()
+
+
+def test_a_static_state_that_goes_to_another_stream_takes_no_report_with_it(fake):
+    c = Ctx(fake)
+    words = [(ctypes.c_uint32 * 16).from_address(fake.fake_pinned(64, fake.fake_pinned_count(64) - 1 - i)) for i in range(4)]
+
+    def path():
+        c.log()
+        assert fake.harvest_fetch_kv_static(c.h, 0, POOL, POOL, 1, 2048, POOL, POOL, POOL, 8, None, None, c.stream) == B.OK
+        return "general" if launches(c.log(), "classify_kv") else "one kernel"
+
+    assert path() == "one kernel"
+    for w in words:
+        w[:4] = [8, 0, 1, 2048]
+    assert path() == "general"
+    assert fake.harvest_release_stream(c.h, c.stream) == B.OK
+    c.stream = fake.fake_stream()
+    assert path() == "one kernel"
+    assert path() == "one kernel"
+    c.close()
