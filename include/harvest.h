@@ -291,8 +291,9 @@ int harvest_fetch_kv_layers(harvest_ctx *ctx, uint32_t layer_first, uint32_t n_l
  * layers (Section 5.2: the table says where every block of the step is; it does not change from layer to layer).  The
  * caller vouches that the table arrays of that call have not changed and are still valid device memory.  When no directory
  * edit has happened since that call, its request lists are used again (an object occupies the same slot in every layer),
- * which saves resolving and compacting the table; otherwise, and for the small tables that are fetched without lists, the
- * table is resolved again - the result is the same either way.  Counters and miss list are those of a fetch of this
+ * which saves resolving and compacting the table; otherwise, for the small tables that are fetched without lists, and on a
+ * stream on which a KV fetch has been recorded into a graph (a replay writes the stream's lists), the table is resolved
+ * again - the result is the same either way.  Counters and miss list are those of a fetch of this
  * layer; the running totals count the requests again.  EINVAL: no such earlier fetch on this stream (a multi-layer call
  * does not count), layer out of range, missing / misaligned destination. */
 int harvest_fetch_kv_again(harvest_ctx *ctx, uint32_t layer, void *d_dst_k, void *d_dst_v, void *stream);

@@ -296,6 +296,7 @@ struct StreamState {
     int last_cls = -1;                      // class of the latest fetch enqueued on this stream, -1: none yet
     bool counted[HARVEST_N_CLASSES] = { false, false };   // the class's latest fetch ran kernels, so its counters are its own
                                             // (an empty block table runs none: that fetch reports zeros)
+    bool recorded = false;                  // a KV fetch was recorded into a graph: its replays write these lists and counters
     bool fixed = false;                     // the lists are borrowed, of a fixed size, and there is no side stream: the
                                             // state of a stream that harvest_fetch_kv_static serves
     // the latest single-layer KV fetch, for harvest_fetch_kv_again
@@ -1650,6 +1651,8 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     if (miss_out) lists.miss = miss_out;
     const KvWork &work = ss->work;
     uint32_t *cnt = lists.cnt;
+    const bool recording = is_capturing(ss->s);
+    if (recording) ss->recorded = true;
     const uint32_t tpc = tiles_per_chunk(c.cfg.chunk_bytes, TILE_4K);
     // A small table: the whole fetch is one kernel (no compaction) - see fetch_kv_small.  Unless most of it is padding: the
     // one kernel has a workgroup for every tile of every cell, and one whose cell asks for nothing still costs 0.4 ns
@@ -1660,7 +1663,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     // fetch that is being recorded: its replays may meet any number of live cells.
     uint64_t dead_tiles = 0;
     const volatile Report &latest = ss->h_feedback[HARVEST_KV];
-    if (ss->feedback_valid[HARVEST_KV] && latest.n_seq == n_seq && latest.max_blocks == max_blocks && !is_capturing(ss->s)) {
+    if (ss->feedback_valid[HARVEST_KV] && latest.n_seq == n_seq && latest.max_blocks == max_blocks && !recording) {
         const uint64_t live = (uint64_t)latest.hbm + latest.host;
         if (live < total) dead_tiles = (total - live) * tpc * c.cfg.n_planes * n_layers;
     }
@@ -1716,7 +1719,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     HIP_TRY(hipGetLastError());
     ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
     // lists recorded into a graph exist only once the graph has been replayed: nothing to use again
-    remember(!is_capturing(ss->s));
+    remember(!recording);
     return launch_gathers(ctx, ss, c, HARVEST_KV, lists, total, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
                           head_major ? &hm : nullptr, n_layers, dst_layer_stride, 0, false, n_seq, max_blocks);
 }
@@ -1735,8 +1738,9 @@ int harvest_fetch_kv_again(harvest_ctx *ctx, uint32_t layer, void *d_dst_k, void
     const auto k = ss->last_kv;
     // The lists of that fetch still describe this one when nothing has edited the directory since (and that fetch made
     // lists at all: small tables are fetched without); otherwise the table is resolved again.
-    // A recorded fetch resolves for itself too: by the time its graph is replayed, residency may be another.
-    if (!k.lists || k.edit_seq != c.edit_seq || is_capturing((hipStream_t)stream))
+    // A recorded fetch resolves for itself too: by the time its graph is replayed, residency may be another.  And once one has
+    // been recorded on this stream, a replay may have put its own requests in the lists' place.
+    if (!k.lists || k.edit_seq != c.edit_seq || ss->recorded || is_capturing((hipStream_t)stream))
         return fetch_kv_locked(ctx, layer, k.table, k.n_blocks, k.n_seq, k.max_blocks, d_dst_k, d_dst_v, k.seq_dst_block,
                                k.seq_cap_blocks, k.dst_cap, k.n_heads, k.block_tokens, stream, 1, 0);
     if (!d_dst_k || (c.cfg.n_planes == 2 && !d_dst_v) || (((uint64_t)d_dst_k | (uint64_t)d_dst_v) & 15)) return HARVEST_EINVAL;

@@ -206,3 +206,28 @@ def test_first_placement_on_a_stream_while_the_null_stream_is_busy():
         h.dev_plane(B.KV, B.CACHE, 0).zero_()
         torch.cuda.synchronize()
     h.close()
+
+
+@pytest.mark.parametrize("flags", [B.FLAG_GENERAL_FETCH, 0])
+def test_again_behind_a_replay_of_another_tables_fetch(flags):
+    rig = Rig(2048, 30, n_layers=2, flags=flags)
+    s, g, lens = torch.cuda.Stream(), torch.cuda.CUDAGraph(), [9, 17]
+    t, dt, dn, df, cap = rig.tables(lens, 20)
+    _, other_dt, other_dn, other_df, other_cap = rig.tables([30, 31], 33, seed=2)
+    (k, v), (ok, ov) = rig.buffers(cap), rig.buffers(other_cap)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        rig.h.fetch_kv(0, other_dt, other_dn, ok, ov, other_df, other_cap)       # the scratch is large enough for either
+    with torch.cuda.graph(g, stream=s):
+        rig.h.fetch_kv(1, other_dt, other_dn, ok, ov, other_df, other_cap)
+    for layer in (1, 0, 1):
+        with torch.cuda.stream(s):
+            rig.h.fetch_kv(1 - layer, dt, dn, k, v, df, cap)
+            g.replay()
+            rig.h.fetch_kv_again(layer, k, v)
+        torch.cuda.synchronize()
+        for p, buf in enumerate([k, v]):
+            got = buf.cpu().numpy()
+            assert np.array_equal(got[:cap * 2048], rig.expected(t, lens, p, layer))
+            assert (got[cap * 2048:] == 0xEE).all()
+    rig.h.close()

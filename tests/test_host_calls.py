@@ -278,3 +278,22 @@ def test_a_static_state_that_goes_to_another_stream_takes_no_report_with_it(fake
     assert path() == "one kernel"
     assert path() == "one kernel"
     c.close()
+
+
+def test_a_repeated_fetch_resolves_again_once_a_fetch_has_been_recorded_on_its_stream(fake):
+    """A replay, which the library cannot see, writes the stream's counters and lists: they no longer belong to the eager fetch
+    that the call repeats, and a count of one table with the list of another reaches beyond the destination."""
+    c = Ctx(fake, flags=B.FLAG_GENERAL_FETCH)
+    fetch = lambda width: fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, width, POOL, POOL, POOL, 8, c.stream)
+    again = lambda: fake.harvest_fetch_kv_again(c.h, 1, POOL, POOL, c.stream)
+    assert fetch(32) == B.OK
+    c.log()
+    assert again() == B.OK and not launches(c.log(), "classify_kv")
+    fake.fake_capture(c.stream)
+    assert fetch(16) == B.OK
+    fake.fake_capture(None)
+    assert fetch(32) == B.OK
+    for _ in range(2):                                    # a replay may come before either
+        c.log()
+        assert again() == B.OK and launches(c.log(), "classify_kv")
+    c.close()
