@@ -547,7 +547,8 @@ __device__ inline void copy_tile(uint64_t src, uint64_t dst, uint64_t len, uint3
 // expects to need the link (link_announce: now + its host-tier bytes at the link's rate, on the device's constant 100 MHz
 // clock); the copies that cross the link outside a fetch - placements, write-backs - look at that word before they take
 // their next tile and stand back while the time has not come (yield_link), though never for longer than YIELD_TICKS per
-// tile, so that they always get on (at a tenth of the link's rate or so when fetches never pause).  A miss is on the
+// 32 KiB, whatever their tiles measure, so that they always get on (12 workgroups: 6.5 GB/s, a ninth of the link, when fetches
+// never pause).  A miss is on the
 // critical path and a placement is best effort (paper Sections 2.2 and 3.1).  An estimate instead of an exact begin /
 // end: nothing has to be counted or taken back, and a word that is stale means no more than "nobody is fetching".  The
 // estimate is on the short side (the rate of an undisturbed fetch, no margin): a copy that follows the fetch on the same
@@ -559,13 +560,14 @@ __device__ inline void link_announce(unsigned long long *lease, uint64_t host_by
     if (!lease || !host_bytes) return;
     atomicMax(lease, (unsigned long long)(wall_clock64() + host_bytes / LINK_BYTES_PER_TICK));
 }
+template <uint32_t TILE>
 __device__ inline void yield_link(const unsigned long long *lease)
 {
     if (!lease) return;
     const uint64_t t0 = wall_clock64();
     for (;;) {
         const uint64_t now = wall_clock64();
-        if (now - t0 >= YIELD_TICKS || now >= __hip_atomic_load(lease, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+        if (now - t0 >= YIELD_TICKS * TILE / 32768 || now >= __hip_atomic_load(lease, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
         __builtin_amdgcn_s_sleep(127);
     }
 }
@@ -1028,7 +1030,7 @@ __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
     constexpr uint32_t TILE = WG * 16 * U;
     __shared__ unsigned long long s_tile[2];
     const uint32_t tid = threadIdx.x;
-    if (tid == 0) { yield_link(a.lease); s_tile[0] = atomicAdd(a.next, 1ull); }
+    if (tid == 0) { yield_link<TILE>(a.lease); s_tile[0] = atomicAdd(a.next, 1ull); }
     __syncthreads();
     uint64_t t = s_tile[0];
     for (uint32_t turn = 1; t < a.n_tiles; turn ^= 1) {
@@ -1042,7 +1044,7 @@ __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
             u32x4 v[U];
 #pragma unroll
             for (int i = 0; i < U; ++i) v[i] = ld16<false>(s + tid + i * WG);
-            if (tid == 0) { yield_link(a.lease); s_tile[turn] = atomicAdd(a.next, 1ull); }
+            if (tid == 0) { yield_link<TILE>(a.lease); s_tile[turn] = atomicAdd(a.next, 1ull); }
             if (m.dst0) {
 #pragma unroll
                 for (int i = 0; i < U; ++i) st16<NT>(d0 + tid + i * WG, v[i]);
@@ -1052,7 +1054,7 @@ __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
                 for (int i = 0; i < U; ++i) st16<NT>(d1 + tid + i * WG, v[i]);
             }
         } else {
-            if (tid == 0) { yield_link(a.lease); s_tile[turn] = atomicAdd(a.next, 1ull); }
+            if (tid == 0) { yield_link<TILE>(a.lease); s_tile[turn] = atomicAdd(a.next, 1ull); }
             const uint32_t n_vec = (uint32_t)(len >> 4);
             for (uint32_t i = tid; i < n_vec; i += WG) {
                 u32x4 v = ld16<false>(s + i);

@@ -231,3 +231,30 @@ def test_again_behind_a_replay_of_another_tables_fetch(flags):
             assert np.array_equal(got[:cap * 2048], rig.expected(t, lens, p, layer))
             assert (got[cap * 2048:] == 0xEE).all()
     rig.h.close()
+
+
+def test_a_write_back_beside_a_fetch_keeps_its_share_of_the_link():
+    """Copies outside a fetch stand back while one needs the link, though never for longer than 60 us per 32 KiB and workgroup: the
+    default 12 workgroups keep 6.5 GB/s.  Three quarters of that are asked for, with 0.1 ms for the host."""
+    n, moved, chunk = 4000, 60, 32768
+    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n, n_host_slots=n, n_cache_slots=1, n_local_slots=0))
+    h.register(B.KV, n, np.arange(n))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    dt, dn, df = dev(np.arange(n, dtype=np.int32)[None]), dev(np.array([n], dtype=np.int32)), dev(np.zeros(1, dtype=np.int64))
+    k, v = (torch.empty(n * chunk, dtype=torch.uint8, device="cuda") for _ in range(2))
+    src = [torch.zeros(moved * chunk, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    ids, at, us = np.arange(moved), np.arange(moved), []
+    for _ in range(6):                                    # (two streams on one hardware queue run one after the other)
+        a, b = torch.cuda.Stream(), torch.cuda.Stream()
+        begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        h.evict(B.KV, -1, ids, src[0], src[1], at, moved, stream=b)
+        torch.cuda.synchronize()
+        h.fetch_kv(0, dt, dn, k, v, df, n, stream=a)      # 4.6 ms of the link
+        begin.record(b)
+        h.evict(B.KV, -1, ids, src[0], src[1], at, moved, stream=b)
+        end.record(b)
+        torch.cuda.synchronize()
+        us.append(begin.elapsed_time(end) * 1e3)
+    print("write-backs of 3.9 MB beside a fetch:", [round(x) for x in us], "us", flush=True)
+    assert max(us) <= 2 * moved * chunk / 6.5e3 / 0.75 + 100
+    h.close()
