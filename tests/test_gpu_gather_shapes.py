@@ -59,18 +59,19 @@ class Rig:
         return [torch.full((self.n_layers * cap * self.chunk + 64,), 0xEE, dtype=torch.uint8, device="cuda") for _ in range(2)]
 
 
-@pytest.mark.parametrize("n_planes", [1, 2])
+@pytest.mark.parametrize("n_planes,layout", [(1, 0), (2, 0), (2, B.FLAG_CACHE_PLANES_ADJACENT)])
 @pytest.mark.parametrize("chunk", [16, 1008, 1024, 2064, 4080, 4096, 4112, 8208, 16384 + 48])
 @pytest.mark.parametrize("threads,host_wgs", [(64, 0), (64, 1), (128, 3), (256, 0)])
-def test_both_tiers_in_one_launch(n_planes, chunk, threads, host_wgs):
-    rig = Rig(chunk, 41, n_layers=3, n_planes=n_planes, flags=B.FLAG_GENERAL_FETCH, gather_threads=threads, host_wgs=host_wgs)
+def test_both_tiers_in_one_launch(n_planes, layout, chunk, threads, host_wgs):
+    """Plane after plane, and both planes of a request in one pass where the cache tier keeps them side by side."""
+    rig = Rig(chunk, 41, n_layers=3, n_planes=n_planes, flags=B.FLAG_GENERAL_FETCH | layout, gather_threads=threads, host_wgs=host_wgs)
     lens = [13, 1, 0, 22]
     t, dt, dn, df, cap = rig.tables(lens, 23)
     for _ in range(2):                                # the second call's grid is sized by the first one's report
         k, v = rig.buffers(cap)
         rig.h.fetch_kv_layers(0, 3, dt, dn, k, v if n_planes == 2 else None, cap * chunk, df, cap)
         counts, miss, n_miss = rig.h.fetch_info(miss_cap=t.size)
-        assert sorted(miss.tolist()) == rig.misses(t, lens) and counts["n_host"] == n_miss
+        assert miss.tolist() == rig.misses(t, lens) and counts["n_host"] == n_miss
         for p, buf in enumerate([k, v][:n_planes]):
             got = buf.cpu().numpy()
             for layer in range(3):
@@ -97,7 +98,7 @@ def test_again_counts_its_requests(host_every, local_every):
 
 
 @pytest.mark.parametrize("n_planes", [1, 2])
-@pytest.mark.parametrize("lens,width", [([1], 1), ([60, 62], 64), ([64, 0], 64), ([50, 79], 129), ([255], 255), ([256, 0], 256), ([200, 55, 257], 257), ([3, 510], 513), ([0, 0], 600),
+@pytest.mark.parametrize("lens,width", [([1], 1), ([64], 64), ([65], 65), ([60, 62], 64), ([64, 0], 64), ([50, 79], 129), ([255], 255), ([256, 0], 256), ([200, 55, 257], 257), ([3, 510], 513), ([0, 0], 600),
                                         ([1, 2, 0, 5], 1024)])
 def test_one_kernel_fetch_at_the_edges_of_its_rounds(n_planes, lens, width):
     """Tables of one cell up to several rounds of 512, twice: the second call of a mostly empty table takes the general path."""
@@ -112,7 +113,7 @@ def test_one_kernel_fetch_at_the_edges_of_its_rounds(n_planes, lens, width):
         k, v = rig.buffers(max(cap, 1))
         rig.h.fetch_kv_layers(0, 2, dt, dn, k, v if n_planes == 2 else None, max(cap, 1) * 4112, df, max(cap, 1))
         counts, miss, _ = rig.h.fetch_info(miss_cap=t.size)
-        assert sorted(miss.tolist()) == rig.misses(np.where(t >= 0, t, rig.n), lens)
+        assert miss.tolist() == rig.misses(np.where(t >= 0, t, rig.n), lens)
         assert counts["n_requests"] == cap and counts["n_invalid"] == bad.sum()
         for p, buf in enumerate([k, v][:n_planes]):
             for layer in range(2):
@@ -123,7 +124,7 @@ def test_one_kernel_fetch_at_the_edges_of_its_rounds(n_planes, lens, width):
     rig.h.close()
 
 
-@pytest.mark.parametrize("lens,width", [([1], 1), ([300, 513], 600), ([5, 9], 4096), ([2, 1, 0], 4)])
+@pytest.mark.parametrize("lens,width", [([1], 1), ([65], 65), ([63, 64], 64), ([129], 129), ([300, 513], 600), ([5, 9], 4096), ([2, 1, 0], 4)])
 def test_static_fetch_hands_out_counters_and_misses_in_order(lens, width):
     rig = Rig(2048, 50)
     t, dt, dn, df, cap = rig.tables(lens, width)
@@ -145,21 +146,31 @@ def test_static_fetch_hands_out_counters_and_misses_in_order(lens, width):
     rig.h.close()
 
 
-@pytest.mark.parametrize("n_planes,flags", [(1, 0), (2, 0), (2, B.FLAG_CACHE_PLANES_ADJACENT)])
+@pytest.mark.parametrize("n_planes,cache", [(1, "slots"), (2, "slots"), (2, "adjacent"), (1, "segments"), (2, "segments")])
 @pytest.mark.parametrize("chunk", [16, 1040, 16384, 32768 + 48])
 @pytest.mark.parametrize("n", [1, 80, 81, 128, 129])
-def test_moves_with_and_without_a_list_on_the_device(n_planes, flags, chunk, n):
-    """place, place_from and evict of as many objects as travel with a launch, and one more; tiles of 1, 16 and 32 KiB."""
-    layers, rng = 2, np.random.default_rng(n)
+def test_moves_with_and_without_a_list_on_the_device(n_planes, cache, chunk, n):
+    """place, place_from and evict of as many objects as travel with a launch, and one more; tiles of 1, 16 and 32 KiB; cache slots per
+    plane, slots with the planes side by side, segments of a shared pool."""
+    layers, rng, granule = 2, np.random.default_rng(n), 256
+    segment = -(-layers * n_planes * chunk // granule) * granule
     h = B.Harvest(kv=B.ClassSpec(n_layers=layers, n_planes=n_planes, chunk_bytes=chunk, max_objects=n + 3, n_host_slots=n + 3,
-                                 n_cache_slots=n, n_local_slots=3), flags=flags)
+                                 n_cache_slots=0 if cache == "segments" else n, n_local_slots=3),
+                  flags=B.FLAG_CACHE_PLANES_ADJACENT if cache == "adjacent" else 0,
+                  **(dict(shared_cache_bytes=n * segment, shared_granule=granule) if cache == "segments" else {}))
     dev = lambda a: torch.from_numpy(a).cuda()
     host_slots = rng.permutation(n + 3).astype(np.int64)
     h.register(B.KV, n, host_slots[:n])
     local = h.register(B.KV, 3, host_slots[n:], tier=B.LOCAL)
     bytes_of = lambda: rng.integers(0, 256, (n_planes, layers, n + 5, chunk), dtype=np.uint8)
     host = lambda: np.stack([h.host_plane(B.KV, p) for p in range(n_planes)])
-    pool = lambda tier: np.stack([h.dev_plane(B.KV, tier, p).cpu().numpy() for p in range(n_planes)])
+
+    def pool(tier):
+        if tier == B.CACHE and cache == "segments":        # taken from the low end on, each [layer][plane][chunk]
+            segments = h.shared_cache.cpu().numpy().reshape(n, segment)[:, :layers * n_planes * chunk]
+            return segments.reshape(n, layers, n_planes, chunk).transpose(2, 1, 0, 3).copy()
+        return np.stack([h.dev_plane(B.KV, tier, p).cpu().numpy() for p in range(n_planes)])
+
     for p in range(n_planes):
         h.host_plane(B.KV, p)[:] = rng.integers(0, 256, (layers, n + 3, chunk), dtype=np.uint8)
     ids, block = rng.permutation(n), rng.permutation(n + 5)[:n]
