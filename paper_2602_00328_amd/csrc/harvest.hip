@@ -779,7 +779,7 @@ hipEvent_t prof_event(harvest_ctx *ctx)
 // Workgroups of nthr threads with HOST_LOADS loads each in flight for the host tier: host_grid counts 8 KiB of loads.
 uint32_t host_workgroups(const harvest_ctx *ctx, uint32_t nthr)
 {
-    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, (uint64_t)ctx->host_grid * 128 / nthr), MAX_GRID / 2);
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, (uint64_t)ctx->host_grid * 256 / nthr), MAX_GRID / 2);
 }
 
 // Launches the gathers of both tiers on the caller's stream.
@@ -811,8 +811,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     ga.dst_step = dst_step;
     ga.chunk_bytes = c.cfg.chunk_bytes;
     ga.tiles_per_chunk = tpc;
-    ga.pages_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16 * HOST_LOADS);
-    ga.n_planes = planes;
+    ga.pages_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16 * HOST_PAGE);
     // timing events cannot be recorded into a graph, and taking one from the pool may allocate
     const bool profile = ctx->profile && !ss->fixed && !is_capturing(ss->s);
     const bool host_tier = c.cfg.n_host_slots != 0;
@@ -840,7 +839,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
         double us_hbm = 2.0 * seen * bytes / 6.0e6, us_host = seen_host * bytes / 57.0e3;     // at 6 TB/s and 57 GB/s
         serial = serial || std::max(us_hbm, us_host) < 35.0 || std::min(us_hbm, us_host) < 8.0;
     }
-    const uint32_t host_wgs = host_tier ? host_workgroups(ctx, hm ? 128 : nthr) : 0;   // head-major: 256 threads with half the loads
+    const uint32_t host_wgs = host_tier ? host_workgroups(ctx, nthr) : 0;
     const uint32_t max_wgs = MAX_GRID - host_wgs;
     const uint32_t hbm_wgs = grid_for(fold ? want * planes : want, ctx->gather_grid ? std::min(ctx->gather_grid, max_wgs) : max_wgs);
     GatherBooks books{};
@@ -1012,8 +1011,8 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
     ctx->host_grid = cfg->host_wgs ? cfg->host_wgs : 24;          // 192 KiB of reads in flight, see host_tier
     ctx->gather_threads = cfg->gather_threads ? cfg->gather_threads : HBM_WG;
     ctx->ctl_grid = 8 * ctx->n_cu;                 // HBM-bound fills
-    // Copies that cross PCIe outside a fetch (place, write-back): persistent workgroups with one 32 KiB tile in flight
-    // each, the tiles counted out to them one at a time; they stand back while a fetch says it needs the link (see
+    // Copies that cross PCIe outside a fetch (place, write-back): persistent workgroups with one tile in flight each (32 KiB from
+    // the host, 16 KiB to it), the tiles counted out to them one at a time; they stand back while a fetch says it needs the link (see
     // link_announce).  Alone, 8 of them already fill the link (a 906 MB placement: 15.9 ms = 57 GB/s with 8, 12, 16 or
     // 64; 24 ms with 4); what the number decides is who gets the link when a fetch on another stream wants it too - the
     // link serves its clients by what they have in flight.  Beside a stream of PCIe-bound KV fetches of 1.04 ms each, a
@@ -1386,7 +1385,7 @@ static int enqueue_poison(harvest_ctx *ctx, ClassState &c, const std::vector<uin
     std::vector<Item> items;
     for (uint32_t s : slots)
         for (uint32_t p = 0; p < c.cfg.n_planes; ++p)
-            for (uint32_t l = 0; l < c.cfg.n_layers; ++l) items.push_back({ 0, c.addr(T_CACHE, p, l, s) });
+            for (uint32_t l = 0; l < c.cfg.n_layers; ++l) items.push_back({ c.addr(T_CACHE, p, l, s) });
     memcpy(st->h, items.data(), items.size() * sizeof(Item));
     void *d_items = nullptr;
     HIP_TRY(hipHostGetDevicePointer(&d_items, st->h, 0));
@@ -1679,10 +1678,10 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         for (int t = 0; t < 3; ++t) ga.layer_stride[t] = cd.layer_stride[t];
         ga.dst_base[0] = (uint64_t)d_dst_k; ga.dst_base[1] = (uint64_t)d_dst_v;
         ga.dst_step = dst_layer_stride; ga.n_rep = n_layers;
-        ga.chunk_bytes = c.cfg.chunk_bytes; ga.n_planes = c.cfg.n_planes;
+        ga.chunk_bytes = c.cfg.chunk_bytes;
         const uint32_t nthr = total <= 64 * ROUND ? 64 : WG;
         ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16);
-        ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr / 2) : 0;                // with half of HOST_LOADS each
+        ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr) : 0;
         ga.hbm_wgs = (uint32_t)total * ga.tiles_per_chunk;
         SmallBooks books{ lists.miss, cnt, info, ctx->d_totals + HARVEST_KV * C_N, ss->d_feedback + HARVEST_KV,
                           c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr, n_seq };

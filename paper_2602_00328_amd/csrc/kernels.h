@@ -20,7 +20,7 @@
 //                              in one pass (measured on MI355X: short workgroups beat deep unrolling and persistent
 //                              grids by ~15%, one-wavefront workgroups beat four-wavefront ones by 2-5%, non-temporal
 //                              accesses are worth ~11%, 64 KiB source runs 4-5% over 32 KiB ones).  Host tier: the
-//                              launch's first workgroups, a few dozen wavefronts that stay, with four loads in
+//                              launch's first workgroups, 96 wavefronts that stay, with two loads in
 //                              flight per thread: enough compute units to keep the PCIe link full, and no more host reads
 //                              in flight than the link absorbs, because the rest would only stand in the HBM tier's way.
 //   gather_hm                : the same into a head-major working layout.
@@ -41,8 +41,9 @@ constexpr int WAVES = WG / 64;
 constexpr uint32_t TILE_4K = WG * 16;           // 4 KiB: one 16-byte access per thread of a 256-thread workgroup
 constexpr int HBM_WG = 64;                      // the HBM-tier gather runs one wavefront per workgroup (see gather)
 constexpr int UNROLL_HOST = 8;
-constexpr uint32_t TILE_HOST = WG * 16 * UNROLL_HOST;   // 32 KiB tiles of the host-built copy lists (place, write-back)
-constexpr int HOST_LOADS = 4;                   // 16-byte loads a thread of the host-tier gather keeps in flight
+constexpr uint32_t TILE_HOST = WG * 16 * UNROLL_HOST;   // 32 KiB tiles of fill_items
+constexpr int HOST_LOADS = 2;                   // 16-byte loads a thread of the host-tier gather keeps in flight
+constexpr int HOST_PAGE = 4;                    // loads a thread makes for one page, see host_tier
 
 // directory entry: [1:0] tier, [31:2] slot in that tier (host slot for HOST), [63:32] generation
 constexpr uint64_t TIER_MASK = 3;
@@ -59,7 +60,7 @@ enum { T_HOST = 0, T_CACHE = 1, T_LOCAL = 2, T_NONE = 3 };
 //   dst = byte offset of the chunk inside the destination plane.
 struct Rec { uint64_t src, dst; };
 // A host-built list names chunks by absolute address (slot poisoning) ...
-struct Item { uint64_t src, dst; };
+struct Item { uint64_t dst; };
 // ... or whole objects (placement, write-back), whose chunks - every plane, every layer of the move - the kernel finds by itself:
 // byte offsets of plane 0, first layer of the move, from the bases in MoveArgs.  dst1 has its tier in bits [1:0].
 constexpr uint64_t NOWHERE = ~0ull;
@@ -76,9 +77,13 @@ struct MoveArgs {
 };
 // The order in which a move takes its chunks follows the layout of the cache tier, so that the writes to slots that were handed
 // out together are one ascending stream: [plane][layer][slot], [layer][slot][plane], or one segment per object (64 blocks of
-// 32 layers from a staged copy, placed and revoked: 66.0 us object after object, 60.9 this way).
+// 32 layers from a staged copy, placed and revoked, in one run: 66.0 us object after object, 60.9 this way).
 enum { ORDER_PLANE_LAYER_OBJ = 0, ORDER_LAYER_OBJ_PLANE, ORDER_OBJ_LAYER_PLANE };
-// Lists of up to this many objects / entries are kernel arguments; longer ones are copied to the device first.
+// Lists of up to this many objects / entries are kernel arguments; longer ones are copied to the device first, which costs a call
+// 7-8 us more whatever their length (32 KiB per object placed from a staged copy and revoked: 17 objects 34.4 us against 41.5 with
+// the list on the device, 80: 51.8 against 60.4; 81 objects, beyond the line, 59.4).  The room itself costs a short list nothing (one
+// object with room for 16, 80 and 160: 31.6, 33.0 and 31.6 us).  80 and 128 fill half of the 4 KiB that kernel arguments may take; nothing
+// that was measured says that they must not fill more.
 #ifdef HARVEST_FAULT_INJECTION
 constexpr uint32_t MOVE_INLINE = 2, DIR_INLINE = 2;      // the CPU tests' lists are short: they are to walk both ways
 #else
@@ -111,7 +116,6 @@ struct GatherArgs {
     uint64_t dst_base[2];     // [plane]
     uint64_t chunk_bytes;
     uint32_t tiles_per_chunk;
-    uint32_t n_planes;
     // consecutive layers gathered from the same lists (an object has the same slot in every layer): repetition r reads
     // layer_stride[tier] * r further and writes dst_step * r further
     uint64_t layer_stride[3];
@@ -585,14 +589,16 @@ __device__ inline void yield_link(const unsigned long long *lease)
 // memory however many loads its threads have outstanding, so the rate is set by how many CUs take part (5 saturate the
 // 57 GB/s link) - and every host read in flight beyond what the link can absorb only queues in the memory pipeline the HBM
 // tier is using at the same time (8 x 256 threads with 16 loads per thread cost it 12 %, 24 x 256 with 2 loads 8 %).  Hence
-// HOST_LOADS loads of 16 bytes per thread in flight and host_grid * 128 threads: 192 KiB.
+// HOST_LOADS loads of 16 bytes per thread in flight and host_grid * 256 threads: 192 KiB.  In 96 wavefronts, because each waits for
+// its own loads and for its stores to be taken: beside another stream's kernel that keeps the memory busy, 48 wavefronts with four
+// loads each let the link idle (402 MB from the host beside a copy: 9.68 ms, alone 7.02; 96 with two: 7.62).
 //
-// Work is cut into pages of 4 loads per thread (4 KiB for one-wavefront workgroups), numbered through the whole list
+// Work is cut into pages of HOST_PAGE loads per thread (4 KiB for one-wavefront workgroups), numbered through the whole list
 // (request * pages per chunk + position), so the bytes in flight do not depend on the chunk size.  A workgroup takes a whole
-// page - of both planes, half a page of each per step, if there are two: one-wavefront workgroups that took 1 KiB pieces in
+// page - of both planes, a load of each per step, if there are two: one-wavefront workgroups that took 1 KiB pieces in
 // turn, so that four of them shared a page of host memory, ran at 57.36 (one plane, 16 MiB chunks), 57.14 and 57.02 GB/s (two
-// planes, 32 and 16 KiB chunks), with whole pages it is 57.51, 57.45 and 57.36; half as many or twice as many
-// threads 57.1-55.3.  Each load is issued as soon as its list entry has arrived.  Lanes beyond a chunk's end re-read
+// planes, 32 and 16 KiB chunks), with whole pages it was 57.51, 57.45 and 57.36; pages of two loads change nothing (15 125
+// blocks, 30 % of them on the host: 5 187 us, whole pages 5 185).  Each load is issued as soon as its list entry has arrived.  Lanes beyond a chunk's end re-read
 // the chunk's first bytes and store nothing: loads stay free of branches.
 template <int NTHR, int PLANES>
 __device__ inline void host_page(const GatherArgs &a, uint64_t src, uint64_t dst, uint32_t page, uint32_t tid)
@@ -600,8 +606,8 @@ __device__ inline void host_page(const GatherArgs &a, uint64_t src, uint64_t dst
     constexpr int L = HOST_LOADS / PLANES;                     // loads per thread, plane and step
     const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
 #pragma unroll
-    for (int s = 0; s < HOST_LOADS; s += L) {
-        const uint32_t u0 = (page * HOST_LOADS + s) * NTHR;
+    for (int s = 0; s < HOST_PAGE; s += L) {
+        const uint32_t u0 = (page * HOST_PAGE + s) * NTHR;
         if (u0 >= chunk_units) break;
         u32x4 v0[L], v1[L];
         uint32_t u[L];

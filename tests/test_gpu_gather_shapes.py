@@ -1,7 +1,7 @@
 """The kernels of the fetch at the edges of their tiles, pages and grids, against numpy indexing of the payload.
 
 A fetch moves bytes, so the comparison is exact.  Sizes are in 16-byte units around what one workgroup takes at a time:
-1 KiB tiles, 4 KiB host pages (64 threads x 4 loads), half pages per plane.
+1 KiB tiles, 4 KiB host pages (64 threads x 4 loads), read two loads at a time.
 """
 import numpy as np
 import pytest
@@ -305,4 +305,38 @@ def test_a_fetch_beside_a_wide_placement_is_seen_by_the_next_tile():
             break
     print(f"{len(beside)} fetches beside a placement: {np.median(beside):.3f} ms, alone {alone:.3f}", flush=True)
     assert np.median(beside) < 4.7 * alone
+    h.close()
+
+
+def test_a_fetch_from_the_host_keeps_its_rate_beside_a_kernel_that_fills_the_device():
+    """The next layer's experts cross PCIe while this layer's are being read (the prefetch ring): loads from the host must go on
+    arriving although every store queues behind the other kernel's.  Each wavefront waits for its own loads, so many with few
+    loads keep the link busy: 96 of them with two loads each, 1.09 times the time alone; 48 with four, 1.38."""
+    n, chunk = 6, 64 << 20
+    h = B.Harvest(expert=B.ClassSpec(n_layers=1, n_planes=1, chunk_bytes=chunk, max_objects=n, n_host_slots=n, n_cache_slots=1,
+                                     n_local_slots=0, n_experts=n))
+    h.register(B.EXPERT, n, np.arange(n))
+    topk = torch.arange(n, dtype=torch.int32, device="cuda")[None]
+    staging, ptrs = torch.empty(n * chunk, dtype=torch.uint8, device="cuda"), torch.zeros(n, dtype=torch.int64, device="cuda")
+    a, b = (torch.empty(1 << 30, dtype=torch.uint8, device="cuda") for _ in range(2))
+    fetches = torch.cuda.Stream()
+
+    def fetch():
+        begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        begin.record(fetches)
+        h.fetch_experts(0, topk, staging, n, ptrs, stream=fetches)
+        end.record(fetches)
+        fetches.synchronize()
+        return begin.elapsed_time(end)
+
+    alone, beside = np.median([fetch() for _ in range(6)][2:]), []
+    for _ in range(6):                                    # (two streams on one hardware queue run one after the other)
+        other = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        for _ in range(40):                               # 13 ms and more beside 7
+            B.plain_copy(b, a, a.numel(), stream=other)
+        beside.append(fetch())
+        torch.cuda.synchronize()
+    print(f"402 MB from the host alone {alone:.2f} ms, beside a copy {[round(x, 2) for x in beside]}", flush=True)
+    assert max(beside) < 1.18 * alone
     h.close()
