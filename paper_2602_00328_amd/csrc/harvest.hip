@@ -981,7 +981,10 @@ int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &r
         return go(in_args ? move_hbm<true> : move_hbm<false>, dim3(grid_for(tiles_hbm, MAX_GRID)), dim3(64));
     }
     // over PCIe (or more tiles than move_hbm counts): persistent workgroups, tiles counted out
-    const int unroll = way == TO_HOST ? 4 : 8;
+    // 32 KiB tiles; 16 KiB ones to the host where chunks are smaller, which would leave every tile of 32 KiB to the loop for
+    // remainders (200 blocks of 2 x 16 KiB beside a copy on another stream: 206 us against 382), while for whole tiles half as
+    // many bytes in flight are too few there (2 x 32 KiB: 365 us against 267; alone 255 and 256)
+    const int unroll = way == TO_HOST && a.chunk_bytes < WG * 16 * 8 ? 4 : 8;
     a.tiles_per_chunk = tiles_per_chunk(a.chunk_bytes, WG * 16 * unroll);
     const uint64_t tiles = items * a.tiles_per_chunk;
     if (tiles >= 0xFFFFFFFFull) return HARVEST_EINVAL;         // 64 TiB
@@ -989,7 +992,8 @@ int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &r
     a.next = ss->next;
     a.lease = way == WITHIN_HBM ? nullptr : ctx->d_lease;
     const dim3 grid(grid_for(tiles, way == WITHIN_HBM ? ctx->ctl_grid : ctx->pcie_grid));
-    if (way == TO_HOST) return go(in_args ? move_pcie<true, 4, true> : move_pcie<false, 4, true>, grid, dim3(WG));
+    if (way == TO_HOST && unroll == 4) return go(in_args ? move_pcie<true, 4, true> : move_pcie<false, 4, true>, grid, dim3(WG));
+    if (way == TO_HOST) return go(in_args ? move_pcie<true, 8, true> : move_pcie<false, 8, true>, grid, dim3(WG));
     return go(in_args ? move_pcie<true, 8, false> : move_pcie<false, 8, false>, grid, dim3(WG));
 }
 
@@ -1011,8 +1015,8 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
     ctx->host_grid = cfg->host_wgs ? cfg->host_wgs : 24;          // 192 KiB of reads in flight, see host_tier
     ctx->gather_threads = cfg->gather_threads ? cfg->gather_threads : HBM_WG;
     ctx->ctl_grid = 8 * ctx->n_cu;                 // HBM-bound fills
-    // Copies that cross PCIe outside a fetch (place, write-back): persistent workgroups with one tile in flight each (32 KiB from
-    // the host, 16 KiB to it), the tiles counted out to them one at a time; they stand back while a fetch says it needs the link (see
+    // Copies that cross PCIe outside a fetch (place, write-back): persistent workgroups with one tile of 32 KiB in flight each
+    // (see launch_move), the tiles counted out to them one at a time; they stand back while a fetch says it needs the link (see
     // link_announce).  Alone, 8 of them already fill the link (a 906 MB placement: 15.9 ms = 57 GB/s with 8, 12, 16 or
     // 64; 24 ms with 4); what the number decides is who gets the link when a fetch on another stream wants it too - the
     // link serves its clients by what they have in flight.  Beside a stream of PCIe-bound KV fetches of 1.04 ms each, a

@@ -1030,8 +1030,8 @@ __device__ inline MoveChunk move_chunk(const MoveArgs &a, uint32_t item)
 // beyond the tiles, and the one that draws the last puts it back.  The next number is drawn while the tile is on its way; whether
 // a fetch needs the link is asked last, right before the next tile's loads go out - asked along with the draw, the answer was a tile
 // old, and a fetch of 200 blocks beside a placement of 32 workgroups took 1.56 ms instead of 0.98 (alone 0.25).
-// Writes to the host are non-temporal, 16 KiB tiles: 16 MiB take 305.8 us (54.9 GB/s) against 316.7 with plain stores of
-// 32 KiB, 2 MiB 43 against 48.
+// Writes to the host are non-temporal: 16 MiB take 308 us in tiles of 16 KiB and 311 in tiles of 32, 317 with plain stores (2 MiB 43
+// against 48).
 template <bool INLINE, int U, bool NT>
 __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
 {
