@@ -11,7 +11,9 @@ when a tail block fills, write it back, demote it, place it in the cache tier an
 Prints ONE JSON line on stdout; progress goes to stderr.
 """
 import argparse
+import gc
 import json
+import math
 import os
 import re
 import sys
@@ -56,7 +58,7 @@ def parse():
                     help="kv_decode: order in which the resident blocks were placed (shuffled = scattered over the cache "
                          "tier, the default; in_sequence_order = a sequence's blocks are neighbours)")
     ap.add_argument("--no-profile", action="store_true",
-                    help="kv_decode only: no timing events on the gather launches (per-kernel figures are then absent)")
+                    help="kv_decode only: leave out the leg that times the tiers' kernels (per-kernel figures are then absent)")
     ap.add_argument("--fetch-layers", type=int, default=1,
                     help="variant: every step fetches this many consecutive layers with one harvest_fetch_kv_layers call "
                          "(must divide --layers); isolation and graph legs are skipped")
@@ -344,30 +346,36 @@ def bench_experts(args, embed=False):
     dev = torch.device("cuda", 0)
     phi = args.workload == "experts_phi"
     L = min(args.layers, 32 if phi else 24)
-    if phi:
-        wl = W.expert_offload(seed=args.seed, shape=W.ExpertShape(n_layers=L))
-    else:
-        wl = W.expert_lru(seed=args.seed, shape=W.ExpertShape(n_layers=L, n_experts=60, d_model=2048, d_ff=1408))
-    t0 = time.time()
-    spec = S.expert_spec(wl)
-    if not args.no_isolation:
-        spec.n_cache_slots = wl.n_objects              # room for the all-cache isolation point
-    eng = HipEngine(expert=spec, profile=True, host_wgs=args.host_wgs, gather_threads=args.gather_threads)
-    run = S.ExpertRun(eng, wl)
-    run._spec = spec
-    torch.cuda.synchronize()
+
+    def set_up(profile):
+        if phi:
+            wl = W.expert_offload(seed=args.seed, shape=W.ExpertShape(n_layers=L))
+        else:
+            wl = W.expert_lru(seed=args.seed, shape=W.ExpertShape(n_layers=L, n_experts=60, d_model=2048, d_ff=1408))
+        t0 = time.time()
+        spec = S.expert_spec(wl)
+        if not args.no_isolation:
+            spec.n_cache_slots = wl.n_objects          # room for the all-cache isolation point
+        eng = HipEngine(expert=spec, profile=profile, host_wgs=args.host_wgs, gather_threads=args.gather_threads)
+        run = S.ExpertRun(eng, wl)
+        run._spec = spec
+        torch.cuda.synchronize()
+        sp = eng.spec[1]
+        log(f"[bench] {args.workload}: {L} layers x {sp.n_experts} experts of {sp.chunk_bytes / 2**20:.1f} MiB, host pool "
+            f"{sp.n_host_slots * sp.chunk_bytes / 2**30:.1f} GiB, set up in {time.time() - t0:.1f}s")
+        return wl, eng, run
+
+    # as in bench_kv: timed as callers run it, the tiers' kernels in a leg of their own
+    wl, eng, run = set_up(False)
     sp = eng.spec[1]
     E = sp.n_experts
-    log(f"[bench] {args.workload}: {L} layers x {E} experts of {sp.chunk_bytes / 2**20:.1f} MiB, host pool "
-        f"{sp.n_host_slots * sp.chunk_bytes / 2**30:.1f} GiB, set up in {time.time() - t0:.1f}s")
     staging = torch.empty(E * sp.chunk_bytes, dtype=torch.uint8, device=dev)
     ptrs = torch.zeros(E, dtype=torch.int64, device=dev)
     n_total = args.warmup + args.steps
     topk = {(t, l): torch.from_numpy(wl.routing(t, l)).to(dev) for t in range(n_total) for l in range(L)}
 
-    eng._last_staging = staging                        # what the LRU's placements copy from (harvest_place_from)
-
     def step(t):
+        eng._last_staging = staging                    # what the LRU's placements copy from (harvest_place_from)
         for l in range(L):
             eng.h.fetch_experts(l, topk[(t, l)], staging, E, ptrs)
             if wl.lru_capacity:
@@ -376,7 +384,6 @@ def bench_experts(args, embed=False):
     for t in range(args.warmup):
         step(t)
     torch.cuda.synchronize()
-    eng.h.profile()
     f0 = eng.h.stats()
     c0 = {k: int(getattr(f0.fetch[1], k)) for k in COUNT_KEYS}
     p0 = int(f0.n_placed[1])
@@ -385,14 +392,11 @@ def bench_experts(args, embed=False):
         step(t)
     torch.cuda.synchronize()
     sec = time.perf_counter() - a
-    pr = eng.h.profile()
     f1 = eng.h.stats()
     d = {k: int(getattr(f1.fetch[1], k)) - c0[k] for k in COUNT_KEYS}
     placed = int(f1.n_placed[1]) - p0
     chunk = sp.chunk_bytes
     payload = (d["n_cache"] + d["n_host"]) * chunk
-    hbm_gbs = 2 * d["n_cache"] * chunk / (pr.hbm_ms * 1e-3) / 1e9 if pr.hbm_ms > 0 and d["n_cache"] else 0.0
-    host_gbs = d["n_host"] * chunk / (pr.host_ms * 1e-3) / 1e9 if pr.host_ms > 0 and d["n_host"] else 0.0
     out = {
         "metric": "fetch GB/s (read+write) and % of HBM/PCIe peak; objects/s; bit-exact vs oracle",
         "value": round(2 * payload / sec / 1e9, 2), "unit": "GB/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -408,20 +412,16 @@ def bench_experts(args, embed=False):
         "objects_per_s": round(d["n_requests"] / sec), "bit_exact": None,
         "served_per_step": {k: round(v / args.steps, 2) for k, v in d.items()},
         "placed_per_step": round(placed / args.steps, 2),
-        "roofline": {"bound": "hbm", "kernel": "gather<64,1,false> (HBM-tier workgroups, whole experts)", "achieved": round(hbm_gbs, 1),
-                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(hbm_gbs / HBM_PEAK_GBS, 4), "traffic": None,
-                     "launches": int(pr.hbm_launches)},
-        "host_tier": {"bound": "pcie", "kernel": "gather (host-tier workgroups)", "achieved": round(host_gbs, 2), "unit": "GB/s",
-                      "launches": int(pr.host_launches)},
         "cpu_baseline": None,
     }
-    log(f"[bench] {args.steps} steps in {sec:.3f}s: {out['ms_per_step']} ms/step; HBM tier {hbm_gbs:.0f} GB/s, host tier "
-        f"{host_gbs:.1f} GB/s; per step {out['served_per_step']}, placed {out['placed_per_step']}")
+    log(f"[bench] {args.steps} steps in {sec:.3f}s: {out['ms_per_step']} ms/step; per step {out['served_per_step']}, "
+        f"placed {out['placed_per_step']}")
     if not args.no_cpu_baseline:
         out["bit_exact"], out["cpu_baseline"] = experts_vs_oracle(args, wl, run, eng, n_total, L)
-    if not args.no_isolation:
-        # ---- isolation points: the same routing with every non-local expert in the cache tier, then on the host ----
-        iso = {}
+    iso = {}
+
+    def isolation():
+        """The same routing with every non-local expert in the cache tier, then on the host."""
         everything = [i for i in range(wl.n_objects) if eng.lookup(1, i)[0] != 2]
         for name in ("all_cache", "all_host"):
             if name == "all_cache":
@@ -440,21 +440,47 @@ def bench_experts(args, embed=False):
             p, s1 = eng.h.profile(), eng.h.stats()
             n_c = int(s1.fetch[1].n_cache) - int(s0.fetch[1].n_cache)
             n_h = int(s1.fetch[1].n_host) - int(s0.fetch[1].n_host)
-            if name == "all_cache":
+            if not p.hbm_launches:
+                iso[name] = {"experts": n_c or n_h, "ms_per_layer": round(dt * 1e3 / L, 3)}
+            elif name == "all_cache":
                 g = 2 * n_c * chunk / (p.hbm_ms * 1e-3) / 1e9
-                iso[name] = {"experts": n_c, "ms_per_layer": round(dt * 1e3 / L, 3), "kernel_ms_per_layer": round(p.hbm_ms / L, 3),
-                             "hbm_gbs_read_write": round(g, 1), "frac_of_hbm_peak": round(g / HBM_PEAK_GBS, 4)}
+                iso[name] |= {"kernel_ms_per_layer": round(p.hbm_ms / L, 3), "hbm_gbs_read_write": round(g, 1),
+                              "frac_of_hbm_peak": round(g / HBM_PEAK_GBS, 4)}
             else:
                 g = n_h * chunk / (p.host_ms * 1e-3) / 1e9
-                iso[name] = {"experts": n_h, "ms_per_layer": round(dt * 1e3 / L, 3), "kernel_ms_per_layer": round(p.host_ms / L, 3),
-                             "pcie_gbs": round(g, 2)}
+                iso[name] |= {"kernel_ms_per_layer": round(p.host_ms / L, 3), "pcie_gbs": round(g, 2)}
             log(f"[bench] isolation {name}: {iso[name]}")
-        out["isolation"] = iso
+
+    if not args.no_isolation:
+        isolation()
         if not wl.lru_capacity:                          # back to the configured residency for the prefetch leg
             eng.place(1, [int(i) for i in wl.place_order])
     if args.prefetch and not wl.lru_capacity:
         out["prefetch"] = bench_prefetch(eng, wl, topk, staging, ptrs, L, E, sp.chunk_bytes, sec / (args.steps * L),
                                          range(args.warmup, n_total))
+    eng.close()
+    wl, eng, run = set_up(True)
+    for t in range(args.warmup):
+        step(t)
+    torch.cuda.synchronize()
+    eng.h.profile()
+    f0 = eng.h.stats()
+    for t in range(args.warmup, n_total):
+        step(t)
+    pr, f1 = eng.h.profile(), eng.h.stats()
+    n_c, n_h = (int(getattr(f1.fetch[1], k)) - int(getattr(f0.fetch[1], k)) for k in ("n_cache", "n_host"))
+    hbm_gbs = 2 * n_c * chunk / (pr.hbm_ms * 1e-3) / 1e9 if pr.hbm_ms > 0 and n_c else 0.0
+    host_gbs = n_h * chunk / (pr.host_ms * 1e-3) / 1e9 if pr.host_ms > 0 and n_h else 0.0
+    log(f"[bench] profiled: HBM tier {hbm_gbs:.0f} GB/s, host tier {host_gbs:.1f} GB/s")
+    out["roofline"] = {"bound": "hbm", "kernel": "gather<64,1,false,false> (HBM-tier workgroups, whole experts)",
+                       "achieved": round(hbm_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(hbm_gbs / HBM_PEAK_GBS, 4),
+                       "traffic": None, "launches": int(pr.hbm_launches),
+                       "note": "from a leg of the same steps in a profiled context, which launches the tiers apart"}
+    out["host_tier"] = {"bound": "pcie", "kernel": "gather (host-tier workgroups)", "achieved": round(host_gbs, 2), "unit": "GB/s",
+                        "launches": int(pr.host_launches)}
+    if not args.no_isolation:
+        isolation()
+        out["isolation"] = iso
     eng.close()
     if embed:
         return out
@@ -888,7 +914,6 @@ def bench_kv(args, seed, full):
     from workloads.hip_engine import HipEngine
     dev = torch.device("cuda", 0)
     n_total = args.warmup + args.steps + args.graph_steps
-    t0 = time.time()
     kv_shape = W.KVShape(n_layers=args.layers, elt_bytes=args.kv_elt_bytes)
     wl = W.kv_decode(seed=seed, n_layers=args.layers, n_steps=n_total, shape=kv_shape, placement=args.placement)
     sh = wl.shape
@@ -899,13 +924,21 @@ def bench_kv(args, seed, full):
     all_cache_slack = int(wl.n_objects - wl.resident.sum())
     n_cache_slots = int(wl.resident.sum()) + (0 if args.no_isolation else all_cache_slack)
     shared_bytes = n_cache_slots * (-(-(2 * chunk * args.layers) // 4096) * 4096) if args.shared_cache else 0
-    eng = HipEngine(kv=S.kv_spec(wl, cache_slack=0 if args.no_isolation else all_cache_slack, shared=args.shared_cache),
-                    profile=not args.no_profile, host_wgs=args.host_wgs, shared_cache_bytes=shared_bytes,
-                    gather_threads=args.gather_threads, cache_planes_adjacent=args.cache_layout == "adjacent")
-    run = S.KVRun(eng, wl)
-    torch.cuda.synchronize()
-    log(f"[bench] pools filled and {len(run.live)} blocks placed in {time.time() - t0:.1f}s")
-    dd = DeviceDecode(run, eng, wl, n_total, head_major=args.head_major, fetch_layers=args.fetch_layers, again=args.fetch_again)
+
+    def set_up(wl, profile):
+        t0 = time.time()
+        eng = HipEngine(kv=S.kv_spec(wl, cache_slack=0 if args.no_isolation else all_cache_slack, shared=args.shared_cache),
+                        profile=profile, host_wgs=args.host_wgs, shared_cache_bytes=shared_bytes,
+                        gather_threads=args.gather_threads, cache_planes_adjacent=args.cache_layout == "adjacent")
+        run = S.KVRun(eng, wl)
+        torch.cuda.synchronize()
+        log(f"[bench] pools filled and {len(run.live)} blocks placed in {time.time() - t0:.1f}s")
+        return eng, run, DeviceDecode(run, eng, wl, n_total, head_major=args.head_major, fetch_layers=args.fetch_layers,
+                                      again=args.fetch_again)
+
+    # Everything up to the tier times runs as callers run it.  A context with HARVEST_FLAG_PROFILE launches the two tiers of
+    # a fetch apart, so that events can time them: that is a leg of its own, at the end, over the same steps.
+    eng, run, dd = set_up(wl, False)
 
     # ---- calibration kernel of known size (for hardware byte counters) + achievable-copy ceiling ----
     cal_bytes = 2 << 30
@@ -962,7 +995,6 @@ def bench_kv(args, seed, full):
     for _ in range(args.warmup):
         dd.step()
     torch.cuda.synchronize()
-    eng.h.profile()
     c0 = kv_totals(eng.h.stats())
     torch.cuda.synchronize()
     t_start = time.perf_counter()
@@ -970,22 +1002,13 @@ def bench_kv(args, seed, full):
         dd.step()
     torch.cuda.synchronize()
     t_end = time.perf_counter()
-    pr = eng.h.profile()
     c1 = kv_totals(eng.h.stats())
     d = {k: c1[k] - c0[k] for k in COUNT_KEYS}
     sec = t_end - t_start
     ms_per_step = sec * 1e3 / args.steps
     FL = args.fetch_layers                                  # requests are counted once per call, bytes move per layer
     payload = d["n_requests"] * 2 * chunk * FL              # bytes delivered into the working layout
-    hbm_payload = (d["n_local"] + d["n_cache"]) * 2 * chunk * FL
-    host_payload = d["n_host"] * 2 * chunk * FL
     value = 2 * payload / sec / 1e9
-    hbm_ms = pr.hbm_ms / max(1, pr.hbm_launches) if pr.hbm_launches else float("nan")
-    host_ms = pr.host_ms / max(1, pr.host_launches) if pr.host_launches else float("nan")
-    hbm_alg_bytes = 2 * hbm_payload / max(1, pr.hbm_launches)     # read + write, per launch
-    host_bytes = host_payload / max(1, pr.host_launches)
-    hbm_gbs = hbm_alg_bytes / (hbm_ms * 1e-3) / 1e9
-    host_gbs = host_bytes / (host_ms * 1e-3) / 1e9
     graph_replay = None
     if args.graph_steps:
         # ---- the same decode, continued, with every fetch replayed from a recorded graph ----
@@ -1006,8 +1029,7 @@ def bench_kv(args, seed, full):
                         "note": "fetches replayed from HIP graphs recorded once per layer; appends, tail write-backs and "
                                 "placements stay eager between the replays; included in the bit_exact check"}
         log(f"[bench] graph replay: {graph_replay['ms_per_step']:.3f} ms/step, {graph_replay['value']:.0f} GB/s")
-    log(f"[bench] {args.steps} steps in {sec:.3f}s: {ms_per_step:.3f} ms/step, {value:.0f} GB/s read+write, "
-        f"HBM-tier kernel {hbm_ms:.3f} ms ({hbm_gbs:.0f} GB/s), host-tier kernel {host_ms:.3f} ms ({host_gbs:.1f} GB/s)")
+    log(f"[bench] {args.steps} steps in {sec:.3f}s: {ms_per_step:.3f} ms/step, {value:.0f} GB/s read+write")
 
     # ---- bit-exactness of the timed configuration against the oracle, and the oracle's own speed ----
     bit_exact, cpu_baseline = None, None
@@ -1109,20 +1131,13 @@ def bench_kv(args, seed, full):
             dd.fetch(0)
             torch.cuda.synchronize()
             counts, _, _ = eng.h.fetch_info()
-            eng.h.profile()
             a = time.perf_counter()
             for i in range(n_it):
                 dd.fetch(i % sh.n_layers)
             torch.cuda.synchronize()
             dt = time.perf_counter() - a
-            p = eng.h.profile()
-            pay = counts["n_requests"] * 2 * chunk
+            iso[name] = {"ms_per_fetch": round(dt * 1e3 / n_it, 4), "objects_per_s": round(counts["n_requests"] / (dt / n_it))}
             if name == "all_cache":
-                k_ms = p.hbm_ms / p.hbm_launches
-                iso[name] = {"ms_per_fetch": round(dt * 1e3 / n_it, 4), "kernel_ms": round(k_ms, 4),
-                             "hbm_gbs_read_write": round(2 * pay / (k_ms * 1e-3) / 1e9, 1),
-                             "frac_of_hbm_peak": round(2 * pay / (k_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                             "objects_per_s": round(counts["n_requests"] / (dt / n_it))}
                 if args.graph_steps:                     # the short fetch is where launch overhead shows: replay it
                     dd.record_graphs()
                     torch.cuda.synchronize()
@@ -1132,13 +1147,60 @@ def bench_kv(args, seed, full):
                     torch.cuda.synchronize()
                     iso[name]["graph_replay_ms_per_fetch"] = round((time.perf_counter() - a) * 1e3 / n_it, 4)
                     dd.graphs = None
-            else:
-                k_ms = p.host_ms / p.host_launches
-                g = counts["n_host"] * 2 * chunk / (k_ms * 1e-3) / 1e9
-                iso[name] = {"ms_per_fetch": round(dt * 1e3 / n_it, 4), "kernel_ms": round(k_ms, 4),
-                             "pcie_gbs": round(g, 2), "frac_of_pcie_peak": round(g / pcie_peak_gbs, 4),
-                             "objects_per_s": round(counts["n_requests"] / (dt / n_it))}
             log(f"[bench] isolation {name}: {iso[name]}")
+
+    # ---- tier times: the same steps and the same isolation points in a profiled context ----
+    eng.close()
+    del eng, run, dd
+    gc.collect()
+    hbm_ms = host_ms = hbm_alg_bytes = host_bytes = hbm_gbs = host_gbs = float("nan")
+    n_launches = [0, 0]
+    if not args.no_profile:
+        wl2 = W.kv_decode(seed=seed, n_layers=args.layers, n_steps=n_total, shape=kv_shape, placement=args.placement)
+        eng, run, dd = set_up(wl2, True)
+        for _ in range(args.warmup):
+            dd.step()
+        torch.cuda.synchronize()
+        eng.h.profile()
+        c0 = kv_totals(eng.h.stats())
+        for _ in range(args.steps):
+            dd.step()
+        pr = eng.h.profile()
+        c1 = kv_totals(eng.h.stats())
+        p = {k: c1[k] - c0[k] for k in COUNT_KEYS}
+        assert p == d
+        n_launches = [int(pr.hbm_launches), int(pr.host_launches)]
+        hbm_ms, host_ms = pr.hbm_ms / max(1, pr.hbm_launches), pr.host_ms / max(1, pr.host_launches)
+        hbm_alg_bytes = 2 * (p["n_local"] + p["n_cache"]) * 2 * chunk * FL / max(1, pr.hbm_launches)     # read + write, per launch
+        host_bytes = p["n_host"] * 2 * chunk * FL / max(1, pr.host_launches)
+        hbm_gbs = hbm_alg_bytes / (hbm_ms * 1e-3) / 1e9
+        host_gbs = host_bytes / (host_ms * 1e-3) / 1e9
+        log(f"[bench] profiled: HBM-tier kernel {hbm_ms:.3f} ms ({hbm_gbs:.0f} GB/s), host-tier kernel {host_ms:.3f} ms "
+            f"({host_gbs:.1f} GB/s)")
+        if not args.no_isolation:
+            closed = [b for s in range(wl2.n_seq) for b in run.tables[s][:-1]]
+            assert (eng.place(0, [b for b in closed if eng.lookup(0, b)[0] == 0]) == 0).all()
+            for name, n_it in (("all_cache", args.iso_steps), ("all_host", max(2, args.iso_steps // 4))):
+                if name == "all_host":
+                    eng.revoke(0, closed)
+                dd.fetch(0)
+                torch.cuda.synchronize()
+                counts, _, _ = eng.h.fetch_info()
+                eng.h.profile()
+                for i in range(n_it):
+                    dd.fetch(i % sh.n_layers)
+                pr = eng.h.profile()
+                if name == "all_cache":
+                    k_ms, pay = pr.hbm_ms / pr.hbm_launches, counts["n_requests"] * 2 * chunk
+                    g = 2 * pay / (k_ms * 1e-3) / 1e9
+                    iso[name] |= {"kernel_ms": round(k_ms, 4), "hbm_gbs_read_write": round(g, 1),
+                                  "frac_of_hbm_peak": round(g / HBM_PEAK_GBS, 4)}
+                else:
+                    k_ms = pr.host_ms / pr.host_launches
+                    g = counts["n_host"] * 2 * chunk / (k_ms * 1e-3) / 1e9
+                    iso[name] |= {"kernel_ms": round(k_ms, 4), "pcie_gbs": round(g, 2), "frac_of_pcie_peak": round(g / pcie_peak_gbs, 4)}
+                log(f"[bench] profiled isolation {name}: {iso[name]}")
+        eng.close()
 
     # Hardware byte counters cannot be read from inside this process: `traffic` is what two rocprofv3 --pmc passes over
     # this same command measured, kept with their command lines in the file named below - a stored figure of the
@@ -1155,7 +1217,7 @@ def bench_kv(args, seed, full):
             traffic_source = ("profiles/gather_hbm_kv_decode_pmc.txt: rocprofv3 --pmc FETCH_SIZE and --pmc WRITE_SIZE passes over "
                               "this command, scaled by the same counters' reading of a 2 GiB plain copy; stored, not measured "
                               "by this run")
-    alone = iso.get("all_cache", {}).get("hbm_gbs_read_write")
+    alone = iso.get("all_cache", {}).get("hbm_gbs_read_write")        # none with --no-profile or --no-isolation
 
     out = {
         "metric": "fetch GB/s (read+write) and % of HBM/PCIe peak; objects/s; bit-exact vs oracle",
@@ -1183,32 +1245,33 @@ def bench_kv(args, seed, full):
         "graph_replay": graph_replay,
         "served": {k: v // args.steps for k, v in d.items()},
         "roofline": {"bound": "hbm", "kernel": ("gather_hm<2>" if args.head_major else
-                                                "gather<%d,2,%s>" % (args.gather_threads or 64, "true" if args.shared_cache or
+                                                "gather<%d,2,%s,false>" % (args.gather_threads or 64, "true" if args.shared_cache or
                                                                      args.cache_layout == "adjacent" else "false"))
                                                + " (HBM-tier workgroups)", "achieved": round(hbm_gbs, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(hbm_gbs / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_source": traffic_source,
-                     "launches": int(pr.hbm_launches), "avg_launch_ms": round(hbm_ms, 5),
-                     "algorithmic_bytes_per_launch": round(hbm_alg_bytes), "plain_copy_gbs": round(plain_gbs, 1),
+                     "launches": n_launches[0], "avg_launch_ms": round(hbm_ms, 5),
+                     "algorithmic_bytes_per_launch": hbm_alg_bytes if math.isnan(hbm_alg_bytes) else round(hbm_alg_bytes), "plain_copy_gbs": round(plain_gbs, 1),
                      "frac_of_plain_copy": round(hbm_gbs / plain_gbs, 4),
                      "read_only_gbs": round(rates["read"], 1), "write_only_gbs": round(rates["write"], 1),
                      "copy_bound_gbs": round(copy_bound_gbs, 1),
                      "copy_bound_note": "a copy moves half its bytes each way over the same memory interface: 2 / (1/read_only + "
                                         "1/write_only), both measured in this run (one 16-byte access per thread; 1024-thread workgroups for the reads, 256 for the writes: one-wavefront workgroups with a single access each are bound by the dispatcher, not by memory)",
-                     "note": "achieved / frac: the kernel inside the timed step, where the host-tier kernel reads over PCIe "
-                             "beside it; alone: the same request list with every block in the cache tier (isolation.all_cache)",
+                     "note": "achieved / frac: a leg of the same steps in a profiled context, which launches the tiers apart so that "
+                             "events can time them (the timed steps launch both in one kernel, unprofiled), the host tier "
+                             "reading over PCIe beside it; alone: the same request list with every block in the cache tier "
+                             "(isolation.all_cache, its kernel figures from that context too)",
                      "achieved_alone": alone, "frac_alone": round(alone / HBM_PEAK_GBS, 4) if alone else None},
         "host_tier": {"bound": "pcie", "kernel": ("gather_hm<2>" if args.head_major else "gather<64,2>") + " (host-tier workgroups, zero-copy over PCIe)",
                       "achieved": round(host_gbs, 2), "peak": round(pcie_peak_gbs, 2), "unit": "GB/s",
-                      "frac": round(host_gbs / pcie_peak_gbs, 4), "launches": int(pr.host_launches),
-                      "avg_launch_ms": round(host_ms, 5), "bytes_per_launch": round(host_bytes),
+                      "frac": round(host_gbs / pcie_peak_gbs, 4), "launches": n_launches[1],
+                      "avg_launch_ms": round(host_ms, 5), "bytes_per_launch": host_bytes if math.isnan(host_bytes) else round(host_bytes),
                       "peak_source": "1 GiB pinned->device hipMemcpyAsync, median of 10, same run"},
         "overlap": {"max_kernel_ms_over_step_ms": round(max(hbm_ms, host_ms) / ms_per_step, 4)},
         "isolation": iso,
         "write_paths": write_paths,
         "cpu_baseline": cpu_baseline,
     }
-    eng.close()
     return out
 
 
