@@ -776,10 +776,10 @@ hipEvent_t prof_event(harvest_ctx *ctx)
     return e;
 }
 
-// Workgroups of nthr threads with HOST_LOADS loads each in flight for the host tier: host_grid counts 8 KiB of loads.
-uint32_t host_workgroups(const harvest_ctx *ctx, uint32_t nthr)
+// Workgroups of nthr threads with `loads` loads each in flight for the host tier: host_grid counts 8 KiB of loads.
+uint32_t host_workgroups(const harvest_ctx *ctx, uint32_t nthr, uint32_t loads = 2)
 {
-    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, (uint64_t)ctx->host_grid * 256 / nthr), MAX_GRID / 2);
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, (uint64_t)ctx->host_grid * 512 / (nthr * loads)), MAX_GRID / 2);
 }
 
 // Launches the gathers of both tiers on the caller's stream.
@@ -827,19 +827,20 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     // (15 000 blocks with the planes side by side: 302.8 us on an exact grid, 307.2 us on one 1/8 short).
     uint64_t max_tiles = max_req * tpc;
     uint64_t want = max_tiles;
-    bool host_stays = host_tier, serial = !host_tier;
+    bool link_bound = host_tier, serial = !host_tier;
     if (ss->feedback_valid[cls]) {
         const volatile Report &r = ss->h_feedback[cls];
         const uint64_t seen = r.hbm, seen_host = r.host;
         uint64_t guess = std::max<uint64_t>(1, cls == HARVEST_KV ? seen : seen - seen / 8) * tpc;
         want = std::min(max_tiles, std::max<uint64_t>(guess, 16ull * ctx->n_cu));
-        // profiled fetches only, see below
-        host_stays = host_tier && seen_host * 48 > seen;
+        // host bytes at the link's rate against HBM bytes, read and written, at HBM's: about 1 : 55 per request
+        link_bound = host_tier && seen_host * 55 > seen;
         double bytes = (double)planes * c.cfg.chunk_bytes * n_rep;
         double us_hbm = 2.0 * seen * bytes / 6.0e6, us_host = seen_host * bytes / 57.0e3;     // at 6 TB/s and 57 GB/s
         serial = serial || std::max(us_hbm, us_host) < 35.0 || std::min(us_hbm, us_host) < 8.0;
     }
-    const uint32_t host_wgs = host_tier ? host_workgroups(ctx, nthr) : 0;
+    ga.host_loads = hm || link_bound ? 2 : HOST_PAGE;         // see host_tier
+    const uint32_t host_wgs = host_tier ? host_workgroups(ctx, nthr, ga.host_loads) : 0;
     const uint32_t max_wgs = MAX_GRID - host_wgs;
     const uint32_t hbm_wgs = grid_for(fold ? want * planes : want, ctx->gather_grid ? std::min(ctx->gather_grid, max_wgs) : max_wgs);
     GatherBooks books{};
@@ -887,10 +888,10 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
         }
         // Timed by tier: the two halves as launches of their own, whose events (attached to the dispatches) read the
         // kernels' own begin and end.  Crossing to the side stream and back costs some 15 us each way, so the one that is
-        // expected to take longer - host bytes at PCIe rate against HBM bytes at HBM rate, about 1 : 48 per request - stays on
+        // expected to take longer stays on
         // the caller's stream and the short one takes the detour inside its shadow; no detour when even the longer one is
         // over in less than the crossings take or the shorter one is next to nothing.
-        hipStream_t s_host = (host_stays || serial) ? ss->s : ss->side, s_hbm = (host_stays && !serial) ? ss->side : ss->s;
+        hipStream_t s_host = (link_bound || serial) ? ss->s : ss->side, s_hbm = (link_bound && !serial) ? ss->side : ss->s;
         if (!serial) {
             HIP_TRY(hipEventRecord(ss->fork, ss->s));
             HIP_TRY(hipStreamWaitEvent(ss->side, ss->fork, 0));

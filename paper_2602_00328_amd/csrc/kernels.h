@@ -20,7 +20,7 @@
 //                              in one pass (measured on MI355X: short workgroups beat deep unrolling and persistent
 //                              grids by ~15%, one-wavefront workgroups beat four-wavefront ones by 2-5%, non-temporal
 //                              accesses are worth ~11%, 64 KiB source runs 4-5% over 32 KiB ones).  Host tier: the
-//                              launch's first workgroups, 96 wavefronts that stay, with two loads in
+//                              launch's first workgroups, 96 or 48 wavefronts that stay, with two or four loads in
 //                              flight per thread: enough compute units to keep the PCIe link full, and no more host reads
 //                              in flight than the link absorbs, because the rest would only stand in the HBM tier's way.
 //   gather_hm                : the same into a head-major working layout.
@@ -42,8 +42,7 @@ constexpr uint32_t TILE_4K = WG * 16;           // 4 KiB: one 16-byte access per
 constexpr int HBM_WG = 64;                      // the HBM-tier gather runs one wavefront per workgroup (see gather)
 constexpr int UNROLL_HOST = 8;
 constexpr uint32_t TILE_HOST = WG * 16 * UNROLL_HOST;   // 32 KiB tiles of fill_items
-constexpr int HOST_LOADS = 2;                   // 16-byte loads a thread of the host-tier gather keeps in flight
-constexpr int HOST_PAGE = 4;                    // loads a thread makes for one page, see host_tier
+constexpr int HOST_PAGE = 4;                    // 16-byte loads a thread of the host-tier gather makes for one page, see host_tier
 
 // directory entry: [1:0] tier, [31:2] slot in that tier (host slot for HOST), [63:32] generation
 constexpr uint64_t TIER_MASK = 3;
@@ -125,6 +124,7 @@ struct GatherArgs {
     // the HBM tier; either may be 0
     uint32_t n_host, hbm_wgs;
     uint32_t pages_per_chunk;            // of the host tier, see host_tier
+    uint32_t host_loads;                 // 2 or HOST_PAGE: loads a thread of the host tier keeps in flight
 };
 // In pinned memory, one per class and stream: requests of either tier of the latest fetch whose kernels have run - hints for the
 // next launch - and the rows and columns of the block table they were asked for with (experts: zero).
@@ -589,21 +589,23 @@ __device__ inline void yield_link(const unsigned long long *lease)
 // memory however many loads its threads have outstanding, so the rate is set by how many CUs take part (5 saturate the
 // 57 GB/s link) - and every host read in flight beyond what the link can absorb only queues in the memory pipeline the HBM
 // tier is using at the same time (8 x 256 threads with 16 loads per thread cost it 12 %, 24 x 256 with 2 loads 8 %).  Hence
-// HOST_LOADS loads of 16 bytes per thread in flight and host_grid * 256 threads: 192 KiB.  In 96 wavefronts, because each waits for
-// its own loads and for its stores to be taken: beside another stream's kernel that keeps the memory busy, 48 wavefronts with four
-// loads each let the link idle (402 MB from the host beside a copy: 9.68 ms, alone 7.02; 96 with two: 7.62).
+// 192 KiB in flight (host_grid * 8 KiB), in 96 wavefronts with two 16-byte loads per thread or in 48 with four.  Each wavefront waits
+// for its own loads and for its stores to be taken, so while the memory is busy 48 of them let the link idle and 96 do not.  That
+// decides: a fetch that is bound by the link gets 96 (402 MB from the host beside another stream's copy: 7.62 ms against
+// 9.68 with 48, alone 7.02; 12 000 blocks, 3 % of them on the host: 424 us against 433), one that is bound by HBM, whose host
+// reads have time, gets 48 and an HBM tier that they disturb less (1.5 % on the host: 256 us against 273; none: 252).
 //
 // Work is cut into pages of HOST_PAGE loads per thread (4 KiB for one-wavefront workgroups), numbered through the whole list
 // (request * pages per chunk + position), so the bytes in flight do not depend on the chunk size.  A workgroup takes a whole
-// page - of both planes, a load of each per step, if there are two: one-wavefront workgroups that took 1 KiB pieces in
+// page - of both planes, half of the loads of a step each, if there are two: one-wavefront workgroups that took 1 KiB pieces in
 // turn, so that four of them shared a page of host memory, ran at 57.36 (one plane, 16 MiB chunks), 57.14 and 57.02 GB/s (two
 // planes, 32 and 16 KiB chunks), with whole pages it was 57.51, 57.45 and 57.36; pages of two loads change nothing (15 125
 // blocks, 30 % of them on the host: 5 187 us, whole pages 5 185).  Each load is issued as soon as its list entry has arrived.  Lanes beyond a chunk's end re-read
 // the chunk's first bytes and store nothing: loads stay free of branches.
-template <int NTHR, int PLANES>
+template <int NTHR, int PLANES, int LOADS>
 __device__ inline void host_page(const GatherArgs &a, uint64_t src, uint64_t dst, uint32_t page, uint32_t tid)
 {
-    constexpr int L = HOST_LOADS / PLANES;                     // loads per thread, plane and step
+    constexpr int L = LOADS / PLANES;                     // loads per thread, plane and step
     const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
 #pragma unroll
     for (int s = 0; s < HOST_PAGE; s += L) {
@@ -628,7 +630,7 @@ __device__ inline void host_page(const GatherArgs &a, uint64_t src, uint64_t dst
     }
 }
 
-template <int NTHR, int PLANES>
+template <int NTHR, int PLANES, int LOADS>
 __device__ inline void host_tier(const Rec *__restrict__ recs, uint32_t n_req, const GatherArgs &a, uint32_t b0)
 {
     const uint32_t ppc = a.pages_per_chunk;
@@ -637,7 +639,7 @@ __device__ inline void host_tier(const Rec *__restrict__ recs, uint32_t n_req, c
         for (uint64_t g = b0; g < n_pages; g += a.n_host) {
             const uint32_t idx = (uint32_t)g / ppc, page = (uint32_t)g - idx * ppc;
             const Rec x = recs[idx];
-            host_page<NTHR, PLANES>(a, (x.src & 0x0000FFFFFFFFFFFCull) + rep * a.layer_stride[T_HOST], x.dst + rep * a.dst_step, page,
+            host_page<NTHR, PLANES, LOADS>(a, (x.src & 0x0000FFFFFFFFFFFCull) + rep * a.layer_stride[T_HOST], x.dst + rep * a.dst_step, page,
                                     threadIdx.x);
         }
 }
@@ -673,7 +675,8 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
             if (books.report) books.report->host = n_req;
             link_announce(books.lease, (uint64_t)n_req * a.chunk_bytes * PLANES * a.n_rep);
         }
-        host_tier<NTHR, PLANES>(host_recs, n_req, a, blockIdx.x);
+        if (a.host_loads == HOST_PAGE) host_tier<NTHR, PLANES, HOST_PAGE>(host_recs, n_req, a, blockIdx.x);
+        else host_tier<NTHR, PLANES, 2>(host_recs, n_req, a, blockIdx.x);
         return;
     }
     const uint32_t bx = blockIdx.x - a.n_host, gx = a.hbm_wgs, plane_y = FOLD ? 0 : blockIdx.y, rep = MULTI ? blockIdx.z : 0;

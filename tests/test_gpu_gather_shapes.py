@@ -80,6 +80,30 @@ def test_both_tiers_in_one_launch(n_planes, layout, chunk, threads, host_wgs):
     rig.h.close()
 
 
+@pytest.mark.parametrize("n_planes,layout", [(1, 0), (2, 0), (2, B.FLAG_CACHE_PLANES_ADJACENT)])
+@pytest.mark.parametrize("chunk", [16, 1008, 2064, 4096, 4112, 16384 + 48])
+@pytest.mark.parametrize("threads", [64, 256])
+def test_a_few_blocks_from_the_host(n_planes, layout, chunk, threads):
+    """The second fetch knows from the first that HBM is what it waits for and reads the host with fewer wavefronts."""
+    rig = Rig(chunk, 300, n_layers=2, n_planes=n_planes, host_every=100, flags=B.FLAG_GENERAL_FETCH | layout, gather_threads=threads)
+    lens = [200, 0, 113]
+    t, dt, dn, df, cap = rig.tables(lens, 201)
+    t[np.isin(t, np.flatnonzero(rig.on_host))] = 0       # a block of the cache tier
+    t[0, :3] = np.flatnonzero(rig.on_host)[:3]
+    dt.copy_(torch.from_numpy(t))
+    for _ in range(3):
+        k, v = rig.buffers(cap)
+        rig.h.fetch_kv_layers(0, 2, dt, dn, k, v if n_planes == 2 else None, cap * chunk, df, cap)
+        counts, miss, _ = rig.h.fetch_info(miss_cap=t.size)
+        assert miss.tolist() == rig.misses(t, lens) and 0 < counts["n_host"] * 55 <= counts["n_cache"] + counts["n_local"]
+        for p, buf in enumerate([k, v][:n_planes]):
+            got = buf.cpu().numpy()
+            for layer in range(2):
+                assert np.array_equal(got[layer * cap * chunk:(layer + 1) * cap * chunk], rig.expected(t, lens, p, layer)), (p, layer)
+            assert (got[2 * cap * chunk:] == 0xEE).all()
+    rig.h.close()
+
+
 @pytest.mark.parametrize("host_every,local_every", [(0, 0), (1, 0), (2, 5)])
 def test_again_counts_its_requests(host_every, local_every):
     """All in the cache tier, all but one request in three on the host, and a mix: a repeated fetch adds to the totals."""

@@ -297,3 +297,22 @@ def test_a_repeated_fetch_resolves_again_once_a_fetch_has_been_recorded_on_its_s
         c.log()
         assert again() == B.OK and launches(c.log(), "classify_kv")
     c.close()
+
+
+def test_the_host_tier_is_spread_wider_when_the_link_is_what_a_fetch_waits_for(fake):
+    """Before anything is known, and when the last report says so: 96 single wavefronts at the head of the grid, otherwise 48."""
+    c = Ctx(fake, flags=B.FLAG_GENERAL_FETCH)
+
+    def head():
+        c.log()
+        assert fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 10000, POOL, POOL, POOL, 8, c.stream) == B.OK
+        log = c.log()
+        return int(re.search(r"grid (\d+),", log[launches(log, "gather")[0]]).group(1))
+
+    tiles = 32                                           # of 1 KiB a block: the HBM tier's share of the grid is known
+    assert head() == 96 + 10000 * tiles
+    words = (ctypes.c_uint32 * 16).from_address(fake.fake_pinned(64, fake.fake_pinned_count(64) - 1))
+    for hbm, host, wavefronts in ((9900, 100, 48), (9800, 200, 96), (10000, 0, 48), (5000, 5000, 96)):
+        words[:4] = [hbm, host, 1, 10000]
+        assert head() == wavefronts + hbm * tiles
+    c.close()
