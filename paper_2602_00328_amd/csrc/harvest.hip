@@ -738,9 +738,10 @@ int order_after_directory_edits(harvest_ctx *ctx, StreamState *ss, int cls)
 
 // Remembers the end of this call's work on the stream for the revocation drain.  Work recorded into a HIP graph runs
 // whenever the caller replays the graph, which no event of ours can see: the drain then waits for the whole device.
-int mark_last(harvest_ctx *ctx, StreamState *ss)
+// recording: whether the stream is being recorded, which every fetch asks once (0.4 us of the host's time).
+int mark_last(harvest_ctx *ctx, StreamState *ss, bool recording)
 {
-    if (is_capturing(ss->s)) {
+    if (recording) {
         ctx->captured_work = true;
         return HARVEST_OK;
     }
@@ -762,10 +763,10 @@ int launch(hipStream_t s, void (*kernel)(P...), dim3 grid, dim3 block, A... args
 // record without a system-scope fence takes; but a host that had run thousands of such launches ahead of the device was slow
 // afterwards - creating a context 640 us instead of 310, placing and revoking a block 75 instead of 35 - and so it is recorded.)
 template <typename... P, typename... A>
-int launch_last(harvest_ctx *ctx, StreamState *ss, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
+int launch_last(harvest_ctx *ctx, StreamState *ss, bool recording, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
 {
     int rc = launch(ss->s, kernel, grid, block, args...);
-    return rc ? rc : mark_last(ctx, ss);
+    return rc ? rc : mark_last(ctx, ss, recording);
 }
 
 hipEvent_t prof_event(harvest_ctx *ctx)
@@ -787,7 +788,7 @@ uint32_t host_workgroups(const harvest_ctx *ctx, uint32_t nthr, uint32_t loads =
 // n_rep > 1 gathers n_rep consecutive layers from the same two lists (they name slots, and an object has the same slot
 // in every layer): repetition r reads layer_stride(tier) * r further into every pool and writes dst_step * r further
 // into the destination.
-int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, const Lists &lists, uint64_t max_req,
+int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState &c, int cls, const Lists &lists, uint64_t max_req,
                    uint64_t dst_base0, uint64_t dst_base1, const HmArgs *hm = nullptr, uint32_t n_rep = 1,
                    uint64_t dst_step = 0, int64_t layer_delta = 0, bool repeat = false, uint32_t n_seq = 0, uint32_t max_blocks = 0)
 {
@@ -813,7 +814,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
     ga.tiles_per_chunk = tpc;
     ga.pages_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16 * HOST_PAGE);
     // timing events cannot be recorded into a graph, and taking one from the pool may allocate
-    const bool profile = ctx->profile && !ss->fixed && !is_capturing(ss->s);
+    const bool profile = ctx->profile && !ss->fixed && !recording;
     const bool host_tier = c.cfg.n_host_slots != 0;
     // one pass over both planes of each request where the cache tier keeps them side by side (see gather; not the
     // head-major gather, see gather_hm)
@@ -856,7 +857,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
         const uint32_t *cnt = lists.cnt;
         if (hm) {
             auto kernel = planes == 2 ? gather_hm<2> : gather_hm<1>;
-            if (!begin) return launch_last(ctx, ss, kernel, g, dim3(nthr), l_hbm, l_host, cnt, ga, *hm, books);
+            if (!begin) return launch_last(ctx, ss, recording, kernel, g, dim3(nthr), l_hbm, l_host, cnt, ga, *hm, books);
             hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, l_host, cnt, ga, *hm, books);
         } else {
             auto pick = [&](auto k64, auto k128, auto k256) { return nthr == 64 ? k64 : (nthr == 128 ? k128 : k256); };
@@ -867,7 +868,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
                                    : pick(gather<64, 1, false, M>, gather<128, 1, false, M>, gather<256, 1, false, M>);
             };
             auto kernel = ga.n_rep > 1 ? of(std::true_type{}) : of(std::false_type{});
-            if (!begin) return launch_last(ctx, ss, kernel, g, dim3(nthr), l_hbm, l_host, cnt, ga, books);
+            if (!begin) return launch_last(ctx, ss, recording, kernel, g, dim3(nthr), l_hbm, l_host, cnt, ga, books);
             hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, l_host, cnt, ga, books);
         }
         HIP_TRY(hipGetLastError());
@@ -912,7 +913,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, ClassState &c, int cls, co
         }
     }
     ss->feedback_valid[cls] = true;
-    return profile ? mark_last(ctx, ss) : HARVEST_OK;
+    return profile ? mark_last(ctx, ss, recording) : HARVEST_OK;
 }
 
 // What a move of objects of class c has in common, from layer l0 on.
@@ -972,7 +973,7 @@ int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &r
         int rc = launch(ss->s, kernel, grid, block, a, list);
         if (rc) return rc;
         *launched = true;
-        return mark_last(ctx, ss);
+        return mark_last(ctx, ss, false);          // (moves are refused on a stream that is being recorded)
     };
     const uint64_t items = (uint64_t)recs.size() * a.n_planes * a.n_layers;
     const uint64_t tiles_hbm = items * tiles_per_chunk(a.chunk_bytes, 64 * 16);
@@ -1018,11 +1019,11 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
     ctx->ctl_grid = 8 * ctx->n_cu;                 // HBM-bound fills
     // Copies that cross PCIe outside a fetch (place, write-back): persistent workgroups with one tile of 32 KiB in flight each
     // (see launch_move), the tiles counted out to them one at a time; they stand back while a fetch says it needs the link (see
-    // link_announce).  Alone, 8 of them already fill the link (a 906 MB placement: 15.9 ms = 57 GB/s with 8, 12, 16 or
-    // 64; 24 ms with 4); what the number decides is who gets the link when a fetch on another stream wants it too - the
-    // link serves its clients by what they have in flight.  Beside a stream of PCIe-bound KV fetches of 1.04 ms each, a
-    // placement with 64 workgroups makes a fetch take 8.1 ms, with 32 or 16: 1.3 ms, with 12: 1.2 ms, with 8: 1.1 ms
-    // (without the standing back: 16.8, 4.4, 1.8, 1.5, 1.3 ms).  A miss waits on the link, where its transfer contends
+    // link_announce).  Alone, 8 of them already fill the link (a 906 MB placement: 15.8-16.1 ms = 57 GB/s with 8, 12, 16, 32 or
+    // 64; 24-26 ms with 4); what the number decides is who gets the link when a fetch on another stream wants it too - the
+    // link serves its clients by what they have in flight.  Beside a stream of PCIe-bound KV fetches of 1.03 ms each, a
+    // placement with 64 workgroups makes a fetch take 16.8 ms, with 32: 3.6, with 16: 1.48, with 12: 1.28, with 8: 1.15 ms
+    // (without the standing back: 17.0, 9.0, 3.2, 2.5, 1.9 ms).  A miss waits on the link, where its transfer contends
     // with whatever else crosses it (paper Section 2.2), and a placement is best effort (Section 3.1), so the copies
     // run narrow.
     ctx->pcie_grid = cfg->pcie_wgs ? cfg->pcie_wgs : 12;
@@ -1694,7 +1695,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         const dim3 grid(n_layers > 1 ? std::max(ga.hbm_wgs, head) : ga.hbm_wgs + head, c.cfg.n_planes, n_layers > 1 ? n_layers + 1 : 1);
         auto kernel = c.cfg.n_planes == 2 ? (nthr == 64 ? fetch_kv_small<2, 64> : fetch_kv_small<2, WG>)
                                           : (nthr == 64 ? fetch_kv_small<1, 64> : fetch_kv_small<1, WG>);
-        if ((rc = launch_last(ctx, ss, kernel, grid, dim3(nthr), cd, layer, d_block_table, d_n_blocks, (uint32_t)total, max_blocks,
+        if ((rc = launch_last(ctx, ss, recording, kernel, grid, dim3(nthr), cd, layer, d_block_table, d_n_blocks, (uint32_t)total, max_blocks,
                               d_seq_dst_block, dst_capacity_blocks, ga, books)))
             return rc;
         ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
@@ -1724,7 +1725,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
     // lists recorded into a graph exist only once the graph has been replayed: nothing to use again
     remember(!recording);
-    return launch_gathers(ctx, ss, c, HARVEST_KV, lists, total, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
+    return launch_gathers(ctx, ss, recording, c, HARVEST_KV, lists, total, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
                           head_major ? &hm : nullptr, n_layers, dst_layer_stride, 0, false, n_seq, max_blocks);
 }
 
@@ -1757,7 +1758,7 @@ int harvest_fetch_kv_again(harvest_ctx *ctx, uint32_t layer, void *d_dst_k, void
         hm.ups = hm.upr * k.block_tokens;
     }
     ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
-    return launch_gathers(ctx, ss, c, HARVEST_KV, ss->lists[HARVEST_KV], (uint64_t)k.n_seq * k.max_blocks, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
+    return launch_gathers(ctx, ss, false, c, HARVEST_KV, ss->lists[HARVEST_KV], (uint64_t)k.n_seq * k.max_blocks, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
                           head_major ? &hm : nullptr, 1, 0, (int64_t)layer - (int64_t)k.layer, true,
                           k.n_seq, k.max_blocks);
 }
@@ -1791,7 +1792,7 @@ int harvest_fetch_kv_static(harvest_ctx *ctx, uint32_t layer, const int32_t *d_b
     rc = fetch_kv_locked(ctx, layer, d_block_table, d_n_blocks, n_seq, max_blocks, d_dst_k, d_dst_v, d_seq_dst_block, nullptr,
                          dst_capacity_blocks, 0, 0, stream, 1, 0, ss, d_miss_idx, d_info);
     if (rc || total || !d_info) return rc;
-    return launch_last(ctx, ss, zero_info, dim3(1), dim3(64), d_info);
+    return launch_last(ctx, ss, is_capturing(ss->s), zero_info, dim3(1), dim3(64), d_info);
 }
 
 int harvest_fetch_kv(harvest_ctx *ctx, uint32_t layer, const int32_t *d_block_table, const int32_t *d_n_blocks,
@@ -1856,7 +1857,7 @@ int harvest_fetch_experts(harvest_ctx *ctx, uint32_t layer, const int32_t *d_top
                        marked ? ss->mark + MAX_EXPERTS / 32 : (uint32_t *)nullptr);
     HIP_TRY(hipGetLastError());
     ss->last_cls = HARVEST_EXPERT; ss->counted[HARVEST_EXPERT] = true;
-    return launch_gathers(ctx, ss, c, HARVEST_EXPERT, lists, std::min<uint64_t>(E, n_staging_slots), (uint64_t)d_staging, 0);
+    return launch_gathers(ctx, ss, is_capturing(ss->s), c, HARVEST_EXPERT, lists, std::min<uint64_t>(E, n_staging_slots), (uint64_t)d_staging, 0);
 }
 
 int harvest_prefetcher_create(harvest_ctx *ctx, void *const d_staging[2], uint32_t n_staging_slots,
