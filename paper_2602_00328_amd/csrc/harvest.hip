@@ -1523,8 +1523,9 @@ static int revoke_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32
         for (harvest_ctx::DrainEvt *w : waits)
             if (e == hipSuccess) e = hipEventSynchronize(w->e);    // (the list's entries stay put while anyone refers to them)
         // the slots go back to their owner, who may hand them to another device or copy into them by DMA, and the callback may
-        // read a host copy that a write-back has just renewed: that takes more than "the kernels have ended"
-        if (e == hipSuccess && system_release(ctx) != HARVEST_OK) e = hipErrorUnknown;
+        // read a host copy that a write-back has just renewed: that takes more than "the kernels have ended".  (Nothing to wait
+        // for: an earlier revocation has waited for everything, and done this.)
+        if (e == hipSuccess && (whole_device || !waits.empty()) && system_release(ctx) != HARVEST_OK) e = hipErrorUnknown;
         std::unique_lock<std::mutex> lk(ctx->mu);
         for (harvest_ctx::DrainEvt *w : waits)
             if (--w->refs == 0) {

@@ -192,6 +192,11 @@ def test_a_revocation_hands_slots_back_behind_a_system_scope_release(fake, recor
     assert len(seen) == 2 and waits and len(fence) == 1 and fence[0] > waits[-1], log
     number = re.search(r"stream (\d+)", log[fence[0]]).group(1)
     assert f"hipStreamSynchronize stream {number}" in log[fence[0]:], log
+    if not recorded:                                      # nothing enqueued since: nothing to wait for and nothing to make visible
+        assert c.place([5, 6]) == B.OK and c.revoke([5]) == B.OK
+        c.log()
+        assert c.revoke([6]) == B.OK
+        assert not launches(seen[-1], "system_fence"), seen[-1]
     c.close()
 
 
