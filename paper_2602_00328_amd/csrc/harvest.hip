@@ -1689,6 +1689,10 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         const uint32_t nthr = total <= 64 * ROUND ? 64 : WG;
         ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16);
         ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr) : 0;
+        // the walk for the host's cells is shared out, see fetch_kv_small: not when it takes a single round, and to groups of at least
+        // 12 workgroups - what a group finds is read by its own workgroups only, and with 4 to a group (2 877 cells, 52 on the
+        // host) the groups that had found less left the link to the others for so long that 37.7 us became 39.4
+        while (ga.n_host >> ga.host_lg_groups >= 24 && total > (uint64_t)nthr * ROUND << ga.host_lg_groups) ga.host_lg_groups++;
         ga.hbm_wgs = (uint32_t)total * ga.tiles_per_chunk;
         SmallBooks books{ lists.miss, cnt, info, ctx->d_totals + HARVEST_KV * C_N, ss->d_feedback + HARVEST_KV,
                           c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr, n_seq };

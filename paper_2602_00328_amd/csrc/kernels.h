@@ -125,6 +125,7 @@ struct GatherArgs {
     uint32_t n_host, hbm_wgs;
     uint32_t pages_per_chunk;            // of the host tier, see host_tier
     uint32_t host_loads;                 // 2 or HOST_PAGE: loads a thread of the host tier keeps in flight
+    uint32_t host_lg_groups;             // of fetch_kv_small: the walk for the host's cells is cut into 1 << host_lg_groups shares
 };
 // In pinned memory, one per class and stream: requests of either tier of the latest fetch whose kernels have run - hints for the
 // next launch - and the rows and columns of the block table they were asked for with (experts: zero).
@@ -726,6 +727,10 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
 //                     flight per thread (see host_tier for why so few): 102 of 256 blocks of 2 x 32 KiB from the host take
 //                     121 us.  When every host tile was read at once, by a workgroup of its own, 6.7 MB of reads queued on
 //                     the link together: 131 us.
+//                     A table that takes several rounds to walk is shared out: workgroup b belongs to group b modulo their number, and a
+//                     group walks its own share of the cells (shared_cell) and reads what it finds.  A round of a walk
+//                     costs its workgroup a microsecond of waits in which it reads nothing: 2 877 cells of 2 x 16 KiB, 52 of them
+//                     on the host, take 37.4-38.3 us in two groups and took 40.0-40.9 when every workgroup walked all six rounds.
 //   the next one      walks the table too and keeps the books: counters, and the miss list in request order.  No atomics on
 //                     shared counters (a thousand of them on one address take longer than the copy), nothing to zero.
 //   the others        copy a tile of 16 bytes a thread if their cell's block is in HBM: nothing is compacted, so the grid covers the padded
@@ -746,6 +751,14 @@ struct SmallBooks {
 };
 
 constexpr uint32_t ROUND = 2;            // cells a thread looks up at a time when a workgroup walks the table
+
+// Cell number i of group q's share, of 1 << lg_groups shares: one of the cells i << lg_groups and on, every group another one.
+// Which one changes from i to i by a hash: with q itself, blocks on the host that recur with the period of the groups - every
+// other row's, say - would all fall to one group.
+__device__ inline uint32_t shared_cell(uint32_t i, uint32_t q, uint32_t lg_groups)
+{
+    return (i << lg_groups) + ((q ^ (i * 0x9E3779B1u >> 16)) & ((1u << lg_groups) - 1u));
+}
 
 template <int PLANES, int NTHR>
 __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t layer, const int32_t *__restrict__ table,
@@ -777,16 +790,19 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
     constexpr uint32_t WAVES_N = NTHR / 64;
     const bool keeper = blockIdx.x == a.n_host;
     const uint32_t wave = tid >> 6;
+    const uint32_t lg = keeper ? 0 : a.host_lg_groups, last = (1u << lg) - 1u;         // the keeper's share is the whole table
+    const uint32_t group = blockIdx.x & last, member = blockIdx.x >> lg, members = (a.n_host - group + last) >> lg, share = (total + last) >> lg;
     __shared__ Rec s_list[NTHR * ROUND];               // the round's cells on the host
     __shared__ uint32_t s_sum[ROUND * WAVES_N];
     __shared__ uint32_t s_cnt[C_N];
     uint32_t n[6] = { 0, 0, 0, 0, 0, 0 };            // requests, local, cache, host, lost, invalid, of this wavefront
     uint32_t n_miss = 0;
     if (tid < C_N) s_cnt[tid] = 0;
+    auto ask = [&](uint32_t i) { return ask_cell(table, n_blocks, max_blocks, seq_dst_block, shared_cell(i, group, lg), total); };
     Ask next[ROUND];
 #pragma unroll
-    for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask_cell(table, n_blocks, max_blocks, seq_dst_block, i * NTHR + tid, total);
-    for (uint32_t first = 0; first < total; first += NTHR * ROUND) {
+    for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask(i * NTHR + tid);
+    for (uint32_t first = 0; first < share; first += NTHR * ROUND) {
         int tier[ROUND];
         Rec rec[ROUND];
         Ask now[ROUND];
@@ -797,8 +813,7 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
             e[i] = c.dir[now[i].n > now[i].j && now[i].b >= 0 && (uint32_t)now[i].b < c.n_objects ? now[i].b : 0];
         }
 #pragma unroll
-        for (uint32_t i = 0; i < ROUND; ++i)
-            next[i] = ask_cell(table, n_blocks, max_blocks, seq_dst_block, first + (ROUND + i) * NTHR + tid, total);
+        for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask(first + (ROUND + i) * NTHR + tid);
         uint32_t rank[ROUND];                        // among the round's listed cells, in cell order: the host's, or the missed ones
 #pragma unroll
         for (uint32_t i = 0; i < ROUND; ++i) {
@@ -839,7 +854,7 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
             const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4), n_tiles = listed * tpc;
             for (uint32_t rep = 0; rep < a.n_rep; ++rep) {
                 const uint64_t s_off = rep * a.layer_stride[T_HOST], d_off = rep * a.dst_step;
-                for (uint32_t g = blockIdx.x * U; g < n_tiles; g += a.n_host * U) {
+                for (uint32_t g = member * U; g < n_tiles; g += members * U) {
                     u32x4 v[2];
                     uint64_t d[U];
                     bool act[U];

@@ -148,6 +148,30 @@ def test_one_kernel_fetch_at_the_edges_of_its_rounds(n_planes, lens, width):
     rig.h.close()
 
 
+@pytest.mark.parametrize("where", ["every cell", "every other cell", "every other row", "one"])
+@pytest.mark.parametrize("host_wgs", [0, 11, 49, 100])        # two, one, four and eight shares of a table that has the rounds
+@pytest.mark.parametrize("lens,width", [([512], 512), ([513], 513), ([512, 500], 512), ([1, 1024], 1025), ([300] * 7, 300), ([4096], 4096)])
+def test_one_kernel_fetch_shares_out_the_walk_for_the_hosts_cells(lens, width, host_wgs, where):
+    """Every cell is in one share, whatever the number of shares and wherever the host's cells are."""
+    rig = Rig(1040, 64, n_layers=2, host_every=2, local_every=0, host_wgs=host_wgs)
+    t, dt, dn, df, cap = rig.tables(lens, width)
+    on_host, cached = np.flatnonzero(rig.on_host), np.flatnonzero(~rig.on_host)
+    cell = np.arange(t.size).reshape(t.shape)
+    hit = {"every cell": cell >= 0, "every other cell": cell % 2 == 1, "every other row": cell // width % 2 == 0, "one": cell == lens[0] - 1}[where]
+    t[t >= 0] = np.where(hit, on_host[cell % len(on_host)], cached[cell % len(cached)])[t >= 0]
+    dt.copy_(torch.from_numpy(t))
+    k, v = rig.buffers(cap)
+    rig.h.fetch_kv_layers(0, 2, dt, dn, k, v, cap * 1040, df, cap)
+    counts, miss, _ = rig.h.fetch_info(miss_cap=t.size)
+    assert miss.tolist() == rig.misses(t, lens) and counts["n_host"] == len(miss) > 0
+    for p, buf in enumerate([k, v]):
+        got = buf.cpu().numpy()
+        for layer in range(2):
+            assert np.array_equal(got[layer * cap * 1040:(layer + 1) * cap * 1040], rig.expected(t, lens, p, layer)), (p, layer)
+        assert (got[2 * cap * 1040:] == 0xEE).all()
+    rig.h.close()
+
+
 @pytest.mark.parametrize("lens,width", [([1], 1), ([65], 65), ([63, 64], 64), ([129], 129), ([300, 513], 600), ([5, 9], 4096), ([2, 1, 0], 4)])
 def test_static_fetch_hands_out_counters_and_misses_in_order(lens, width):
     rig = Rig(2048, 50)
