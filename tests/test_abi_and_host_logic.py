@@ -312,3 +312,35 @@ def test_the_papers_three_calls():
         h.register_cb(B.KV, 99)
     assert e.value.code == B.ENOENT
     h.close(); oc.close()
+
+
+@pytest.mark.parametrize("n_slots", [1, 63, 64, 65, 4096, 4097, 64 ** 3 + 1])
+def test_slots_are_handed_out_lowest_first(n_slots):
+    """At the edges of the words and levels in which free slots are kept: taken to the last one, given back in any order."""
+    rng = np.random.default_rng(n_slots)
+    n = n_slots + 3
+    h = B.Harvest(kv=spec(max_objects=n, n_host=n, n_cache=n_slots, n_local=0), flags=B.FLAG_NO_DEVICE)
+    h.register(B.KV, n, np.arange(n))
+    order = rng.permutation(n).astype(np.uint32)
+    st = h.place(B.KV, order)
+    assert (st[:n_slots] == B.OK).all() and (st[n_slots:] == B.ENOSPC).all()
+    slot_of = {int(i): s for s, i in enumerate(order[:n_slots])}
+    probe = order[rng.integers(0, n_slots, 50)]
+    assert [h.lookup(B.KV, i)[1] for i in probe] == [slot_of[int(i)] for i in probe]
+    free, out = [], [int(i) for i in order[n_slots:]]
+    for _ in range(12):
+        leave = rng.choice(list(slot_of), size=min(len(slot_of), int(rng.integers(1, 200))), replace=False).astype(np.uint32)
+        h.revoke(B.KV, leave)
+        free = sorted(free + [slot_of.pop(int(i)) for i in leave])
+        out += [int(i) for i in leave]
+        back, out = out[:int(rng.integers(1, 150))], out[150:] + out[:150]
+        back = [i for i in back if i not in slot_of]
+        st = h.place(B.KV, np.array(back, dtype=np.uint32))
+        for i, s in zip(back, st):
+            assert (s == B.OK) == bool(free)
+            if free:
+                slot_of[i] = free.pop(0)
+                assert h.lookup(B.KV, i)[1] == slot_of[i]
+        out = [i for i in out if i not in slot_of]
+        assert h.stats().cache_slots_in_use[B.KV] == len(slot_of) == n_slots - len(free)
+    h.close()
