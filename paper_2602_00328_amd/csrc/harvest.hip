@@ -192,6 +192,8 @@ struct ClassState {
     uint64_t cache_in_use = 0;
     bool adjacent = false;                  // equal-size cache slots laid out [layer][slot][plane][chunk] in one buffer
     uint64_t *d_dir = nullptr;
+    uint32_t *d_done = nullptr;             // the number of the latest edit that is complete, and a counter: see dir_write
+    uint32_t n_lossy = 0;                   // objects registered without a host slot
     // The edits of this class's directory form one chain on the device, in the order the host made them: every edit is a
     // dir_write kernel on some stream (the caller's for place / evict, the control stream for register / restore /
     // revoke) that first waits for edit_evt - the class's previous edit - unless that ran on the same stream, and then
@@ -221,11 +223,11 @@ struct ClassState {
     // host-side statistics
     uint64_t n_placed = 0, n_enospc = 0, n_revoked = 0, n_evicted = 0, n_demoted = 0;
 
-    uint64_t packed(uint32_t id) const
+    uint64_t packed(uint32_t id, uint32_t edit) const
     {
         uint32_t t = tier[id];
         uint32_t s = t == T_HOST ? (uint32_t)host_slot[id] : (t == T_NONE ? 0u : (uint32_t)slot[id]);
-        return make_entry(t, s, gen[id]);
+        return make_entry(t, s, edit);
     }
     // Room in the cache tier for one object: the lowest free slot, or a best-fit segment.  -1: none.
     int64_t cache_take()
@@ -340,8 +342,9 @@ struct StreamState {
     // fetch scratch
     Lists lists[HARVEST_N_CLASSES];
     KvWork work;
-    uint32_t *cnt_block = nullptr;          // the counters of both classes and, behind them, `next`: one allocation
+    uint32_t *cnt_block = nullptr;          // the counters of both classes and, behind them, `next` and `snap`: one allocation
     unsigned long long *next = nullptr;     // tile counter of move_pcie, zero between launches
+    uint32_t *snap = nullptr;               // of a recorded one-kernel fetch: see snap_edit
     uint32_t *mark = nullptr;               // [MAX_EXPERTS / 32 + 1] routed-set bitmap and invalid-id count of large batches;
                                             // zero between fetches
     int last_cls = -1;                      // class of the latest fetch enqueued on this stream, -1: none yet
@@ -385,7 +388,7 @@ constexpr size_t SO_MISS = SO_HOST + align256((size_t)STATIC_CELLS * sizeof(Rec)
 constexpr size_t SO_KIND = SO_MISS + align256((size_t)STATIC_CELLS * sizeof(uint32_t));
 constexpr size_t SO_BLK = SO_KIND + align256((size_t)STATIC_CELLS);
 constexpr size_t SO_CNT = SO_BLK + align256(STATIC_ROWS * BC_N * sizeof(uint32_t));
-constexpr size_t STATIC_BYTES = SO_CNT + align256(C_N * sizeof(uint32_t));
+constexpr size_t STATIC_BYTES = SO_CNT + align256((C_N + 1) * sizeof(uint32_t));       // the counters and `snap`
 static_assert(STATIC_ROWS <= 1024, "the fixed scratch has no room for the grouped compaction of very large tables");
 
 static __device__ __align__(256) unsigned char scratch[STATIC_BYTES];
@@ -516,12 +519,13 @@ int init_stream_state(StreamState *ss)
     for (hipEvent_t *e : { &ss->fork, &ss->join })
         HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&ss->last, LATEST_WORK));
-    const size_t cnt_bytes = HARVEST_N_CLASSES * C_N * sizeof(uint32_t);
-    HIP_TRY(hipMalloc(&ss->cnt_block, cnt_bytes + sizeof *ss->next));
+    const size_t cnt_bytes = HARVEST_N_CLASSES * C_N * sizeof(uint32_t), block_bytes = cnt_bytes + sizeof *ss->next + sizeof *ss->snap;
+    HIP_TRY(hipMalloc(&ss->cnt_block, block_bytes));
     // cleared on the stream itself: hipMemset would leave that to the null stream, which neither the host nor a stream made
     // non-blocking waits for
-    HIP_TRY(hipMemsetAsync(ss->cnt_block, 0, cnt_bytes + sizeof *ss->next, ss->s));
+    HIP_TRY(hipMemsetAsync(ss->cnt_block, 0, block_bytes, ss->s));
     ss->next = (unsigned long long *)((char *)ss->cnt_block + cnt_bytes);
+    ss->snap = (uint32_t *)(ss->next + 1);
     for (int k = 0; k < HARVEST_N_CLASSES; ++k) ss->lists[k].cnt = ss->cnt_block + k * C_N;
     HIP_TRY(hipMalloc(&ss->mark, (MAX_EXPERTS / 32 + 1) * sizeof(uint32_t)));
     HIP_TRY(hipMemsetAsync(ss->mark, 0, (MAX_EXPERTS / 32 + 1) * sizeof(uint32_t), ss->s));
@@ -751,17 +755,19 @@ int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, h
     if (c.edit_seq && c.edit_stream != on) DEV_TRY(hipStreamWaitEvent(on, c.edit_evt, 0));
     void *d_st = nullptr;
     if (n > DIR_INLINE) DEV_TRY(hipHostGetDevicePointer(&d_st, st->h, 0));
+    const uint32_t edit = (uint32_t)(c.edit_seq + 1);
     if (!ctx->no_device && n <= DIR_INLINE) {
         DirList l;
-        for (size_t i = 0; i < n; ++i) { l.entry[i] = c.packed(ids[i]); l.id[i] = ids[i]; }
-        hipLaunchKernelGGL(dir_write_inline, dim3(1), dim3(DIR_INLINE), 0, on, c.d_dir, (uint64_t)n, l);
+        for (size_t i = 0; i < n; ++i) { l.entry[i] = c.packed(ids[i], edit); l.id[i] = ids[i]; }
+        hipLaunchKernelGGL(dir_write_inline, dim3(1), dim3(DIR_INLINE), 0, on, DirArgs{ c.d_dir, c.d_done, (uint32_t)n, edit }, l);
     } else if (!ctx->no_device) {
         uint64_t *ent = (uint64_t *)st->h;
         uint32_t *idv = (uint32_t *)(ent + n);
-        for (size_t i = 0; i < n; ++i) { ent[i] = c.packed(ids[i]); idv[i] = ids[i]; }
+        for (size_t i = 0; i < n; ++i) { ent[i] = c.packed(ids[i], edit); idv[i] = ids[i]; }
         uint64_t *d_ent = (uint64_t *)d_st;
         uint32_t *d_ids = (uint32_t *)(d_ent + n);
-        hipLaunchKernelGGL(dir_write, dim3((uint32_t)((n + WG - 1) / WG)), dim3(WG), 0, on, c.d_dir, d_ids, d_ent, (uint32_t)n);
+        hipLaunchKernelGGL(dir_write, dim3((uint32_t)((n + WG - 1) / WG)), dim3(WG), 0, on, c.d_dir, d_ids, d_ent, (uint32_t)n,
+                           c.d_done, edit);
     }
     DEV_TRY(hipGetLastError());
     if (committed) *committed = true;
@@ -778,12 +784,19 @@ int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, h
 // not waited for: a fetch is on the critical path and a placement is best effort (it may sit behind hundreds of MiB of
 // copies on another stream), and until its entry is seen the older one names the host copy, which holds the same bytes.
 // Nothing to do either when the latest edit ran on this very stream: the chain put every earlier one before it.
+//
+// seen_seq is also what a one-kernel fetch goes by (see fetch_kv_small): entries of later edits it copies twice, so a placement
+// that another stream has finished is noticed here.
 int order_after_directory_edits(harvest_ctx *ctx, StreamState *ss, int cls)
 {
     const ClassState &c = ctx->cls[cls];
-    if (ss->seen_seq[cls] >= c.must_seq || is_capturing(ss->s)) return HARVEST_OK;
-    if (c.edit_stream != ss->s) HIP_TRY(hipStreamWaitEvent(ss->s, c.edit_evt, 0));
-    ss->seen_seq[cls] = c.edit_seq;
+    uint64_t &seen = ss->seen_seq[cls];
+    if (seen == c.edit_seq || is_capturing(ss->s)) return HARVEST_OK;
+    if (c.edit_stream != ss->s) {
+        if (seen < c.must_seq) HIP_TRY(hipStreamWaitEvent(ss->s, c.edit_evt, 0));
+        else if (cls != HARVEST_KV || hipEventQuery(c.edit_evt) != hipSuccess) return HARVEST_OK;
+    }
+    seen = c.edit_seq;
     return HARVEST_OK;
 }
 
@@ -1089,6 +1102,8 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
         if (!c.used) continue;
         HIP_TRY(hipEventCreateWithFlags(&c.edit_evt, hipEventDisableTiming));
         HIP_TRY(hipMalloc(&c.d_dir, (size_t)c.cfg.max_objects * sizeof(uint64_t)));
+        HIP_TRY(hipMalloc(&c.d_done, 2 * sizeof(uint32_t)));
+        HIP_TRY(hipMemset(c.d_done, 0, 2 * sizeof(uint32_t)));
         HIP_TRY(hipMemset(c.d_dir, 0xFF, (size_t)c.cfg.max_objects * sizeof(uint64_t)));   // tier NONE everywhere
         for (uint32_t p = 0; p < c.cfg.n_planes; ++p) {
             if (!c.cfg.n_host_slots) continue;
@@ -1113,6 +1128,7 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
             Lists &l = ss.lists[HARVEST_KV];
             l.hbm = (Rec *)(base + SO_HBM); l.host = (Rec *)(base + SO_HOST); l.miss = (uint32_t *)(base + SO_MISS);
             l.cnt = (uint32_t *)(base + SO_CNT); l.cap = STATIC_CELLS;
+            ss.snap = l.cnt + C_N;
             ss.work.tmp = (Rec *)(base + SO_TMP); ss.work.kind = base + SO_KIND;
             ss.work.blk_counts = (uint32_t *)(base + SO_BLK);
         }
@@ -1255,7 +1271,7 @@ int harvest_destroy(harvest_ctx *ctx)
         for (auto e : ctx->prof_pool) (void)hipEventDestroy(e);
         for (auto e : ctx->evt_pool) (void)hipEventDestroy(e);
         for (auto &d : ctx->draining) (void)hipEventDestroy(d.e);
-        for (auto &c : ctx->cls) if (c.d_dir) (void)hipFree(c.d_dir);
+        for (auto &c : ctx->cls) { (void)hipFree(c.d_dir); (void)hipFree(c.d_done); }
         (void)hipFree(ctx->d_totals);
         (void)hipFree(ctx->d_lease);
         for (auto &c : ctx->cls) if (c.edit_evt) (void)hipEventDestroy(c.edit_evt);
@@ -1292,6 +1308,7 @@ int harvest_register(harvest_ctx *ctx, int cls, uint32_t n, const int64_t *host_
         c.tier.push_back((uint8_t)tier);
         c.gen.push_back(0);
         c.host_slot.push_back(host_slot ? host_slot[i] : -1);
+        c.n_lossy += !host_slot;
         if (host_slot) c.host_used[host_slot[i]] = 1;
         c.cb.push_back(cb);
         c.cb_user.push_back(user);
@@ -1730,7 +1747,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         const uint64_t live = (uint64_t)latest.hbm + latest.host;
         if (live < total) dead_tiles = (total - live) * tpc * c.cfg.n_planes * n_layers;
     }
-    if (!ctx->general_fetch && !head_major && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
+    if (!ctx->general_fetch && !c.n_lossy && !head_major && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
         total * tpc * n_layers <= (1ull << 31) && dead_tiles <= DEAD_TILES) {
         GatherArgs ga{};
         const ClassDev cd = class_dev(c);
@@ -1743,6 +1760,11 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         ga.dst_base[0] = (uint64_t)d_dst_k; ga.dst_base[1] = (uint64_t)d_dst_v;
         ga.dst_step = dst_layer_stride; ga.n_rep = n_layers;
         ga.chunk_bytes = c.cfg.chunk_bytes;
+        ga.seen = (uint32_t)ss->seen_seq[HARVEST_KV];
+        if (recording) {
+            ga.snap = ss->snap;
+            if ((rc = launch(ss->s, snap_edit, dim3(1), dim3(1), (const uint32_t *)c.d_done, ss->snap))) return rc;
+        }
         const uint32_t nthr = total <= 64 * ROUND ? 64 : WG;
         ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16);
         ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr) : 0;

@@ -44,14 +44,17 @@ constexpr int UNROLL_HOST = 8;
 constexpr uint32_t TILE_HOST = WG * 16 * UNROLL_HOST;   // 32 KiB tiles of fill_items
 constexpr int HOST_PAGE = 4;                    // 16-byte loads a thread of the host-tier gather makes for one page, see host_tier
 
-// directory entry: [1:0] tier, [31:2] slot in that tier (host slot for HOST), [63:32] generation
+// directory entry: [1:0] tier, [31:2] slot in that tier (host slot for HOST), [63:32] number of the edit that wrote it
 constexpr uint64_t TIER_MASK = 3;
 __host__ __device__ inline uint32_t entry_tier(uint64_t e) { return (uint32_t)(e & TIER_MASK); }
 __host__ __device__ inline uint32_t entry_slot(uint64_t e) { return (uint32_t)(e >> 2) & 0x3FFFFFFFu; }
-__host__ __device__ inline uint64_t make_entry(uint32_t tier, uint32_t slot, uint32_t gen)
+__host__ __device__ inline uint64_t make_entry(uint32_t tier, uint32_t slot, uint32_t edit)
 {
-    return (uint64_t)tier | ((uint64_t)(slot & 0x3FFFFFFFu) << 2) | ((uint64_t)gen << 32);
+    return (uint64_t)tier | ((uint64_t)(slot & 0x3FFFFFFFu) << 2) | ((uint64_t)edit << 32);
 }
+// Written by an edit that the fetch is not known to come after (`seen`: the latest that it does): another workgroup of the same
+// launch may have read the entry before it.
+__device__ inline bool entry_young(uint64_t e, uint32_t seen) { return (int32_t)((uint32_t)(e >> 32) - seen) > 0; }
 enum { T_HOST = 0, T_CACHE = 1, T_LOCAL = 2, T_NONE = 3 };
 
 // One request of a fetch, the same for every plane of its class:
@@ -125,6 +128,8 @@ struct GatherArgs {
     uint32_t n_host, hbm_wgs;
     uint32_t pages_per_chunk;            // of the host tier, see host_tier
     uint32_t host_loads;                 // 2 or HOST_PAGE: loads a thread of the host tier keeps in flight
+    uint32_t seen;                       // of fetch_kv_small: the latest directory edit that it comes after, or where that is kept
+    const uint32_t *snap;
     uint32_t host_lg_groups;             // of fetch_kv_small: the walk for the host's cells is cut into 1 << host_lg_groups shares
 };
 // In pinned memory, one per class and stream: requests of either tier of the latest fetch whose kernels have run - hints for the
@@ -739,6 +744,13 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
 //                     takes longer than that saves).  Non-temporal accesses: on blocks that are in no cache 1 000 take 23.4 us
 //                     against 27.1 for plain ones, 2 000 43.7 against 51.3.
 //
+// Nothing makes the directory hold still meanwhile: a revocation publishes its entries while fetches are in flight, and a placement
+// on another stream when its copy has ended.  So a cell's tile workgroups and the host's may read different entries, and each leave
+// the cell to the other (4 096 blocks fetched from the cache tier and revoked by the next call: up to all of them missing in the
+// destination).  Hence an entry that may have changed under the launch (entry_young) is copied by whoever reads it, from where the
+// entry says: whichever of them saw the older entry, the other then sees the younger one or copies anyway.  (Objects without a
+// host copy can leave nothing to copy from: with any around, fetches resolve in one place, on the general path.)
+//
 // A walk goes ROUND * WG cells at a time; the next round's row lengths, block numbers and destinations are on their way while
 // this one's directory entries are, so a round costs one memory latency, not two.  The code of the walk is kept short on
 // purpose: it runs once, and one wavefront doing the books with everything unrolled took 7 us for a table of 8 cells.
@@ -751,6 +763,7 @@ struct SmallBooks {
 };
 
 constexpr uint32_t ROUND = 2;            // cells a thread looks up at a time when a workgroup walks the table
+constexpr uint32_t OF_OTHERS = 1u << 31; // in a wavefront's number of listed cells: some of them are in another tier than the host's
 
 // Cell number i of group q's share, of 1 << lg_groups shares: one of the cells i << lg_groups and on, every group another one.
 // Which one changes from i to i by a hash: with q itself, blocks on the host that recur with the period of the groups - every
@@ -779,8 +792,16 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
         if (nb <= 0 || j >= (uint32_t)nb || b < 0 || (uint32_t)b >= c.n_objects || dst_chunk >= dst_cap) return;
         const uint64_t e = c.dir[b];
         const int tier = (int)entry_tier(e);
-        if ((tier != T_CACHE && tier != T_LOCAL) || entry_slot(e) >= slots_of(c, tier)) return;
         const uint64_t off = (uint64_t)k * (NTHR * 16);
+        if (tier != T_CACHE && tier != T_LOCAL) {                  // (apart: what a workgroup works out first is kept short)
+            if (tier != T_HOST || !entry_young(e, a.snap ? *a.snap : a.seen) || entry_slot(e) >= c.n_slots[T_HOST]) return;
+            const uint64_t src = (plane ? a.src_base[T_HOST][1] : a.src_base[T_HOST][0]) + chunk_offset(c, T_HOST, layer + z, entry_slot(e)) + off;
+            const uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + z * a.dst_step + dst_chunk * c.chunk_bytes + off;
+            if (off + tid * 16 < a.chunk_bytes)
+                st16<true>(reinterpret_cast<u32x4 *>(dst) + tid, ld16<false>(reinterpret_cast<const u32x4 *>(src) + tid));
+            return;
+        }
+        if (entry_slot(e) >= slots_of(c, tier)) return;
         const uint64_t src = src_base_of(a, (uint32_t)tier, plane) + chunk_offset(c, tier, layer + z, entry_slot(e)) + off;
         const uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + z * a.dst_step + dst_chunk * c.chunk_bytes + off;
         copy_tile<NTHR, 1, true>(src, dst, a.chunk_bytes - off, tid);
@@ -789,7 +810,7 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
     if (blockIdx.y || blockIdx.x > a.n_host) return;
     constexpr uint32_t WAVES_N = NTHR / 64;
     const bool keeper = blockIdx.x == a.n_host;
-    const uint32_t wave = tid >> 6;
+    const uint32_t wave = tid >> 6, seen = a.snap ? *a.snap : a.seen;
     const uint32_t lg = keeper ? 0 : a.host_lg_groups, last = (1u << lg) - 1u;         // the keeper's share is the whole table
     const uint32_t group = blockIdx.x & last, member = blockIdx.x >> lg, members = (a.n_host - group + last) >> lg, share = (total + last) >> lg;
     __shared__ Rec s_list[NTHR * ROUND];               // the round's cells on the host
@@ -824,35 +845,34 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
                      (tier[i] != T_NONE && entry_slot(e[i]) >= slots_of(c, tier[i]))) tier[i] = 4;
             rec[i].src = chunk_offset(c, T_HOST, layer, entry_slot(e[i]));
             rec[i].dst = dst_chunk * c.chunk_bytes;
+            const bool young = !keeper && (tier[i] == T_CACHE || tier[i] == T_LOCAL) && entry_young(e[i], seen);
+            if (young) {
+                rec[i].src = chunk_offset(c, tier[i], layer, entry_slot(e[i])) | (uint64_t)tier[i];
+                tier[i] = T_HOST;                    // (T_HOST is 0: other sources have their tier in bits [1:0])
+            }
             uint32_t in_wave;
             rank[i] = wave_rank(tier[i] == T_HOST || (keeper && tier[i] == T_NONE), in_wave);
-            if (lane_id() == 0) s_sum[i * WAVES_N + wave] = in_wave;
+            const uint32_t of_others = __ballot(young) ? OF_OTHERS : 0;
+            if (lane_id() == 0) s_sum[i * WAVES_N + wave] = in_wave | of_others;
         }
         __syncthreads();
         uint32_t listed = 0;
+        bool mixed = false;                          // the list has cells of other tiers too
 #pragma unroll
         for (uint32_t k = 0; k < ROUND * WAVES_N; ++k) {
             const uint32_t before = listed;
-            listed += s_sum[k];
+            listed += s_sum[k] & ~OF_OTHERS;
+            mixed |= (s_sum[k] & OF_OTHERS) != 0;
             if ((k & (WAVES_N - 1)) == wave) rank[k / WAVES_N] += before;
         }
-        if (keeper) {
-#pragma unroll
-            for (uint32_t i = 0; i < ROUND; ++i) {
-                if (tier[i] == T_HOST || tier[i] == T_NONE) books.miss_idx[n_miss + rank[i]] = first + i * NTHR + tid;
-                const bool pred[6] = { tier[i] >= 0, tier[i] == T_LOCAL, tier[i] == T_CACHE, tier[i] == T_HOST, tier[i] == T_NONE, tier[i] == 4 };
-#pragma unroll
-                for (int k = 0; k < 6; ++k) n[k] += (uint32_t)__popcll(__ballot(pred[k]));
-            }
-            n_miss += listed;
-        } else if (listed) {
+        if (!keeper && listed) {
 #pragma unroll
             for (uint32_t i = 0; i < ROUND; ++i)
                 if (tier[i] == T_HOST) s_list[rank[i]] = rec[i];
             __syncthreads();
             constexpr int U = 2 / PLANES;            // tiles per step
             const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4), n_tiles = listed * tpc;
-            for (uint32_t rep = 0; rep < a.n_rep; ++rep) {
+            for (uint32_t rep = 0; rep < (mixed ? 0 : a.n_rep); ++rep) {
                 const uint64_t s_off = rep * a.layer_stride[T_HOST], d_off = rep * a.dst_step;
                 for (uint32_t g = member * U; g < n_tiles; g += members * U) {
                     u32x4 v[2];
@@ -876,6 +896,29 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
                     }
                 }
             }
+            // rare: one tile of one plane at a time, from wherever it is
+#pragma unroll 1
+            for (uint32_t rep = 0; rep < (mixed ? a.n_rep : 0); ++rep)
+#pragma unroll 1
+                for (uint32_t g = member; g < n_tiles * PLANES; g += members) {
+                    const uint32_t p = g >= n_tiles, gi = p ? g - n_tiles : g, idx = gi / tpc, u = (gi - idx * tpc) * NTHR + tid;
+                    if (u >= chunk_units) continue;
+                    const Rec x = s_list[idx];
+                    const uint32_t from = (uint32_t)(x.src & 3);
+                    const uint64_t at = src_base_of(a, from, p) + (x.src & ~(uint64_t)3) + rep * layer_stride_of(a, from);
+                    st16<true>(reinterpret_cast<u32x4 *>((p ? a.dst_base[1] : a.dst_base[0]) + x.dst + rep * a.dst_step) + u,
+                               ld16<false>(reinterpret_cast<const u32x4 *>(at) + u));
+                }
+        }
+        if (keeper) {
+#pragma unroll
+            for (uint32_t i = 0; i < ROUND; ++i) {
+                if (tier[i] == T_HOST || tier[i] == T_NONE) books.miss_idx[n_miss + rank[i]] = first + i * NTHR + tid;
+                const bool pred[6] = { tier[i] >= 0, tier[i] == T_LOCAL, tier[i] == T_CACHE, tier[i] == T_HOST, tier[i] == T_NONE, tier[i] == 4 };
+#pragma unroll
+                for (int k = 0; k < 6; ++k) n[k] += (uint32_t)__popcll(__ballot(pred[k]));
+            }
+            n_miss += listed;
         }
         __syncthreads();                             // s_sum and s_list are written again
     }
@@ -1153,17 +1196,39 @@ __global__ __launch_bounds__(NTHR) void fill_items_hbm(const Item *__restrict__ 
     }
 }
 
-// Directory edits: from a host-built list, or (up to DIR_INLINE of them) from the kernel's arguments.
+// Directory edits: from a host-built list, or (up to DIR_INLINE of them) from the kernel's arguments.  Every entry carries the
+// number of its edit, and `done` says which edits are complete (for fetches in recorded graphs, which learn it when they are
+// replayed): done[0] is the latest, done[1] counts workgroups.  Entries are written through to where every XCD sees them and
+// waited for (a barrier of the workgroup alone waits for no store) before the number is.
+__device__ inline void write_entry(uint64_t *dir, uint32_t id, uint64_t entry)
+{
+    __hip_atomic_store(dir + id, entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
 __global__ __launch_bounds__(WG) void dir_write(uint64_t *dir, const uint32_t *__restrict__ ids,
-                                                const uint64_t *__restrict__ entries, uint32_t n)
+                                                const uint64_t *__restrict__ entries, uint32_t n, uint32_t *done, uint32_t edit)
 {
     uint32_t i = blockIdx.x * WG + threadIdx.x;
-    if (i < n) dir[ids[i]] = entries[i];
+    if (i < n) write_entry(dir, ids[i], entries[i]);
+    __syncthreads();
+    if (threadIdx.x) return;
+    if (__hip_atomic_fetch_add(done + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1) return;
+    __hip_atomic_store(done + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(done, edit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__global__ __launch_bounds__(DIR_INLINE) void dir_write_inline(uint64_t *dir, uint64_t n, DirList)
+struct DirArgs { uint64_t *dir; uint32_t *done; uint32_t n, edit; };
+static_assert(sizeof(DirArgs) % 8 == 0, "DirList follows DirArgs in the kernel's arguments");
+__global__ __launch_bounds__(DIR_INLINE) void dir_write_inline(DirArgs a, DirList)
 {
-    k_DirList *l = (k_DirList *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + 16);
-    if (threadIdx.x < n) dir[l->id[threadIdx.x]] = l->entry[threadIdx.x];
+    k_DirList *l = (k_DirList *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(DirArgs));
+    if (threadIdx.x < a.n) write_entry(a.dir, l->id[threadIdx.x], l->entry[threadIdx.x]);
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(a.done, a.edit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The latest complete edit, for the fetch behind this kernel on the stream.
+__global__ void snap_edit(const uint32_t *done, uint32_t *snap)
+{
+    *snap = __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __global__ void system_fence() { __threadfence_system(); }

@@ -172,6 +172,54 @@ def test_one_kernel_fetch_shares_out_the_walk_for_the_hosts_cells(lens, width, h
     rig.h.close()
 
 
+@pytest.mark.parametrize("recorded", [False, True])
+@pytest.mark.parametrize("edit", ["revoke", "place"])
+def test_a_one_kernel_fetch_is_whole_when_the_directory_changes_under_it(edit, recorded):
+    """Its workgroups read the directory for themselves, and an edit that does not wait for the fetch - a revocation publishes
+    first and drains then, a placement runs on another stream - must not make a block fall between those that copy from HBM and
+    those that copy from the host: each would leave it to the other."""
+    n, chunk = (4096, 32768) if edit == "revoke" else (1024, 32768)
+    rng = np.random.default_rng(3)
+    payload = [rng.integers(0, 2 ** 31, (n, chunk // 4), dtype=np.int32) for _ in range(2)]
+    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n, n_host_slots=n, n_cache_slots=n, n_local_slots=0))
+    for p in range(2):
+        h.host_plane(B.KV, p).view(np.int32).reshape(n, -1)[:] = payload[p]
+    ids = h.register(B.KV, n, np.arange(n))
+    for i in ids:
+        h.register_cb(B.KV, int(i), enabled=False)
+    table = torch.arange(n, dtype=torch.int32, device="cuda").reshape(1, n)
+    n_blocks, first = torch.tensor([n], dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")
+    k, v = (torch.zeros(n * chunk, dtype=torch.uint8, device="cuda") for _ in range(2))
+    want = [torch.from_numpy(x).cuda().reshape(-1) for x in payload]
+    side, main = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(main):
+        h.fetch_kv(0, table, n_blocks, k, v, first, n)            # makes the stream's scratch
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        if recorded:
+            with torch.cuda.graph(graph, stream=main):
+                h.fetch_kv(0, table, n_blocks, k, v, first, n)
+    batches = np.array_split(ids, 12)
+    for _ in range(3):
+        h.revoke(B.KV, ids)
+        if edit == "revoke":
+            h.place(B.KV, ids, stream=side)
+        torch.cuda.synchronize()
+        k.zero_(), v.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(main):
+            graph.replay() if recorded else h.fetch_kv(0, table, n_blocks, k, v, first, n)
+        if edit == "revoke":
+            h.revoke(B.KV, ids)
+        else:
+            for b in batches:                                     # from device memory: not behind the fetch on the link
+                h.place_from(B.KV, b, want[0].data_ptr(), want[1].data_ptr(), b.astype(np.uint64), n, stream=side)
+        torch.cuda.synchronize()
+        for got, x in zip((k, v), want):
+            assert torch.equal(got.view(torch.int32), x), int((got.view(torch.int32) != x).reshape(n, -1).any(1).sum())
+    h.close()
+
+
 @pytest.mark.parametrize("lens,width", [([1], 1), ([65], 65), ([63, 64], 64), ([129], 129), ([300, 513], 600), ([5, 9], 4096), ([2, 1, 0], 4)])
 def test_static_fetch_hands_out_counters_and_misses_in_order(lens, width):
     rig = Rig(2048, 50)

@@ -321,3 +321,33 @@ def test_the_host_tier_is_spread_wider_when_the_link_is_what_a_fetch_waits_for(f
         words[:4] = [hbm, host, 1, 10000]
         assert head() == wavefronts + hbm * tiles
     c.close()
+
+
+def test_the_one_kernel_fetch_knows_the_edits_it_comes_after(fake):
+    """One that is being recorded learns them from a kernel in front of it.  With an object around that a revocation can leave
+    nothing to copy from, every fetch resolves in one place."""
+    c = Ctx(fake, n_local=4)
+    fetch = lambda: fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 8, POOL, POOL, POOL, 8, c.stream)
+    assert fetch() == B.OK
+    for recorded in (False, True):
+        fake.fake_capture(c.stream if recorded else None)
+        c.log()
+        assert fetch() == B.OK
+        log = c.log()
+        snap, small = launches(log, "snap_edit"), launches(log, "fetch_kv_small")
+        assert len(small) == 1 and len(snap) == recorded and snap + small == sorted(snap + small), log
+    fake.fake_capture(None)
+    c.close()
+    cfg = B.harvest_config()
+    kv = cfg.cls[B.KV]
+    kv.n_layers, kv.n_planes, kv.chunk_bytes, kv.max_objects, kv.n_host_slots, kv.n_cache_slots, kv.n_local_slots = 1, 1, 4096, 8, 4, 4, 4
+    kv.host_pool[0], kv.d_cache_pool[0], kv.d_local_pool[0] = POOL, POOL * 2, POOL * 3
+    h, stream, slots, out = ctypes.c_void_p(), fake.fake_stream(), np.arange(4, dtype=np.int64), np.empty(4, dtype=np.uint32)
+    assert fake.harvest_create(ctypes.byref(cfg), ctypes.byref(h)) == B.OK
+    for lossy in (False, True):
+        assert fake.harvest_register(h, B.KV, 4, None if lossy else slots.ctypes.data, B.LOCAL if lossy else B.HOST, B.REVOKE_CB(), None, out.ctypes.data) == B.OK
+        fake.fake_log()
+        assert fake.harvest_fetch_kv(h, 0, POOL, POOL, 1, 8, POOL, None, POOL, 8, stream) == B.OK
+        log = fake.fake_log().decode().splitlines()
+        assert bool(launches(log, "classify_kv")) == lossy and bool(launches(log, "fetch_kv_small")) != lossy, log
+    assert fake.harvest_destroy(h) == B.OK
