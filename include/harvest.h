@@ -153,7 +153,8 @@ typedef struct harvest_config {
     uint32_t pcie_wgs;              /* tuning: persistent workgroups of the copies that cross PCIe outside a fetch (place,
                                        write-back), each with one 32 KiB tile in flight (16 KiB for
                                        write-backs of chunks below 32 KiB); 0 = default (12: enough to fill the link
-                                       when alone, few enough that a fetch on another stream keeps most of it) */
+                                       when alone, few enough that a fetch on another stream keeps most of it);
+                                       write-backs run 5/3 as many */
     uint32_t reserved[2];           /* must be 0 */
     void *d_shared_cache;           /* optional shared cache pool (device memory, 256-byte aligned), see below */
     uint64_t shared_cache_bytes;    /* its size: a multiple of the granule, at most 2^30 granules */

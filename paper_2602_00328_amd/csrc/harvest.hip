@@ -343,7 +343,7 @@ struct StreamState {
     Lists lists[HARVEST_N_CLASSES];
     KvWork work;
     uint32_t *cnt_block = nullptr;          // the counters of both classes and, behind them, `next` and `snap`: one allocation
-    unsigned long long *next = nullptr;     // tile counter of move_pcie, zero between launches
+    unsigned long long *next = nullptr;     // tile counter of the copies over PCIe, zero between launches
     uint32_t *snap = nullptr;               // of a recorded one-kernel fetch: see snap_edit
     uint32_t *mark = nullptr;               // [MAX_EXPERTS / 32 + 1] routed-set bitmap and invalid-id count of large batches;
                                             // zero between fetches
@@ -1057,10 +1057,21 @@ int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &r
     a.n_tiles = (uint32_t)tiles;
     a.next = ss->next;
     a.lease = way == WITHIN_HBM ? nullptr : ctx->d_lease;
-    const dim3 grid(grid_for(tiles, way == WITHIN_HBM ? ctx->ctl_grid : ctx->pcie_grid));
-    if (way == TO_HOST && unroll == 4) return go(in_args ? move_pcie<true, 4, true> : move_pcie<false, 4, true>, grid, dim3(WG));
-    if (way == TO_HOST) return go(in_args ? move_pcie<true, 8, true> : move_pcie<false, 8, true>, grid, dim3(WG));
-    return go(in_args ? move_pcie<true, 8, false> : move_pcie<false, 8, false>, grid, dim3(WG));
+    // To the host with 5/3 as many workgroups, 20: stores at system scope wait for the host.  Beside a kernel that fills the device
+    // 12 / 16 / 20 / 24 workgroups write 200 blocks of 2 x 32 KiB back in 282 / 258 / 253 / 250 us and 2 x 16 KiB in 207 / 164 / 142
+    // / 139 (12 with non-temporal stores: 252 and 151; alone any number 243 and 128, 253 and 133); a fetch of 880 blocks from the
+    // host, 1.01 ms alone, takes 1.05 / 1.08 / 1.16 / 1.26 ms beside a stream of write-backs (non-temporal: 1.20).
+    const dim3 grid(grid_for(tiles, way == WITHIN_HBM ? ctx->ctl_grid : way == TO_HOST ? ctx->pcie_grid * 5 / 3 : ctx->pcie_grid));
+    if (way == TO_HOST) {
+        const bool through = items * a.chunk_bytes > THROUGH_FROM;
+        auto of = [&](auto in) {
+            constexpr bool I = decltype(in)::value;
+            return unroll == 4 ? (through ? move_pcie<I, 4, THROUGH_STORES> : move_pcie<I, 4, NT_STORES>)
+                               : (through ? move_pcie<I, 8, THROUGH_STORES> : move_pcie<I, 8, NT_STORES>);
+        };
+        return go(in_args ? of(std::true_type{}) : of(std::false_type{}), grid, dim3(WG));
+    }
+    return go(in_args ? move_pcie<true, 8, PLAIN_STORES> : move_pcie<false, 8, PLAIN_STORES>, grid, dim3(WG));
 }
 
 int check_class(harvest_ctx *ctx, int cls)

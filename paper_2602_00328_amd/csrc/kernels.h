@@ -74,7 +74,7 @@ struct MoveArgs {
     uint32_t n_planes, n_layers, n_obj, tiles_per_chunk, n_tiles;
     uint32_t order;                                                        // ORDER_*: which chunk comes after which
     const MoveRec *recs;                                                   // null: the list travels with the launch (MoveList)
-    unsigned long long *next;                                              // tile counter of move_pcie
+    unsigned long long *next;                                              // tile counter of the copies over PCIe
     const unsigned long long *lease;
 };
 // The order in which a move takes its chunks follows the layout of the cache tier, so that the writes to slots that were handed
@@ -1091,12 +1091,23 @@ __device__ inline MoveChunk move_chunk(const MoveArgs &a, uint32_t item)
 // beyond the tiles, and the one that draws the last puts it back.  The next number is drawn while the tile is on its way; whether
 // a fetch needs the link is asked last, right before the next tile's loads go out - asked along with the draw, the answer was a tile
 // old, and a fetch of 200 blocks beside a placement of 32 workgroups took 1.56 ms instead of 0.98 (alone 0.25).
-// Writes to the host are non-temporal: 16 MiB take 308 us in tiles of 16 KiB and 311 in tiles of 32, 317 with plain stores (2 MiB 43
-// against 48).
-template <bool INLINE, int U, bool NT>
+//
+// TO_HOST, writes to the host: stores at system scope, which the L2 passes on as they come - 16 MiB take 296.5 us in tiles of 32 KiB
+// (56.6 GB/s, the DMA engine 55.3), 304 with non-temporal stores, 316 with plain ones; 64 MiB 1 177, 1 203 and 1 220 us.  They are
+// acknowledged by the host, so it takes more workgroups to keep their rate beside a kernel that fills the device (launch_move).  A
+// list of up to THROUGH_FROM bytes the L2 takes as a whole, and non-temporal stores are faster (1 MiB: 22.3 us, 23.1 at system scope).
+enum StoreWay { PLAIN_STORES, NT_STORES, THROUGH_STORES };
+constexpr uint64_t THROUGH_FROM = 2u << 20;
+template <int WAY> __device__ inline void st16_to(u32x4 *p, u32x4 v)
+{
+    if (WAY == THROUGH_STORES) __builtin_amdgcn_global_store_b128((g_u32x4 *)(uint64_t)p, v, "");
+    else st16<WAY == NT_STORES>(p, v);
+}
+template <bool INLINE, int U, int WAY>
 __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
 {
     constexpr uint32_t TILE = WG * 16 * U;
+    constexpr int WAY1 = WAY == PLAIN_STORES ? PLAIN_STORES : NT_STORES;        // of the copy that stays in HBM
     __shared__ unsigned long long s_tile[2];
     const uint32_t tid = threadIdx.x;
     if (tid == 0) { yield_link<TILE>(a.lease); s_tile[0] = atomicAdd(a.next, 1ull); }
@@ -1116,19 +1127,19 @@ __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
             if (tid == 0) s_tile[turn] = atomicAdd(a.next, 1ull);
             if (m.dst0) {
 #pragma unroll
-                for (int i = 0; i < U; ++i) st16<NT>(d0 + tid + i * WG, v[i]);
+                for (int i = 0; i < U; ++i) st16_to<WAY>(d0 + tid + i * WG, v[i]);
             }
             if (m.dst1) {
 #pragma unroll
-                for (int i = 0; i < U; ++i) st16<NT>(d1 + tid + i * WG, v[i]);
+                for (int i = 0; i < U; ++i) st16_to<WAY1>(d1 + tid + i * WG, v[i]);
             }
         } else {
             if (tid == 0) s_tile[turn] = atomicAdd(a.next, 1ull);
             const uint32_t n_vec = (uint32_t)(len >> 4);
             for (uint32_t i = tid; i < n_vec; i += WG) {
                 u32x4 v = ld16<false>(s + i);
-                if (m.dst0) st16<NT>(d0 + i, v);
-                if (m.dst1) st16<NT>(d1 + i, v);
+                if (m.dst0) st16_to<WAY>(d0 + i, v);
+                if (m.dst1) st16_to<WAY1>(d1 + i, v);
             }
         }
         if (tid == 0) yield_link<TILE>(a.lease);

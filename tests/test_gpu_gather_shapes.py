@@ -297,6 +297,25 @@ def test_moves_with_and_without_a_list_on_the_device(n_planes, cache, chunk, n):
     h.close()
 
 
+@pytest.mark.parametrize("chunk,n", [(16384, 64), (16384, 65), (32768, 32), (32768, 33), (32768 + 16, 32)])
+def test_write_backs_around_the_size_from_which_stores_go_through(chunk, n):
+    """2 MiB and the first size beyond, in tiles of 16 and 32 KiB and with a remainder: host copies and cache slots are the source's."""
+    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n, n_host_slots=n, n_cache_slots=n, n_local_slots=0))
+    rng = np.random.default_rng(n)
+    slots = rng.permutation(n).astype(np.int64)
+    ids = h.register(B.KV, n, slots)
+    h.place(B.KV, ids[:n // 2])
+    src = [torch.from_numpy(rng.integers(0, 256, (n, chunk), dtype=np.uint8)).cuda() for _ in range(2)]
+    at = rng.permutation(n).astype(np.uint64)
+    h.evict(B.KV, -1, ids, src[0], src[1], at, n)
+    torch.cuda.synchronize()
+    for p in range(2):
+        want = src[p].cpu().numpy()[at.astype(np.int64)]
+        assert np.array_equal(h.host_plane(B.KV, p)[0][slots], want)
+        assert np.array_equal(h.dev_plane(B.KV, B.CACHE, p)[0, :n // 2].cpu().numpy(), want[:n // 2])
+    h.close()
+
+
 def test_first_placement_on_a_stream_while_the_null_stream_is_busy():
     n, layers, chunk, rng = 40, 4, 16384, np.random.default_rng(3)
     h = B.Harvest(kv=B.ClassSpec(n_layers=layers, n_planes=1, chunk_bytes=chunk, max_objects=n, n_host_slots=n, n_cache_slots=n, n_local_slots=0))
