@@ -106,7 +106,7 @@ enum harvest_flags {
     HARVEST_FLAG_POISON = 2,     /* revoke overwrites the freed cache slot with 0xA5 after the drain */
     HARVEST_FLAG_PROFILE = 4,    /* bracket the gather kernels with events; read them with harvest_profile
                                     (launches recorded into a graph are not timed) */
-    HARVEST_FLAG_GENERAL_FETCH = 8, /* harvest_fetch_kv never takes its one-kernel form for small block tables (up to
+    HARVEST_FLAG_GENERAL_FETCH = 8, /* KV fetches never take their one-kernel form for small block tables (up to
                                     4096 cells): every fetch runs resolve, compaction and the gather - for
                                     measurements and tests of that path; results are the same either way */
     HARVEST_FLAG_CACHE_PLANES_ADJACENT = 16 /* two-plane classes with cache slots of their own keep them in ONE buffer,
@@ -146,7 +146,7 @@ typedef struct harvest_config {
     uint32_t host_wgs;              /* tuning: 8 KiB of host-tier (PCIe) reads in flight per unit; 0 = default (24) */
     uint32_t shared_granule;        /* segment granule of the shared cache pool in bytes: a power of two >= 256;
                                        0 = 4096 */
-    uint32_t small_fetch_cells;     /* tuning: harvest_fetch_kv takes its one-kernel form for block tables of up to this
+    uint32_t small_fetch_cells;     /* tuning: a KV fetch, of either layout, takes its one-kernel form for block tables of up to this
                                        many cells (n_seq * max_blocks); 0 = default (4096) */
     uint32_t gather_threads;        /* tuning: threads per workgroup of the HBM-tier gather, 64, 128 or 256; 0 = default
                                        (64: one wavefront per workgroup, 1 KiB tiles) */

@@ -1758,7 +1758,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         const uint64_t live = (uint64_t)latest.hbm + latest.host;
         if (live < total) dead_tiles = (total - live) * tpc * c.cfg.n_planes * n_layers;
     }
-    if (!ctx->general_fetch && !c.n_lossy && !head_major && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
+    if (!ctx->general_fetch && !c.n_lossy && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
         total * tpc * n_layers <= (1ull << 31) && dead_tiles <= DEAD_TILES) {
         GatherArgs ga{};
         const ClassDev cd = class_dev(c);
@@ -1788,10 +1788,14 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
                           c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr, n_seq };
         const uint32_t head = ga.n_host + 1;
         const dim3 grid(n_layers > 1 ? std::max(ga.hbm_wgs, head) : ga.hbm_wgs + head, c.cfg.n_planes, n_layers > 1 ? n_layers + 1 : 1);
-        auto kernel = c.cfg.n_planes == 2 ? (nthr == 64 ? fetch_kv_small<2, 64> : fetch_kv_small<2, WG>)
-                                          : (nthr == 64 ? fetch_kv_small<1, 64> : fetch_kv_small<1, WG>);
+        auto of = [&](auto with_hm) {
+            constexpr bool HM = decltype(with_hm)::value;
+            return c.cfg.n_planes == 2 ? (nthr == 64 ? fetch_kv_small<2, 64, HM> : fetch_kv_small<2, WG, HM>)
+                                       : (nthr == 64 ? fetch_kv_small<1, 64, HM> : fetch_kv_small<1, WG, HM>);
+        };
+        auto kernel = head_major ? of(std::true_type{}) : of(std::false_type{});
         if ((rc = launch_last(ctx, ss, recording, kernel, grid, dim3(nthr), cd, layer, d_block_table, d_n_blocks, (uint32_t)total, max_blocks,
-                              d_seq_dst_block, dst_capacity_blocks, ga, books)))
+                              d_seq_dst_block, dst_capacity_blocks, ga, books, hm, d_seq_cap_blocks)))
             return rc;
         ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
         ss->feedback_valid[HARVEST_KV] = true;

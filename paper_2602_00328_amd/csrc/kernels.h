@@ -194,15 +194,17 @@ enum { BC_HBM = 0, BC_HOST, BC_MISS, BC_REQ, BC_LOCAL, BC_CACHE, BC_LOST, BC_INV
 // request (unknown block, or a destination that does not fit).  For tiers 0..2 rec names source and destination.  The loads
 // wait for nothing but their addresses - row length, block number and destination go out together, then the directory
 // entry of block 0 if the cell names none - so a cell costs two memory latencies, not four.
-struct Ask { uint64_t first; uint32_t n, j; int32_t b; };     // the sequence's first destination block and its length; column; block
+struct Ask { uint64_t first; uint32_t n, j; int32_t b; uint32_t cap; };     // the sequence's first destination block and its length; column;
+                                                                            // block; destination blocks (head-major layout)
 __device__ inline Ask ask_cell(const int32_t *__restrict__ table, const int32_t *__restrict__ n_blocks, uint32_t max_blocks,
-                               const uint64_t *__restrict__ seq_dst_block, uint32_t r, uint32_t total)
+                               const uint64_t *__restrict__ seq_dst_block, uint32_t r, uint32_t total,
+                               const uint32_t *__restrict__ seq_cap_blocks = nullptr)
 {
     const bool there = r < total;
     if (!there) r = total - 1;
     const uint32_t s = r / max_blocks;
     const int32_t n = n_blocks[s];
-    return { seq_dst_block[s], there && n > 0 ? (uint32_t)n : 0u, r - s * max_blocks, table[r] };
+    return { seq_dst_block[s], there && n > 0 ? (uint32_t)n : 0u, r - s * max_blocks, table[r], seq_cap_blocks ? seq_cap_blocks[s] : 0u };
 }
 __device__ inline int resolve_cell(const ClassDev &c, uint32_t layer, const int32_t *__restrict__ table,
                                    const int32_t *__restrict__ n_blocks, uint32_t max_blocks,
@@ -722,7 +724,29 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
     }
 }
 
-// The whole KV fetch in one kernel, for small block tables (token-major layout).  A fetch of a few blocks is made of launch
+// A head-major working layout: a pool block is [token][head][head_bytes], the destination of a sequence [head][token][head_bytes].
+struct HmArgs {
+    uint32_t n_heads;
+    uint32_t upr;             // 16-byte units per head row (head_bytes / 16)
+    uint32_t ups;             // units one block adds to one head strip (block_tokens * upr)
+    uint32_t pad;
+    // unit number u of a block in destination order: where it is in the block, in units, and where it goes from the sequence's
+    // first row of this block on, in bytes (cap: destination blocks of the sequence)
+    __device__ inline void by_destination(uint32_t u, uint64_t cap, uint32_t &unit, uint64_t &to) const
+    {
+        const uint32_t head = u / ups, rem = u - head * ups, tok = rem / upr, col = rem - tok * upr;
+        unit = (tok * n_heads + head) * upr + col;
+        to = head * (cap * ups * 16) + (uint64_t)rem * 16;
+    }
+    // ... and of unit number u in source order, where it goes
+    __device__ inline uint64_t by_source(uint32_t u, uint64_t cap) const
+    {
+        const uint32_t row_units = n_heads * upr, tok = u / row_units, rem = u - tok * row_units, head = rem / upr, col = rem - head * upr;
+        return head * (cap * ups * 16) + (uint64_t)(tok * upr + col) * 16;
+    }
+};
+
+// The whole KV fetch in one kernel, for small block tables.  A fetch of a few blocks is made of launch
 // gaps, not of bytes.  blockIdx.y is the plane, blockIdx.z counts consecutive layers (an object has the same slot in every
 // layer): layer + z is read, dst_step * z further into the destination is written.  NTHR is 256, or 64 for tables of up to 64 *
 // ROUND cells, which a single wavefront walks at once and whose tiles are a little faster as workgroups of one (16 blocks of 32
@@ -751,6 +775,9 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
 // entry says: whichever of them saw the older entry, the other then sees the younger one or copies anyway.  (Objects without a
 // host copy can leave nothing to copy from: with any around, fetches resolve in one place, on the general path.)
 //
+// HM: into the head-major layout.  Tiles of the HBM tier are taken in destination order, the host's in source order, as in gather_hm
+// and host_tier_hm.  8 x 16 blocks of 2 x 32 KiB take 9.6 us (17.6 in three launches), 1 024 blocks 26.9 (31.4), 4 096 95.1 (96.9).
+//
 // A walk goes ROUND * WG cells at a time; the next round's row lengths, block numbers and destinations are on their way while
 // this one's directory entries are, so a round costs one memory latency, not two.  The code of the walk is kept short on
 // purpose: it runs once, and one wavefront doing the books with everything unrolled took 7 us for a table of 8 cells.
@@ -763,6 +790,7 @@ struct SmallBooks {
 };
 
 constexpr uint32_t ROUND = 2;            // cells a thread looks up at a time when a workgroup walks the table
+constexpr uint64_t SRC_MASK = 0x0000FFFFFFFFFFFCull;      // of a record's source: without tier and capacity
 constexpr uint32_t OF_OTHERS = 1u << 31; // in a wavefront's number of listed cells: some of them are in another tier than the host's
 
 // Cell number i of group q's share, of 1 << lg_groups shares: one of the cells i << lg_groups and on, every group another one.
@@ -773,11 +801,12 @@ __device__ inline uint32_t shared_cell(uint32_t i, uint32_t q, uint32_t lg_group
     return (i << lg_groups) + ((q ^ (i * 0x9E3779B1u >> 16)) & ((1u << lg_groups) - 1u));
 }
 
-template <int PLANES, int NTHR>
+template <int PLANES, int NTHR, bool HM>
 __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t layer, const int32_t *__restrict__ table,
                                                         const int32_t *__restrict__ n_blocks, uint32_t total,
                                                         uint32_t max_blocks, const uint64_t *__restrict__ seq_dst_block,
-                                                        uint64_t dst_cap, GatherArgs a, SmallBooks books)
+                                                        uint64_t dst_cap, GatherArgs a, SmallBooks books, HmArgs h,
+                                                        const uint32_t *__restrict__ seq_cap_blocks)
 {
     const uint32_t tpc = a.tiles_per_chunk, tid = threadIdx.x;
     // several layers: blockIdx.z == 0 is a slice of its own for the head workgroups, not n_host + 1 idle ones in every layer
@@ -788,11 +817,24 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
         const uint32_t r = t / tpc, k = t - r * tpc, plane = blockIdx.y;
         const uint32_t s = r / max_blocks, j = r - s * max_blocks;
         const int32_t nb = n_blocks[s], b = table[r];              // as resolve_cell, but out at the first answer
-        const uint64_t dst_chunk = seq_dst_block[s] + j;
-        if (nb <= 0 || j >= (uint32_t)nb || b < 0 || (uint32_t)b >= c.n_objects || dst_chunk >= dst_cap) return;
+        const uint64_t first = seq_dst_block[s], dst_chunk = first + j;
+        const uint64_t cap = HM ? seq_cap_blocks[s] : 0;
+        if (nb <= 0 || j >= (uint32_t)nb || b < 0 || (uint32_t)b >= c.n_objects) return;
+        if (HM ? first + cap > dst_cap || j >= cap || cap >= 65536 : dst_chunk >= dst_cap) return;
         const uint64_t e = c.dir[b];
         const int tier = (int)entry_tier(e);
         const uint64_t off = (uint64_t)k * (NTHR * 16);
+        if (HM) {
+            if (tier == T_NONE || entry_slot(e) >= slots_of(c, tier) || off + tid * 16 >= a.chunk_bytes) return;
+            if (tier == T_HOST && !entry_young(e, a.snap ? *a.snap : a.seen)) return;
+            uint32_t unit;
+            uint64_t to;
+            h.by_destination(k * NTHR + tid, cap, unit, to);
+            const uint64_t src = src_base_of(a, (uint32_t)tier, plane) + chunk_offset(c, tier, layer, entry_slot(e));
+            const uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + first * c.chunk_bytes + (uint64_t)j * h.ups * 16 + to;
+            st16<true>(reinterpret_cast<u32x4 *>(dst), ld16<true>(reinterpret_cast<const u32x4 *>(src) + unit));
+            return;
+        }
         if (tier != T_CACHE && tier != T_LOCAL) {                  // (apart: what a workgroup works out first is kept short)
             if (tier != T_HOST || !entry_young(e, a.snap ? *a.snap : a.seen) || entry_slot(e) >= c.n_slots[T_HOST]) return;
             const uint64_t src = (plane ? a.src_base[T_HOST][1] : a.src_base[T_HOST][0]) + chunk_offset(c, T_HOST, layer + z, entry_slot(e)) + off;
@@ -819,7 +861,7 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
     uint32_t n[6] = { 0, 0, 0, 0, 0, 0 };            // requests, local, cache, host, lost, invalid, of this wavefront
     uint32_t n_miss = 0;
     if (tid < C_N) s_cnt[tid] = 0;
-    auto ask = [&](uint32_t i) { return ask_cell(table, n_blocks, max_blocks, seq_dst_block, shared_cell(i, group, lg), total); };
+    auto ask = [&](uint32_t i) { return ask_cell(table, n_blocks, max_blocks, seq_dst_block, shared_cell(i, group, lg), total, HM ? seq_cap_blocks : nullptr); };
     Ask next[ROUND];
 #pragma unroll
     for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask(i * NTHR + tid);
@@ -841,15 +883,17 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
             const uint64_t dst_chunk = now[i].first + now[i].j;
             tier[i] = (int)entry_tier(e[i]);
             if (now[i].n <= now[i].j) tier[i] = -1;
-            else if (now[i].b < 0 || (uint32_t)now[i].b >= c.n_objects || dst_chunk >= dst_cap ||
+            else if (now[i].b < 0 || (uint32_t)now[i].b >= c.n_objects ||
+                     (HM ? now[i].first + now[i].cap > dst_cap || now[i].j >= now[i].cap || now[i].cap >= 65536 : dst_chunk >= dst_cap) ||
                      (tier[i] != T_NONE && entry_slot(e[i]) >= slots_of(c, tier[i]))) tier[i] = 4;
             rec[i].src = chunk_offset(c, T_HOST, layer, entry_slot(e[i]));
-            rec[i].dst = dst_chunk * c.chunk_bytes;
+            rec[i].dst = HM ? now[i].first * c.chunk_bytes + (uint64_t)now[i].j * h.ups * 16 : dst_chunk * c.chunk_bytes;
             const bool young = !keeper && (tier[i] == T_CACHE || tier[i] == T_LOCAL) && entry_young(e[i], seen);
             if (young) {
                 rec[i].src = chunk_offset(c, tier[i], layer, entry_slot(e[i])) | (uint64_t)tier[i];
                 tier[i] = T_HOST;                    // (T_HOST is 0: other sources have their tier in bits [1:0])
             }
+            if (HM) rec[i].src |= (uint64_t)now[i].cap << 48;
             uint32_t in_wave;
             rank[i] = wave_rank(tier[i] == T_HOST || (keeper && tier[i] == T_NONE), in_wave);
             const uint32_t of_others = __ballot(young) ? OF_OTHERS : 0;
@@ -883,8 +927,8 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
                         const uint32_t gi = g + i < n_tiles ? g + i : g, idx = gi / tpc, u = (gi - idx * tpc) * NTHR + tid;
                         const Rec x = s_list[idx];
                         act[i] = g + i < n_tiles && u < chunk_units;
-                        const uint64_t off = act[i] ? (uint64_t)u * 16 : 0, at = x.src + s_off + off;
-                        d[i] = x.dst + d_off + off;
+                        const uint64_t off = act[i] ? (uint64_t)u * 16 : 0, at = (HM ? x.src & SRC_MASK : x.src) + s_off + off;
+                        d[i] = x.dst + d_off + (HM ? h.by_source(act[i] ? u : 0, x.src >> 48) : off);
                         v[i] = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][0] + at));
                         if (PLANES == 2) v[1] = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][1] + at));
                     }
@@ -905,8 +949,9 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
                     if (u >= chunk_units) continue;
                     const Rec x = s_list[idx];
                     const uint32_t from = (uint32_t)(x.src & 3);
-                    const uint64_t at = src_base_of(a, from, p) + (x.src & ~(uint64_t)3) + rep * layer_stride_of(a, from);
-                    st16<true>(reinterpret_cast<u32x4 *>((p ? a.dst_base[1] : a.dst_base[0]) + x.dst + rep * a.dst_step) + u,
+                    const uint64_t at = src_base_of(a, from, p) + (x.src & (HM ? SRC_MASK : ~(uint64_t)3)) + rep * layer_stride_of(a, from);
+                    const uint64_t to = x.dst + rep * a.dst_step + (HM ? h.by_source(u, x.src >> 48) : (uint64_t)u * 16);
+                    st16<true>(reinterpret_cast<u32x4 *>((p ? a.dst_base[1] : a.dst_base[0]) + to),
                                ld16<false>(reinterpret_cast<const u32x4 *>(at) + u));
                 }
         }
@@ -947,15 +992,6 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
     }
 }
 
-// The gather into a head-major working layout: a pool block is [token][head][head_bytes], the destination of a
-// sequence is [head][token][head_bytes].
-struct HmArgs {
-    uint32_t n_heads;
-    uint32_t upr;             // 16-byte units per head row (head_bytes / 16)
-    uint32_t ups;             // units one block adds to one head strip (block_tokens * upr)
-    uint32_t pad;
-};
-
 // Host tier, WG threads, one load per plane in flight and twice as many threads as host_tier's (24 workgroups: 57.5 GB/s at
 // 32 KiB chunks).  Threads walk the block in SOURCE order, so that every wave load is one contiguous kilobyte (PCIe reads of
 // 256-byte pieces reach only 22 GB/s); the stores, which go to HBM, are the ones cut into head rows.  K and V of a unit go
@@ -967,7 +1003,6 @@ __device__ inline void host_tier_hm(const Rec *__restrict__ recs, uint32_t n_req
     const uint32_t spc = a.tiles_per_chunk;
     const uint64_t n_sub = (uint64_t)n_req * spc;
     const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
-    const uint32_t row_units = h.n_heads * h.upr;              // one token: all heads
     for (uint64_t g = b0; g < n_sub; g += a.n_host) {
         const uint32_t idx = (uint32_t)g / spc;
         const Rec x = recs[idx];
@@ -975,9 +1010,7 @@ __device__ inline void host_tier_hm(const Rec *__restrict__ recs, uint32_t n_req
         const uint64_t src = (x.src & 0x0000FFFFFFFFFFFCull) + (uint64_t)unit * 16;
         u32x4 v0 = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][0] + src)), v1;
         if (PLANES == 2) v1 = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][1] + src));
-        uint32_t tok = unit / row_units, rem = unit - tok * row_units;
-        uint32_t head = rem / h.upr, col = rem - head * h.upr;
-        uint64_t d = x.dst + head * ((x.src >> 48) * h.ups * 16) + (uint64_t)(tok * h.upr + col) * 16;
+        const uint64_t d = x.dst + h.by_source(unit, x.src >> 48);
         if (u < chunk_units) {
             st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[0] + d), v0);
             if (PLANES == 2) st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[1] + d), v1);
@@ -1035,11 +1068,9 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
         uint64_t src = src_base_of(a, (uint32_t)(x.src & 3), plane) + (x.src & 0x0000FFFFFFFFFFFCull);
         uint64_t dst = dst_plane + x.dst;
         if (u < chunk_units) {
-            // unit u (in walking order) -> source unit and destination byte offset
-            uint32_t head = u / h.ups, rem = u - head * h.ups;
-            uint32_t tok = rem / h.upr, col = rem - tok * h.upr;
-            uint32_t s_unit = (tok * h.n_heads + head) * h.upr + col;
-            uint64_t d_off = head * (cap * h.ups * 16) + (uint64_t)rem * 16;
+            uint32_t s_unit;
+            uint64_t d_off;
+            h.by_destination(u, cap, s_unit, d_off);
             st16<true>(reinterpret_cast<u32x4 *>(dst + d_off), ld16<true>(reinterpret_cast<const u32x4 *>(src) + s_unit));
         }
         t += gx;

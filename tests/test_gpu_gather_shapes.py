@@ -172,9 +172,44 @@ def test_one_kernel_fetch_shares_out_the_walk_for_the_hosts_cells(lens, width, h
     rig.h.close()
 
 
+@pytest.mark.parametrize("n_planes", [1, 2])
+@pytest.mark.parametrize("heads,tokens,head_bytes", [(1, 1, 16), (3, 5, 48), (8, 16, 256), (2, 16, 512)])     # blocks of 16 B, 720 B, 32 KiB, 16 KiB
+@pytest.mark.parametrize("lens,width", [([1], 1), ([128, 0], 64), ([65, 64], 65), ([256, 200, 1], 256), ([513], 513), ([30, 0, 7, 700], 701)])
+def test_one_kernel_head_major_fetch_at_the_edges_of_its_rounds(n_planes, heads, tokens, head_bytes, lens, width):
+    """Against the general path and numpy: blocks of all three tiers, blocks that do not exist, and a sequence whose destination
+    has less room than its length."""
+    chunk, outs = heads * tokens * head_bytes, []
+    lens = [min(k, width) for k in lens]
+    caps = np.array([k + i for i, k in enumerate(lens)], dtype=np.int32)
+    caps[-1] = max(lens[-1] - 2, 1)
+    first = np.cumsum([0] + caps[:-1].tolist())
+    room = int(caps.sum())
+    for flags in (0, B.FLAG_GENERAL_FETCH):
+        rig = Rig(chunk, 37, n_planes=n_planes, flags=flags)
+        t, dt, dn, _, _ = rig.tables(lens, width)
+        if lens[0] > 100:
+            t[0, 5], t[0, 70] = -4, rig.n
+            dt.copy_(torch.from_numpy(t))
+        k, v = rig.buffers(room)
+        df, dc = torch.from_numpy(first.astype(np.int64)).cuda(), torch.from_numpy(caps).cuda()
+        rig.h.fetch_kv_head_major(0, dt, dn, k, v if n_planes == 2 else None, df, dc, room, heads, tokens)
+        counts, miss, _ = rig.h.fetch_info(miss_cap=t.size)
+        outs.append((k.cpu().numpy(), v.cpu().numpy(), counts, miss.tolist()))
+        if not flags:
+            for p, buf in enumerate(outs[0][:n_planes]):
+                for s, n in enumerate(lens):
+                    got = buf[first[s] * chunk:(first[s] + caps[s]) * chunk].reshape(heads, caps[s] * tokens, head_bytes)
+                    for j in range(min(n, caps[s])):
+                        if 0 <= t[s, j] < rig.n:
+                            want = rig.payload[p][0][rig.order[t[s, j]]].reshape(tokens, heads, head_bytes).transpose(1, 0, 2)
+                            assert np.array_equal(got[:, j * tokens:(j + 1) * tokens], want), (p, s, j)
+        rig.h.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*(o[:2] for o in outs))) and outs[0][2:] == outs[1][2:]
+
+
 @pytest.mark.parametrize("recorded", [False, True])
-@pytest.mark.parametrize("edit", ["revoke", "place"])
-def test_a_one_kernel_fetch_is_whole_when_the_directory_changes_under_it(edit, recorded):
+@pytest.mark.parametrize("edit,head_major", [("revoke", False), ("place", False), ("revoke", True)])
+def test_a_one_kernel_fetch_is_whole_when_the_directory_changes_under_it(edit, head_major, recorded):
     """Its workgroups read the directory for themselves, and an edit that does not wait for the fetch - a revocation publishes
     first and drains then, a placement runs on another stream - must not make a block fall between those that copy from HBM and
     those that copy from the host: each would leave it to the other."""
@@ -190,15 +225,24 @@ def test_a_one_kernel_fetch_is_whole_when_the_directory_changes_under_it(edit, r
     table = torch.arange(n, dtype=torch.int32, device="cuda").reshape(1, n)
     n_blocks, first = torch.tensor([n], dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")
     k, v = (torch.zeros(n * chunk, dtype=torch.uint8, device="cuda") for _ in range(2))
-    want = [torch.from_numpy(x).cuda().reshape(-1) for x in payload]
+    want = source = [torch.from_numpy(x).cuda().reshape(-1) for x in payload]
+    if head_major:
+        want = [x.view(n * 16, 8, -1).transpose(0, 1).reshape(-1) for x in source]
     side, main = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def fetch():
+        if head_major:
+            h.fetch_kv_head_major(0, table, n_blocks, k, v, first, n_blocks, n, 8, 16)
+        else:
+            h.fetch_kv(0, table, n_blocks, k, v, first, n)
+
     with torch.cuda.stream(main):
-        h.fetch_kv(0, table, n_blocks, k, v, first, n)            # makes the stream's scratch
+        fetch()                                                   # makes the stream's scratch
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         if recorded:
             with torch.cuda.graph(graph, stream=main):
-                h.fetch_kv(0, table, n_blocks, k, v, first, n)
+                fetch()
     batches = np.array_split(ids, 12)
     for _ in range(3):
         h.revoke(B.KV, ids)
@@ -208,12 +252,12 @@ def test_a_one_kernel_fetch_is_whole_when_the_directory_changes_under_it(edit, r
         k.zero_(), v.zero_()
         torch.cuda.synchronize()
         with torch.cuda.stream(main):
-            graph.replay() if recorded else h.fetch_kv(0, table, n_blocks, k, v, first, n)
+            graph.replay() if recorded else fetch()
         if edit == "revoke":
             h.revoke(B.KV, ids)
         else:
             for b in batches:                                     # from device memory: not behind the fetch on the link
-                h.place_from(B.KV, b, want[0].data_ptr(), want[1].data_ptr(), b.astype(np.uint64), n, stream=side)
+                h.place_from(B.KV, b, source[0].data_ptr(), source[1].data_ptr(), b.astype(np.uint64), n, stream=side)
         torch.cuda.synchronize()
         for got, x in zip((k, v), want):
             assert torch.equal(got.view(torch.int32), x), int((got.view(torch.int32) != x).reshape(n, -1).any(1).sum())
