@@ -104,6 +104,29 @@ def test_a_few_blocks_from_the_host(n_planes, layout, chunk, threads):
     rig.h.close()
 
 
+@pytest.mark.parametrize("flags", [0, B.FLAG_GENERAL_FETCH])
+@pytest.mark.parametrize("host_wgs", [0, 1, 5])
+@pytest.mark.parametrize("n_planes,chunk,n_host", [(1, 1040, 1), (2, 1040, 3), (1, 4112, 2), (2, 32768, 1), (2, 16384, 5)])
+def test_layers_with_fewer_host_pages_than_workgroups(n_planes, chunk, n_host, host_wgs, flags):
+    """The host's pages of all layers are dealt out as one sequence; the small tables walk their cells in 64 and in 256 threads."""
+    for width in (40, 150):
+        rig = Rig(chunk, 40, n_layers=7, n_planes=n_planes, host_every=4, flags=flags, host_wgs=host_wgs)
+        lens = [width, 3]
+        t, dt, dn, df, cap = rig.tables(lens, width)
+        t[np.isin(t, np.flatnonzero(rig.on_host))] = 0       # a block of the cache tier
+        t[0, 7:7 + n_host] = np.flatnonzero(rig.on_host)[:n_host]
+        dt.copy_(torch.from_numpy(t))
+        for _ in range(2):
+            k, v = rig.buffers(cap)
+            rig.h.fetch_kv_layers(0, 7, dt, dn, k, v if n_planes == 2 else None, cap * chunk, df, cap)
+            assert rig.h.fetch_info(miss_cap=t.size)[0]["n_host"] == n_host
+            for p, buf in enumerate([k, v][:n_planes]):
+                got = buf.cpu().numpy()
+                for layer in range(7):
+                    assert np.array_equal(got[layer * cap * chunk:(layer + 1) * cap * chunk], rig.expected(t, lens, p, layer)), (p, layer)
+        rig.h.close()
+
+
 @pytest.mark.parametrize("host_every,local_every", [(0, 0), (1, 0), (2, 5)])
 def test_again_counts_its_requests(host_every, local_every):
     """All in the cache tier, all but one request in three on the host, and a mix: a repeated fetch adds to the totals."""
