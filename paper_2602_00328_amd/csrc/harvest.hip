@@ -192,7 +192,7 @@ struct ClassState {
     uint64_t cache_in_use = 0;
     bool adjacent = false;                  // equal-size cache slots laid out [layer][slot][plane][chunk] in one buffer
     uint64_t *d_dir = nullptr;
-    uint32_t *d_done = nullptr;             // the number of the latest edit that is complete, and a counter: see dir_write
+    uint32_t *d_done = nullptr;             // (in ctx->d_lease's block) the number of the latest edit that is complete, and a counter: see dir_write
     uint32_t n_lossy = 0;                   // objects registered without a host slot
     // The edits of this class's directory form one chain on the device, in the order the host made them: every edit is a
     // dir_write kernel on some stream (the caller's for place / evict, the control stream for register / restore /
@@ -430,7 +430,8 @@ struct harvest_ctx {
     hipStream_t drain = nullptr;          // the poisoning of revoked slots (hundreds of MiB at times): kept off `ctl`, so that no
                                           // directory edit queues up behind it
     unsigned long long *d_totals = nullptr;  // [HARVEST_N_CLASSES][C_N]
-    unsigned long long *d_lease = nullptr;   // until when (device clock) a fetch expects to need the PCIe link: see link_announce
+    unsigned long long *d_lease = nullptr;   // until when (device clock) a fetch expects to need the PCIe link: see link_announce;
+                                             // behind it, from byte 128 on, the classes' d_done
     std::map<hipStream_t, std::unique_ptr<StreamState>> streams;
     std::deque<Staging> staging;          // deque: references stay valid when it grows
     std::vector<ProfPair> prof;
@@ -1113,8 +1114,7 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
         if (!c.used) continue;
         HIP_TRY(hipEventCreateWithFlags(&c.edit_evt, hipEventDisableTiming));
         HIP_TRY(hipMalloc(&c.d_dir, (size_t)c.cfg.max_objects * sizeof(uint64_t)));
-        HIP_TRY(hipMalloc(&c.d_done, 2 * sizeof(uint32_t)));
-        HIP_TRY(hipMemset(c.d_done, 0, 2 * sizeof(uint32_t)));
+        c.d_done = (uint32_t *)((char *)ctx->d_lease + 128 + 64 * k);
         HIP_TRY(hipMemset(c.d_dir, 0xFF, (size_t)c.cfg.max_objects * sizeof(uint64_t)));   // tier NONE everywhere
         for (uint32_t p = 0; p < c.cfg.n_planes; ++p) {
             if (!c.cfg.n_host_slots) continue;
@@ -1282,7 +1282,7 @@ int harvest_destroy(harvest_ctx *ctx)
         for (auto e : ctx->prof_pool) (void)hipEventDestroy(e);
         for (auto e : ctx->evt_pool) (void)hipEventDestroy(e);
         for (auto &d : ctx->draining) (void)hipEventDestroy(d.e);
-        for (auto &c : ctx->cls) { (void)hipFree(c.d_dir); (void)hipFree(c.d_done); }
+        for (auto &c : ctx->cls) if (c.d_dir) (void)hipFree(c.d_dir);
         (void)hipFree(ctx->d_totals);
         (void)hipFree(ctx->d_lease);
         for (auto &c : ctx->cls) if (c.edit_evt) (void)hipEventDestroy(c.edit_evt);
