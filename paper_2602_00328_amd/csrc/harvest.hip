@@ -344,7 +344,7 @@ struct StreamState {
     KvWork work;
     uint32_t *cnt_block = nullptr;          // the counters of both classes and, behind them, `next` and `snap`: one allocation
     unsigned long long *next = nullptr;     // tile counter of the copies over PCIe, zero between launches
-    uint32_t *snap = nullptr;               // of a recorded one-kernel fetch: see snap_edit
+    uint32_t *snap = nullptr;               // of a one-kernel fetch that cannot be told the edits it comes after: see snap_edit
     uint32_t *mark = nullptr;               // [MAX_EXPERTS / 32 + 1] routed-set bitmap and invalid-id count of large batches;
                                             // zero between fetches
     int last_cls = -1;                      // class of the latest fetch enqueued on this stream, -1: none yet
@@ -786,8 +786,8 @@ int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, h
 // copies on another stream), and until its entry is seen the older one names the host copy, which holds the same bytes.
 // Nothing to do either when the latest edit ran on this very stream: the chain put every earlier one before it.
 //
-// seen_seq is also what a one-kernel fetch goes by (see fetch_kv_small): entries of later edits it copies twice, so a placement
-// that another stream has finished is noticed here.
+// seen_seq is also what a one-kernel fetch goes by (see fetch_kv_small), so placements that another stream has finished are
+// noticed here.
 int order_after_directory_edits(harvest_ctx *ctx, StreamState *ss, int cls)
 {
     const ClassState &c = ctx->cls[cls];
@@ -1772,7 +1772,10 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         ga.dst_step = dst_layer_stride; ga.n_rep = n_layers;
         ga.chunk_bytes = c.cfg.chunk_bytes;
         ga.seen = (uint32_t)ss->seen_seq[HARVEST_KV];
-        if (recording) {
+        // Replays come after other edits than this call.  And while another stream is placing blocks, which of its edits are complete
+        // is asked on the device, or all that it has placed since `seen` would be copied twice (600 blocks beside a stream of placements:
+        // 40 us; 33 when a fetch could lose blocks under them).
+        if (recording || ss->seen_seq[HARVEST_KV] != c.edit_seq) {
             ga.snap = ss->snap;
             if ((rc = launch(ss->s, snap_edit, dim3(1), dim3(1), (const uint32_t *)c.d_done, ss->snap))) return rc;
         }

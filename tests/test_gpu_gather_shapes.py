@@ -274,13 +274,18 @@ def test_a_one_kernel_fetch_is_whole_when_the_directory_changes_under_it(edit, h
         torch.cuda.synchronize()
         k.zero_(), v.zero_()
         torch.cuda.synchronize()
+        def place(b):                                             # from device memory: not behind the fetch on the link
+            h.place_from(B.KV, b, source[0].data_ptr(), source[1].data_ptr(), b.astype(np.uint64), n, stream=side)
+
+        if edit == "place":                                       # one that is under way when the fetch is enqueued
+            place(batches[0])
         with torch.cuda.stream(main):
             graph.replay() if recorded else fetch()
         if edit == "revoke":
             h.revoke(B.KV, ids)
         else:
-            for b in batches:                                     # from device memory: not behind the fetch on the link
-                h.place_from(B.KV, b, source[0].data_ptr(), source[1].data_ptr(), b.astype(np.uint64), n, stream=side)
+            for b in batches[1:]:
+                place(b)
         torch.cuda.synchronize()
         for got, x in zip((k, v), want):
             assert torch.equal(got.view(torch.int32), x), int((got.view(torch.int32) != x).reshape(n, -1).any(1).sum())
