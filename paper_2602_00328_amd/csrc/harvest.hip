@@ -1784,11 +1784,12 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         // A third more reads of the host in flight than in the general path, where the tables are not tiny: the tile workgroups keep
         // the host's waiting at the compute units.  1 of 32 blocks on the host: 2 877 cells of 2 x 16 KiB 37.7 us against 38.9, 4 000
         // of 2 x 32 KiB 146.4 against 148.2; 1 of 100: 89.7 against 89.1; 4 of 10 (1 600 KiB of them or more): the same.
-        ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr) * (nthr == WG ? 4 : 3) / 3 : 0;
+        ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr) * 4 / 3 : 0;
         // the walk for the host's cells is shared out, see fetch_kv_small: not when it takes a single round, and to groups of at least
         // 12 workgroups - what a group finds is read by its own workgroups only, and with 4 to a group (2 877 cells, 52 on the
         // host) the groups that had found less left the link to the others for so long that 37.7 us became 39.4
         while (ga.n_host >> ga.host_lg_groups >= 24 && total > (uint64_t)nthr * ROUND << ga.host_lg_groups) ga.host_lg_groups++;
+        deal_out_host_pieces(ga, c.cfg.n_planes, nthr);
         ga.hbm_wgs = (uint32_t)total * ga.tiles_per_chunk;
         SmallBooks books{ lists.miss, cnt, info, ctx->d_totals + HARVEST_KV * C_N, ss->d_feedback + HARVEST_KV,
                           c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr, n_seq };

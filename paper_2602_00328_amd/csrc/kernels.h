@@ -131,6 +131,9 @@ struct GatherArgs {
     uint32_t seen;                       // of fetch_kv_small: the latest directory edit that it comes after, or where that is kept
     const uint32_t *snap;
     uint32_t host_lg_groups;             // of fetch_kv_small: the walk for the host's cells is cut into 1 << host_lg_groups shares
+    uint32_t host_lg_run;                // ... and what a workgroup reads of a cell at a time is 1 << host_lg_run KiB, a piece:
+    uint32_t host_ppc, host_pieces;      // this many to a plane and layer, to a cell
+    uint32_t host_per_cell, host_starts, host_step;      // at most so many are a workgroup's; see first_piece
 };
 // In pinned memory, one per class and stream: requests of either tier of the latest fetch whose kernels have run - hints for the
 // next launch - and the rows and columns of the block table they were asked for with (experts: zero).
@@ -145,10 +148,19 @@ struct GatherBooks {
 
 __device__ inline uint32_t lane_id() { return __lane_id(); }
 
-// Selects instead of indexing: a variable index into a kernel-argument struct would send it to scratch memory.
+// A value that all lanes of the wavefront have, for the scalar registers.
+__device__ inline uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ inline uint64_t uniform(uint64_t x) { return (uint64_t)uniform((uint32_t)(x >> 32)) << 32 | uniform((uint32_t)x); }
+// Selects instead of indexing: a variable index into a kernel-argument struct would send it to scratch memory.  Of values that are in
+// registers: a select between two arguments becomes a load through a selected address, by every lane for itself.
+template <typename T> __device__ inline T of_tier(int tier, T host, T cache, T local)
+{
+    host = uniform(host); cache = uniform(cache); local = uniform(local);
+    return tier == T_HOST ? host : (tier == T_CACHE ? cache : local);
+}
 __device__ inline uint32_t slots_of(const ClassDev &c, int tier)
 {
-    return tier == T_HOST ? c.n_slots[T_HOST] : (tier == T_CACHE ? c.n_slots[T_CACHE] : c.n_slots[T_LOCAL]);
+    return of_tier(tier, c.n_slots[T_HOST], c.n_slots[T_CACHE], c.n_slots[T_LOCAL]);
 }
 __device__ inline uint64_t chunk_offset(const ClassDev &c, int tier, uint32_t layer, uint32_t slot)
 {
@@ -176,6 +188,12 @@ __device__ inline uint32_t wave_rank(bool pred, uint32_t &total)
     return (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull));
 }
 
+
+// The value that lane k of the wavefront has, k the same in all of them (and, at the end of a pair, one too many: that of lane 0 then).
+__device__ inline uint32_t lane_value(uint32_t x, uint32_t k) { return __builtin_amdgcn_readlane(x, k & 63); }
+__device__ inline uint64_t lane_value(uint64_t x, uint32_t k) { return (uint64_t)lane_value((uint32_t)(x >> 32), k) << 32 | lane_value((uint32_t)x, k); }
+__device__ inline uint32_t min64(uint32_t x) { return x < 64 ? x : 64; }
+
 __device__ inline uint32_t wave_sum(uint32_t v)
 {
 #pragma unroll
@@ -194,31 +212,29 @@ enum { BC_HBM = 0, BC_HOST, BC_MISS, BC_REQ, BC_LOCAL, BC_CACHE, BC_LOST, BC_INV
 // request (unknown block, or a destination that does not fit).  For tiers 0..2 rec names source and destination.  The loads
 // wait for nothing but their addresses - row length, block number and destination go out together, then the directory
 // entry of block 0 if the cell names none - so a cell costs two memory latencies, not four.
-struct Ask { uint64_t first; uint32_t n, j; int32_t b; uint32_t cap; };     // the sequence's first destination block and its length; column;
-                                                                            // block; destination blocks (head-major layout)
-__device__ inline Ask ask_cell(const int32_t *__restrict__ table, const int32_t *__restrict__ n_blocks, uint32_t max_blocks,
-                               const uint64_t *__restrict__ seq_dst_block, uint32_t r, uint32_t total,
-                               const uint32_t *__restrict__ seq_cap_blocks = nullptr)
+struct Ask { uint32_t n, s, j; int32_t b; };     // the sequence's length and number; column; block
+__device__ inline Ask ask_cell(const int32_t *__restrict__ table, const int32_t *__restrict__ n_blocks, uint32_t max_blocks, uint32_t r,
+                               uint32_t total)
 {
     const bool there = r < total;
     if (!there) r = total - 1;
     const uint32_t s = r / max_blocks;
     const int32_t n = n_blocks[s];
-    return { seq_dst_block[s], there && n > 0 ? (uint32_t)n : 0u, r - s * max_blocks, table[r], seq_cap_blocks ? seq_cap_blocks[s] : 0u };
+    return { there && n > 0 ? (uint32_t)n : 0u, s, r - s * max_blocks, table[r] };
 }
 __device__ inline int resolve_cell(const ClassDev &c, uint32_t layer, const int32_t *__restrict__ table,
                                    const int32_t *__restrict__ n_blocks, uint32_t max_blocks,
                                    const uint64_t *__restrict__ seq_dst_block, uint64_t dst_cap,
                                    const uint32_t *__restrict__ seq_cap_blocks, uint64_t strip_bytes, uint32_t r, Rec &rec)
 {
-    const Ask x = ask_cell(table, n_blocks, max_blocks, seq_dst_block, r, r + 1);
-    const uint64_t cap = seq_cap_blocks ? seq_cap_blocks[r / max_blocks] : 0, dst_chunk = x.first + x.j;
+    const Ask x = ask_cell(table, n_blocks, max_blocks, r, r + 1);
+    const uint64_t first = seq_dst_block[x.s], cap = seq_cap_blocks ? seq_cap_blocks[x.s] : 0, dst_chunk = first + x.j;
     const bool asked = x.j < x.n;
-    const bool fits = seq_cap_blocks ? x.first + cap <= dst_cap && x.j < cap && cap < 65536 : dst_chunk < dst_cap;
+    const bool fits = seq_cap_blocks ? first + cap <= dst_cap && x.j < cap && cap < 65536 : dst_chunk < dst_cap;
     const bool known = asked && x.b >= 0 && (uint32_t)x.b < c.n_objects;
     const uint64_t e = c.dir[known ? (uint32_t)x.b : 0u];
     const int tier = (int)entry_tier(e);
-    rec.dst = seq_cap_blocks ? x.first * c.chunk_bytes + (uint64_t)x.j * strip_bytes : dst_chunk * c.chunk_bytes;
+    rec.dst = seq_cap_blocks ? first * c.chunk_bytes + (uint64_t)x.j * strip_bytes : dst_chunk * c.chunk_bytes;
     if (tier != T_NONE) rec.src = chunk_offset(c, tier, layer, entry_slot(e)) | (uint64_t)tier | (cap << 48);
     if (!asked) return -1;
     if (!known || !fits) return 4;
@@ -760,12 +776,12 @@ struct HmArgs {
 //
 //   the first n_host  walk the table, list the host's cells in LDS and read them over PCIe, all planes and layers, two loads in
 //                     flight per thread (see host_tier for why so few): 102 of 256 blocks of 2 x 32 KiB from the host take
-//                     121 us.  When every host tile was read at once, by a workgroup of its own, 6.7 MB of reads queued on
-//                     the link together: 131 us.
+//                     123.6 us, the call.  When every host tile was read at once, by a workgroup of its own, 6.7 MB of reads queued
+//                     on the link together: 134 us.
 //                     A table that takes several rounds to walk is shared out: workgroup b belongs to group b modulo their number, and a
 //                     group walks its own share of the cells (shared_cell) and reads what it finds.  A round of a walk
 //                     costs its workgroup a microsecond of waits in which it reads nothing: 2 877 cells of 2 x 16 KiB, 52 of them
-//                     on the host, take 37.4-38.3 us in two groups and took 40.0-40.9 when every workgroup walked all six rounds.
+//                     on the host, take 38.1-38.5 us in two groups and took 39.5-40.9 when every workgroup walked all six rounds.
 //   the next one      walks the table too and keeps the books: counters, and the miss list in request order.  No atomics on
 //                     shared counters (a thousand of them on one address take longer than the copy), nothing to zero.
 //   the others        copy a tile of 16 bytes a thread if their cell's block is in HBM: nothing is compacted, so the grid covers the padded
@@ -775,11 +791,14 @@ struct HmArgs {
 //                     against 27.1 for plain ones, 2 000 43.7 against 51.3.
 //
 // Nothing makes the directory hold still meanwhile: a revocation publishes its entries while fetches are in flight, and a placement
-// on another stream when its copy has ended.  So a cell's tile workgroups and the host's may read different entries, and each leave
-// the cell to the other (4 096 blocks fetched from the cache tier and revoked by the next call: up to all of them missing in the
-// destination).  Hence an entry that may have changed under the launch (entry_young) is copied by whoever reads it, from where the
-// entry says: whichever of them saw the older entry, the other then sees the younger one or copies anyway.  (Objects without a
-// host copy can leave nothing to copy from: with any around, fetches resolve in one place, on the general path.)
+// on another stream when its copy has ended.  So workgroups may read different entries of a cell.  Two rules see to it that every byte
+// is copied all the same.  An entry that may have changed under the launch (entry_young) is copied by whoever reads it, from where the
+// entry says: of a cell's tile workgroup and its reader in the host's groups, whichever saw the older entry, the other then sees the
+// younger one or copies anyway (4 096 blocks fetched from the cache tier and revoked by the next call: without it up to all of them were
+// missing in the destination).  And which member of a group reads which piece of a cell follows from the cell's number alone
+// (first_piece), whatever else that member has listed: were the list dealt out by position, members that had listed one cell more or
+// less than others would leave pieces of cells that nobody has edited to each other.  (Objects without a host copy can leave nothing to
+// copy from: with any around, fetches resolve in one place, on the general path.)
 //
 // HM: into the head-major layout.  Tiles of the HBM tier are taken in destination order, the host's in source order, as in gather_hm
 // and host_tier_hm.  8 x 16 blocks of 2 x 32 KiB take 9.6 us (17.6 in three launches), 1 024 blocks 26.9 (31.4), 4 096 95.1 (96.9).
@@ -797,7 +816,6 @@ struct SmallBooks {
 
 constexpr uint32_t ROUND = 2;            // cells a thread looks up at a time when a workgroup walks the table
 constexpr uint64_t SRC_MASK = 0x0000FFFFFFFFFFFCull;      // of a record's source: without tier and capacity
-constexpr uint32_t OF_OTHERS = 1u << 31; // in a wavefront's number of listed cells: some of them are in another tier than the host's
 
 // Cell number i of group q's share, of 1 << lg_groups shares: one of the cells i << lg_groups and on, every group another one.
 // Which one changes from i to i by a hash: with q itself, blocks on the host that recur with the period of the groups - every
@@ -805,6 +823,37 @@ constexpr uint32_t OF_OTHERS = 1u << 31; // in a wavefront's number of listed ce
 __device__ inline uint32_t shared_cell(uint32_t i, uint32_t q, uint32_t lg_groups)
 {
     return (i << lg_groups) + ((q ^ (i * 0x9E3779B1u >> 16)) & ((1u << lg_groups) - 1u));
+}
+// What a group's members read of cell number i of its share: its `pieces` - 1 << host_lg_run KiB of one plane and layer, plane after
+// plane, layer after layer - are dealt out in turn, and this is the first one that `member` gets; every members-th from there on is its
+// too.  The cell's first piece goes to a member that a hash of i names (top bits of the product: cells that follow each other are
+// spread evenly, as are most that are a fixed distance apart), one of host_starts that are host_step apart.
+__host__ __device__ inline uint32_t first_piece(uint32_t i, uint32_t member, uint32_t members, uint32_t starts, uint32_t step)
+{
+    const uint32_t at = ((i * 0x9E3779B1u >> 16) * starts >> 16) * step;
+    return member >= at ? member - at : member + members - at;
+}
+
+// The numbers that follow from n_host, host_lg_groups, chunk_bytes and n_rep.  A piece is 4 KiB, a page of host memory, which the four
+// wavefronts of a workgroup read side by side, or half or a quarter of that where a cell would not have one for every member otherwise.
+// Members whose loads are uneven leave the link idle at the end: 52 blocks of 2 x 16 KiB among 2 877 cells 38.1 us (4 KiB in any case:
+// 38.1-39.8), 102 of 256 blocks of 2 x 32 KiB 123.6 (124.0), 300 of 2 000 of 2 x 16 KiB 178.9 (179.7).
+inline void deal_out_host_pieces(GatherArgs &a, uint32_t n_planes, uint32_t nthr)
+{
+    a.n_host &= ~((1u << a.host_lg_groups) - 1u);                // groups of the same size
+    const uint32_t members = a.n_host >> a.host_lg_groups;
+    auto cut = [&](uint32_t lg_run) {
+        a.host_lg_run = lg_run;
+        a.host_ppc = (uint32_t)((a.chunk_bytes + (1024ull << lg_run) - 1) >> (10 + lg_run));
+        a.host_pieces = a.host_ppc * n_planes * a.n_rep;
+    };
+    cut(nthr == 64 ? 0 : 2);
+    while (a.host_lg_run && a.host_pieces < members) cut(a.host_lg_run - 1);
+    if (!members) return;
+    a.host_per_cell = (a.host_pieces + members - 1) / members;
+    const bool in_runs = members % a.host_pieces == 0;
+    a.host_starts = in_runs ? members / a.host_pieces : members;
+    a.host_step = in_runs ? a.host_pieces : 1;
 }
 
 template <int PLANES, int NTHR, bool HM>
@@ -860,111 +909,115 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
     const bool keeper = blockIdx.x == a.n_host;
     const uint32_t wave = tid >> 6, seen = a.snap ? *a.snap : a.seen;
     const uint32_t lg = keeper ? 0 : a.host_lg_groups, last = (1u << lg) - 1u;         // the keeper's share is the whole table
-    const uint32_t group = blockIdx.x & last, member = blockIdx.x >> lg, members = (a.n_host - group + last) >> lg, share = (total + last) >> lg;
-    __shared__ Rec s_list[NTHR * ROUND];               // the round's cells on the host
+    const uint32_t group = blockIdx.x & last, member = blockIdx.x >> lg, members = a.n_host >> lg, share = (total + last) >> lg;
+    __shared__ Rec s_list[NTHR * ROUND];               // the round's cells on the host of which this workgroup reads something
+    __shared__ uint32_t s_first[NTHR * ROUND];         // ... its first piece of each
     __shared__ uint32_t s_sum[ROUND * WAVES_N];
     __shared__ uint32_t s_cnt[C_N];
     uint32_t n[6] = { 0, 0, 0, 0, 0, 0 };            // requests, local, cache, host, lost, invalid, of this wavefront
     uint32_t n_miss = 0;
     if (tid < C_N) s_cnt[tid] = 0;
-    auto ask = [&](uint32_t i) { return ask_cell(table, n_blocks, max_blocks, seq_dst_block, shared_cell(i, group, lg), total, HM ? seq_cap_blocks : nullptr); };
+    auto ask = [&](uint32_t i) { return ask_cell(table, n_blocks, max_blocks, shared_cell(i, group, lg), total); };
     Ask next[ROUND];
 #pragma unroll
     for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask(i * NTHR + tid);
     for (uint32_t first = 0; first < share; first += NTHR * ROUND) {
         int tier[ROUND];
-        Rec rec[ROUND];
         Ask now[ROUND];
-        uint64_t e[ROUND];
+        uint64_t e[ROUND], to0[ROUND];               // directory entry; the sequence's first destination block
+        uint32_t cap[ROUND];                         // ... and how many it has (head-major)
 #pragma unroll
         for (uint32_t i = 0; i < ROUND; ++i) {
             now[i] = next[i];
+            to0[i] = seq_dst_block[now[i].s];
+            cap[i] = HM ? seq_cap_blocks[now[i].s] : 0;
             e[i] = c.dir[now[i].n > now[i].j && now[i].b >= 0 && (uint32_t)now[i].b < c.n_objects ? now[i].b : 0];
         }
 #pragma unroll
         for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask(first + (ROUND + i) * NTHR + tid);
+        uint32_t piece0[ROUND];
+#pragma unroll
+        for (uint32_t i = 0; i < ROUND; ++i) piece0[i] = first_piece(first + i * NTHR + tid, member, members, a.host_starts, a.host_step);
         uint32_t rank[ROUND];                        // among the round's listed cells, in cell order: the host's, or the missed ones
+        bool lists[ROUND];
 #pragma unroll
         for (uint32_t i = 0; i < ROUND; ++i) {
-            const uint64_t dst_chunk = now[i].first + now[i].j;
+            const uint64_t dst_chunk = to0[i] + now[i].j;
             tier[i] = (int)entry_tier(e[i]);
             if (now[i].n <= now[i].j) tier[i] = -1;
             else if (now[i].b < 0 || (uint32_t)now[i].b >= c.n_objects ||
-                     (HM ? now[i].first + now[i].cap > dst_cap || now[i].j >= now[i].cap || now[i].cap >= 65536 : dst_chunk >= dst_cap) ||
+                     (HM ? to0[i] + cap[i] > dst_cap || now[i].j >= cap[i] || cap[i] >= 65536 : dst_chunk >= dst_cap) ||
                      (tier[i] != T_NONE && entry_slot(e[i]) >= slots_of(c, tier[i]))) tier[i] = 4;
-            rec[i].src = chunk_offset(c, T_HOST, layer, entry_slot(e[i]));
-            rec[i].dst = HM ? now[i].first * c.chunk_bytes + (uint64_t)now[i].j * h.ups * 16 : dst_chunk * c.chunk_bytes;
-            const bool young = !keeper && (tier[i] == T_CACHE || tier[i] == T_LOCAL) && entry_young(e[i], seen);
-            if (young) {
-                rec[i].src = chunk_offset(c, tier[i], layer, entry_slot(e[i])) | (uint64_t)tier[i];
-                tier[i] = T_HOST;                    // (T_HOST is 0: other sources have their tier in bits [1:0])
-            }
-            if (HM) rec[i].src |= (uint64_t)now[i].cap << 48;
+            lists[i] = tier[i] == T_HOST || (keeper ? tier[i] == T_NONE : (tier[i] == T_CACHE || tier[i] == T_LOCAL) && entry_young(e[i], seen));
+            if (!keeper) lists[i] &= piece0[i] < a.host_pieces;
             uint32_t in_wave;
-            rank[i] = wave_rank(tier[i] == T_HOST || (keeper && tier[i] == T_NONE), in_wave);
-            const uint32_t of_others = __ballot(young) ? OF_OTHERS : 0;
-            if (lane_id() == 0) s_sum[i * WAVES_N + wave] = in_wave | of_others;
+            rank[i] = wave_rank(lists[i], in_wave);
+            if (lane_id() == 0) s_sum[i * WAVES_N + wave] = in_wave;
         }
         __syncthreads();
         uint32_t listed = 0;
-        bool mixed = false;                          // the list has cells of other tiers too
 #pragma unroll
         for (uint32_t k = 0; k < ROUND * WAVES_N; ++k) {
-            const uint32_t before = listed;
-            listed += s_sum[k] & ~OF_OTHERS;
-            mixed |= (s_sum[k] & OF_OTHERS) != 0;
-            if ((k & (WAVES_N - 1)) == wave) rank[k / WAVES_N] += before;
+            if ((k & (WAVES_N - 1)) == wave) rank[k / WAVES_N] += listed;
+            listed += s_sum[k];
         }
+        listed = uniform(listed);
         if (!keeper && listed) {
 #pragma unroll
-            for (uint32_t i = 0; i < ROUND; ++i)
-                if (tier[i] == T_HOST) s_list[rank[i]] = rec[i];
+            for (uint32_t i = 0; i < ROUND; ++i) {
+                if (!lists[i]) continue;
+                uint64_t src = chunk_offset(c, T_HOST, layer, entry_slot(e[i]));
+                if (tier[i] != T_HOST) src = chunk_offset(c, tier[i], layer, entry_slot(e[i])) | (uint64_t)tier[i];      // (T_HOST is 0)
+                s_list[rank[i]] = { src | (HM ? (uint64_t)cap[i] << 48 : 0), to0[i] * c.chunk_bytes + now[i].j * (HM ? (uint64_t)h.ups * 16 : c.chunk_bytes) };
+                s_first[rank[i]] = piece0[i];
+            }
             __syncthreads();
-            constexpr int U = 2 / PLANES;            // tiles per step
-            const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4), n_tiles = listed * tpc;
-            // the steps of all layers are one sequence, as in host_tier
-            const uint32_t n_steps = (n_tiles + U - 1) / U;
-            uint32_t rep = mixed ? a.n_rep : 0, at_step = member, step_reps = 0, step = members;
-            if (a.n_rep > 1) { step_reps = step / n_steps; step -= step_reps * n_steps; rep += at_step / n_steps; at_step %= n_steps; }
-            for (;; rep += step_reps, at_step += step) {
-                if (at_step >= n_steps) { at_step -= n_steps; rep++; }
-                if (rep >= a.n_rep) break;
-                const uint64_t s_off = rep * a.layer_stride[T_HOST], d_off = rep * a.dst_step;
-                const uint32_t g = at_step * U;
-                u32x4 v[2];
-                uint64_t d[U];
-                bool act[U];
-#pragma unroll
-                for (int i = 0; i < U; ++i) {        // lanes beyond a chunk's end re-read its first bytes and store nothing
-                    const uint32_t gi = g + i < n_tiles ? g + i : g, idx = gi / tpc, u = (gi - idx * tpc) * NTHR + tid;
-                    const Rec x = s_list[idx];
-                    act[i] = g + i < n_tiles && u < chunk_units;
-                    const uint64_t off = act[i] ? (uint64_t)u * 16 : 0, at = (HM ? x.src & SRC_MASK : x.src) + s_off + off;
-                    d[i] = x.dst + d_off + (HM ? h.by_source(act[i] ? u : 0, x.src >> 48) : off);
-                    v[i] = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][0] + at));
-                    if (PLANES == 2) v[1] = ld16<false>(reinterpret_cast<const u32x4 *>(a.src_base[T_HOST][1] + at));
+            // A piece is read by 1 << lg_run wavefronts, a kilobyte each; the workgroup's other wavefronts are at other pieces meanwhile.
+            // The lanes work out 64 pieces at a time, which all of them then read one after the other, two in flight.
+            const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4), lg_run = NTHR == 64 ? 0 : a.host_lg_run, sets = WAVES_N >> lg_run;
+            const uint32_t set = uniform(wave >> lg_run), sub = uniform(wave & ((1u << lg_run) - 1u));
+            const uint32_t n_slots = listed * a.host_per_cell;
+            for (uint32_t slot0 = set; slot0 < n_slots; slot0 += 64 * sets) {
+                const uint32_t slot = slot0 + lane_id() * sets;
+                bool there = slot < n_slots;
+                uint32_t idx = there ? slot : 0, later = 0, rep = 0;
+                if (a.host_per_cell > 1) { idx /= a.host_per_cell; later = (slot - idx * a.host_per_cell) * members; }
+                const Rec x = s_list[idx];
+                uint32_t piece = s_first[idx] + later;
+                if (piece >= a.host_pieces) { there = false; piece = 0; }
+                if (a.n_rep > 1) { rep = piece / (a.host_ppc * PLANES); piece -= rep * (a.host_ppc * PLANES); }
+                const uint32_t plane = PLANES == 2 && piece >= a.host_ppc;
+                const uint32_t from = (uint32_t)(x.src & 3);
+                const uint32_t unit = there ? (((piece - plane * a.host_ppc) << lg_run) + sub) * 64 : chunk_units, cap_of = HM ? (uint32_t)(x.src >> 48) : 0;
+                // (the second plane as a difference, or every lane would load its pool's address from the arguments by itself)
+                uint64_t src = a.src_base[T_HOST][0] + (plane ? a.src_base[T_HOST][1] - a.src_base[T_HOST][0] : 0);
+                uint64_t dst = a.dst_base[0] + (plane ? a.dst_base[1] - a.dst_base[0] : 0) + x.dst;
+                if (a.n_rep > 1) { src += rep * a.layer_stride[T_HOST]; dst += rep * a.dst_step; }
+                if (__ballot(from != T_HOST)) {      // rare
+                    if (from != T_HOST) src = src_base_of(a, from, plane) + rep * layer_stride_of(a, from);
                 }
-#pragma unroll
-                for (int i = 0; i < U; ++i) {
-                    if (!act[i]) continue;
-                    st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[0] + d[i]), v[i]);
-                    if (PLANES == 2) st16<true>(reinterpret_cast<u32x4 *>(a.dst_base[1] + d[i]), v[1]);
+                src += x.src & (HM ? SRC_MASK : ~(uint64_t)3);
+                const uint64_t whole = __ballot(unit + 64 <= chunk_units), any = __ballot(there);
+                auto from_at = [&](uint32_t k, uint32_t u) { return reinterpret_cast<const u32x4 *>(lane_value(src, k)) + u; };
+                auto to_at = [&](uint32_t k, uint32_t u) {
+                    const uint64_t to = lane_value(dst, k);
+                    return reinterpret_cast<u32x4 *>(to + (HM ? h.by_source(u, lane_value(cap_of, k)) : (uint64_t)u * 16));
+                };
+                for (uint32_t k = 0; k < 64; k += 2) {
+                    const uint32_t u0 = lane_value(unit, k) + lane_id(), u1 = lane_value(unit, k + 1) + lane_id();
+                    if ((whole >> k & 3) == 3) {     // (without a condition on the loads, or the second would wait for the first)
+                        const u32x4 v0 = ld16<false>(from_at(k, u0)), v1 = ld16<false>(from_at(k + 1, u1));
+                        st16<true>(to_at(k, u0), v0);
+                        st16<true>(to_at(k + 1, u1), v1);
+                        continue;
+                    }
+                    if (!(any >> k)) break;
+                    const u32x4 *f0 = from_at(k, u0), *f1 = from_at(k + 1, u1);
+                    u32x4 *t0 = to_at(k, u0), *t1 = to_at(k + 1, u1);
+                    if (u0 < chunk_units) st16<true>(t0, ld16<false>(f0));
+                    if (u1 < chunk_units) st16<true>(t1, ld16<false>(f1));
                 }
             }
-            // rare: one tile of one plane at a time, from wherever it is
-#pragma unroll 1
-            for (uint32_t rep = 0; rep < (mixed ? a.n_rep : 0); ++rep)
-#pragma unroll 1
-                for (uint32_t g = member; g < n_tiles * PLANES; g += members) {
-                    const uint32_t p = g >= n_tiles, gi = p ? g - n_tiles : g, idx = gi / tpc, u = (gi - idx * tpc) * NTHR + tid;
-                    if (u >= chunk_units) continue;
-                    const Rec x = s_list[idx];
-                    const uint32_t from = (uint32_t)(x.src & 3);
-                    const uint64_t at = src_base_of(a, from, p) + (x.src & (HM ? SRC_MASK : ~(uint64_t)3)) + rep * layer_stride_of(a, from);
-                    const uint64_t to = x.dst + rep * a.dst_step + (HM ? h.by_source(u, x.src >> 48) : (uint64_t)u * 16);
-                    st16<true>(reinterpret_cast<u32x4 *>((p ? a.dst_base[1] : a.dst_base[0]) + to),
-                               ld16<false>(reinterpret_cast<const u32x4 *>(at) + u));
-                }
         }
         if (keeper) {
 #pragma unroll

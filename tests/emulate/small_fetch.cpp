@@ -1,0 +1,189 @@
+// fetch_kv_small on a CPU, with a directory that changes while it runs.  A workgroup's lanes are fibers that meet at barriers and
+// ballots; workgroups run one after the other, which is one of the orders a GPU may take, and each sees the versions of the
+// directory at barriers of its own (`when`), which is what workgroups that run at the same time and at different speeds see.
+#include <hip/hip_runtime.h>
+#include "kernels.h"
+
+#include <ucontext.h>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <vector>
+
+dim3 threadIdx, blockIdx, gridDim;
+uint32_t __shfl_xor(uint32_t, int) { abort(); }
+uint32_t __shfl_up(uint32_t, int) { abort(); }
+void __threadfence_system() {}
+
+namespace {
+enum State { READY, AT_BALLOT, AT_BARRIER, DONE };          // (a lane that reads another's register meets the others as at a ballot)
+struct Lane { ucontext_t ctx; State state; bool pred; uint32_t value; uint64_t mask; std::vector<char> stack; };
+std::vector<Lane> g_lanes(256);
+ucontext_t g_scheduler;
+uint32_t g_current = 0;
+bool g_fibers = false;
+std::function<void()> g_kernel;
+
+void wait(State s)
+{
+    if (!g_fibers) { fprintf(stderr, "a tile workgroup met a barrier\n"); abort(); }
+    Lane &l = g_lanes[g_current];
+    const dim3 me = threadIdx;
+    l.state = s;
+    swapcontext(&l.ctx, &g_scheduler);
+    threadIdx = me;
+}
+void lane_main()
+{
+    g_kernel();
+    g_lanes[g_current].state = DONE;
+    swapcontext(&g_lanes[g_current].ctx, &g_scheduler);
+}
+// Runs the workgroup blockIdx of n threads; at_barrier(k) is called when all have met for the k-th time, and with 0 before they start.
+void run_workgroup(uint32_t n, const std::function<void(uint32_t)> &at_barrier)
+{
+    g_fibers = true;
+    for (uint32_t i = 0; i < n; ++i) {
+        Lane &l = g_lanes[i];
+        l.stack.resize(128 << 10);
+        getcontext(&l.ctx);
+        l.ctx.uc_stack.ss_sp = l.stack.data();
+        l.ctx.uc_stack.ss_size = l.stack.size();
+        l.ctx.uc_link = nullptr;
+        makecontext(&l.ctx, lane_main, 0);
+        l.state = READY;
+    }
+    uint32_t barriers = 0;
+    at_barrier(0);
+    for (;;) {
+        bool progress = false;
+        for (uint32_t i = 0; i < n; ++i)
+            if (g_lanes[i].state == READY) {
+                progress = true;
+                g_current = i;
+                threadIdx = { i, 0, 0 };
+                swapcontext(&g_scheduler, &g_lanes[i].ctx);
+            }
+        uint32_t done = 0, met = 0;
+        for (uint32_t w = 0; w < n; w += 64) {
+            uint64_t mask = 0;
+            uint32_t there = 0;
+            for (uint32_t i = w; i < w + 64; ++i) {
+                const Lane &l = g_lanes[i];
+                if (l.state == AT_BALLOT) { there++; mask |= (uint64_t)l.pred << (i - w); }
+                done += l.state == DONE;
+                met += l.state == AT_BARRIER;
+            }
+            if (there == 64)
+                for (uint32_t i = w; i < w + 64; ++i) { g_lanes[i].mask = mask; g_lanes[i].state = READY; progress = true; }
+        }
+        if (done == n) return;
+        if (met && met + done == n) {
+            at_barrier(++barriers);
+            for (uint32_t i = 0; i < n; ++i) if (g_lanes[i].state == AT_BARRIER) g_lanes[i].state = READY;
+            progress = true;
+        }
+        if (!progress) { fprintf(stderr, "lanes wait for each other\n"); abort(); }
+    }
+}
+}  // namespace
+
+void __syncthreads() { wait(AT_BARRIER); }
+uint64_t __ballot(bool pred)
+{
+    g_lanes[g_current].pred = pred;
+    wait(AT_BALLOT);
+    return g_lanes[g_current].mask;
+}
+
+uint32_t read_lane(uint32_t x, uint32_t k)
+{
+    g_lanes[g_current].value = x;
+    wait(AT_BALLOT);                                     // all have said theirs
+    const uint32_t got = g_lanes[(g_current & ~63u) + k].value;
+    wait(AT_BALLOT);                                     // all have read it
+    return got;
+}
+
+extern "C" {
+struct Fetch {
+    uint32_t n_planes, nthr, head_major, n_layers, n_objects, n_seq, max_blocks, n_host, lg_groups, seen, n_versions, n_heads, block_tokens, n_slots;
+    uint64_t chunk_bytes, dst_cap, dst_step;
+    uint64_t pool[3][2], dst[2];                 // [tier][plane]: pools [layer][slot][chunk]; destinations [layer][dst_cap][chunk]
+    const int32_t *table, *n_blocks;
+    const uint64_t *seq_dst;
+    const uint32_t *seq_cap;
+    const uint64_t *versions;                    // [n_versions][n_objects]: directories, from the one that `seen` stands for on
+    const uint32_t *when;                        // [head or tile workgroup][n_versions - 1]: at which barrier each next one is seen
+    uint32_t *cnt, *miss;
+};
+
+// Workgroups in the order of `when`: n_host that read the host, the one with the books, the tiles (x, then plane, then layer).
+int run_fetch(const Fetch *f)
+{
+    using namespace hv;
+    ClassDev c{};
+    std::vector<uint64_t> dir(f->versions, f->versions + f->n_objects);
+    c.dir = dir.data();
+    c.n_objects = f->n_objects; c.n_planes = f->n_planes; c.chunk_bytes = f->chunk_bytes;
+    GatherArgs a{};
+    for (int t = 0; t < 3; ++t) {
+        for (int p = 0; p < 2; ++p) c.pool[t][p] = a.src_base[t][p] = f->pool[t][p];
+        c.n_slots[t] = f->n_slots;
+        c.slot_stride[t] = f->chunk_bytes;
+        c.layer_stride[t] = a.layer_stride[t] = f->n_slots * f->chunk_bytes;
+    }
+    a.dst_base[0] = f->dst[0]; a.dst_base[1] = f->dst[1];
+    a.chunk_bytes = f->chunk_bytes;
+    a.tiles_per_chunk = (uint32_t)((f->chunk_bytes + f->nthr * 16 - 1) / (f->nthr * 16));
+    a.dst_step = f->dst_step; a.n_rep = f->n_layers; a.n_host = f->n_host; a.host_lg_groups = f->lg_groups; a.seen = f->seen;
+    deal_out_host_pieces(a, f->n_planes, f->nthr);
+    const uint32_t total = f->n_seq * f->max_blocks;
+    a.hbm_wgs = total * a.tiles_per_chunk;
+    HmArgs h{};
+    if (f->head_major) {
+        h.n_heads = f->n_heads;
+        h.upr = (uint32_t)(f->chunk_bytes / (f->n_heads * f->block_tokens) / 16);
+        h.ups = h.upr * f->block_tokens;
+    }
+    std::vector<unsigned long long> totals(C_N);
+    alignas(16) Report report;
+    SmallBooks books{ f->miss, f->cnt, nullptr, totals.data(), &report, nullptr, f->n_seq };
+    auto call = [&](auto kernel) {
+        g_kernel = [&, kernel] { kernel(c, 0, f->table, f->n_blocks, total, f->max_blocks, f->seq_dst, f->dst_cap, a, books, h, f->seq_cap); };
+    };
+    if (f->n_planes == 2 && f->nthr == 64) f->head_major ? call(fetch_kv_small<2, 64, true>) : call(fetch_kv_small<2, 64, false>);
+    else if (f->n_planes == 2) f->head_major ? call(fetch_kv_small<2, 256, true>) : call(fetch_kv_small<2, 256, false>);
+    else if (f->nthr == 64) f->head_major ? call(fetch_kv_small<1, 64, true>) : call(fetch_kv_small<1, 64, false>);
+    else f->head_major ? call(fetch_kv_small<1, 256, true>) : call(fetch_kv_small<1, 256, false>);
+
+    const bool sliced = f->n_layers > 1;
+    const uint32_t head = a.n_host + 1;
+    gridDim = { sliced ? (a.hbm_wgs > head ? a.hbm_wgs : head) : a.hbm_wgs + head, f->n_planes, sliced ? f->n_layers + 1 : 1 };
+    const uint32_t *when = f->when;
+    uint32_t shown = 0;
+    auto show = [&](uint32_t version) {
+        if (version != shown) memcpy(dir.data(), f->versions + (uint64_t)version * f->n_objects, f->n_objects * 8);
+        shown = version;
+    };
+    auto versions_at = [&](uint32_t barrier) {
+        uint32_t v = 0;
+        while (v + 1 < f->n_versions && when[v] <= barrier) v++;
+        show(v);
+    };
+    for (uint32_t x = 0; x < head; ++x, when += f->n_versions - 1) {
+        blockIdx = { x, 0, 0 };
+        run_workgroup(f->nthr, versions_at);
+    }
+    g_fibers = false;
+    for (uint32_t z = 0; z < f->n_layers; ++z)
+        for (uint32_t p = 0; p < f->n_planes; ++p)
+            for (uint32_t t = 0; t < a.hbm_wgs; ++t, when += f->n_versions - 1) {
+                versions_at(0);
+                blockIdx = { sliced ? t : t + head, p, sliced ? z + 1 : 0 };
+                for (uint32_t i = 0; i < f->nthr; ++i) { threadIdx = { i, 0, 0 }; g_kernel(); }
+            }
+    return 0;
+}
+}  // extern "C"

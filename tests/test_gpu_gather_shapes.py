@@ -292,6 +292,54 @@ def test_a_one_kernel_fetch_is_whole_when_the_directory_changes_under_it(edit, h
     h.close()
 
 
+@pytest.mark.parametrize("n_planes,n_layers,n,layout,entry", [(2, 1, 4090, 0, "fetch"), (1, 1, 4090, 0, "fetch"), (2, 3, 1301, 0, "layers"), (2, 40, 100, 0, "layers"),
+                                                              (2, 1, 3001, B.FLAG_CACHE_PLANES_ADJACENT, "fetch"), (2, 1, 3001, 0, "static"), (2, 1, 3001, 0, "head_major")])
+def test_blocks_that_nobody_edits_are_whole_when_others_change_under_a_one_kernel_fetch(n_planes, n_layers, n, layout, entry):
+    """Half of the blocks are on the host; a few of those are placed by another stream while the fetch runs, and a few of the cached
+    ones are revoked.  Workgroups that list the host's blocks before and after such an edit have different lists."""
+    rig = Rig(32768, n, n_layers=n_layers, n_planes=n_planes, host_every=2, local_every=0, flags=layout)
+    for i in range(n):
+        rig.h.register_cb(B.KV, i, enabled=False)
+    t, dt, dn, df, cap = rig.tables([n], n)
+    t[0] = np.random.default_rng(7).permutation(n)
+    dt.copy_(torch.from_numpy(t))
+    k, v = rig.buffers(cap)
+    bufs, side, span = [k, v][:n_planes], torch.cuda.Stream(), n * 32768
+    info, miss = (torch.zeros(m, dtype=torch.int32, device="cuda") for m in (8, n))
+
+    def fetch():
+        if entry == "layers":
+            rig.h.fetch_kv_layers(0, n_layers, dt, dn, k, v, span, df, cap)
+        elif entry == "static":
+            rig.h.fetch_kv_static(0, dt, dn, k, v, df, cap, info, miss)
+        elif entry == "head_major":
+            rig.h.fetch_kv_head_major(0, dt, dn, k, v, df, dn, cap, 8, 16)
+        else:
+            rig.h.fetch_kv(0, dt, dn, k, v if n_planes == 2 else None, df, cap)
+
+    want = [[torch.from_numpy(rig.expected(t, [n], p, layer)).cuda() for layer in range(n_layers)] for p in range(n_planes)]
+    if entry == "head_major":
+        want = [[x.view(n * 16, 8, -1).transpose(0, 1).reshape(-1) for x in w] for w in want]
+    hosts, cached = np.flatnonzero(rig.on_host), np.flatnonzero(~rig.on_host)
+    fetch()
+    some = max(1, n // 300)
+    rig.h.revoke(B.KV, cached[:some])                             # there is room for the placements
+    for turn in range(1, 5):
+        torch.cuda.synchronize()
+        [b.zero_() for b in bufs]
+        torch.cuda.synchronize()
+        fetch()
+        placed, revoked = hosts[turn * some:(turn + 1) * some], cached[turn * some:(turn + 1) * some]
+        rig.h.place(B.KV, placed, stream=side)
+        rig.h.revoke(B.KV, revoked)
+        torch.cuda.synchronize()
+        for p, b in enumerate(bufs):
+            for layer in range(n_layers):
+                got = b[layer * span:(layer + 1) * span]
+                assert torch.equal(got, want[p][layer]), (turn, p, layer, int((got != want[p][layer]).reshape(n, -1).any(1).sum()))
+    rig.h.close()
+
+
 @pytest.mark.parametrize("lens,width", [([1], 1), ([65], 65), ([63, 64], 64), ([129], 129), ([300, 513], 600), ([5, 9], 4096), ([2, 1, 0], 4)])
 def test_static_fetch_hands_out_counters_and_misses_in_order(lens, width):
     rig = Rig(2048, 50)

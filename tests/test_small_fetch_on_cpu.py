@@ -1,0 +1,158 @@
+"""fetch_kv_small, compiled for the CPU and run lane by lane (tests/emulate/small_fetch.cpp), while the directory changes under it.
+Every workgroup reads the directory for itself, each at times of its own: whatever mixture of older and younger entries they meet, every
+byte of the destination has to be there - of the blocks that are edited and of those that are not."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+pytestmark = pytest.mark.skipif(shutil.which(CLANG) is None, reason="needs clang's vector extensions")
+HOST, CACHE, LOCAL = 0, 1, 2
+NEVER = 1 << 30
+u32, u64, vp = ctypes.c_uint32, ctypes.c_uint64, ctypes.c_void_p
+
+
+class Fetch(ctypes.Structure):
+    _fields_ = [(n, u32) for n in ("n_planes", "nthr", "head_major", "n_layers", "n_objects", "n_seq", "max_blocks", "n_host", "lg_groups", "seen",
+                                   "n_versions", "n_heads", "block_tokens", "n_slots")]
+    _fields_ += [("chunk_bytes", u64), ("dst_cap", u64), ("dst_step", u64), ("pool", u64 * 2 * 3), ("dst", u64 * 2)]
+    _fields_ += [(n, vp) for n in ("table", "n_blocks", "seq_dst", "seq_cap", "versions", "when", "cnt", "miss")]
+
+
+@pytest.fixture(scope="module")
+def emulated(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("emulate") / "libsmall_fetch.so")
+    here = os.path.join(ROOT, "tests", "emulate")
+    subprocess.check_call([CLANG, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", here, "-I", os.path.join(ROOT, "paper_2602_00328_amd", "csrc"),
+                           "-o", so, os.path.join(here, "small_fetch.cpp")])
+    return ctypes.CDLL(so)
+
+
+def aligned(shape, dtype=np.uint8):
+    n = int(np.prod(shape)) * np.dtype(dtype).itemsize
+    raw = np.zeros(n + 64, dtype=np.uint8)
+    at = -raw.ctypes.data % 64
+    return raw[at:at + n].view(dtype).reshape(shape)
+
+
+def entry(tier, slot, edit):
+    return np.uint64(int(tier) | int(slot) << 2 | (int(edit) & 0xFFFFFFFF) << 32)
+
+
+class Case:
+    """Objects have one slot number in every tier, which all hold the same bytes; `tiers[v]` are their tiers in version v."""
+
+    def __init__(self, lib, rng, lens, width, chunk, n_planes=2, nthr=256, head_major=False, n_layers=1, n_host=32, lg=0, heads=(2, 1)):
+        self.lib, self.rng, self.n_layers, self.n_planes = lib, rng, n_layers, n_planes
+        self.n_objects = n = len(lens) * width
+        f = self.f = Fetch(n_planes=n_planes, nthr=nthr, head_major=head_major, n_layers=n_layers, n_objects=n, n_seq=len(lens), max_blocks=width,
+                           n_host=n_host, lg_groups=lg, seen=7, n_heads=heads[0], block_tokens=heads[1], n_slots=n, chunk_bytes=chunk)
+        self.cap = sum(lens)
+        f.dst_cap, f.dst_step = self.cap, self.cap * chunk
+        self.payload = aligned((n_planes, n_layers, n, chunk))
+        self.payload[:] = rng.integers(0, 256, self.payload.shape, dtype=np.uint8)
+        self.pools = [[aligned(self.payload.shape[1:]) for _ in range(n_planes)] for _ in range(3)]
+        for t in range(3):
+            for p in range(n_planes):
+                self.pools[t][p][:] = self.payload[p]
+                f.pool[t][p] = self.pools[t][p].ctypes.data
+        self.table = np.arange(n, dtype=np.int32)
+        rng.shuffle(self.table)
+        self.n_blocks = np.array(lens, dtype=np.int32)
+        self.first = np.cumsum([0] + list(lens[:-1])).astype(np.uint64)
+        self.caps = np.array(lens, dtype=np.uint32)
+        self.cells = np.concatenate([np.arange(k) + s * width for s, k in enumerate(lens)])
+        f.table, f.n_blocks, f.seq_dst, f.seq_cap = (x.ctypes.data for x in (self.table, self.n_blocks, self.first, self.caps))
+        self.heads = heads
+
+    def run(self, tiers, when=None):
+        f, n = self.f, self.n_objects
+        versions = np.empty((len(tiers), n), dtype=np.uint64)
+        for v, tier in enumerate(tiers):
+            for i in range(n):
+                versions[v, i] = entry(tier[i], i, 3) if v == 0 else (versions[v - 1, i] if tier[i] == tiers[v - 1][i] else entry(tier[i], i, 7 + v))
+        tiles = -(-f.chunk_bytes // (f.nthr * 16)) * n * f.n_planes * f.n_layers
+        n_wgs = f.n_host + 1 + int(tiles)
+        if when is None:                      # every workgroup at its own time, most of them within the walk
+            when = self.rng.choice([0, 1, 2, 3, 4, 5, 7, 9, NEVER], (n_wgs, len(tiers) - 1))
+        when = np.ascontiguousarray(np.sort(np.broadcast_to(when, (n_wgs, len(tiers) - 1)), axis=1), dtype=np.uint32)
+        dst = [aligned((self.n_layers, self.cap, f.chunk_bytes)) for _ in range(f.n_planes)]
+        cnt, miss = np.zeros(16, dtype=np.uint32), np.zeros(n, dtype=np.uint32)
+        f.n_versions, f.versions, f.when, f.cnt, f.miss = len(tiers), versions.ctypes.data, when.ctypes.data, cnt.ctypes.data, miss.ctypes.data
+        for p in range(f.n_planes):
+            f.dst[p] = dst[p].ctypes.data
+        self.lib.run_fetch(ctypes.byref(f))
+        for p in range(f.n_planes):
+            want = self.payload[p][:, self.table[self.cells]]
+            got = dst[p]
+            if f.head_major:
+                h, t = self.heads
+                want = want[0].reshape(self.cap, t, h, -1)
+                want = np.concatenate([want[a:a + k].reshape(k * t, h, -1).transpose(1, 0, 2).reshape(-1) for a, k in zip(self.first.astype(int), self.caps)])
+                got = got.reshape(-1)
+                assert np.array_equal(got, want), f"plane {p}: {np.count_nonzero(got != want)} bytes missing"
+                continue
+            wrong = (got != want).any(axis=2)
+            assert not wrong.any(), f"plane {p}: {wrong.sum()} of {wrong.size} chunks are not whole"
+        return cnt, miss
+
+
+SHAPES = [         # threads, planes, layers, chunk, lengths, width, workgroups at the host, shares (log2)
+    (256, 2, 1, 8192, [300, 280], 300, 32, 1),
+    (256, 2, 1, 32768, [60, 70], 140, 32, 0),
+    (256, 2, 1, 4096 + 16, [513], 513, 7, 0),
+    (256, 1, 1, 4096, [512, 90], 512, 25, 2),
+    (256, 1, 3, 16384, [140], 140, 32, 0),
+    (256, 2, 2, 12288, [130, 1], 200, 25, 2),
+    (64, 2, 1, 1024, [128], 128, 128, 0),
+    (64, 1, 5, 2048 + 16, [17, 30], 40, 7, 0),
+    (64, 2, 3, 3072, [20], 20, 1, 0),
+]
+
+
+@pytest.mark.parametrize("edit", ["revoked", "placed", "placed and revoked"])
+@pytest.mark.parametrize("nthr,n_planes,n_layers,chunk,lens,width,n_host,lg", SHAPES)
+def test_every_block_is_whole_when_entries_change_under_the_fetch(emulated, edit, nthr, n_planes, n_layers, chunk, lens, width, n_host, lg):
+    rng = np.random.default_rng(n_host * 100 + lg * 10 + len(edit))
+    c = Case(emulated, rng, lens, width, chunk, n_planes, nthr, n_layers=n_layers, n_host=n_host, lg=lg)
+    tier = rng.choice([HOST, CACHE, LOCAL], c.n_objects, p=[0.4, 0.5, 0.1])
+    for how_many in (1, 20):
+        tiers = [tier]
+        if edit == "revoked":
+            tiers.append(tier.copy())
+            tiers[1][rng.permutation(np.flatnonzero(tier == CACHE))[:how_many]] = HOST
+        else:
+            moved = rng.permutation(np.flatnonzero(tier == HOST))[:how_many]
+            tiers.append(tier.copy())
+            tiers[1][moved] = CACHE
+            if edit != "placed":
+                tiers.append(tiers[1].copy())
+                tiers[2][moved[::2]] = HOST
+        c.run(tiers)
+
+
+@pytest.mark.parametrize("n_planes,nthr,heads,lens,width", [(2, 256, (8, 16), [300, 250], 300), (1, 256, (3, 5), [400], 400), (2, 64, (2, 4), [60, 61], 64)])
+@pytest.mark.parametrize("edit", ["revoked", "placed"])
+def test_every_head_major_block_is_whole_when_entries_change_under_the_fetch(emulated, edit, n_planes, nthr, heads, lens, width):
+    rng = np.random.default_rng(3)
+    c = Case(emulated, rng, lens, width, heads[0] * heads[1] * 48, n_planes, nthr, head_major=True, n_host=9, lg=1 if nthr == 256 else 0, heads=heads)
+    tier = rng.choice([HOST, CACHE, LOCAL], c.n_objects, p=[0.4, 0.5, 0.1])
+    after = tier.copy()
+    after[rng.permutation(np.flatnonzero(tier == (CACHE if edit == "revoked" else HOST)))[:9]] = HOST if edit == "revoked" else CACHE
+    c.run([tier, after])
+
+
+def test_counters_and_misses_of_a_directory_that_holds_still(emulated):
+    rng = np.random.default_rng(5)
+    for nthr, lens, width, lg in ((256, [513, 300], 600, 1), (64, [40, 50], 64, 0)):
+        c = Case(emulated, rng, lens, width, 1040, 2, nthr, n_layers=2, n_host=24, lg=lg)
+        tier = rng.choice([HOST, CACHE, LOCAL], c.n_objects, p=[0.4, 0.5, 0.1])
+        cnt, miss = c.run([tier])
+        asked = tier[c.table[c.cells]]
+        assert cnt[:6].tolist() == [len(asked), (asked == LOCAL).sum(), (asked == CACHE).sum(), (asked == HOST).sum(), 0, 0]
+        assert miss[:(asked == HOST).sum()].tolist() == c.cells[asked == HOST].tolist()
