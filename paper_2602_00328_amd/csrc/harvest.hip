@@ -481,6 +481,17 @@ bool is_capturing(hipStream_t s)
     return st != hipStreamCaptureStatusNone;
 }
 
+// Whether the work that the event stands for has ended.  Asked in relaxed mode: while any stream is being recorded in global mode, the
+// default, the query would be refused, and the recording invalidated.
+hipError_t event_status(hipEvent_t e)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t q = hipEventQuery(e);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return q;
+}
+
 // Latest-work events only answer whether a kernel has ended: they are recorded behind every fetch and carry no system-scope fence
 // (recorded behind a 10 us kernel such an event makes the next one wait 1.0 us, with the fence 2.9 us).  The revocation that waits
 // for them makes up for it once, see system_release.
@@ -632,7 +643,7 @@ int acquire_staging(harvest_ctx *ctx, size_t bytes, Staging **out)
     for (auto &st : ctx->staging) {
         if (st.cap < bytes || st.held) continue;
         if (st.busy) {
-            hipError_t q = hipEventQuery(st.done);
+            hipError_t q = event_status(st.done);
             if (q == hipErrorNotReady) continue;
             if (q != hipSuccess) return HARVEST_EHIP;
             st.busy = false;
@@ -749,7 +760,7 @@ int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, h
     // takes (a placement of some hundred MiB: milliseconds), and a caller stream that HIP happens to map to the same
     // queue stands still meanwhile.  (Not onto a stream that is being recorded into a graph: then the control stream waits.)
     if (on == ctx->ctl && c.edit_seq && c.edit_stream != ctx->ctl && !ctx->no_device && !is_capturing(c.edit_stream)) {
-        hipError_t q = hipEventQuery(c.edit_evt);
+        hipError_t q = event_status(c.edit_evt);
         if (q == hipErrorNotReady) on = c.edit_stream;
         else if (q != hipSuccess) HIP_TRY(q);
     }
@@ -795,7 +806,7 @@ int order_after_directory_edits(harvest_ctx *ctx, StreamState *ss, int cls)
     if (seen == c.edit_seq || is_capturing(ss->s)) return HARVEST_OK;
     if (c.edit_stream != ss->s) {
         if (seen < c.must_seq) HIP_TRY(hipStreamWaitEvent(ss->s, c.edit_evt, 0));
-        else if (cls != HARVEST_KV || hipEventQuery(c.edit_evt) != hipSuccess) return HARVEST_OK;
+        else if (cls != HARVEST_KV || event_status(c.edit_evt) != hipSuccess) return HARVEST_OK;
     }
     seen = c.edit_seq;
     return HARVEST_OK;

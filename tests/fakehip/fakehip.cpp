@@ -12,6 +12,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 namespace {
@@ -24,6 +25,8 @@ std::vector<unsigned char> g_symbol_store;
 std::map<const void *, std::string> &kernels() { static std::map<const void *, std::string> m; return m; }
 std::map<const void *, size_t> &symbols() { static std::map<const void *, size_t> m; return m; }
 const void *g_capturing = nullptr;
+hipStreamCaptureMode g_mode = hipStreamCaptureModeGlobal;
+bool g_not_ready = false;
 struct Config { dim3 grid, block; size_t shared; hipStream_t s; };
 std::vector<Config> g_config;
 
@@ -65,6 +68,7 @@ const char *fake_log()                                   // the log since the la
 void fake_fail(const char *call, int nth) { g_fail_call = call; g_fail_nth = nth; }      // the nth such call from now on; 0: none
 int fake_fail_pending() { return g_fail_nth > 0; }
 void fake_capture(const void *stream) { g_capturing = stream; }                         // null: nothing is being recorded
+void fake_not_ready(int yes) { g_not_ready = yes; }                                     // what events answer from now on
 void *fake_stream() { return new Handle{ ++g_streams, 0 }; }
 int fake_number(const void *handle) { return number_of(handle); }
 void *fake_pinned(size_t bytes, size_t nth) { return nth < g_pinned[bytes].size() ? g_pinned[bytes][nth] : nullptr; }
@@ -193,7 +197,17 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
         ((Handle *)e)->flags & hipEventDisableSystemFence ? " no-system-fence" : "");
     return outcome("hipEventRecord");
 }
-hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *mode)
+{
+    std::swap(*mode, g_mode);
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e)
+{
+    say("hipEventQuery event %d%s", number_of(e), g_mode == hipStreamCaptureModeRelaxed ? " relaxed" : "");
+    if (g_capturing && g_mode != hipStreamCaptureModeRelaxed) return g_last = hipErrorStreamCaptureUnsupported;
+    return g_not_ready ? hipErrorNotReady : hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t e)
 {
     say("hipEventSynchronize event %d%s", number_of(e), ((Handle *)e)->flags & hipEventDisableSystemFence ? " no-system-fence" : "");

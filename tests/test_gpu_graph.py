@@ -133,3 +133,50 @@ def test_captured_expert_fetch_follows_residency_changes_across_replays():
         replay_and_check("replay 4 (unchanged)")
     finally:
         eh.close(); eo.close()
+
+
+@pytest.mark.parametrize("pending", [False, True])
+def test_a_fetch_on_another_stream_leaves_a_recording_alone(pending):
+    """While one stream is being recorded (global mode, the default), a second one fetches and a third has placed blocks, which may
+    or may not have arrived: neither the fetch nor the recording fails, and the replay delivers."""
+    from paper_2602_00328_amd import binding as B
+    n, chunk = 96, 4096
+    rng = np.random.default_rng(1)
+    payload = rng.integers(0, 256, (2, n, chunk), dtype=np.uint8)
+    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n, n_host_slots=n, n_cache_slots=n, n_local_slots=0))
+    for p in range(2):
+        h.host_plane(B.KV, p)[0] = payload[p]
+    ids = h.register(B.KV, n, np.arange(n))
+    table = torch.from_numpy(rng.permutation(n).astype(np.int32)).cuda().reshape(1, n)
+    n_blocks, first = torch.tensor([n], dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")
+    bufs = [[torch.zeros(n * chunk, dtype=torch.uint8, device="cuda") for _ in range(2)] for _ in range(2)]
+    recorded, eager, placing = (torch.cuda.Stream() for _ in range(3))
+
+    def fetch(stream, k, v):
+        with torch.cuda.stream(stream):
+            h.fetch_kv(0, table, n_blocks, k, v, first, n)
+
+    for s in (recorded, eager, placing):
+        fetch(s, *bufs[0])
+    h.place(B.KV, ids[:8], stream=placing)
+    torch.cuda.synchronize()
+    if pending:
+        with torch.cuda.stream(placing):
+            torch.cuda._sleep(20_000_000)
+    h.place(B.KV, ids[8:16], stream=placing)
+    if not pending:
+        torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=recorded, capture_error_mode="global"):
+        fetch(recorded, *bufs[0])
+        fetch(eager, *bufs[1])
+    for _ in range(2):
+        torch.cuda.synchronize()
+        [b.zero_() for b in bufs[0]]
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for pair in bufs:
+            for p, b in enumerate(pair):
+                assert np.array_equal(b.cpu().numpy().reshape(n, chunk), payload[p][table.cpu().numpy()[0]])
+    h.close()

@@ -351,3 +351,23 @@ def test_the_one_kernel_fetch_knows_the_edits_it_comes_after(fake):
         log = fake.fake_log().decode().splitlines()
         assert bool(launches(log, "classify_kv")) == lossy and bool(launches(log, "fetch_kv_small")) != lossy, log
     assert fake.harvest_destroy(h) == B.OK
+
+
+def test_a_fetch_beside_another_streams_placement_and_recording(fake):
+    """Whether the placement is through is asked so that it disturbs no recording on another stream; while it is not, the kernel in
+    front of the one-kernel fetch asks the device which edits are complete."""
+    c = Ctx(fake)
+    other = fake.fake_stream()
+    fetch = lambda s: fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 8, POOL, POOL, POOL, 8, s)
+    assert fetch(other) == B.OK and fetch(c.stream) == B.OK and c.place([1, 2]) == B.OK
+    fake.fake_capture(c.stream)
+    for pending in (True, False):
+        fake.fake_not_ready(pending)
+        c.log()
+        assert fetch(other) == B.OK
+        log = c.log()
+        assert len(launches(log, "snap_edit")) == pending and len(launches(log, "fetch_kv_small")) == 1, log
+        assert [line.split()[-1] for line in log if line.startswith("hipEventQuery")] == ["relaxed"], log
+    fake.fake_capture(None)
+    fake.fake_not_ready(False)
+    c.close()
