@@ -1771,49 +1771,62 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     }
     if (!ctx->general_fetch && !c.n_lossy && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
         total * tpc * n_layers <= (1ull << 31) && dead_tiles <= DEAD_TILES) {
-        GatherArgs ga{};
+        SmallArgs ga{};
+        SmallWalk gw{};
         const ClassDev cd = class_dev(c);
-        for (uint32_t p = 0; p < 2; ++p) {
-            ga.src_base[T_HOST][p] = cd.pool[T_HOST][p];
-            ga.src_base[T_CACHE][p] = cd.pool[T_CACHE][p];
-            ga.src_base[T_LOCAL][p] = cd.pool[T_LOCAL][p];
-        }
-        for (int t = 0; t < 3; ++t) ga.layer_stride[t] = cd.layer_stride[t];
+        ga.dst_cap = dst_capacity_blocks;
+        ga.dir = cd.dir;
+        ga.chunk_bytes = cd.chunk_bytes;
+        ga.max_blocks = max_blocks; ga.n_objects = cd.n_objects; ga.n_rep = n_layers;
         ga.dst_base[0] = (uint64_t)d_dst_k; ga.dst_base[1] = (uint64_t)d_dst_v;
-        ga.dst_step = dst_layer_stride; ga.n_rep = n_layers;
-        ga.chunk_bytes = c.cfg.chunk_bytes;
-        ga.seen = (uint32_t)ss->seen_seq[HARVEST_KV];
+        ga.dst_step = dst_layer_stride;
+        auto tier = [&](int t) {
+            return SmallTier{ { cd.pool[t][0] + layer * cd.layer_stride[t], cd.pool[t][1] + layer * cd.layer_stride[t] }, cd.layer_stride[t], cd.slot_stride[t] };
+        };
+        ga.cache = tier(T_CACHE); ga.local = tier(T_LOCAL); gw.host = tier(T_HOST);
+        ga.n_cache_slots = cd.n_slots[T_CACHE]; ga.n_local_slots = cd.n_slots[T_LOCAL]; gw.n_host_slots = cd.n_slots[T_HOST];
+        gw.total = (uint32_t)total;
+        gw.seen = (uint32_t)ss->seen_seq[HARVEST_KV];
         // Replays come after other edits than this call.  And while another stream is placing blocks, which of its edits are complete
         // is asked on the device, or all that it has placed since `seen` would be copied twice (600 blocks beside a stream of placements:
         // 40 us; 33 when a fetch could lose blocks under them).
         if (recording || ss->seen_seq[HARVEST_KV] != c.edit_seq) {
-            ga.snap = ss->snap;
+            gw.snap = ss->snap;
             if ((rc = launch(ss->s, snap_edit, dim3(1), dim3(1), (const uint32_t *)c.d_done, ss->snap))) return rc;
         }
         const uint32_t nthr = total <= 64 * ROUND ? 64 : WG;
         ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16);
-        // A third more reads of the host in flight than in the general path, where the tables are not tiny: the tile workgroups keep
-        // the host's waiting at the compute units.  1 of 32 blocks on the host: 2 877 cells of 2 x 16 KiB 37.7 us against 38.9, 4 000
-        // of 2 x 32 KiB 146.4 against 148.2; 1 of 100: 89.7 against 89.1; 4 of 10 (1 600 KiB of them or more): the same.
-        ga.n_host = c.cfg.n_host_slots ? host_workgroups(ctx, nthr) * 4 / 3 : 0;
+        // A third more reads of the host in flight than in the general path: the tile workgroups
+        // keep the host's waiting at the compute units, and members of a group whose number divides the pieces of a cell have even shares.
+        // 24 / 32 / 40 workgroups of 256 threads: 256 cells, 102 on the host 124.5 / 123.1 / 124.2 us; 2 000 of 2 x 16 KiB, 300 184.9 /
+        // 178.8 / 179.4; 1 750, 52 41.8 / 37.4-38.6 / 37.4; 4 000 of 2 x 32 KiB, 120 149.2 / 145.8 / 145.6; 3 000, 30 66.3 / 66.7 / 68.0.
+        // Single wavefronts have four loads each: 60 cells, 6 on the host, 12.7 us with 64 of them (two loads: 12.7; 96 or 128 of them
+        // 13.1); 128 cells, all on the host 152.9 (153.4; 153.7-153.8); 32 layers of 5 blocks, one on the host 42.8 (43.3; 43.0).
+        const uint32_t host_wgs = host_workgroups(ctx, nthr, nthr == 64 ? 4 : 2);
+        ga.n_host = c.cfg.n_host_slots ? host_wgs * 4 / 3 : 0;
         // the walk for the host's cells is shared out, see fetch_kv_small: not when it takes a single round, and to groups of at least
         // 12 workgroups - what a group finds is read by its own workgroups only, and with 4 to a group (2 877 cells, 52 on the
         // host) the groups that had found less left the link to the others for so long that 37.7 us became 39.4
-        while (ga.n_host >> ga.host_lg_groups >= 24 && total > (uint64_t)nthr * ROUND << ga.host_lg_groups) ga.host_lg_groups++;
-        deal_out_host_pieces(ga, c.cfg.n_planes, nthr);
+        while (ga.n_host >> gw.host_lg_groups >= 24 && total > (uint64_t)nthr * ROUND << gw.host_lg_groups) gw.host_lg_groups++;
+        deal_out_host_pieces(ga, gw, c.cfg.n_planes, nthr);
         ga.hbm_wgs = (uint32_t)total * ga.tiles_per_chunk;
-        SmallBooks books{ lists.miss, cnt, info, ctx->d_totals + HARVEST_KV * C_N, ss->d_feedback + HARVEST_KV,
-                          c.cfg.n_host_slots ? ctx->d_lease : (unsigned long long *)nullptr, n_seq };
+        gw.n_seq = n_seq;
+        gw.miss_idx = lists.miss; gw.cnt = cnt; gw.info = info;
+        gw.totals = ctx->d_totals + HARVEST_KV * C_N;
+        gw.report = ss->d_feedback + HARVEST_KV;
+        gw.lease = c.cfg.n_host_slots ? ctx->d_lease : nullptr;
         const uint32_t head = ga.n_host + 1;
         const dim3 grid(n_layers > 1 ? std::max(ga.hbm_wgs, head) : ga.hbm_wgs + head, c.cfg.n_planes, n_layers > 1 ? n_layers + 1 : 1);
-        auto of = [&](auto with_hm) {
+        auto run = [&](auto with_hm, const auto &h) {
             constexpr bool HM = decltype(with_hm)::value;
-            return c.cfg.n_planes == 2 ? (nthr == 64 ? fetch_kv_small<2, 64, HM> : fetch_kv_small<2, WG, HM>)
-                                       : (nthr == 64 ? fetch_kv_small<1, 64, HM> : fetch_kv_small<1, WG, HM>);
+            auto kernel = c.cfg.n_planes == 2 ? (nthr == 64 ? fetch_kv_small<2, 64, HM> : fetch_kv_small<2, WG, HM>)
+                                              : (nthr == 64 ? fetch_kv_small<1, 64, HM> : fetch_kv_small<1, WG, HM>);
+            return launch_last(ctx, ss, recording, kernel, grid, dim3(nthr), d_block_table, d_n_blocks, d_seq_dst_block, ga, gw, h);
         };
-        auto kernel = head_major ? of(std::true_type{}) : of(std::false_type{});
-        if ((rc = launch_last(ctx, ss, recording, kernel, grid, dim3(nthr), cd, layer, d_block_table, d_n_blocks, (uint32_t)total, max_blocks,
-                              d_seq_dst_block, dst_capacity_blocks, ga, books, hm, d_seq_cap_blocks)))
+        SmallHm<true> h;
+        static_cast<HmArgs &>(h) = hm;
+        h.seq_cap_blocks = d_seq_cap_blocks;
+        if ((rc = head_major ? run(std::true_type{}, h) : run(std::false_type{}, SmallHm<false>{})))
             return rc;
         ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
         ss->feedback_valid[HARVEST_KV] = true;

@@ -128,12 +128,6 @@ struct GatherArgs {
     uint32_t n_host, hbm_wgs;
     uint32_t pages_per_chunk;            // of the host tier, see host_tier
     uint32_t host_loads;                 // 2 or HOST_PAGE: loads a thread of the host tier keeps in flight
-    uint32_t seen;                       // of fetch_kv_small: the latest directory edit that it comes after, or where that is kept
-    const uint32_t *snap;
-    uint32_t host_lg_groups;             // of fetch_kv_small: the walk for the host's cells is cut into 1 << host_lg_groups shares
-    uint32_t host_lg_run;                // ... and what a workgroup reads of a cell at a time is 1 << host_lg_run KiB, a piece:
-    uint32_t host_ppc, host_pieces;      // this many to a plane and layer, to a cell
-    uint32_t host_per_cell, host_starts, host_step;      // at most so many are a workgroup's; see first_piece
 };
 // In pinned memory, one per class and stream: requests of either tier of the latest fetch whose kernels have run - hints for the
 // next launch - and the rows and columns of the block table they were asked for with (experts: zero).
@@ -151,16 +145,10 @@ __device__ inline uint32_t lane_id() { return __lane_id(); }
 // A value that all lanes of the wavefront have, for the scalar registers.
 __device__ inline uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ inline uint64_t uniform(uint64_t x) { return (uint64_t)uniform((uint32_t)(x >> 32)) << 32 | uniform((uint32_t)x); }
-// Selects instead of indexing: a variable index into a kernel-argument struct would send it to scratch memory.  Of values that are in
-// registers: a select between two arguments becomes a load through a selected address, by every lane for itself.
-template <typename T> __device__ inline T of_tier(int tier, T host, T cache, T local)
-{
-    host = uniform(host); cache = uniform(cache); local = uniform(local);
-    return tier == T_HOST ? host : (tier == T_CACHE ? cache : local);
-}
+// Selects instead of indexing: a variable index into a kernel-argument struct would send it to scratch memory.
 __device__ inline uint32_t slots_of(const ClassDev &c, int tier)
 {
-    return of_tier(tier, c.n_slots[T_HOST], c.n_slots[T_CACHE], c.n_slots[T_LOCAL]);
+    return tier == T_HOST ? c.n_slots[T_HOST] : (tier == T_CACHE ? c.n_slots[T_CACHE] : c.n_slots[T_LOCAL]);
 }
 __device__ inline uint64_t chunk_offset(const ClassDev &c, int tier, uint32_t layer, uint32_t slot)
 {
@@ -188,11 +176,10 @@ __device__ inline uint32_t wave_rank(bool pred, uint32_t &total)
     return (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull));
 }
 
-
-// The value that lane k of the wavefront has, k the same in all of them (and, at the end of a pair, one too many: that of lane 0 then).
-__device__ inline uint32_t lane_value(uint32_t x, uint32_t k) { return __builtin_amdgcn_readlane(x, k & 63); }
+// The value that lane k of the wavefront has, k the same in all of them.
+__device__ inline uint32_t lane_value(uint32_t x, uint32_t k) { return __builtin_amdgcn_readlane(x, k); }
 __device__ inline uint64_t lane_value(uint64_t x, uint32_t k) { return (uint64_t)lane_value((uint32_t)(x >> 32), k) << 32 | lane_value((uint32_t)x, k); }
-__device__ inline uint32_t min64(uint32_t x) { return x < 64 ? x : 64; }
+template <uint32_t N> struct Count { static constexpr uint32_t value = N; };
 
 __device__ inline uint32_t wave_sum(uint32_t v)
 {
@@ -776,12 +763,12 @@ struct HmArgs {
 //
 //   the first n_host  walk the table, list the host's cells in LDS and read them over PCIe, all planes and layers, two loads in
 //                     flight per thread (see host_tier for why so few): 102 of 256 blocks of 2 x 32 KiB from the host take
-//                     123.6 us, the call.  When every host tile was read at once, by a workgroup of its own, 6.7 MB of reads queued
+//                     123.0 us, the call.  When every host tile was read at once, by a workgroup of its own, 6.7 MB of reads queued
 //                     on the link together: 134 us.
 //                     A table that takes several rounds to walk is shared out: workgroup b belongs to group b modulo their number, and a
 //                     group walks its own share of the cells (shared_cell) and reads what it finds.  A round of a walk
 //                     costs its workgroup a microsecond of waits in which it reads nothing: 2 877 cells of 2 x 16 KiB, 52 of them
-//                     on the host, take 38.1-38.5 us in two groups and took 39.5-40.9 when every workgroup walked all six rounds.
+//                     on the host, take 37.4-38.3 us in two groups and took 39.5-40.9 when every workgroup walked all six rounds.
 //   the next one      walks the table too and keeps the books: counters, and the miss list in request order.  No atomics on
 //                     shared counters (a thousand of them on one address take longer than the copy), nothing to zero.
 //   the others        copy a tile of 16 bytes a thread if their cell's block is in HBM: nothing is compacted, so the grid covers the padded
@@ -806,13 +793,40 @@ struct HmArgs {
 // A walk goes ROUND * WG cells at a time; the next round's row lengths, block numbers and destinations are on their way while
 // this one's directory entries are, so a round costs one memory latency, not two.  The code of the walk is kept short on
 // purpose: it runs once, and one wavefront doing the books with everything unrolled took 7 us for a table of 8 cells.
-struct SmallBooks {
-    uint32_t *miss_idx, *cnt, *info;     // info may be null
+struct SmallTier { uint64_t base[2], layer_stride, slot_stride; };     // [plane], at the fetch's first layer
+// What every workgroup is told ...
+struct SmallArgs {
+    uint64_t dst_cap;
+    const uint64_t *dir;
+    uint64_t chunk_bytes;
+    uint32_t max_blocks, n_objects, n_rep, tiles_per_chunk, n_host, hbm_wgs;
+    uint32_t n_cache_slots, n_local_slots;
+    uint64_t dst_base[2], dst_step;      // [plane]; from one layer to the next
+    SmallTier cache, local;
+};
+// ... and what only those need that walk the table, and tiles of blocks that are just changing.  They read it where they need it: as
+// an ordinary argument all of it would be loaded at the start of the kernel and spilled to be out of the way (23 to 34 registers are
+// spilled in the token-major forms, two of them by a tile's workgroup; 57 to 100, 38 of them there, in one argument: 16 blocks of 32 layers 15.7 us
+// instead of 14.1, 300 blocks 10.8 instead of 9.7).
+struct SmallWalk {
+    SmallTier host;
+    uint32_t n_host_slots, total;
+    uint32_t n_seq, seen;                // the latest directory edit that the fetch comes after ...
+    const uint32_t *snap;                // ... or where that is kept
+    // the host's readers: the walk for the host's cells is cut into 1 << host_lg_groups shares, and what a workgroup reads of a cell at a
+    // time is 1 << host_lg_run KiB, a piece: this many to a plane and layer, to a cell; of a cell at most so many are a workgroup's;
+    // see first_piece
+    uint32_t host_lg_groups, host_lg_run, host_ppc, host_pieces, host_per_cell, host_starts, host_step, pad;
+    uint32_t *miss_idx, *cnt, *info;     // the books; info may be null
     unsigned long long *totals;
     Report *report;
     unsigned long long *lease;
-    uint32_t n_seq;
 };
+typedef const __attribute__((address_space(4))) SmallWalk k_SmallWalk;
+constexpr uint32_t SMALL_WALK_AT = 3 * sizeof(void *) + sizeof(SmallArgs);      // among the kernel's arguments
+static_assert(sizeof(SmallArgs) % 8 == 0, "SmallWalk follows in the kernel's arguments");
+template <bool HM> struct SmallHm { __device__ uint64_t by_source(uint32_t, uint64_t) const { return 0; } };
+template <> struct SmallHm<true> : HmArgs { const uint32_t *seq_cap_blocks; };
 
 constexpr uint32_t ROUND = 2;            // cells a thread looks up at a time when a workgroup walks the table
 constexpr uint64_t SRC_MASK = 0x0000FFFFFFFFFFFCull;      // of a record's source: without tier and capacity
@@ -835,81 +849,92 @@ __host__ __device__ inline uint32_t first_piece(uint32_t i, uint32_t member, uin
 }
 
 // The numbers that follow from n_host, host_lg_groups, chunk_bytes and n_rep.  A piece is 4 KiB, a page of host memory, which the four
-// wavefronts of a workgroup read side by side, or half or a quarter of that where a cell would not have one for every member otherwise.
-// Members whose loads are uneven leave the link idle at the end: 52 blocks of 2 x 16 KiB among 2 877 cells 38.1 us (4 KiB in any case:
-// 38.1-39.8), 102 of 256 blocks of 2 x 32 KiB 123.6 (124.0), 300 of 2 000 of 2 x 16 KiB 178.9 (179.7).
-inline void deal_out_host_pieces(GatherArgs &a, uint32_t n_planes, uint32_t nthr)
+// wavefronts of a workgroup read side by side, or half or a quarter of that where a cell would not have one for every member otherwise:
+// members whose loads are uneven leave the link idle at the end (102 of 256 blocks of 2 x 32 KiB from the host 123.6 us, 124.0 with 4 KiB
+// in any case; 300 of 2 000 of 2 x 16 KiB 178.9 and 179.7).
+inline void deal_out_host_pieces(SmallArgs &a, SmallWalk &w, uint32_t n_planes, uint32_t nthr)
 {
-    a.n_host &= ~((1u << a.host_lg_groups) - 1u);                // groups of the same size
-    const uint32_t members = a.n_host >> a.host_lg_groups;
+    a.n_host &= ~((1u << w.host_lg_groups) - 1u);                // groups of the same size
+    const uint32_t members = a.n_host >> w.host_lg_groups;
     auto cut = [&](uint32_t lg_run) {
-        a.host_lg_run = lg_run;
-        a.host_ppc = (uint32_t)((a.chunk_bytes + (1024ull << lg_run) - 1) >> (10 + lg_run));
-        a.host_pieces = a.host_ppc * n_planes * a.n_rep;
+        w.host_lg_run = lg_run;
+        w.host_ppc = (uint32_t)((a.chunk_bytes + (1024ull << lg_run) - 1) >> (10 + lg_run));
+        w.host_pieces = w.host_ppc * n_planes * a.n_rep;
     };
     cut(nthr == 64 ? 0 : 2);
-    while (a.host_lg_run && a.host_pieces < members) cut(a.host_lg_run - 1);
+    while (w.host_lg_run && w.host_pieces < members) cut(w.host_lg_run - 1);
     if (!members) return;
-    a.host_per_cell = (a.host_pieces + members - 1) / members;
-    const bool in_runs = members % a.host_pieces == 0;
-    a.host_starts = in_runs ? members / a.host_pieces : members;
-    a.host_step = in_runs ? a.host_pieces : 1;
+    w.host_per_cell = (w.host_pieces + members - 1) / members;
+    const bool in_runs = members % w.host_pieces == 0;
+    w.host_starts = in_runs ? members / w.host_pieces : members;
+    w.host_step = in_runs ? w.host_pieces : 1;
+}
+
+// These values are in registers from here on.  An argument is loaded where it is used, and every such load is a wait; a tile's workgroup
+// has to wait for its directory entry anyway and gets its addresses meanwhile (300 blocks 9.77 us without, 9.69 with).
+template <typename A, typename B, typename C, typename D> __device__ inline void in_registers(A a, B b, C c, D d)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
+#endif
 }
 
 template <int PLANES, int NTHR, bool HM>
-__global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t layer, const int32_t *__restrict__ table,
-                                                        const int32_t *__restrict__ n_blocks, uint32_t total,
-                                                        uint32_t max_blocks, const uint64_t *__restrict__ seq_dst_block,
-                                                        uint64_t dst_cap, GatherArgs a, SmallBooks books, HmArgs h,
-                                                        const uint32_t *__restrict__ seq_cap_blocks)
+__global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restrict__ table, const int32_t *__restrict__ n_blocks,
+                                                        const uint64_t *__restrict__ seq_dst_block, SmallArgs a, SmallWalk, SmallHm<HM> h)
 {
-    const uint32_t tpc = a.tiles_per_chunk, tid = threadIdx.x;
+    k_SmallWalk &w = *(k_SmallWalk *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + SMALL_WALK_AT);
+    const uint32_t tpc = a.tiles_per_chunk, tid = threadIdx.x, max_blocks = a.max_blocks;
     // several layers: blockIdx.z == 0 is a slice of its own for the head workgroups, not n_host + 1 idle ones in every layer
     const bool sliced = a.n_rep > 1, head = sliced ? blockIdx.z == 0 : blockIdx.x <= a.n_host;
     if (!head) {
         const uint32_t t = sliced ? blockIdx.x : blockIdx.x - a.n_host - 1, z = sliced ? blockIdx.z - 1 : 0;
-        if (sliced && t >= a.hbm_wgs) return;                      // (the head slice is the wider one)
+        if (t >= a.hbm_wgs) return;                                // (several layers, and the head slice is the wider one)
         const uint32_t r = t / tpc, k = t - r * tpc, plane = blockIdx.y;
         const uint32_t s = r / max_blocks, j = r - s * max_blocks;
-        const int32_t nb = n_blocks[s], b = table[r];              // as resolve_cell, but out at the first answer
+        const int32_t nb = n_blocks[s], b = table[r];
         const uint64_t first = seq_dst_block[s], dst_chunk = first + j;
-        const uint64_t cap = HM ? seq_cap_blocks[s] : 0;
-        if (nb <= 0 || j >= (uint32_t)nb || b < 0 || (uint32_t)b >= c.n_objects) return;
-        if (HM ? first + cap > dst_cap || j >= cap || cap >= 65536 : dst_chunk >= dst_cap) return;
-        const uint64_t e = c.dir[b];
+        uint64_t cap = 0;
+        bool fits;
+        if constexpr (HM) { cap = h.seq_cap_blocks[s]; fits = (first + cap <= a.dst_cap) & (j < cap) & (cap < 65536); }
+        else fits = dst_chunk < a.dst_cap;
+        // as resolve_cell; one condition, so that the loads before it are on their way together
+        if (!(fits & (nb > 0) & (j < (uint32_t)nb) & (b >= 0) & ((uint32_t)b < a.n_objects))) return;
+        const uint64_t e = a.dir[b];
+        const uint64_t dst_plane = (plane ? a.dst_base[1] : a.dst_base[0]) + (sliced ? z * a.dst_step : 0);
+        const uint64_t cache = plane ? a.cache.base[1] : a.cache.base[0], local = plane ? a.local.base[1] : a.local.base[0];
+        in_registers(cache, local, a.cache.slot_stride, a.n_cache_slots);
         const int tier = (int)entry_tier(e);
         const uint64_t off = (uint64_t)k * (NTHR * 16);
-        if (HM) {
-            if (tier == T_NONE || entry_slot(e) >= slots_of(c, tier) || off + tid * 16 >= a.chunk_bytes) return;
-            if (tier == T_HOST && !entry_young(e, a.snap ? *a.snap : a.seen)) return;
+        const uint64_t slot = entry_slot(e);
+        uint64_t src;
+        if (tier == T_CACHE || tier == T_LOCAL) {
+            const bool cached = tier == T_CACHE;
+            if (slot >= (cached ? a.n_cache_slots : a.n_local_slots)) return;
+            src = (cached ? cache : local) + slot * (cached ? a.cache.slot_stride : a.local.slot_stride);
+            if (sliced) src += z * (cached ? a.cache.layer_stride : a.local.layer_stride);
+        } else {
+            if (tier != T_HOST || !entry_young(e, w.snap ? *w.snap : w.seen) || slot >= w.n_host_slots) return;
+            src = (plane ? w.host.base[1] : w.host.base[0]) + slot * w.host.slot_stride + z * w.host.layer_stride;
+        }
+        if constexpr (HM) {
+            if (off + tid * 16 >= a.chunk_bytes) return;
             uint32_t unit;
             uint64_t to;
             h.by_destination(k * NTHR + tid, cap, unit, to);
-            const uint64_t src = src_base_of(a, (uint32_t)tier, plane) + chunk_offset(c, tier, layer, entry_slot(e));
-            const uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + first * c.chunk_bytes + (uint64_t)j * h.ups * 16 + to;
+            const uint64_t dst = dst_plane + first * a.chunk_bytes + (uint64_t)j * h.ups * 16 + to;
             st16<true>(reinterpret_cast<u32x4 *>(dst), ld16<true>(reinterpret_cast<const u32x4 *>(src) + unit));
-            return;
+        } else {
+            copy_tile<NTHR, 1, true>(src + off, dst_plane + dst_chunk * a.chunk_bytes + off, a.chunk_bytes - off, tid);
         }
-        if (tier != T_CACHE && tier != T_LOCAL) {                  // (apart: what a workgroup works out first is kept short)
-            if (tier != T_HOST || !entry_young(e, a.snap ? *a.snap : a.seen) || entry_slot(e) >= c.n_slots[T_HOST]) return;
-            const uint64_t src = (plane ? a.src_base[T_HOST][1] : a.src_base[T_HOST][0]) + chunk_offset(c, T_HOST, layer + z, entry_slot(e)) + off;
-            const uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + z * a.dst_step + dst_chunk * c.chunk_bytes + off;
-            if (off + tid * 16 < a.chunk_bytes)
-                st16<true>(reinterpret_cast<u32x4 *>(dst) + tid, ld16<false>(reinterpret_cast<const u32x4 *>(src) + tid));
-            return;
-        }
-        if (entry_slot(e) >= slots_of(c, tier)) return;
-        const uint64_t src = src_base_of(a, (uint32_t)tier, plane) + chunk_offset(c, tier, layer + z, entry_slot(e)) + off;
-        const uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + z * a.dst_step + dst_chunk * c.chunk_bytes + off;
-        copy_tile<NTHR, 1, true>(src, dst, a.chunk_bytes - off, tid);
         return;
     }
     if (blockIdx.y || blockIdx.x > a.n_host) return;
     constexpr uint32_t WAVES_N = NTHR / 64;
     const bool keeper = blockIdx.x == a.n_host;
-    const uint32_t wave = tid >> 6, seen = a.snap ? *a.snap : a.seen;
-    const uint32_t lg = keeper ? 0 : a.host_lg_groups, last = (1u << lg) - 1u;         // the keeper's share is the whole table
-    const uint32_t group = blockIdx.x & last, member = blockIdx.x >> lg, members = a.n_host >> lg, share = (total + last) >> lg;
+    const uint32_t wave = tid >> 6, seen = w.snap ? *w.snap : w.seen;
+    const uint32_t lg = keeper ? 0 : w.host_lg_groups, last = (1u << lg) - 1u;         // the keeper's share is the whole table
+    const uint32_t group = blockIdx.x & last, member = blockIdx.x >> lg, members = a.n_host >> lg, share = (w.total + last) >> lg;
     __shared__ Rec s_list[NTHR * ROUND];               // the round's cells on the host of which this workgroup reads something
     __shared__ uint32_t s_first[NTHR * ROUND];         // ... its first piece of each
     __shared__ uint32_t s_sum[ROUND * WAVES_N];
@@ -917,7 +942,7 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
     uint32_t n[6] = { 0, 0, 0, 0, 0, 0 };            // requests, local, cache, host, lost, invalid, of this wavefront
     uint32_t n_miss = 0;
     if (tid < C_N) s_cnt[tid] = 0;
-    auto ask = [&](uint32_t i) { return ask_cell(table, n_blocks, max_blocks, shared_cell(i, group, lg), total); };
+    auto ask = [&](uint32_t i) { return ask_cell(table, n_blocks, max_blocks, shared_cell(i, group, lg), w.total); };
     Ask next[ROUND];
 #pragma unroll
     for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask(i * NTHR + tid);
@@ -930,26 +955,29 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
         for (uint32_t i = 0; i < ROUND; ++i) {
             now[i] = next[i];
             to0[i] = seq_dst_block[now[i].s];
-            cap[i] = HM ? seq_cap_blocks[now[i].s] : 0;
-            e[i] = c.dir[now[i].n > now[i].j && now[i].b >= 0 && (uint32_t)now[i].b < c.n_objects ? now[i].b : 0];
+            cap[i] = 0;
+            if constexpr (HM) cap[i] = h.seq_cap_blocks[now[i].s];
+            e[i] = a.dir[now[i].n > now[i].j && now[i].b >= 0 && (uint32_t)now[i].b < a.n_objects ? now[i].b : 0];
         }
 #pragma unroll
         for (uint32_t i = 0; i < ROUND; ++i) next[i] = ask(first + (ROUND + i) * NTHR + tid);
         uint32_t piece0[ROUND];
 #pragma unroll
-        for (uint32_t i = 0; i < ROUND; ++i) piece0[i] = first_piece(first + i * NTHR + tid, member, members, a.host_starts, a.host_step);
+        for (uint32_t i = 0; i < ROUND; ++i) piece0[i] = first_piece(first + i * NTHR + tid, member, members, w.host_starts, w.host_step);
         uint32_t rank[ROUND];                        // among the round's listed cells, in cell order: the host's, or the missed ones
         bool lists[ROUND];
 #pragma unroll
         for (uint32_t i = 0; i < ROUND; ++i) {
-            const uint64_t dst_chunk = to0[i] + now[i].j;
-            tier[i] = (int)entry_tier(e[i]);
-            if (now[i].n <= now[i].j) tier[i] = -1;
-            else if (now[i].b < 0 || (uint32_t)now[i].b >= c.n_objects ||
-                     (HM ? to0[i] + cap[i] > dst_cap || now[i].j >= cap[i] || cap[i] >= 65536 : dst_chunk >= dst_cap) ||
-                     (tier[i] != T_NONE && entry_slot(e[i]) >= slots_of(c, tier[i]))) tier[i] = 4;
-            lists[i] = tier[i] == T_HOST || (keeper ? tier[i] == T_NONE : (tier[i] == T_CACHE || tier[i] == T_LOCAL) && entry_young(e[i], seen));
-            if (!keeper) lists[i] &= piece0[i] < a.host_pieces;
+            // (Without branches.  They cost more than what they skip; and written with && and ||, the compiler once left out the very
+            // assignment of 4.)
+            const int t = (int)entry_tier(e[i]);
+            const bool known = (now[i].b >= 0) & ((uint32_t)now[i].b < a.n_objects), asked = now[i].n > now[i].j;
+            const bool fits = HM ? (to0[i] + cap[i] <= a.dst_cap) & (now[i].j < cap[i]) & (cap[i] < 65536) : to0[i] + now[i].j < a.dst_cap;
+            const bool there = (t == T_NONE) | (entry_slot(e[i]) < (t == T_HOST ? w.n_host_slots : t == T_CACHE ? a.n_cache_slots : a.n_local_slots));
+            tier[i] = asked ? ((known & fits & there) ? t : 4) : -1;
+            const bool young = ((tier[i] == T_CACHE) | (tier[i] == T_LOCAL)) & entry_young(e[i], seen);
+            lists[i] = (tier[i] == T_HOST) | (keeper ? tier[i] == T_NONE : young);
+            lists[i] &= keeper | (piece0[i] < w.host_pieces);
             uint32_t in_wave;
             rank[i] = wave_rank(lists[i], in_wave);
             if (lane_id() == 0) s_sum[i * WAVES_N + wave] = in_wave;
@@ -966,63 +994,76 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
 #pragma unroll
             for (uint32_t i = 0; i < ROUND; ++i) {
                 if (!lists[i]) continue;
-                uint64_t src = chunk_offset(c, T_HOST, layer, entry_slot(e[i]));
-                if (tier[i] != T_HOST) src = chunk_offset(c, tier[i], layer, entry_slot(e[i])) | (uint64_t)tier[i];      // (T_HOST is 0)
-                s_list[rank[i]] = { src | (HM ? (uint64_t)cap[i] << 48 : 0), to0[i] * c.chunk_bytes + now[i].j * (HM ? (uint64_t)h.ups * 16 : c.chunk_bytes) };
+                uint64_t src = entry_slot(e[i]) * w.host.slot_stride, dst = to0[i] * a.chunk_bytes;
+                if (tier[i] != T_HOST)               // (T_HOST is 0)
+                    src = entry_slot(e[i]) * (tier[i] == T_CACHE ? a.cache.slot_stride : a.local.slot_stride) | (uint64_t)tier[i];
+                if constexpr (HM) { src |= (uint64_t)cap[i] << 48; dst += (uint64_t)now[i].j * h.ups * 16; }
+                else dst += now[i].j * a.chunk_bytes;
+                s_list[rank[i]] = { src, dst };
                 s_first[rank[i]] = piece0[i];
             }
             __syncthreads();
             // A piece is read by 1 << lg_run wavefronts, a kilobyte each; the workgroup's other wavefronts are at other pieces meanwhile.
-            // The lanes work out 64 pieces at a time, which all of them then read one after the other, two in flight.
-            const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4), lg_run = NTHR == 64 ? 0 : a.host_lg_run, sets = WAVES_N >> lg_run;
+            // The lanes work out 64 pieces at a time, which all of them then read one after the other, two in flight (four where there
+            // are single wavefronts).
+            const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4), lg_run = NTHR == 64 ? 0 : w.host_lg_run, sets = WAVES_N >> lg_run;
             const uint32_t set = uniform(wave >> lg_run), sub = uniform(wave & ((1u << lg_run) - 1u));
-            const uint32_t n_slots = listed * a.host_per_cell;
+            const uint32_t n_slots = listed * w.host_per_cell;
             for (uint32_t slot0 = set; slot0 < n_slots; slot0 += 64 * sets) {
                 const uint32_t slot = slot0 + lane_id() * sets;
                 bool there = slot < n_slots;
                 uint32_t idx = there ? slot : 0, later = 0, rep = 0;
-                if (a.host_per_cell > 1) { idx /= a.host_per_cell; later = (slot - idx * a.host_per_cell) * members; }
+                if (w.host_per_cell > 1) { idx /= w.host_per_cell; later = (slot - idx * w.host_per_cell) * members; }
                 const Rec x = s_list[idx];
                 uint32_t piece = s_first[idx] + later;
-                if (piece >= a.host_pieces) { there = false; piece = 0; }
-                if (a.n_rep > 1) { rep = piece / (a.host_ppc * PLANES); piece -= rep * (a.host_ppc * PLANES); }
-                const uint32_t plane = PLANES == 2 && piece >= a.host_ppc;
+                if (piece >= w.host_pieces) { there = false; piece = 0; }
+                if (a.n_rep > 1) { rep = piece / (w.host_ppc * PLANES); piece -= rep * (w.host_ppc * PLANES); }
+                const uint32_t plane = PLANES == 2 && piece >= w.host_ppc;
                 const uint32_t from = (uint32_t)(x.src & 3);
-                const uint32_t unit = there ? (((piece - plane * a.host_ppc) << lg_run) + sub) * 64 : chunk_units, cap_of = HM ? (uint32_t)(x.src >> 48) : 0;
+                const uint32_t unit = there ? (((piece - plane * w.host_ppc) << lg_run) + sub) * 64 : chunk_units, cap_of = HM ? (uint32_t)(x.src >> 48) : 0;
                 // (the second plane as a difference, or every lane would load its pool's address from the arguments by itself)
-                uint64_t src = a.src_base[T_HOST][0] + (plane ? a.src_base[T_HOST][1] - a.src_base[T_HOST][0] : 0);
+                uint64_t src = w.host.base[0] + (plane ? w.host.base[1] - w.host.base[0] : 0);
                 uint64_t dst = a.dst_base[0] + (plane ? a.dst_base[1] - a.dst_base[0] : 0) + x.dst;
-                if (a.n_rep > 1) { src += rep * a.layer_stride[T_HOST]; dst += rep * a.dst_step; }
+                if (a.n_rep > 1) { src += rep * w.host.layer_stride; dst += rep * a.dst_step; }
                 if (__ballot(from != T_HOST)) {      // rare
-                    if (from != T_HOST) src = src_base_of(a, from, plane) + rep * layer_stride_of(a, from);
+                    const SmallTier &x1 = a.cache, &x2 = a.local;
+                    if (from == T_CACHE) src = (plane ? x1.base[1] : x1.base[0]) + rep * x1.layer_stride;
+                    if (from == T_LOCAL) src = (plane ? x2.base[1] : x2.base[0]) + rep * x2.layer_stride;
                 }
                 src += x.src & (HM ? SRC_MASK : ~(uint64_t)3);
                 const uint64_t whole = __ballot(unit + 64 <= chunk_units), any = __ballot(there);
-                auto from_at = [&](uint32_t k, uint32_t u) { return reinterpret_cast<const u32x4 *>(lane_value(src, k)) + u; };
                 auto to_at = [&](uint32_t k, uint32_t u) {
                     const uint64_t to = lane_value(dst, k);
                     return reinterpret_cast<u32x4 *>(to + (HM ? h.by_source(u, lane_value(cap_of, k)) : (uint64_t)u * 16));
                 };
-                for (uint32_t k = 0; k < 64; k += 2) {
-                    const uint32_t u0 = lane_value(unit, k) + lane_id(), u1 = lane_value(unit, k + 1) + lane_id();
-                    if ((whole >> k & 3) == 3) {     // (without a condition on the loads, or the second would wait for the first)
-                        const u32x4 v0 = ld16<false>(from_at(k, u0)), v1 = ld16<false>(from_at(k + 1, u1));
-                        st16<true>(to_at(k, u0), v0);
-                        st16<true>(to_at(k + 1, u1), v1);
-                        continue;
+                auto from_at = [&](uint32_t k, uint32_t u) { return reinterpret_cast<const u32x4 *>(lane_value(src, k)) + u; };
+                auto unit_at = [&](uint32_t k) { return lane_value(unit, k) + lane_id(); };
+                auto read = [&](uint32_t k, auto count) {        // whole pieces: with a condition on a load the next one would wait for it
+                    constexpr uint32_t N = decltype(count)::value;
+                    u32x4 v[N];
+#pragma unroll
+                    for (uint32_t i = 0; i < N; ++i) v[i] = ld16<false>(from_at(k + i, unit_at(k + i)));
+#pragma unroll
+                    for (uint32_t i = 0; i < N; ++i) st16<true>(to_at(k + i, unit_at(k + i)), v[i]);
+                    return N;
+                };
+                for (uint32_t k = 0; k < 64 && any >> k;) {
+                    if (NTHR == 64 && (whole >> k & 15) == 15) k += read(k, Count<4>{});
+                    else if ((whole >> k & 3) == 3) k += read(k, Count<2>{});
+                    else {                           // the last of them, or a chunk's last piece
+                        const uint32_t u = unit_at(k);
+                        const u32x4 *from = from_at(k, u);
+                        u32x4 *to = to_at(k, u);
+                        if (u < chunk_units) st16<true>(to, ld16<false>(from));
+                        k++;
                     }
-                    if (!(any >> k)) break;
-                    const u32x4 *f0 = from_at(k, u0), *f1 = from_at(k + 1, u1);
-                    u32x4 *t0 = to_at(k, u0), *t1 = to_at(k + 1, u1);
-                    if (u0 < chunk_units) st16<true>(t0, ld16<false>(f0));
-                    if (u1 < chunk_units) st16<true>(t1, ld16<false>(f1));
                 }
             }
         }
         if (keeper) {
 #pragma unroll
             for (uint32_t i = 0; i < ROUND; ++i) {
-                if (tier[i] == T_HOST || tier[i] == T_NONE) books.miss_idx[n_miss + rank[i]] = first + i * NTHR + tid;
+                if (tier[i] == T_HOST || tier[i] == T_NONE) w.miss_idx[n_miss + rank[i]] = first + i * NTHR + tid;
                 const bool pred[6] = { tier[i] >= 0, tier[i] == T_LOCAL, tier[i] == T_CACHE, tier[i] == T_HOST, tier[i] == T_NONE, tier[i] == 4 };
 #pragma unroll
                 for (int k = 0; k < 6; ++k) n[k] += (uint32_t)__popcll(__ballot(pred[k]));
@@ -1040,19 +1081,19 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(ClassDev c, uint32_t l
     __syncthreads();
     if (tid <= C_INVALID) {
         const uint32_t x = s_cnt[tid];
-        books.cnt[tid] = x;
-        if (x) atomicAdd(&books.totals[tid], (unsigned long long)x);
-        if (books.info) books.info[tid] = x;
+        w.cnt[tid] = x;
+        if (x) atomicAdd(&w.totals[tid], (unsigned long long)x);
+        if (w.info) w.info[tid] = x;
     }
     if (tid == 0) {
         const uint32_t hbm = s_cnt[C_LOCAL] + s_cnt[C_CACHE], host = s_cnt[C_HOST];
-        books.cnt[C_HBM_REQ] = hbm;
-        books.cnt[C_HOST_REQ] = host;
-        books.cnt[C_MISS] = n_miss;
-        if (books.info) { books.info[6] = n_miss; books.info[7] = 0; }
-        const u32x4 r = { hbm, host, books.n_seq, max_blocks };        // one store
-        *reinterpret_cast<u32x4 *>(books.report) = r;
-        link_announce(books.lease, (uint64_t)host * a.chunk_bytes * PLANES * a.n_rep);
+        w.cnt[C_HBM_REQ] = hbm;
+        w.cnt[C_HOST_REQ] = host;
+        w.cnt[C_MISS] = n_miss;
+        if (w.info) { w.info[6] = n_miss; w.info[7] = 0; }
+        const u32x4 r = { hbm, host, w.n_seq, max_blocks };        // one store
+        *reinterpret_cast<u32x4 *>(w.report) = r;
+        link_announce(w.lease, (uint64_t)host * a.chunk_bytes * PLANES * a.n_rep);
     }
 }
 

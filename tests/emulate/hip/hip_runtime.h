@@ -34,5 +34,6 @@ inline uint32_t atomicAdd(uint32_t *p, int v) { uint32_t old = *p; *p += v; retu
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_readlane(x, k) read_lane(x, k)
 #define __builtin_amdgcn_s_setprio(n) ((void)0)
-#define __builtin_amdgcn_kernarg_segment_ptr() ((const __attribute__((address_space(4))) void *)0)
+extern const char *kernel_arguments;                    // laid out as a launch would have them
+#define __builtin_amdgcn_kernarg_segment_ptr() ((const __attribute__((address_space(4))) void *)kernel_arguments)
 #define __builtin_amdgcn_global_store_b128(p, v, scope) (void)(*(p) = (v))

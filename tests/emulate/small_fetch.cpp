@@ -5,6 +5,7 @@
 #include "kernels.h"
 
 #include <ucontext.h>
+#include <cstddef>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -12,6 +13,7 @@
 #include <vector>
 
 dim3 threadIdx, blockIdx, gridDim;
+const char *kernel_arguments;
 uint32_t __shfl_xor(uint32_t, int) { abort(); }
 uint32_t __shfl_up(uint32_t, int) { abort(); }
 void __threadfence_system() {}
@@ -123,40 +125,41 @@ struct Fetch {
 int run_fetch(const Fetch *f)
 {
     using namespace hv;
-    ClassDev c{};
     std::vector<uint64_t> dir(f->versions, f->versions + f->n_objects);
-    c.dir = dir.data();
-    c.n_objects = f->n_objects; c.n_planes = f->n_planes; c.chunk_bytes = f->chunk_bytes;
-    GatherArgs a{};
-    for (int t = 0; t < 3; ++t) {
-        for (int p = 0; p < 2; ++p) c.pool[t][p] = a.src_base[t][p] = f->pool[t][p];
-        c.n_slots[t] = f->n_slots;
-        c.slot_stride[t] = f->chunk_bytes;
-        c.layer_stride[t] = a.layer_stride[t] = f->n_slots * f->chunk_bytes;
-    }
-    a.dst_base[0] = f->dst[0]; a.dst_base[1] = f->dst[1];
-    a.chunk_bytes = f->chunk_bytes;
-    a.tiles_per_chunk = (uint32_t)((f->chunk_bytes + f->nthr * 16 - 1) / (f->nthr * 16));
-    a.dst_step = f->dst_step; a.n_rep = f->n_layers; a.n_host = f->n_host; a.host_lg_groups = f->lg_groups; a.seen = f->seen;
-    deal_out_host_pieces(a, f->n_planes, f->nthr);
     const uint32_t total = f->n_seq * f->max_blocks;
+    struct { const void *pointers[3]; SmallArgs a; SmallWalk w; } arguments{};
+    static_assert(offsetof(decltype(arguments), w) == SMALL_WALK_AT);
+    kernel_arguments = (const char *)&arguments;
+    SmallArgs &a = arguments.a;
+    SmallWalk &w = arguments.w;
+    a.dst_cap = f->dst_cap; a.dir = dir.data(); a.chunk_bytes = f->chunk_bytes;
+    a.max_blocks = f->max_blocks; a.n_objects = f->n_objects; a.n_rep = f->n_layers;
+    a.tiles_per_chunk = (uint32_t)((f->chunk_bytes + f->nthr * 16 - 1) / (f->nthr * 16));
     a.hbm_wgs = total * a.tiles_per_chunk;
-    HmArgs h{};
+    a.dst_base[0] = f->dst[0]; a.dst_base[1] = f->dst[1]; a.dst_step = f->dst_step;
+    auto tier = [&](int t) { return SmallTier{ { f->pool[t][0], f->pool[t][1] }, f->n_slots * f->chunk_bytes, f->chunk_bytes }; };
+    a.cache = tier(T_CACHE); a.local = tier(T_LOCAL); w.host = tier(T_HOST);
+    a.n_cache_slots = a.n_local_slots = w.n_host_slots = f->n_slots;
+    w.total = total; w.seen = f->seen; a.n_host = f->n_host; w.host_lg_groups = f->lg_groups;
+    deal_out_host_pieces(a, w, f->n_planes, f->nthr);
+    SmallHm<true> h{};
     if (f->head_major) {
         h.n_heads = f->n_heads;
         h.upr = (uint32_t)(f->chunk_bytes / (f->n_heads * f->block_tokens) / 16);
         h.ups = h.upr * f->block_tokens;
+        h.seq_cap_blocks = f->seq_cap;
     }
     std::vector<unsigned long long> totals(C_N);
     alignas(16) Report report;
-    SmallBooks books{ f->miss, f->cnt, nullptr, totals.data(), &report, nullptr, f->n_seq };
-    auto call = [&](auto kernel) {
-        g_kernel = [&, kernel] { kernel(c, 0, f->table, f->n_blocks, total, f->max_blocks, f->seq_dst, f->dst_cap, a, books, h, f->seq_cap); };
+    w.n_seq = f->n_seq; w.miss_idx = f->miss; w.cnt = f->cnt; w.totals = totals.data(); w.report = &report;
+    auto call = [&](auto plain, auto with_hm) {
+        if (f->head_major) g_kernel = [&, with_hm] { with_hm(f->table, f->n_blocks, f->seq_dst, a, w, h); };
+        else g_kernel = [&, plain] { plain(f->table, f->n_blocks, f->seq_dst, a, w, SmallHm<false>{}); };
     };
-    if (f->n_planes == 2 && f->nthr == 64) f->head_major ? call(fetch_kv_small<2, 64, true>) : call(fetch_kv_small<2, 64, false>);
-    else if (f->n_planes == 2) f->head_major ? call(fetch_kv_small<2, 256, true>) : call(fetch_kv_small<2, 256, false>);
-    else if (f->nthr == 64) f->head_major ? call(fetch_kv_small<1, 64, true>) : call(fetch_kv_small<1, 64, false>);
-    else f->head_major ? call(fetch_kv_small<1, 256, true>) : call(fetch_kv_small<1, 256, false>);
+    if (f->n_planes == 2 && f->nthr == 64) call(fetch_kv_small<2, 64, false>, fetch_kv_small<2, 64, true>);
+    else if (f->n_planes == 2) call(fetch_kv_small<2, 256, false>, fetch_kv_small<2, 256, true>);
+    else if (f->nthr == 64) call(fetch_kv_small<1, 64, false>, fetch_kv_small<1, 64, true>);
+    else call(fetch_kv_small<1, 256, false>, fetch_kv_small<1, 256, true>);
 
     const bool sliced = f->n_layers > 1;
     const uint32_t head = a.n_host + 1;

@@ -292,6 +292,35 @@ def test_a_one_kernel_fetch_is_whole_when_the_directory_changes_under_it(edit, h
     h.close()
 
 
+@pytest.mark.parametrize("head_major", [False, True])
+@pytest.mark.parametrize("n_planes", [1, 2])
+@pytest.mark.parametrize("lens,width", [([60, 40], 60), ([300, 250], 300), ([40, 700], 700)])
+def test_cells_without_room_are_counted_and_write_nothing(lens, width, n_planes, head_major):
+    """The last sequence's region ends seven blocks early: blocks of every tier that do not fit, in a destination that goes on behind."""
+    chunk, room = 2048, sum(lens) - 7
+    rig = Rig(chunk, 50, n_planes=n_planes, host_every=2)
+    t, dt, dn, df, cap = rig.tables(lens, width)
+    k, v = rig.buffers(cap)
+    if head_major:
+        caps = torch.tensor([lens[0], lens[1] - 7], dtype=torch.int32, device="cuda")
+        rig.h.fetch_kv_head_major(0, dt, dn, k, v if n_planes == 2 else None, df, caps, room, 4, 4)
+    else:
+        rig.h.fetch_kv(0, dt, dn, k, v if n_planes == 2 else None, df, room)
+    counts, miss, _ = rig.h.fetch_info(miss_cap=t.size)
+    fit = [lens[0], lens[1] - 7]
+    assert miss.tolist() == rig.misses(t, fit) and counts["n_invalid"] == 7 and counts["n_requests"] == cap
+    for p, buf in enumerate([k, v][:n_planes]):
+        got, at = buf.cpu().numpy(), 0
+        assert (got[room * chunk:] == 0xEE).all()
+        for s, n in enumerate(fit):
+            want = rig.payload[p][0][rig.order[t[s, :n]]]
+            if head_major:
+                want = want.reshape(n * 4, 4, -1).transpose(1, 0, 2)
+            assert np.array_equal(got[at:at + n * chunk], want.reshape(-1)), (p, s)
+            at += n * chunk
+    rig.h.close()
+
+
 @pytest.mark.parametrize("n_planes,n_layers,n,layout,entry", [(2, 1, 4090, 0, "fetch"), (1, 1, 4090, 0, "fetch"), (2, 3, 1301, 0, "layers"), (2, 40, 100, 0, "layers"),
                                                               (2, 1, 3001, B.FLAG_CACHE_PLANES_ADJACENT, "fetch"), (2, 1, 3001, 0, "static"), (2, 1, 3001, 0, "head_major")])
 def test_blocks_that_nobody_edits_are_whole_when_others_change_under_a_one_kernel_fetch(n_planes, n_layers, n, layout, entry):

@@ -156,3 +156,17 @@ def test_counters_and_misses_of_a_directory_that_holds_still(emulated):
         asked = tier[c.table[c.cells]]
         assert cnt[:6].tolist() == [len(asked), (asked == LOCAL).sum(), (asked == CACHE).sum(), (asked == HOST).sum(), 0, 0]
         assert miss[:(asked == HOST).sum()].tolist() == c.cells[asked == HOST].tolist()
+
+
+@pytest.mark.parametrize("n_planes", [1, 2])
+@pytest.mark.parametrize("nthr", [64, 256])
+def test_head_major_cells_beyond_a_sequences_room_are_invalid(emulated, n_planes, nthr):
+    """The last sequence's destination has room for two blocks less than it has."""
+    rng = np.random.default_rng(6)
+    c = Case(emulated, rng, [65, 62], 65, 16, n_planes, nthr, head_major=True, n_host=8, heads=(1, 1))
+    c.n_blocks[1] = 64
+    tier = rng.choice([HOST, CACHE, LOCAL], c.n_objects, p=[0.4, 0.5, 0.1])
+    cnt, miss = c.run([tier])
+    asked = tier[c.table[c.cells]]
+    assert cnt[:6].tolist() == [129, (asked == LOCAL).sum(), (asked == CACHE).sum(), (asked == HOST).sum(), 0, 2]
+    assert miss[:(asked == HOST).sum()].tolist() == c.cells[asked == HOST].tolist()
