@@ -143,7 +143,8 @@ typedef struct harvest_config {
     uint32_t gather_wg_per_cu;      /* tuning: cap the HBM-tier gather at this many workgroups per CU (they then loop
                                        over tiles, and take a request's planes one after the other); 0 = default, one workgroup
                                        per tile of gather_threads * 16 bytes */
-    uint32_t host_wgs;              /* tuning: 8 KiB of host-tier (PCIe) reads in flight per unit; 0 = default (24) */
+    uint32_t host_wgs;              /* tuning: 8 KiB of host-tier (PCIe) reads in flight per unit; 0 = default (24; the
+                                       one-kernel form of small KV fetches 32) */
     uint32_t shared_granule;        /* segment granule of the shared cache pool in bytes: a power of two >= 256;
                                        0 = 4096 */
     uint32_t small_fetch_cells;     /* tuning: a KV fetch, of either layout, takes its one-kernel form for block tables of up to this
@@ -153,8 +154,8 @@ typedef struct harvest_config {
     uint32_t pcie_wgs;              /* tuning: persistent workgroups of the copies that cross PCIe outside a fetch (place,
                                        write-back), each with one 32 KiB tile in flight (16 KiB for
                                        write-backs of chunks below 32 KiB); 0 = default (12: enough to fill the link
-                                       when alone, few enough that a fetch on another stream keeps most of it);
-                                       write-backs run 5/3 as many */
+                                       when alone, few enough that a fetch on another stream keeps most of it;
+                                       write-backs, whose stores wait for the host, 20) */
     uint32_t reserved[2];           /* must be 0 */
     void *d_shared_cache;           /* optional shared cache pool (device memory, 256-byte aligned), see below */
     uint64_t shared_cache_bytes;    /* its size: a multiple of the granule, at most 2^30 granules */

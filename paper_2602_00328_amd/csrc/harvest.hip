@@ -422,7 +422,7 @@ struct harvest_ctx {
     harvest_config cfg{};
     bool no_device = false, poison = false, profile = false, general_fetch = false;
     int n_cu = 256;
-    uint32_t gather_grid = 0, host_grid = 0, ctl_grid = 0, pcie_grid = 0;
+    uint32_t gather_grid = 0, host_grid = 0, ctl_grid = 0, pcie_grid = 0, to_host_grid = 0;
     uint32_t gather_threads = HBM_WG;     // threads per workgroup of the HBM-tier gather (64, 128 or 256)
     uint64_t small_cells = 0;             // block tables up to this many cells are fetched by one kernel
     ClassState cls[HARVEST_N_CLASSES];
@@ -1069,11 +1069,13 @@ int launch_move(harvest_ctx *ctx, StreamState *ss, const std::vector<MoveRec> &r
     a.n_tiles = (uint32_t)tiles;
     a.next = ss->next;
     a.lease = way == WITHIN_HBM ? nullptr : ctx->d_lease;
-    // To the host with 5/3 as many workgroups, 20: stores at system scope wait for the host.  Beside a kernel that fills the device
+    // To the host with 20 workgroups unless the caller has said how many: stores at system scope wait for the host.  Beside a kernel that fills the device
     // 12 / 16 / 20 / 24 workgroups write 200 blocks of 2 x 32 KiB back in 282 / 258 / 253 / 250 us and 2 x 16 KiB in 207 / 164 / 142
     // / 139 (12 with non-temporal stores: 252 and 151; alone any number 243 and 128, 253 and 133); a fetch of 880 blocks from the
-    // host, 1.01 ms alone, takes 1.05 / 1.08 / 1.16 / 1.26 ms beside a stream of write-backs (non-temporal: 1.20).
-    const dim3 grid(grid_for(tiles, way == WITHIN_HBM ? ctx->ctl_grid : way == TO_HOST ? ctx->pcie_grid * 5 / 3 : ctx->pcie_grid));
+    // host, 1.01 ms alone, takes 1.05 / 1.08 / 1.16 / 1.26 ms beside a stream of write-backs (non-temporal: 1.20).  Lists of up to 2 MiB,
+    // with 12 and 20 (non-temporal either way): 32 blocks of 2 x 32 KiB 42.1 and 41.9 us, of 2 x 16 KiB 24.5 and 23.4, 16 of them 14.7 and
+    // 13.8; such a fetch beside a stream of them 1.21 and 1.30 ms, 0.57 and 0.60 (0.51 alone), 0.54 and 0.55.
+    const dim3 grid(grid_for(tiles, way == WITHIN_HBM ? ctx->ctl_grid : way == TO_HOST ? ctx->to_host_grid : ctx->pcie_grid));
     if (way == TO_HOST) {
         const bool through = items * a.chunk_bytes > THROUGH_FROM;
         auto of = [&](auto in) {
@@ -1114,6 +1116,7 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
     // with whatever else crosses it (paper Section 2.2), and a placement is best effort (Section 3.1), so the copies
     // run narrow.
     ctx->pcie_grid = cfg->pcie_wgs ? cfg->pcie_wgs : 12;
+    ctx->to_host_grid = cfg->pcie_wgs ? cfg->pcie_wgs : 20;       // see launch_move
     HIP_TRY(hipStreamCreateWithFlags(&ctx->ctl, hipStreamNonBlocking));
     HIP_TRY(hipStreamCreateWithFlags(&ctx->drain, hipStreamNonBlocking));
     HIP_TRY(hipMalloc(&ctx->d_totals, HARVEST_N_CLASSES * C_N * sizeof(unsigned long long)));
@@ -1796,14 +1799,14 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         }
         const uint32_t nthr = total <= 64 * ROUND ? 64 : WG;
         ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16);
-        // A third more reads of the host in flight than in the general path: the tile workgroups
+        // Unless the caller has said how wide, a third more reads of the host in flight than in the general path: the tile workgroups
         // keep the host's waiting at the compute units, and members of a group whose number divides the pieces of a cell have even shares.
         // 24 / 32 / 40 workgroups of 256 threads: 256 cells, 102 on the host 124.5 / 123.1 / 124.2 us; 2 000 of 2 x 16 KiB, 300 184.9 /
         // 178.8 / 179.4; 1 750, 52 41.8 / 37.4-38.6 / 37.4; 4 000 of 2 x 32 KiB, 120 149.2 / 145.8 / 145.6; 3 000, 30 66.3 / 66.7 / 68.0.
         // Single wavefronts have four loads each: 60 cells, 6 on the host, 12.7 us with 64 of them (two loads: 12.7; 96 or 128 of them
         // 13.1); 128 cells, all on the host 152.9 (153.4; 153.7-153.8); 32 layers of 5 blocks, one on the host 42.8 (43.3; 43.0).
         const uint32_t host_wgs = host_workgroups(ctx, nthr, nthr == 64 ? 4 : 2);
-        ga.n_host = c.cfg.n_host_slots ? host_wgs * 4 / 3 : 0;
+        ga.n_host = !c.cfg.n_host_slots ? 0 : ctx->cfg.host_wgs ? host_wgs : host_wgs * 4 / 3;
         // the walk for the host's cells is shared out, see fetch_kv_small: not when it takes a single round, and to groups of at least
         // 12 workgroups - what a group finds is read by its own workgroups only, and with 4 to a group (2 877 cells, 52 on the
         // host) the groups that had found less left the link to the others for so long that 37.7 us became 39.4

@@ -45,9 +45,11 @@ def fake(tmp_path_factory):
 class Ctx:
     """A context with a KV class of n objects (32 KiB chunks unless said otherwise), all on the host."""
 
-    def __init__(self, lib, n=200, n_local=0, n_layers=2, chunk=32768, flags=0, cb=None):
+    def __init__(self, lib, n=200, n_local=0, n_layers=2, chunk=32768, flags=0, cb=None, **tuning):
         self.lib, cfg = lib, B.harvest_config()
         cfg.flags = flags
+        for name, value in tuning.items():
+            setattr(cfg, name, value)
         kv = cfg.cls[B.KV]
         kv.n_layers, kv.n_planes, kv.chunk_bytes, kv.max_objects = n_layers, 2, chunk, n + n_local
         kv.n_host_slots, kv.n_cache_slots, kv.n_local_slots = n + n_local, n, max(n_local, 1)
@@ -370,4 +372,17 @@ def test_a_fetch_beside_another_streams_placement_and_recording(fake):
         assert [line.split()[-1] for line in log if line.startswith("hipEventQuery")] == ["relaxed"], log
     fake.fake_capture(None)
     fake.fake_not_ready(False)
+    c.close()
+
+
+@pytest.mark.parametrize("tuning,readers,writers", [({}, 32, 20), (dict(host_wgs=5, pcie_wgs=7), 5, 7)])
+def test_a_callers_numbers_of_workgroups_are_taken_as_they_are(fake, tuning, readers, writers):
+    """Of a one-kernel fetch (64 KiB blocks: 16 tiles a cell) those that read the host, and those of a write-back."""
+    c = Ctx(fake, chunk=65536, **tuning)
+    grid = lambda name: (lambda log: int(re.search(r"grid (\d+),", log[launches(log, name)[0]]).group(1)))(c.log())
+    c.log()
+    assert fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 300, POOL, POOL, POOL, 300, c.stream) == B.OK
+    assert grid("fetch_kv_small") == 300 * 16 + readers + 1
+    assert c.evict(np.arange(150)) == B.OK
+    assert grid("move_pcie") == writers
     c.close()
