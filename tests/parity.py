@@ -127,3 +127,16 @@ def streams_run_independently(dev, a, b, ms=30.0):
     independent = not still.query()
     torch.cuda.synchronize()
     return independent, cycles
+
+
+def stream_independent_of(dev, fixed, first, ms=30.0, busy_is_fixed=True, tries=8):
+    """A stream whose work does not wait for `fixed`'s (busy_is_fixed) or the other way round: `first`, or else the first of several
+    fresh ones - which of its hardware queues HIP gives a stream is not for the test to say.  None if there is none; and the cycles of a
+    sleep of about `ms`."""
+    import torch
+    for i in range(tries):
+        s = first if i == 0 else torch.cuda.Stream(dev)
+        independent, cycles = streams_run_independently(dev, fixed, s, ms) if busy_is_fixed else streams_run_independently(dev, s, fixed, ms)
+        if independent:
+            return s, cycles
+    return None, cycles

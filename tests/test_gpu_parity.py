@@ -641,7 +641,7 @@ def test_two_revocations_at_once_both_wait_for_the_work_in_flight():
 def test_a_kv_fetch_does_not_wait_for_the_experts_directory_edits():
     """Directory edits are ordered per class. The expert stream is held up by a sleeping kernel with a placement (copies,
     then the directory write that publishes them) queued behind it; a KV fetch on the other stream completes while that
-    kernel still sleeps. Skipped when the device runs the two streams through one hardware queue."""
+    kernel still sleeps. Skipped when the device runs every stream through the expert stream's hardware queue."""
     import torch
     say("a KV fetch while the experts' directory edits are pending")
     wl = W.kv_decode(seed=31, n_layers=1, n_seq=2, min_len=300, max_len=600, n_steps=1)
@@ -661,9 +661,15 @@ def test_a_kv_fetch_does_not_wait_for_the_experts_directory_edits():
         d_sdb = torch.from_numpy(rh.seq_dst_block.view(np.int64)).to(eh.dev)
         dst = [torch.zeros(rh.cap * wl.shape.chunk_bytes, dtype=torch.uint8, device=eh.dev) for _ in range(2)]
         torch.cuda.synchronize()
-        independent, cycles = P.streams_run_independently(eh.dev, x_stream, kv_stream, ms=150.0)
-        if not independent:
-            pytest.skip("the two streams share a hardware queue in this process")
+        kv_stream, cycles = P.stream_independent_of(eh.dev, x_stream, kv_stream, ms=150.0)
+        if kv_stream is None:
+            pytest.skip("every stream shares a hardware queue with the expert stream in this process")
+        with torch.cuda.stream(kv_stream):                                 # its scratch too
+            eh.h.fetch_kv(0, d_table, d_nb, dst[0], dst[1], d_sdb, rh.cap)
+        torch.cuda.synchronize()
+        for t in dst:
+            t.zero_()
+        torch.cuda.synchronize()
         with torch.cuda.stream(x_stream):
             torch.cuda._sleep(cycles)
         st = eh.place(S.EXPERT, cached[:2])                                # queued behind the sleeping kernel
@@ -702,9 +708,9 @@ def test_a_kv_fetch_does_not_wait_for_a_placement_on_another_stream():
         warm, on_host = on_host[300:], on_host[:300]
         other = torch.cuda.Stream(eh.dev)
         main = torch.cuda.current_stream()
-        independent, cycles = P.streams_run_independently(eh.dev, other, main, ms=150.0)
-        if not independent:
-            pytest.skip("the two streams share a hardware queue in this process")
+        other, cycles = P.stream_independent_of(eh.dev, main, other, ms=150.0, busy_is_fixed=False)
+        if other is None:
+            pytest.skip("every stream shares a hardware queue with the current one in this process")
         table, nb = rh.table_arrays()
         d_table, d_nb = torch.from_numpy(table).to(eh.dev), torch.from_numpy(nb).to(eh.dev)
         d_sdb = torch.from_numpy(rh.seq_dst_block.view(np.int64)).to(eh.dev)
