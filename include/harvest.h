@@ -27,7 +27,11 @@
  *     harvest_fetch_experts may be recorded into a HIP graph (stream capture)
  *     once such a call has run on that stream outside capture: they use no
  *     memset and read residency from device memory, so a replay follows every
- *     place / revoke made since.  harvest_place and harvest_evict refuse a
+ *     place / revoke made since (of the objects there were when it was recorded:
+ *     a block number registered later counts as unknown).  The replays of all
+ *     graphs recorded on one stream, and the fetches enqueued on it, share that
+ *     stream's scratch: the caller keeps them from overlapping (one stream, or
+ *     events), as for harvest_fetch_kv_static.  harvest_place and harvest_evict refuse a
  *     capturing stream, harvest_revoke refuses while any stream the context
  *     knows is capturing (EINVAL, nothing changed).  While a context has recorded work,
  *     harvest_revoke drains by waiting for the whole device.  Directory edits made by place /
@@ -105,7 +109,8 @@ enum harvest_flags {
     HARVEST_FLAG_NO_DEVICE = 1,  /* directory bookkeeping only (no HIP call at all): for host-side tests */
     HARVEST_FLAG_POISON = 2,     /* revoke overwrites the freed cache slot with 0xA5 after the drain */
     HARVEST_FLAG_PROFILE = 4,    /* bracket the gather kernels with events; read them with harvest_profile
-                                    (launches recorded into a graph are not timed) */
+                                    (launches recorded into a graph are not timed, nor are KV fetches in their one-kernel
+                                    form, whose tiers are not apart: HARVEST_FLAG_GENERAL_FETCH) */
     HARVEST_FLAG_GENERAL_FETCH = 8, /* KV fetches never take their one-kernel form for small block tables (up to
                                     4096 cells): every fetch runs resolve, compaction and the gather - for
                                     measurements and tests of that path; results are the same either way */
@@ -148,7 +153,9 @@ typedef struct harvest_config {
     uint32_t shared_granule;        /* segment granule of the shared cache pool in bytes: a power of two >= 256;
                                        0 = 4096 */
     uint32_t small_fetch_cells;     /* tuning: a KV fetch, of either layout, takes its one-kernel form for block tables of up to this
-                                       many cells (n_seq * max_blocks); 0 = default (4096) */
+                                       many cells (n_seq * max_blocks); 0 = default (4096).  Not once an object has been
+                                       registered without a host copy: a revocation can then leave a fetch in flight nothing
+                                       to copy from, and only the general path resolves a block in one place */
     uint32_t gather_threads;        /* tuning: threads per workgroup of the HBM-tier gather, 64, 128 or 256; 0 = default
                                        (64: one wavefront per workgroup, 1 KiB tiles) */
     uint32_t pcie_wgs;              /* tuning: persistent workgroups of the copies that cross PCIe outside a fetch (place,

@@ -180,3 +180,44 @@ def test_a_fetch_on_another_stream_leaves_a_recording_alone(pending):
             for p, b in enumerate(pair):
                 assert np.array_equal(b.cpu().numpy().reshape(n, chunk), payload[p][table.cpu().numpy()[0]])
     h.close()
+
+
+def test_a_replay_knows_the_objects_of_its_recording():
+    """Blocks without a host copy, registered after a one-kernel fetch was recorded: a table that names them gets no part of them from
+    a replay, before and after one is revoked; an eager fetch does."""
+    from paper_2602_00328_amd import binding as B
+    n, chunk = 16, 4096
+    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n, n_host_slots=n // 2, n_cache_slots=n, n_local_slots=n // 2))
+    for p in range(2):
+        h.host_plane(B.KV, p)[:] = 7
+        h.dev_plane(B.KV, B.LOCAL, p).fill_(9)
+    h.register(B.KV, n // 2, np.arange(n // 2))
+    table = torch.arange(n, dtype=torch.int32, device="cuda").reshape(1, n) % (n // 2)
+    n_blocks, first = torch.tensor([n], dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")
+    k, v = (torch.zeros(n * chunk, dtype=torch.uint8, device="cuda") for _ in range(2))
+    s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    fetch = lambda: h.fetch_kv(0, table, n_blocks, k, v, first, n)
+    with torch.cuda.stream(s):
+        fetch()
+    with torch.cuda.graph(g, stream=s):
+        fetch()
+    lossy = h.register(B.KV, n // 2, None, tier=B.LOCAL)
+    table.copy_(torch.arange(n, dtype=torch.int32).reshape(1, n))
+    for turn in range(3):
+        if turn == 1:
+            h.evict(B.KV, -1, lossy[:4], h.dev_plane(B.KV, B.LOCAL, 0), h.dev_plane(B.KV, B.LOCAL, 1), np.arange(4, dtype=np.uint64), n // 2, B.EVICT_DEMOTE)
+        if turn == 2:
+            h.revoke(B.KV, lossy[:2])
+        for run, there in ((g.replay, 0), (fetch, 8 - 2 * (turn == 2))):
+            k.zero_(), v.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(s):
+                run()
+                counts, _, _ = h.fetch_info(miss_cap=n, cls=B.KV)
+            torch.cuda.synchronize()
+            assert (counts["n_invalid"], counts["n_lost"]) == ((8, 0) if run == g.replay else (0, 8 - there))
+            for b in (k, v):
+                got = b.cpu().numpy().reshape(n, chunk)
+                assert (got[:8] == 7).all() and (got[16 - there:] == 9).all() and not got[8:16 - there].any()
+    h.close()
