@@ -763,12 +763,12 @@ struct HmArgs {
 //
 //   the first n_host  walk the table, list the host's cells in LDS and read them over PCIe, all planes and layers, two loads in
 //                     flight per thread (see host_tier for why so few): 102 of 256 blocks of 2 x 32 KiB from the host take
-//                     123.0 us, the call.  When every host tile was read at once, by a workgroup of its own, 6.7 MB of reads queued
+//                     122.7 us, the call.  When every host tile was read at once, by a workgroup of its own, 6.7 MB of reads queued
 //                     on the link together: 134 us.
 //                     A table that takes several rounds to walk is shared out: workgroup b belongs to group b modulo their number, and a
 //                     group walks its own share of the cells (shared_cell) and reads what it finds.  A round of a walk
 //                     costs its workgroup a microsecond of waits in which it reads nothing: 2 877 cells of 2 x 16 KiB, 52 of them
-//                     on the host, take 37.4-38.3 us in two groups and took 39.5-40.9 when every workgroup walked all six rounds.
+//                     on the host, take 37.1-37.8 us in two groups and took 39.6-40.9 when every workgroup walked all six rounds.
 //   the next one      walks the table too and keeps the books: counters, and the miss list in request order.  No atomics on
 //                     shared counters (a thousand of them on one address take longer than the copy), nothing to zero.
 //   the others        copy a tile of 16 bytes a thread if their cell's block is in HBM: nothing is compacted, so the grid covers the padded
@@ -788,7 +788,7 @@ struct HmArgs {
 // copy from: with any around, fetches resolve in one place, on the general path.)
 //
 // HM: into the head-major layout.  Tiles of the HBM tier are taken in destination order, the host's in source order, as in gather_hm
-// and host_tier_hm.  8 x 16 blocks of 2 x 32 KiB take 9.6 us (17.6 in three launches), 1 024 blocks 26.9 (31.4), 4 096 95.1 (96.9).
+// and host_tier_hm.  8 x 16 blocks of 2 x 32 KiB take 7.8 us (15.7 in three launches), 1 024 blocks 25.3 (31.4), 4 096 90.6 (97.0).
 //
 // A walk goes ROUND * WG cells at a time; the next round's row lengths, block numbers and destinations are on their way while
 // this one's directory entries are, so a round costs one memory latency, not two.  The code of the walk is kept short on
