@@ -790,8 +790,8 @@ struct HmArgs {
 // HM: into the head-major layout.  Tiles of the HBM tier are taken in destination order, the host's in source order, as in gather_hm
 // and host_tier_hm.  8 x 16 blocks of 2 x 32 KiB take 7.8 us (15.7 in three launches), 1 024 blocks 25.3 (31.4), 4 096 90.6 (97.0).
 //
-// A walk goes ROUND * WG cells at a time; the next round's row lengths, block numbers and destinations are on their way while
-// this one's directory entries are, so a round costs one memory latency, not two.  The code of the walk is kept short on
+// A walk goes ROUND * NTHR cells at a time; the next round's row lengths and block numbers are on their way while this one's directory
+// entries and destinations are, so a round costs one memory latency, not two.  The code of the walk is kept short on
 // purpose: it runs once, and one wavefront doing the books with everything unrolled took 7 us for a table of 8 cells.
 struct SmallTier { uint64_t base[2], layer_stride, slot_stride; };     // [plane], at the fetch's first layer
 // What every workgroup is told ...
