@@ -326,12 +326,12 @@ struct Lists {
     uint32_t cap = 0;                       // requests the three lists have room for
 };
 
-// Intermediate arrays of the KV resolve (classify_kv -> scan_groups -> compact_kv), one entry or row per table cell.
+// What the KV resolve leaves for its gathers besides the lists: see KvLists.
 struct KvWork {
-    Rec *tmp = nullptr;
-    uint8_t *kind = nullptr;
-    uint32_t *blk_counts = nullptr;
-    uint32_t *grp_totals = nullptr, *row_prefix = nullptr;     // large tables: the middle pass of the compaction
+    uint32_t *seg_miss = nullptr;           // one per table cell
+    uint32_t *counts = nullptr;             // [SC_N][SEGS]
+    uint32_t *row_groups = nullptr;
+    uint32_t n_seg = 0, seg_cells = 0;      // of the latest resolve
 };
 
 struct StreamState {
@@ -379,17 +379,16 @@ struct StreamState {
 // ends; the address is asked for once per device (scratch_of_device), with that device current, and only that
 // address is ever handed to a kernel - the array's name is a host-side stand-in, not a device address.
 constexpr uint32_t STATIC_CELLS = HARVEST_STATIC_MAX_CELLS;
-constexpr size_t STATIC_ROWS = (STATIC_CELLS + WG - 1) / WG;
+constexpr size_t STATIC_ROW_GROUPS = STATIC_CELLS / ROW_GROUP + 1;
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-constexpr size_t SO_TMP = 0;
-constexpr size_t SO_HBM = SO_TMP + align256((size_t)STATIC_CELLS * sizeof(Rec));
+constexpr size_t SO_HBM = 0;
 constexpr size_t SO_HOST = SO_HBM + align256((size_t)STATIC_CELLS * sizeof(Rec));
 constexpr size_t SO_MISS = SO_HOST + align256((size_t)STATIC_CELLS * sizeof(Rec));
-constexpr size_t SO_KIND = SO_MISS + align256((size_t)STATIC_CELLS * sizeof(uint32_t));
-constexpr size_t SO_BLK = SO_KIND + align256((size_t)STATIC_CELLS);
-constexpr size_t SO_CNT = SO_BLK + align256(STATIC_ROWS * BC_N * sizeof(uint32_t));
+constexpr size_t SO_SEG_MISS = SO_MISS + align256((size_t)STATIC_CELLS * sizeof(uint32_t));
+constexpr size_t SO_COUNTS = SO_SEG_MISS + align256((size_t)STATIC_CELLS * sizeof(uint32_t));
+constexpr size_t SO_ROWS = SO_COUNTS + align256(SC_N * SEGS * sizeof(uint32_t));
+constexpr size_t SO_CNT = SO_ROWS + align256(STATIC_ROW_GROUPS * sizeof(uint32_t));
 constexpr size_t STATIC_BYTES = SO_CNT + align256((C_N + 1) * sizeof(uint32_t));       // the counters and `snap`
-static_assert(STATIC_ROWS <= 1024, "the fixed scratch has no room for the grouped compaction of very large tables");
 
 static __device__ __align__(256) unsigned char scratch[STATIC_BYTES];
 
@@ -518,8 +517,7 @@ void free_stream_state(StreamState *ss)
         return;
     }
     for (Lists &l : ss->lists) { (void)hipFree(l.hbm); (void)hipFree(l.host); (void)hipFree(l.miss); }
-    (void)hipFree(ss->work.tmp); (void)hipFree(ss->work.kind); (void)hipFree(ss->work.blk_counts);
-    (void)hipFree(ss->work.grp_totals); (void)hipFree(ss->work.row_prefix);
+    (void)hipFree(ss->work.seg_miss); (void)hipFree(ss->work.counts); (void)hipFree(ss->work.row_groups);
     (void)hipFree(ss->cnt_block); (void)hipFree(ss->mark);
     (void)hipFree(ss->ctl_buf);
     if (ss->h_feedback) (void)hipHostFree(ss->h_feedback);
@@ -588,15 +586,12 @@ int ensure_req_cap(StreamState *ss, int cls, uint32_t n_req)
         HIP_TRY(hipStreamSynchronize(ss->side));
     }
     uint32_t cap = std::max<uint32_t>(1024, n_req + n_req / 4);
-    size_t n_rows = (cap + WG - 1) / WG;
     const bool kv = cls == HARVEST_KV;
-    void *fresh[8] = { nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr };
-    const size_t bytes[8] = { (size_t)cap * sizeof(Rec), (size_t)cap * sizeof(Rec), (size_t)cap * sizeof(uint32_t),
-                              kv ? (size_t)cap * sizeof(Rec) : 0, kv ? (size_t)cap : 0,
-                              kv ? n_rows * BC_N * sizeof(uint32_t) : 0,
-                              kv ? ((n_rows + WG - 1) / WG) * BC_N * sizeof(uint32_t) : 0,
-                              kv ? n_rows * 3 * sizeof(uint32_t) : 0 };
-    for (int i = 0; i < 8; ++i) {
+    void *fresh[6] = { nullptr, nullptr, nullptr, nullptr, nullptr, nullptr };
+    const size_t bytes[6] = { (size_t)cap * sizeof(Rec), (size_t)cap * sizeof(Rec), (size_t)cap * sizeof(uint32_t),
+                              kv ? (size_t)cap * sizeof(uint32_t) : 0, kv ? SC_N * SEGS * sizeof(uint32_t) : 0,
+                              kv ? (cap / ROW_GROUP + 1) * sizeof(uint32_t) : 0 };
+    for (int i = 0; i < 6; ++i) {
         if (!bytes[i]) continue;
         hipError_t e = hipMalloc(&fresh[i], bytes[i]);
         if (e != hipSuccess) {
@@ -609,10 +604,8 @@ int ensure_req_cap(StreamState *ss, int cls, uint32_t n_req)
     l.hbm = (Rec *)fresh[0]; l.host = (Rec *)fresh[1]; l.miss = (uint32_t *)fresh[2];
     if (kv) {
         KvWork &w = ss->work;
-        (void)hipFree(w.tmp); (void)hipFree(w.kind); (void)hipFree(w.blk_counts); (void)hipFree(w.grp_totals);
-        (void)hipFree(w.row_prefix);
-        w.tmp = (Rec *)fresh[3]; w.kind = (uint8_t *)fresh[4]; w.blk_counts = (uint32_t *)fresh[5];
-        w.grp_totals = (uint32_t *)fresh[6]; w.row_prefix = (uint32_t *)fresh[7];
+        (void)hipFree(w.seg_miss); (void)hipFree(w.counts); (void)hipFree(w.row_groups);
+        w.seg_miss = (uint32_t *)fresh[3]; w.counts = (uint32_t *)fresh[4]; w.row_groups = (uint32_t *)fresh[5];
         ss->last_kv.valid = false;              // the lists that fetch left are gone
     }
     l.cap = cap;
@@ -692,7 +685,6 @@ constexpr uint64_t SMALL_FETCH_CELLS = 4096;      // block tables up to this man
 constexpr uint64_t SMALL_FETCH_TILES = 1u << 22;      // and never more workgroups than this in x
 constexpr uint64_t DEAD_TILES = 20000;                // nor with more workgroups than this (8 us) for cells that ask for nothing
 constexpr uint32_t MARKED_BATCH_IDS = 32768;      // routing-id batches beyond this take the two-kernel resolve
-constexpr uint32_t GROUPED_SCAN_ROWS = 1024;      // block tables of more than 262 144 cells take the three-kernel compaction
 
 uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t)((chunk_bytes + tile - 1) / tile); }
 
@@ -866,11 +858,11 @@ uint32_t host_workgroups(const harvest_ctx *ctx, uint32_t nthr, uint32_t loads =
 // into the destination.
 int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState &c, int cls, const Lists &lists, uint64_t max_req,
                    uint64_t dst_base0, uint64_t dst_base1, const HmArgs *hm = nullptr, uint32_t n_rep = 1,
-                   uint64_t dst_step = 0, int64_t layer_delta = 0, bool repeat = false, uint32_t n_seq = 0, uint32_t max_blocks = 0)
+                   uint64_t dst_step = 0, int64_t layer_delta = 0, uint32_t books = BOOKS_COUNTED, uint32_t n_seq = 0, uint32_t max_blocks = 0,
+                   uint32_t *info = nullptr)
 {
     // layer_delta: the lists were made for another layer; an object has the same slot in every layer, so adding that many
-    // layer strides to every pool base retargets them.  repeat: these requests have been counted for the lists' first
-    // use only - add them to the running totals again.
+    // layer strides to every pool base retargets them.  books: see GatherRest.
     const ClassDev cd = class_dev(c);
     const uint32_t planes = c.cfg.n_planes;
     // the head-major gather runs 256 threads per workgroup, the token-major one gather_threads; a tile is 16 bytes per thread
@@ -920,21 +912,27 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
     const uint32_t host_wgs = host_tier ? host_workgroups(ctx, nthr, ga.host_loads) : 0;
     const uint32_t max_wgs = MAX_GRID - host_wgs;
     const uint32_t hbm_wgs = grid_for(fold ? want * planes : want, ctx->gather_grid ? std::min(ctx->gather_grid, max_wgs) : max_wgs);
-    GatherBooks books{};
-    books.report = ss->d_feedback + cls;
-    books.n_seq = n_seq; books.max_blocks = max_blocks;
-    books.lease = ctx->d_lease;
-    books.totals = repeat ? ctx->d_totals + cls * C_N : nullptr;
+    GatherRest rest{};
+    rest.host_recs = lists.host;
+    const bool kv = cls == HARVEST_KV;             // the lists of an expert fetch are one segment
+    rest.counts = kv ? ss->work.counts : lists.cnt + C_HOST_REQ;
+    rest.n_seg = kv ? ss->work.n_seg : 1; rest.seg_cells = kv ? ss->work.seg_cells : 0;
+    rest.n_seq = n_seq; rest.max_blocks = max_blocks;
+    rest.lease = ctx->d_lease;
+    rest.report = ss->d_feedback + cls;
+    rest.books = books;
+    rest.cnt = lists.cnt; rest.info = info; rest.miss_idx = lists.miss; rest.seg_miss = ss->work.seg_miss;
+    rest.totals = ctx->d_totals + cls * C_N;
     auto launch = [&](uint32_t n_host, uint32_t n_hbm, hipStream_t s, hipEvent_t begin, hipEvent_t end) -> int {
         ga.n_host = n_host;
         ga.hbm_wgs = n_hbm;
         const dim3 g(n_host + n_hbm, n_hbm && !fold ? planes : 1, n_hbm ? ga.n_rep : 1);
-        const Rec *l_hbm = lists.hbm, *l_host = lists.host;
+        const Rec *l_hbm = lists.hbm;
         const uint32_t *cnt = lists.cnt;
         if (hm) {
             auto kernel = planes == 2 ? gather_hm<2> : gather_hm<1>;
-            if (!begin) return launch_last(ctx, ss, recording, kernel, g, dim3(nthr), l_hbm, l_host, cnt, ga, *hm, books);
-            hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, l_host, cnt, ga, *hm, books);
+            if (!begin) return launch_last(ctx, ss, recording, kernel, g, dim3(nthr), l_hbm, cnt, ga, *hm, rest);
+            hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, cnt, ga, *hm, rest);
         } else {
             auto pick = [&](auto k64, auto k128, auto k256) { return nthr == 64 ? k64 : (nthr == 128 ? k128 : k256); };
             auto of = [&](auto multi) {
@@ -944,8 +942,8 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
                                    : pick(gather<64, 1, false, M>, gather<128, 1, false, M>, gather<256, 1, false, M>);
             };
             auto kernel = ga.n_rep > 1 ? of(std::true_type{}) : of(std::false_type{});
-            if (!begin) return launch_last(ctx, ss, recording, kernel, g, dim3(nthr), l_hbm, l_host, cnt, ga, books);
-            hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, l_host, cnt, ga, books);
+            if (!begin) return launch_last(ctx, ss, recording, kernel, g, dim3(nthr), l_hbm, cnt, ga, rest);
+            hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, cnt, ga, rest);
         }
         HIP_TRY(hipGetLastError());
         return HARVEST_OK;
@@ -957,7 +955,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
             for (int t = 0; t < 3; ++t)
                 for (uint32_t p = 0; p < 2; ++p) ga.src_base[t][p] += (uint64_t)MAX_GRID_Z * ga.layer_stride[t];
             for (uint32_t p = 0; p < 2; ++p) ga.dst_base[p] += (uint64_t)MAX_GRID_Z * dst_step;
-            books.totals = nullptr;
+            rest.books = BOOKS_NONE;
         }
         if (!profile) {
             if ((rc = launch(host_wgs, hbm_wgs, ss->s, nullptr, nullptr))) return rc;
@@ -1154,8 +1152,8 @@ int init_device(harvest_ctx *ctx, const harvest_config *cfg)
             l.hbm = (Rec *)(base + SO_HBM); l.host = (Rec *)(base + SO_HOST); l.miss = (uint32_t *)(base + SO_MISS);
             l.cnt = (uint32_t *)(base + SO_CNT); l.cap = STATIC_CELLS;
             ss.snap = l.cnt + C_N;
-            ss.work.tmp = (Rec *)(base + SO_TMP); ss.work.kind = base + SO_KIND;
-            ss.work.blk_counts = (uint32_t *)(base + SO_BLK);
+            ss.work.seg_miss = (uint32_t *)(base + SO_SEG_MISS); ss.work.counts = (uint32_t *)(base + SO_COUNTS);
+            ss.work.row_groups = (uint32_t *)(base + SO_ROWS);
         }
     }
     HIP_TRY(hipDeviceSynchronize());
@@ -1754,7 +1752,6 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     if ((rc = ensure_req_cap(ss, HARVEST_KV, (uint32_t)total))) return rc;
     Lists lists = ss->lists[HARVEST_KV];
     if (miss_out) lists.miss = miss_out;
-    const KvWork &work = ss->work;
     uint32_t *cnt = lists.cnt;
     const bool recording = is_capturing(ss->s);
     if (recording) ss->recorded = true;
@@ -1836,30 +1833,22 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         remember(false);
         return HARVEST_OK;
     }
-    uint32_t n_wg = (uint32_t)((total + WG - 1) / WG);
-    hipLaunchKernelGGL(classify_kv, dim3(n_wg), dim3(WG), 0, ss->s, class_dev(c), layer, d_block_table, d_n_blocks, n_seq,
-                       max_blocks, d_seq_dst_block, dst_capacity_blocks, work.tmp, work.kind, work.blk_counts,
-                       d_seq_cap_blocks, (uint64_t)hm.ups * 16);
-    HIP_TRY(hipGetLastError());
-    // Beyond this many rows of workgroup totals the compaction's own adding-up of all earlier rows (quadratic) costs more
-    // than one more small kernel that groups them first (2 M cells: 70 us against about 10).
-    const bool grouped = n_wg > GROUPED_SCAN_ROWS;
-    if (grouped) {
-        hipLaunchKernelGGL(scan_groups, dim3((n_wg + WG - 1) / WG), dim3(WG), 0, ss->s, (const uint32_t *)work.blk_counts, n_wg,
-                           work.grp_totals, work.row_prefix);
-        HIP_TRY(hipGetLastError());
-    }
-    hipLaunchKernelGGL(compact_kv, dim3(n_wg), dim3(WG), 0, ss->s, (uint32_t)total, (const Rec *)work.tmp,
-                       (const uint8_t *)work.kind, (const uint32_t *)work.blk_counts, lists.hbm, lists.host,
-                       lists.miss, cnt, ctx->d_totals + HARVEST_KV * C_N,
-                       grouped ? (const uint32_t *)work.grp_totals : (const uint32_t *)nullptr,
-                       grouped ? (const uint32_t *)work.row_prefix : (const uint32_t *)nullptr, info);
-    HIP_TRY(hipGetLastError());
+    KvWork &w = ss->work;
+    const bool wide = total > (uint64_t)SEGS * WG;         // more cells than SEGS workgroups of WG threads have lanes
+    const uint32_t seg_threads = wide ? 1024 : WG;
+    w.seg_cells = (uint32_t)((total + (uint64_t)SEGS * seg_threads - 1) / ((uint64_t)SEGS * seg_threads)) * seg_threads;
+    w.n_seg = (uint32_t)((total + w.seg_cells - 1) / w.seg_cells);
+    const bool many_rows = n_seq > ROW_GROUP;
+    if (many_rows && (rc = launch(ss->s, sum_rows, dim3(n_seq / ROW_GROUP + 1), dim3(WG), d_n_blocks, n_seq, max_blocks, w.row_groups))) return rc;
+    const KvLists out{ lists.hbm, lists.host, w.seg_miss, w.counts, cnt, many_rows ? w.row_groups : nullptr, w.seg_cells };
+    if ((rc = launch(ss->s, wide ? classify_kv<1024> : classify_kv<WG>, dim3(w.n_seg), dim3(seg_threads), class_dev(c), layer, d_block_table, d_n_blocks,
+                     (uint32_t)total, max_blocks, d_seq_dst_block, dst_capacity_blocks, out, d_seq_cap_blocks, (uint64_t)hm.ups * 16)))
+        return rc;
     ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
     // lists recorded into a graph exist only once the graph has been replayed: nothing to use again
     remember(!recording);
     return launch_gathers(ctx, ss, recording, c, HARVEST_KV, lists, total, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
-                          head_major ? &hm : nullptr, n_layers, dst_layer_stride, 0, false, n_seq, max_blocks);
+                          head_major ? &hm : nullptr, n_layers, dst_layer_stride, 0, BOOKS_RESOLVED, n_seq, max_blocks, info);
 }
 
 int harvest_fetch_kv_again(harvest_ctx *ctx, uint32_t layer, void *d_dst_k, void *d_dst_v, void *stream)
@@ -1892,7 +1881,7 @@ int harvest_fetch_kv_again(harvest_ctx *ctx, uint32_t layer, void *d_dst_k, void
     }
     ss->last_cls = HARVEST_KV; ss->counted[HARVEST_KV] = true;
     return launch_gathers(ctx, ss, false, c, HARVEST_KV, ss->lists[HARVEST_KV], (uint64_t)k.n_seq * k.max_blocks, (uint64_t)d_dst_k, (uint64_t)d_dst_v,
-                          head_major ? &hm : nullptr, 1, 0, (int64_t)layer - (int64_t)k.layer, true,
+                          head_major ? &hm : nullptr, 1, 0, (int64_t)layer - (int64_t)k.layer, BOOKS_AGAIN,
                           k.n_seq, k.max_blocks);
 }
 

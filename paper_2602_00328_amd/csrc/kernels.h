@@ -2,13 +2,13 @@
 //
 // Everything here is byte movement plus a few integers of metadata: no floating point, no MFMA.
 //
-//   classify_kv + compact_kv : directory lookup (paper Section 5.2: the extended KV block table), classification of
-//                              every request by tier, and an ORDER-PRESERVING compaction into an HBM list and a host
-//                              (miss) list: wavefront ballots rank the lanes, LDS carries the wave totals, and the
-//                              workgroup totals of the first kernel become the offsets of the second.  Keeping the
+//   classify_kv              : directory lookup (paper Section 5.2: the extended KV block table), classification of
+//                              every request by tier, and an ORDER-PRESERVING compaction: into one HBM list whose places follow
+//                              from the block table alone, and per segment of the table into the host's requests and the misses:
+//                              wavefront ballots rank the lanes, LDS carries the wave totals.  Keeping the
 //                              lists in request order makes the gather's writes one ascending stream, worth ~6% of
 //                              HBM bandwidth over lists ordered by racing atomics.
-//                              Very large tables get a middle pass (scan_groups) that groups the workgroup totals.
+//                              Tables of very many rows get a pass in front (sum_rows) that adds up groups of row lengths.
 //   fetch_kv_small           : small block tables - the whole fetch in one launch: a workgroup per tile of HBM-tier payload that
 //                              resolves its own cell, a couple of dozen that find the host tier's cells, one for the books.
 //   resolve_experts          : the same for expert weights (Section 4.3: residency map) - one workgroup forms the
@@ -95,9 +95,7 @@ struct MoveList { MoveRec r[MOVE_INLINE]; };
 struct DirList { uint64_t entry[DIR_INLINE]; uint32_t id[DIR_INLINE]; };
 
 // per-fetch counters (uint32) and running totals (uint64) share these indices
-enum { C_REQ = 0, C_LOCAL, C_CACHE, C_HOST, C_LOST, C_INVALID, C_HBM_REQ, C_HOST_REQ, C_MISS, C_N = 16 };
-// request kinds handed from classify_kv to compact_kv
-enum { K_NONE = 0, K_HBM = 1, K_HOST = 2, K_LOST = 3 };
+enum { C_REQ = 0, C_LOCAL, C_CACHE, C_HOST, C_LOST, C_INVALID, C_HBM_REQ, C_HOST_REQ, C_MISS, C_LIST, C_N = 16 };
 
 struct ClassDev {
     const uint64_t *dir;
@@ -132,19 +130,52 @@ struct GatherArgs {
 // In pinned memory, one per class and stream: requests of either tier of the latest fetch whose kernels have run - hints for the
 // next launch - and the rows and columns of the block table they were asked for with (experts: zero).
 struct Report { uint32_t hbm, host, n_seq, max_blocks; };
-// What a gather reports besides the bytes; every pointer may be null.
-struct GatherBooks {
-    Report *report;
-    uint32_t n_seq, max_blocks;
+// The table cells of a KV fetch are resolved in up to SEGS segments of consecutive cells, by a workgroup each, which leaves its
+// requests to the host and its misses at the start of its own stretch of a list and says in counts[SC_* * SEGS + segment] how many
+// there are.  (Four segments to a lane: a wavefront that reads the counts can say which segment has the n-th request without
+// touching memory again, see HostList.)
+constexpr uint32_t SEGS = 256;
+enum { SC_HOST = 0, SC_MISS, SC_REQ, SC_LOCAL, SC_INVALID, SC_N };
+constexpr uint32_t ROW_GROUP = 4096;     // rows whose lengths sum_rows adds up
+// What only the host tier's workgroups and the one that keeps the books need.  They read it where they need it: as an ordinary argument
+// it would be loaded at the start of every workgroup.
+enum { BOOKS_NONE = 0, BOOKS_COUNTED, BOOKS_AGAIN, BOOKS_RESOLVED };
+struct GatherRest {
+    const Rec *host_recs;
+    const uint32_t *counts;              // of the segments
+    uint32_t n_seg, seg_cells;
+    uint32_t n_seq, max_blocks;          // for the report
     unsigned long long *lease;           // see link_announce
-    unsigned long long *totals;          // running totals, to which a fetch repeated from older lists adds their counters
+    Report *report;
+    // Books, by the first BOOK_WGS workgroups of the HBM tier once they have copied their tiles.  BOOKS_COUNTED: *cnt is there, report it.
+    // BOOKS_AGAIN: and add it to the running totals, for a fetch repeated from older lists.  BOOKS_RESOLVED: the segments' counts make
+    // up *cnt, the running totals and the caller's copy (info, may be null), and their misses one list.
+    uint32_t books, pad;
+    uint32_t *cnt, *info, *miss_idx;
+    const uint32_t *seg_miss;
+    unsigned long long *totals;
 };
+constexpr uint32_t BOOK_WGS = 16;
+typedef const __attribute__((address_space(4))) GatherRest k_GatherRest;
+template <uint32_t AT> __device__ inline k_GatherRest &gather_rest()       // AT: where it is among the kernel's arguments
+{
+    return *(k_GatherRest *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + AT);
+}
 
 __device__ inline uint32_t lane_id() { return __lane_id(); }
 
 // A value that all lanes of the wavefront have, for the scalar registers.
 __device__ inline uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ inline uint64_t uniform(uint64_t x) { return (uint64_t)uniform((uint32_t)(x >> 32)) << 32 | uniform((uint32_t)x); }
+// These values are in registers from here on.  An argument is loaded where it is used, and every such load is a wait; a tile's workgroup
+// has to wait for its directory entry anyway and gets its addresses meanwhile (300 blocks 9.77 us without, 9.69 with).
+template <typename A, typename B, typename C, typename D> __device__ inline void in_registers(A a, B b, C c, D d)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
+#endif
+}
+
 // Selects instead of indexing: a variable index into a kernel-argument struct would send it to scratch memory.
 __device__ inline uint32_t slots_of(const ClassDev &c, int tier)
 {
@@ -156,6 +187,7 @@ __device__ inline uint64_t chunk_offset(const ClassDev &c, int tier, uint32_t la
     uint64_t ss = tier == T_HOST ? c.slot_stride[T_HOST] : (tier == T_CACHE ? c.slot_stride[T_CACHE] : c.slot_stride[T_LOCAL]);
     return (uint64_t)layer * ls + (uint64_t)slot * ss;
 }
+__device__ inline bool in_hbm(uint32_t tier) { return (tier + 1) & 2; }        // T_CACHE or T_LOCAL
 __device__ inline uint64_t src_base_of(const GatherArgs &a, uint32_t tier, uint32_t plane)
 {
     uint64_t h = plane ? a.src_base[T_HOST][1] : a.src_base[T_HOST][0];
@@ -187,13 +219,6 @@ __device__ inline uint32_t wave_sum(uint32_t v)
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
-
-// ---------------------------------------------------------------------------------------------------------
-// KV, pass 1: one thread per (sequence, block-table column) looks its block up and says what kind of request
-// it is; every workgroup leaves its totals in blk_counts[BC_N * blockIdx + ...].  Nothing is accumulated with
-// atomics and nothing needs zeroing, so a fetch can be replayed from a captured graph as it is.
-// ---------------------------------------------------------------------------------------------------------
-enum { BC_HBM = 0, BC_HOST, BC_MISS, BC_REQ, BC_LOCAL, BC_CACHE, BC_LOST, BC_INVALID, BC_N = 8 };
 
 // What cell r of the block table asks for: -1 nothing (beyond the row's length), 0..3 the tier of its block, 4 an invalid
 // request (unknown block, or a destination that does not fit).  For tiers 0..2 rec names source and destination.  The loads
@@ -228,164 +253,158 @@ __device__ inline int resolve_cell(const ClassDev &c, uint32_t layer, const int3
     return tier != T_NONE && entry_slot(e) >= slots_of(c, tier) ? 4 : tier;     // never for a directory the library wrote
 }
 
-__global__ __launch_bounds__(WG) void classify_kv(ClassDev c, uint32_t layer, const int32_t *__restrict__ table,
-                                                  const int32_t *__restrict__ n_blocks, uint32_t n_seq,
-                                                  uint32_t max_blocks, const uint64_t *__restrict__ seq_dst_block,
-                                                  uint64_t dst_cap, Rec *__restrict__ tmp, uint8_t *__restrict__ kind,
-                                                  uint32_t *__restrict__ blk_counts,
-                                                  const uint32_t *__restrict__ seq_cap_blocks, uint64_t strip_bytes)
+// ---------------------------------------------------------------------------------------------------------
+// KV: every (sequence, block-table column) looks its block up, once.  The HBM list has an entry for every request, in request order; one
+// that HBM does not serve is marked T_NONE and the gather passes over it.  So the place of an entry follows from the block table alone -
+// the lengths of the rows before it - and no workgroup has to know what another found in the directory: one launch, where counting the
+// tiers first and placing the entries second took two.  A chain of a few memory latencies bounds it, and the way between kernels that
+// fill the device: a fetch costs 4.9 us more than the same one repeated from its lists, 7.8 with the second launch (3 536 blocks of
+// 2 x 32 KiB into the head-major layout 86.7 us before, 83.9 now; 15 125 token-major 315.1 and 311.7).
+// What the host serves, and the misses, stay in the segment's own stretch; the gather's workgroups put the stretches together while
+// the HBM tier is on its way (HostList, keep_books).  Nothing is accumulated with atomics and nothing needs zeroing, so a fetch can be
+// replayed from a captured graph as it is.
+// ---------------------------------------------------------------------------------------------------------
+__device__ inline uint32_t row_requests(int32_t n, uint32_t max_blocks) { return n <= 0 ? 0u : (uint32_t)n < max_blocks ? (uint32_t)n : max_blocks; }
+
+struct KvLists {
+    Rec *hbm, *host;
+    uint32_t *miss, *counts, *cnt;       // misses and counts of the segments; of the fetch's counters, C_LIST is written here
+    const uint32_t *row_groups;          // from sum_rows, or null: few rows
+    uint32_t seg_cells;                  // a multiple of the workgroup's threads
+};
+
+template <int NTHR>
+__global__ __launch_bounds__(NTHR) void classify_kv(ClassDev c, uint32_t layer, const int32_t *__restrict__ table,
+                                                    const int32_t *__restrict__ n_blocks, uint32_t total, uint32_t max_blocks,
+                                                    const uint64_t *__restrict__ seq_dst_block, uint64_t dst_cap, KvLists l,
+                                                    const uint32_t *__restrict__ seq_cap_blocks, uint64_t strip_bytes)
 {
     // seq_cap_blocks != nullptr selects the head-major working layout: sequence s owns seq_cap_blocks[s] destination
     // blocks, laid out [head][token][head_bytes]; strip_bytes = block_tokens * head_bytes is what one block adds to
     // one head's strip.  The record then carries the sequence's capacity (in blocks) in bits [63:48] of src.
-    __shared__ uint32_t s_cnt[BC_N];
-    uint32_t tid = threadIdx.x;
-    uint32_t r = blockIdx.x * WG + tid;
-    if (tid < BC_N) s_cnt[tid] = 0;
-    __syncthreads();
-    uint32_t total = n_seq * max_blocks;
-    int tier = -1;                       // -1 no request, 0..3 tier, 4 invalid
-    Rec rec = { 0, 0 };
-    if (r < total)
-        tier = resolve_cell(c, layer, table, n_blocks, max_blocks, seq_dst_block, dst_cap, seq_cap_blocks, strip_bytes, r, rec);
-    uint32_t k = (tier == T_LOCAL || tier == T_CACHE) ? K_HBM
-                                                      : (tier == T_HOST ? K_HOST : (tier == T_NONE ? K_LOST : K_NONE));
-    if (r < total) {
-        kind[r] = (uint8_t)k;
-        if (k == K_HBM || k == K_HOST) tmp[r] = rec;
+    constexpr uint32_t WAVES_N = NTHR / 64;
+    __shared__ uint32_t s_before[WAVES_N], s_sum[2][SC_N][WAVES_N];
+    const uint32_t tid = threadIdx.x, wave = tid >> 6;
+    const uint32_t first = blockIdx.x * l.seg_cells, end = total - first < l.seg_cells ? total : first + l.seg_cells;
+    const uint32_t s0 = first / max_blocks, j0 = first - s0 * max_blocks;
+    // requests of the rows before the segment, and of its first row before its first cell
+    uint32_t before = 0, s = 0;
+    if (l.row_groups) {
+        s = s0 / ROW_GROUP * ROW_GROUP;
+        for (uint32_t g = tid; g < s0 / ROW_GROUP; g += NTHR) before += l.row_groups[g];
     }
-    // wave ballots -> LDS -> one row of totals per workgroup
-    const int which[BC_N] = { BC_HBM, BC_HOST, BC_MISS, BC_REQ, BC_LOCAL, BC_CACHE, BC_LOST, BC_INVALID };
-    const bool pred[BC_N] = { k == K_HBM, k == K_HOST, k == K_HOST || k == K_LOST, tier >= 0,
-                              tier == T_LOCAL, tier == T_CACHE, tier == T_NONE, tier == 4 };
+    for (s += tid; s < s0; s += NTHR) before += row_requests(n_blocks[s], max_blocks);
+    if (tid == 0) before += row_requests(n_blocks[s0], j0);
+    uint32_t run[SC_N] = { 0, 0, 0, 0, 0 };               // of the segment so far
+    uint32_t turn = 0;
+    for (uint32_t r0 = first; r0 < end; r0 += NTHR, turn ^= 1) {
+        const uint32_t r = r0 + tid;
+        int tier = -1;                                    // -1 no request, 0..3 tier, 4 invalid
+        Rec rec = { 0, 0 };
+        if (r < end)
+            tier = resolve_cell(c, layer, table, n_blocks, max_blocks, seq_dst_block, dst_cap, seq_cap_blocks, strip_bytes, r, rec);
+        const bool is[SC_N] = { tier == T_HOST, tier == T_HOST || tier == T_NONE, tier >= 0, tier == T_LOCAL, tier == 4 };
+        uint32_t rank[SC_N];
 #pragma unroll
-    for (int i = 0; i < BC_N; ++i) {
-        uint32_t n = (uint32_t)__popcll(__ballot(pred[i]));
-        if (lane_id() == 0 && n) atomicAdd(&s_cnt[which[i]], n);
+        for (int k = 0; k < SC_N; ++k) {
+            uint32_t in_wave;
+            rank[k] = wave_rank(is[k], in_wave);
+            if (lane_id() == 0) s_sum[turn][k][wave] = in_wave;
+        }
+        if (r0 == first) {
+            before = wave_sum(before);
+            if (lane_id() == 0) s_before[wave] = before;
+        }
+        __syncthreads();                                  // (two sets of sums in turn: nobody reads the one that is written next)
+        if (r0 == first) {
+            before = 0;
+#pragma unroll
+            for (uint32_t w = 0; w < WAVES_N; ++w) before += s_before[w];
+        }
+#pragma unroll
+        for (int k = 0; k < SC_N; ++k) {
+            rank[k] += run[k];
+#pragma unroll
+            for (uint32_t w = 0; w < WAVES_N; ++w) {
+                const uint32_t n = s_sum[turn][k][w];
+                rank[k] += w < wave ? n : 0;
+                run[k] += n;
+            }
+        }
+        if (is[SC_HOST]) l.host[first + rank[SC_HOST]] = rec;
+        if (is[SC_MISS]) l.miss[first + rank[SC_MISS]] = r;
+        if (tier != T_LOCAL && tier != T_CACHE) rec = { T_NONE, 0 };
+        if (is[SC_REQ]) l.hbm[before + rank[SC_REQ]] = rec;
     }
-    __syncthreads();
-    if (tid < BC_N) blk_counts[blockIdx.x * BC_N + tid] = s_cnt[tid];
+    if (tid < SC_N) l.counts[tid * SEGS + blockIdx.x] = tid == SC_HOST ? run[SC_HOST] : tid == SC_MISS ? run[SC_MISS] : tid == SC_REQ ? run[SC_REQ]
+                                                      : tid == SC_LOCAL ? run[SC_LOCAL] : run[SC_INVALID];
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) l.cnt[C_LIST] = before + run[SC_REQ];
 }
 
-// KV, middle pass for large tables only.  In pass 2 every workgroup adds up the rows of all workgroups before it: fine for
-// a few hundred rows, quadratic beyond (a table of 8 M cells has 32 768 rows: 17 GB of reads).  This pass makes groups of
-// WG rows: workgroup g leaves the totals of its group in grp_totals[g] and, for each of its rows, the list counters of the
-// group's earlier rows in row_prefix[row] - pass 2 then adds up whole groups only.
-__global__ __launch_bounds__(WG) void scan_groups(const uint32_t *__restrict__ blk_counts, uint32_t n_rows,
-                                                  uint32_t *__restrict__ grp_totals, uint32_t *__restrict__ row_prefix)
+// Block tables of many rows: what each ROW_GROUP of them asks for, so that a segment need not add up all rows before it.
+__global__ __launch_bounds__(WG) void sum_rows(const int32_t *__restrict__ n_blocks, uint32_t n_seq, uint32_t max_blocks, uint32_t *__restrict__ row_groups)
 {
-    __shared__ uint32_t s_wave[WAVES][BC_N];
-    uint32_t tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
-    uint32_t row = blockIdx.x * WG + tid;
-    uint32_t v[BC_N], incl[3];
-#pragma unroll
-    for (int i = 0; i < BC_N; ++i) v[i] = row < n_rows ? blk_counts[row * BC_N + i] : 0u;
-    // inclusive scan of the three list counters (BC_HBM, BC_HOST, BC_MISS are 0, 1, 2) within the wavefront
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        uint32_t x = v[k];
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            uint32_t y = __shfl_up(x, o);
-            if (lane >= (uint32_t)o) x += y;
-        }
-        incl[k] = x;
+    __shared__ uint32_t s_wave[WAVES];
+    uint32_t sum = 0;
+    for (uint32_t i = threadIdx.x; i < ROW_GROUP; i += WG) {
+        const uint64_t s = (uint64_t)blockIdx.x * ROW_GROUP + i;
+        if (s < n_seq) sum += row_requests(n_blocks[s], max_blocks);
     }
-    uint32_t tot[BC_N];
-#pragma unroll
-    for (int i = 0; i < BC_N; ++i) tot[i] = wave_sum(v[i]);
-    if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < BC_N; ++i) s_wave[wave][i] = tot[i];
-    }
+    sum = wave_sum(sum);
+    if (lane_id() == 0) s_wave[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (row < n_rows) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            uint32_t before = 0;
-            for (uint32_t w = 0; w < wave; ++w) before += s_wave[w][k];
-            row_prefix[row * 3 + k] = before + incl[k] - v[k];
-        }
-    }
-    if (tid < BC_N) {
-        uint32_t t = 0;
-        for (int w = 0; w < WAVES; ++w) t += s_wave[w][tid];
-        grp_totals[blockIdx.x * BC_N + tid] = t;
-    }
+    if (threadIdx.x) return;
+    for (int w = 1; w < WAVES; ++w) sum += s_wave[w];
+    row_groups[blockIdx.x] = sum;
 }
 
-// KV, pass 2: list position = (totals of the workgroups before mine) + (totals of the waves before mine in the
-// workgroup) + (rank in my wave), so the lists come out in request order.  The last workgroup has seen every
-// total: it writes the counters of this fetch and adds them to the running totals.
-__global__ __launch_bounds__(WG) void compact_kv(uint32_t total, const Rec *__restrict__ tmp,
-                                                 const uint8_t *__restrict__ kind, const uint32_t *__restrict__ blk_counts,
-                                                 Rec *__restrict__ hbm_recs, Rec *__restrict__ host_recs,
-                                                 uint32_t *__restrict__ miss_idx, uint32_t *cnt,
-                                                 unsigned long long *totals, const uint32_t *__restrict__ grp_totals,
-                                                 const uint32_t *__restrict__ row_prefix, uint32_t *__restrict__ info)
-{
-    // grp_totals / row_prefix: what scan_groups left (large tables), or null - then the rows themselves are added up.
-    __shared__ uint32_t s_pre[BC_N];
-    __shared__ uint32_t s_wave[WAVES][3];
-    uint32_t tid = threadIdx.x, wave = tid >> 6;
-    uint32_t r = blockIdx.x * WG + tid;
-    bool last = blockIdx.x == gridDim.x - 1;
-    if (wave == 0) {
-        uint32_t a[BC_N];
+// One row of the segments' counts in a wavefront's registers, as running sums: lane i has segments 4 i to 4 i + 3.
+struct SegSums {
+    uint32_t upto[4], before, total;
+    template <typename P> __device__ inline SegSums(P counts, uint32_t n_seg)
+    {
+        const uint32_t at = lane_id() * 4;
+        uint32_t n[4];
 #pragma unroll
-        for (int i = 0; i < BC_N; ++i) a[i] = 0;
-        const uint32_t *rows = grp_totals ? grp_totals : blk_counts;
-        uint32_t n_all = grp_totals ? (gridDim.x + WG - 1) / WG : gridDim.x;
-        uint32_t mine = grp_totals ? blockIdx.x / WG : blockIdx.x;
-        uint32_t upto = last ? n_all : mine;                    // the last workgroup sums everybody, itself included
-        for (uint32_t b = lane_id(); b < upto; b += 64) {
+        for (uint32_t i = 0; i < 4; ++i) n[i] = counts[at + i < n_seg ? at + i : 0];
 #pragma unroll
-            for (int i = 0; i < BC_N; ++i) a[i] += rows[b * BC_N + i];
+        for (uint32_t i = 0; i < 4; ++i) upto[i] = (i ? upto[i ? i - 1 : 0] : 0) + (at + i < n_seg ? n[i] : 0);
+        uint32_t all = upto[3];
+#pragma unroll
+        for (uint32_t o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(all, o);
+            if (lane_id() >= o) all += y;
         }
+        before = all - upto[3];
 #pragma unroll
-        for (int i = 0; i < BC_N; ++i) a[i] = wave_sum(a[i]);
-        if (lane_id() == 0) {
-#pragma unroll
-            for (int i = 0; i < BC_N; ++i) s_pre[i] = a[i];
-        }
+        for (uint32_t i = 0; i < 4; ++i) upto[i] += before;
+        total = lane_value(all, 63);
     }
-    uint32_t k = r < total ? kind[r] : (uint32_t)K_NONE;
-    uint32_t n_hbm, n_host, n_miss;
-    uint32_t p_hbm = wave_rank(k == K_HBM, n_hbm);
-    uint32_t p_host = wave_rank(k == K_HOST, n_host);
-    uint32_t p_miss = wave_rank(k == K_HOST || k == K_LOST, n_miss);
-    if (lane_id() == 0) { s_wave[wave][0] = n_hbm; s_wave[wave][1] = n_host; s_wave[wave][2] = n_miss; }
-    __syncthreads();
-    uint32_t b_hbm = s_pre[BC_HBM], b_host = s_pre[BC_HOST], b_miss = s_pre[BC_MISS];
-    if (last) {                                  // its sums included its own row (its whole group): take that out
-        const uint32_t *own = grp_totals ? grp_totals + (blockIdx.x / WG) * BC_N : blk_counts + blockIdx.x * BC_N;
-        b_hbm -= own[BC_HBM];
-        b_host -= own[BC_HOST];
-        b_miss -= own[BC_MISS];
+    // The segment that has number idx of the list (idx < total, the same in all lanes), and how many are in the segments before it.
+    __device__ inline uint32_t find(uint32_t idx, uint32_t &in_front) const
+    {
+        const uint32_t k = (uint32_t)__popcll(__ballot(upto[3] <= idx));
+        const uint32_t u0 = lane_value(upto[0], k), u1 = lane_value(upto[1], k), u2 = lane_value(upto[2], k);
+        in_front = idx >= u2 ? u2 : idx >= u1 ? u1 : idx >= u0 ? u0 : lane_value(before, k);
+        return 4 * k + (idx >= u0) + (idx >= u1) + (idx >= u2);
     }
-    if (row_prefix) {                            // the rows of my group before mine
-        b_hbm += row_prefix[blockIdx.x * 3 + BC_HBM];
-        b_host += row_prefix[blockIdx.x * 3 + BC_HOST];
-        b_miss += row_prefix[blockIdx.x * 3 + BC_MISS];
+};
+// The host's requests in request order.  (Constant address space: the entries come by scalar loads, which wait for none of the
+// payload's accesses; as vector loads behind the stores 402 MB beside another stream's copy took 8.7 ms instead of 7.6.)
+typedef const __attribute__((address_space(4))) Rec k_Rec;
+struct HostList {
+    k_Rec *recs;
+    uint32_t seg_cells;
+    SegSums sums;
+    __device__ inline HostList(k_GatherRest &r) : recs((k_Rec *)(uint64_t)r.host_recs), seg_cells(r.seg_cells), sums(r.counts + SC_HOST * SEGS, r.n_seg) {}
+    __device__ inline Rec operator[](uint32_t idx) const
+    {
+        uint32_t in_front;
+        const uint32_t seg = sums.find(idx, in_front);
+        k_Rec &x = recs[(uint64_t)seg * seg_cells + (idx - in_front)];
+        return { x.src, x.dst };
     }
-    for (uint32_t w = 0; w < wave; ++w) { b_hbm += s_wave[w][0]; b_host += s_wave[w][1]; b_miss += s_wave[w][2]; }
-    if (k == K_HBM) hbm_recs[b_hbm + p_hbm] = tmp[r];
-    if (k == K_HOST) host_recs[b_host + p_host] = tmp[r];
-    if (k == K_HOST || k == K_LOST) miss_idx[b_miss + p_miss] = r;
-    if (last && tid < BC_N) {                    // one counter a thread: six in turn by one thread took 1 us longer
-        const uint32_t v = s_pre[tid];
-        const int to = tid == BC_HBM ? C_HBM_REQ : tid == BC_HOST ? C_HOST_REQ : tid == BC_MISS ? C_MISS : tid == BC_REQ ? C_REQ
-                     : tid == BC_LOCAL ? C_LOCAL : tid == BC_CACHE ? C_CACHE : tid == BC_LOST ? C_LOST : C_INVALID;
-        cnt[to] = v;
-        if (tid == BC_HOST) cnt[C_HOST] = v;
-        const int total_of = tid == BC_HOST ? C_HOST : to;
-        if (total_of <= C_INVALID) {
-            if (v) atomicAdd(&totals[total_of], (unsigned long long)v);
-            if (info) info[total_of] = v;
-        }
-        if (info && tid == BC_MISS) { info[6] = v; info[7] = 0; }
-    }
-}
+};
 
 // ---------------------------------------------------------------------------------------------------------
 // Experts: one workgroup forms the distinct set of the routed expert numbers (bitmap in LDS), then walks the
@@ -512,7 +531,7 @@ __global__ __launch_bounds__(WG) void resolve_experts(ClassDev c, uint32_t layer
         __syncthreads();
     }
     if (tid < C_N) {
-        cnt[tid] = s_cnt[tid];
+        cnt[tid] = s_cnt[tid == C_LIST ? C_HBM_REQ : tid];
         if (tid <= C_INVALID && s_cnt[tid]) atomicAdd(&totals[tid], (unsigned long long)s_cnt[tid]);
     }
 }
@@ -645,9 +664,9 @@ __device__ inline void host_page(const GatherArgs &a, uint64_t src, uint64_t dst
 // workgroups (2 x 32 KiB blocks of 32 layers: 5 of 140 on the host 206.9 us layer after layer, 196.1 this way; in the one-kernel
 // fetch 1 of 5 52.0 and 42.9; 20 of 620 fp8 blocks of 10 layers, nearly a page for every workgroup, 126.5 and 127.9).
 template <int NTHR, int PLANES, int LOADS>
-__device__ inline void host_tier(const Rec *__restrict__ recs, uint32_t n_req, const GatherArgs &a, uint32_t b0)
+__device__ inline void host_tier(const HostList &recs, const GatherArgs &a, uint32_t b0)
 {
-    const uint32_t ppc = a.pages_per_chunk, n_pages = n_req * ppc;      // (fits: the host bounds requests times 1 KiB tiles)
+    const uint32_t ppc = a.pages_per_chunk, n_pages = recs.sums.total * ppc;      // (fits: the host bounds requests times 1 KiB tiles)
     if (!n_pages) return;
     uint32_t rep = 0, g = b0, step_reps = 0, step = a.n_host;
     if (a.n_rep > 1) { step_reps = step / n_pages; step -= step_reps * n_pages; rep = g / n_pages; g %= n_pages; }
@@ -658,6 +677,39 @@ __device__ inline void host_tier(const Rec *__restrict__ recs, uint32_t n_req, c
         const Rec x = recs[idx];
         host_page<NTHR, PLANES, LOADS>(a, (x.src & 0x0000FFFFFFFFFFFCull) + rep * a.layer_stride[T_HOST], x.dst + rep * a.dst_step, page,
                                        threadIdx.x);
+    }
+}
+
+// The books of a fetch, see GatherRest: by workgroup bx of the HBM tier's n_wgs in a plane.
+template <int NTHR>
+__device__ inline void keep_books(k_GatherRest &r, uint32_t bx, uint32_t n_wgs)
+{
+    const uint32_t tid = threadIdx.x, lane = lane_id();
+    if (bx == 0 && tid < 64 && r.books) {
+        uint32_t v = 0;                                   // lane i has counter i
+        if (r.books == BOOKS_RESOLVED) {
+            uint32_t n[SC_N];
+#pragma unroll
+            for (int k = 0; k < SC_N; ++k) n[k] = SegSums(r.counts + k * SEGS, r.n_seg).total;
+            const uint32_t hbm = n[SC_REQ] - n[SC_MISS] - n[SC_INVALID];
+            v = lane == C_REQ ? n[SC_REQ] : lane == C_LOCAL ? n[SC_LOCAL] : lane == C_CACHE ? hbm - n[SC_LOCAL] : lane == C_LOST ? n[SC_MISS] - n[SC_HOST]
+              : lane == C_INVALID ? n[SC_INVALID] : lane == C_HBM_REQ ? hbm : lane == C_MISS ? n[SC_MISS] : n[SC_HOST];
+            if (lane <= C_MISS) r.cnt[lane] = v;
+            if (r.info && lane < 8) r.info[lane] = lane <= C_INVALID ? v : lane == 6 ? n[SC_MISS] : 0;
+        } else if (lane <= C_MISS) v = r.cnt[lane];
+        if (r.books != BOOKS_COUNTED && lane <= C_INVALID && v) atomicAdd(&r.totals[lane], (unsigned long long)v);
+        const u32x4 report = { lane_value(v, C_HBM_REQ), lane_value(v, C_HOST_REQ), r.n_seq, r.max_blocks };
+        if (lane == 0) *reinterpret_cast<u32x4 *>(r.report) = report;
+    }
+    if (r.books != BOOKS_RESOLVED) return;
+    const uint32_t n_books = n_wgs < BOOK_WGS ? n_wgs : BOOK_WGS;
+    const SegSums missed(r.counts + SC_MISS * SEGS, r.n_seg);
+    if (!missed.total) return;
+    for (uint32_t seg = bx; seg < r.n_seg; seg += n_books) {
+        const uint32_t lane_of = seg >> 2, i = seg & 3;
+        const uint32_t before = lane_value(i == 0 ? missed.before : i == 1 ? missed.upto[0] : i == 2 ? missed.upto[1] : missed.upto[2], lane_of);
+        const uint32_t n = lane_value(i == 0 ? missed.upto[0] : i == 1 ? missed.upto[1] : i == 2 ? missed.upto[2] : missed.upto[3], lane_of) - before;
+        for (uint32_t k = tid; k < n; k += NTHR) r.miss_idx[before + k] = r.seg_miss[(uint64_t)seg * r.seg_cells + k];
     }
 }
 
@@ -681,19 +733,17 @@ __device__ inline void host_tier(const Rec *__restrict__ recs, uint32_t n_req, c
 // blockIdx.y is the plane (unless folded), blockIdx.z the layer (MULTI): what a workgroup that lives for one load and one store
 // has to work out first is kept to a division.
 template <int NTHR, int PLANES, bool FOLD, bool MULTI>
-__global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs, const Rec *__restrict__ host_recs,
-                                               const uint32_t *__restrict__ cnt, GatherArgs a, GatherBooks books)
+__global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs, const uint32_t *__restrict__ cnt, GatherArgs a, GatherRest)
 {
     constexpr uint32_t TILE = NTHR * 16;
+    constexpr uint32_t REST = 2 * sizeof(void *) + sizeof(GatherArgs);
     if (blockIdx.x < a.n_host) {
         if (blockIdx.y | blockIdx.z) return;               // the host tier's workgroups walk all planes and layers themselves
-        const uint32_t n_req = cnt[C_HOST_REQ];
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            if (books.report) books.report->host = n_req;
-            link_announce(books.lease, (uint64_t)n_req * a.chunk_bytes * PLANES * a.n_rep);
-        }
-        if (a.host_loads == HOST_PAGE) host_tier<NTHR, PLANES, HOST_PAGE>(host_recs, n_req, a, blockIdx.x);
-        else host_tier<NTHR, PLANES, 2>(host_recs, n_req, a, blockIdx.x);
+        k_GatherRest &rest = gather_rest<REST>();
+        const HostList recs(rest);
+        if (blockIdx.x == 0 && threadIdx.x == 0) link_announce(rest.lease, (uint64_t)recs.sums.total * a.chunk_bytes * PLANES * a.n_rep);
+        if (a.host_loads == HOST_PAGE) host_tier<NTHR, PLANES, HOST_PAGE>(recs, a, blockIdx.x);
+        else host_tier<NTHR, PLANES, 2>(recs, a, blockIdx.x);
         return;
     }
     const uint32_t bx = blockIdx.x - a.n_host, gx = a.hbm_wgs, plane_y = FOLD ? 0 : blockIdx.y, rep = MULTI ? blockIdx.z : 0;
@@ -706,31 +756,26 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
     uint64_t t = bx;
     uint32_t idx = (uint32_t)t / tpr;
     Rec x = hbm_recs[idx];
-    uint32_t n_req = cnt[C_HBM_REQ];
-    if (bx == 0 && plane_y == 0 && rep == 0) {
-        if (books.report && threadIdx.x == 0) {
-            books.report->hbm = n_req;
-            books.report->n_seq = books.n_seq;
-            books.report->max_blocks = books.max_blocks;
-        }
-        if (books.totals && threadIdx.x <= C_INVALID && cnt[threadIdx.x])
-            atomicAdd(&books.totals[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
-    }
+    uint32_t n_req = cnt[C_LIST];
+    in_registers(x.src, x.dst, n_req, tpr);
     uint64_t n_tiles = (uint64_t)n_req * tpr;
     while (t < n_tiles) {
         uint32_t k = (uint32_t)t - idx * tpr;
         uint32_t plane = FOLD ? (k >= tpc ? 1u : 0u) : plane_y;
         uint64_t off = (uint64_t)(FOLD ? k - plane * tpc : k) * TILE;
         uint32_t tier = (uint32_t)(x.src & 3);
-        uint64_t src = src_base_of(a, tier, plane) + (x.src & ~(uint64_t)3) + off;
-        uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + x.dst + off;
-        if (MULTI) { src += rep * layer_stride_of(a, tier); dst += rep * a.dst_step; }
-        copy_tile<NTHR, 1, true>(src, dst, a.chunk_bytes - off, threadIdx.x);
+        if (in_hbm(tier)) {
+            uint64_t src = src_base_of(a, tier, plane) + (x.src & ~(uint64_t)3) + off;
+            uint64_t dst = (plane ? a.dst_base[1] : a.dst_base[0]) + x.dst + off;
+            if (MULTI) { src += rep * layer_stride_of(a, tier); dst += rep * a.dst_step; }
+            copy_tile<NTHR, 1, true>(src, dst, a.chunk_bytes - off, threadIdx.x);
+        }
         t += gx;
         if (t >= n_tiles) break;
         idx = (uint32_t)t / tpr;
         x = hbm_recs[idx];
     }
+    if (bx < BOOK_WGS && plane_y == 0 && rep == 0) keep_books<NTHR>(gather_rest<REST>(), bx, gx);
 }
 
 // A head-major working layout: a pool block is [token][head][head_bytes], the destination of a sequence [head][token][head_bytes].
@@ -868,15 +913,6 @@ inline void deal_out_host_pieces(SmallArgs &a, SmallWalk &w, uint32_t n_planes, 
     const bool in_runs = members % w.host_pieces == 0;
     w.host_starts = in_runs ? members / w.host_pieces : members;
     w.host_step = in_runs ? w.host_pieces : 1;
-}
-
-// These values are in registers from here on.  An argument is loaded where it is used, and every such load is a wait; a tile's workgroup
-// has to wait for its directory entry anyway and gets its addresses meanwhile (300 blocks 9.77 us without, 9.69 with).
-template <typename A, typename B, typename C, typename D> __device__ inline void in_registers(A a, B b, C c, D d)
-{
-#ifdef __HIP_DEVICE_COMPILE__
-    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
-#endif
 }
 
 template <int PLANES, int NTHR, bool HM>
@@ -1102,11 +1138,10 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restr
 // 256-byte pieces reach only 22 GB/s); the stores, which go to HBM, are the ones cut into head rows.  K and V of a unit go
 // to the same place in their planes: one address computation serves both.
 template <int PLANES>
-__device__ inline void host_tier_hm(const Rec *__restrict__ recs, uint32_t n_req, const GatherArgs &a, const HmArgs &h,
-                                    uint32_t b0)
+__device__ inline void host_tier_hm(const HostList &recs, const GatherArgs &a, const HmArgs &h, uint32_t b0)
 {
     const uint32_t spc = a.tiles_per_chunk;
-    const uint64_t n_sub = (uint64_t)n_req * spc;
+    const uint64_t n_sub = (uint64_t)recs.sums.total * spc;
     const uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
     for (uint64_t g = b0; g < n_sub; g += a.n_host) {
         const uint32_t idx = (uint32_t)g / spc;
@@ -1132,17 +1167,16 @@ __device__ inline void host_tier_hm(const Rec *__restrict__ recs, uint32_t n_req
 // looping, feedback-sized launch.  One-wavefront workgroups (1 KiB tiles), the token-major gather's shape, are a
 // wash here: 5.95 against 5.90 TB/s alone, 5.32 against 5.35 inside the step.
 template <int PLANES>
-__global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs, const Rec *__restrict__ host_recs,
-                                                const uint32_t *__restrict__ cnt, GatherArgs a, HmArgs h, GatherBooks books)
+__global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs, const uint32_t *__restrict__ cnt, GatherArgs a, HmArgs h,
+                                                GatherRest)
 {
+    constexpr uint32_t REST = 2 * sizeof(void *) + sizeof(GatherArgs) + sizeof(HmArgs);
     if (blockIdx.x < a.n_host) {
         if (blockIdx.y) return;
-        const uint32_t n_req = cnt[C_HOST_REQ];
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            if (books.report) books.report->host = n_req;
-            link_announce(books.lease, (uint64_t)n_req * a.chunk_bytes * PLANES);
-        }
-        host_tier_hm<PLANES>(host_recs, n_req, a, h, blockIdx.x);
+        k_GatherRest &rest = gather_rest<REST>();
+        const HostList recs(rest);
+        if (blockIdx.x == 0 && threadIdx.x == 0) link_announce(rest.lease, (uint64_t)recs.sums.total * a.chunk_bytes * PLANES);
+        host_tier_hm<PLANES>(recs, a, h, blockIdx.x);
         return;
     }
     // plane after plane: taking both planes of a request in one pass, as gather does for a cache tier that keeps
@@ -1153,16 +1187,8 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
     uint64_t t = bx;
     uint32_t idx = (uint32_t)t / tpr;
     Rec x = hbm_recs[idx];                               // speculative, as in gather
-    uint32_t n_req = cnt[C_HBM_REQ];
-    if (bx == 0 && plane == 0) {
-        if (books.report && threadIdx.x == 0) {
-            books.report->hbm = n_req;
-            books.report->n_seq = books.n_seq;
-            books.report->max_blocks = books.max_blocks;
-        }
-        if (books.totals && threadIdx.x <= C_INVALID && cnt[threadIdx.x])
-            atomicAdd(&books.totals[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
-    }
+    uint32_t n_req = cnt[C_LIST];
+    in_registers(x.src, x.dst, n_req, tpr);
     uint64_t n_tiles = (uint64_t)n_req * tpr;
     uint32_t chunk_units = (uint32_t)(a.chunk_bytes >> 4);
     while (t < n_tiles) {
@@ -1172,7 +1198,7 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
         uint64_t cap = x.src >> 48;
         uint64_t src = src_base_of(a, (uint32_t)(x.src & 3), plane) + (x.src & 0x0000FFFFFFFFFFFCull);
         uint64_t dst = dst_plane + x.dst;
-        if (u < chunk_units) {
+        if (in_hbm((uint32_t)(x.src & 3)) && u < chunk_units) {
             uint32_t s_unit;
             uint64_t d_off;
             h.by_destination(u, cap, s_unit, d_off);
@@ -1183,6 +1209,7 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
         idx = (uint32_t)t / tpr;
         x = hbm_recs[idx];
     }
+    if (bx < BOOK_WGS && plane == 0) keep_books<WG>(gather_rest<REST>(), bx, gx);
 }
 
 // ---------------------------------------------------------------------------------------------------------

@@ -640,3 +640,67 @@ def test_a_write_back_keeps_its_rate_beside_a_kernel_that_fills_the_device(chunk
     if side_by_side:
         assert np.median(side_by_side) < (2.1 if chunk < 32768 else 1.25) * alone
     h.close()
+
+
+@pytest.mark.parametrize("revoked", [False, True])
+@pytest.mark.parametrize("n_seq,width", [(1, 1), (1, 256), (1, 257), (3, 85), (7, 731), (300, 1), (256, 256), (4096, 16), (4097, 15), (5000, 3), (65537, 1), (9, 7300),
+                                         (4200, 40), (2, 300000)])
+def test_the_segments_of_a_resolve(n_seq, width, revoked):
+    """One cell to several rounds of 1 024 a segment, one segment to 256 of them, more rows than one workgroup adds up: rows of no, of
+    negative and of more than the table's length, blocks that do not exist and destinations that do not fit, of every tier."""
+    chunk, n = 32, 500
+    rig = Rig(chunk, n, n_layers=2, host_every=4, flags=B.FLAG_GENERAL_FETCH)
+    rng = np.random.default_rng(n_seq + width)
+    kinds = rng.integers(0, 6, n_seq)
+    lens = np.where(kinds == 0, 0, np.where(kinds == 1, -3, np.where(kinds == 2, width + 5, rng.integers(0, width + 1, n_seq)))).astype(np.int32)
+    lens[0] = min(width, 200000)
+    live = np.clip(lens, 0, width).astype(np.int64)
+    t = rng.integers(-1, n + 2, (n_seq, width), dtype=np.int32)
+    asked = np.arange(width)[None, :] < live[:, None]
+    first = np.cumsum(live) - live
+    first[rng.random(n_seq) < 0.1] += 1 << 40                # some rows have no room at all
+    first[0] = 0
+    cap = int(live.sum())
+    dst = first[:, None] + np.arange(width)[None, :]
+    fits = dst < cap
+    known = (t >= 0) & (t < n)
+    good = asked & fits & known
+    host = np.zeros(n + 2, dtype=bool)
+    host[:len(rig.on_host)] = rig.on_host
+    if revoked:
+        gone = np.flatnonzero(~rig.on_host)[::5]
+        rig.h.revoke(B.KV, gone)
+        host[gone] = True
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    dt, dn, df = dev(t), dev(lens), dev(first.astype(np.int64))
+    want_miss = np.flatnonzero((good & host[np.where(known, t, n)]).reshape(-1))
+    n_local = int((good & (t >= len(rig.on_host))).sum())
+    totals = []
+    for turn in range(2):                                   # the second call's grid is sized by the first one's report
+        k, v = rig.buffers(max(cap, 1))
+        rig.h.fetch_kv(0, dt, dn, k, v, df, cap)
+        counts, miss, n_miss = rig.h.fetch_info(miss_cap=t.size)
+        assert n_miss == len(want_miss) and np.array_equal(miss, want_miss)
+        assert counts == dict(n_requests=int(asked.sum()), n_local=n_local, n_cache=int(good.sum()) - n_local - n_miss, n_host=n_miss, n_lost=0,
+                              n_invalid=int((asked & ~(fits & known)).sum()))
+        rig.h.fetch_kv_again(1, k[rig.chunk * max(cap, 1):], v[rig.chunk * max(cap, 1):])
+        for p, buf in enumerate([k, v]):
+            got = buf.cpu().numpy()[:2 * max(cap, 1) * chunk].reshape(2, max(cap, 1), chunk)
+            for layer in range(2):
+                want = np.full((max(cap, 1), chunk), 0xEE, dtype=np.uint8)
+                want[dst[good]] = rig.payload[p][layer][rig.order[t[good]]]
+                assert np.array_equal(got[layer], want), (turn, p, layer)
+        totals.append(rig.h.stats().fetch[B.KV].as_dict())
+        assert totals[-1] == {name: 2 * (turn + 1) * x for name, x in counts.items()}
+    if t.size <= 65536:
+        info = torch.full((8,), 77, dtype=torch.int32, device="cuda")
+        missed = torch.full((t.size,), -7, dtype=torch.int32, device="cuda")
+        k, v = rig.buffers(max(cap, 1))
+        rig.h.fetch_kv_static(0, dt, dn, k, v, df, cap, info, missed)
+        c = counts
+        assert info.tolist() == [c["n_requests"], c["n_local"], c["n_cache"], c["n_host"], 0, c["n_invalid"], n_miss, 0]
+        assert np.array_equal(missed.cpu().numpy()[:n_miss], want_miss) and (missed.cpu().numpy()[n_miss:] == -7).all()
+        want = np.full((max(cap, 1), chunk), 0xEE, dtype=np.uint8)
+        want[dst[good]] = rig.payload[1][0][rig.order[t[good]]]
+        assert np.array_equal(v.cpu().numpy()[:max(cap, 1) * chunk].reshape(-1, chunk), want)
+    rig.h.close()
