@@ -683,7 +683,9 @@ int release_after(harvest_ctx *ctx, Staging *st, hipStream_t s)
 constexpr uint64_t SMALL_FETCH_CELLS = 4096;      // block tables up to this many cells are fetched by one kernel (measured:
                                                   // it wins up to 4 096 cells and loses from 8 192 on)
 constexpr uint64_t SMALL_FETCH_TILES = 1u << 22;      // and never more workgroups than this in x
-constexpr uint64_t DEAD_TILES = 20000;                // nor with more workgroups than this (8 us) for cells that ask for nothing
+constexpr uint64_t DEAD_TILES = 20000;                // nor with more workgroups than this (8 us) for cells that ask for nothing ...
+constexpr uint64_t DEAD_TILES_2 = 10000;              // ... where they make two loads a thread and no read of the host hides them (4 us)
+constexpr uint64_t UNROLLED_TILES = 65536;            // up to this many tiles of 4 KiB a one-kernel fetch may make two loads a thread
 constexpr uint32_t MARKED_BATCH_IDS = 32768;      // routing-id batches beyond this take the two-kernel resolve
 
 uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t)((chunk_bytes + tile - 1) / tile); }
@@ -691,6 +693,9 @@ uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t
 // one workgroup per tile up to here; beyond, the kernels loop.  Kept below 2^32 threads per launch dimension.
 constexpr uint32_t MAX_GRID = 0xFFFFFFFFu / WG;
 constexpr uint32_t MAX_GRID_Z = 65535;
+
+// Host bytes at the link's rate against HBM bytes, read and written, at HBM's: about 1 : 55 per request.
+bool is_link_bound(uint64_t n_hbm, uint64_t n_host) { return n_host * 55 > n_hbm; }
 
 uint32_t grid_for(uint64_t n_tiles, uint32_t max_grid)
 {
@@ -902,8 +907,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
         const uint64_t seen = r.hbm, seen_host = r.host;
         uint64_t guess = std::max<uint64_t>(1, cls == HARVEST_KV ? seen : seen - seen / 8) * tpc;
         want = std::min(max_tiles, std::max<uint64_t>(guess, 16ull * ctx->n_cu));
-        // host bytes at the link's rate against HBM bytes, read and written, at HBM's: about 1 : 55 per request
-        link_bound = host_tier && seen_host * 55 > seen;
+        link_bound = host_tier && is_link_bound(seen, seen_host);
         double bytes = (double)planes * c.cfg.chunk_bytes * n_rep;
         double us_hbm = 2.0 * seen * bytes / 6.0e6, us_host = seen_host * bytes / 57.0e3;     // at 6 TB/s and 57 GB/s
         serial = serial || std::max(us_hbm, us_host) < 35.0 || std::min(us_hbm, us_host) < 8.0;
@@ -1757,20 +1761,32 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     if (recording) ss->recorded = true;
     const uint32_t tpc = tiles_per_chunk(c.cfg.chunk_bytes, TILE_4K);
     // A small table: the whole fetch is one kernel (no compaction) - see fetch_kv_small.  Unless most of it is padding: the
-    // one kernel has a workgroup for every tile of every cell, and one whose cell asks for nothing still costs 0.4 ns
-    // (4 096 cells, 64 of them live: 27 us), where the general path spends about 8 us more on two small kernels and none
-    // on cells that are not there.  How many are live is known when the latest report on this stream came from a table of these
+    // one kernel has a workgroup for every tile of every cell, and one whose cell asks for nothing still costs 0.2 to 0.5 ns
+    // (4 096 cells, 64 of them live: 27 us with one load a thread), where the general path spends about 5 us more on a small kernel and
+    // none on cells that are not there (2 048 cells, two loads a thread: 1 024 live 25.3 us against 27.6, 512 live 19.4 and 17.3).  How many are live is known when the latest report on this stream came from a table of these
     // rows and columns - a step's table keeps its shape from layer to layer and mostly from step to step; of any other table
-    // (two that take turns, say) they are taken to be live, for a wrong guess costs those 8 us.  So they are for a
+    // (two that take turns, say) they are taken to be live, for a wrong guess costs those 5 us.  So they are for a
     // fetch that is being recorded: its replays may meet any number of live cells.
-    uint64_t dead_tiles = 0;
+    uint64_t dead_cells = 0;
     const volatile Report &latest = ss->h_feedback[HARVEST_KV];
-    if (ss->feedback_valid[HARVEST_KV] && latest.n_seq == n_seq && latest.max_blocks == max_blocks && !recording) {
+    const bool reported = ss->feedback_valid[HARVEST_KV] && !recording;
+    if (reported && latest.n_seq == n_seq && latest.max_blocks == max_blocks) {
         const uint64_t live = (uint64_t)latest.hbm + latest.host;
-        if (live < total) dead_tiles = (total - live) * tpc * c.cfg.n_planes * n_layers;
+        if (live < total) dead_cells = total - live;
     }
+    const uint32_t nthr = total <= 64 * ROUND ? 64 : WG;
+    // Two loads a thread: what a tile's workgroup has to work out first is shared by twice the bytes, and there are half as many workgroups
+    // for cells that ask for nothing.  512 / 1 024 / 2 048 / 4 096 blocks of 2 x 32 KiB 14.1 / 24.8 / 45.9 / 88.7 us with one, 13.7 / 24.1 /
+    // 45.3 / 88.5 with two; 8 192 174.7 and 178.2, more bytes in flight than the memory takes; 1 024 of 2 048 cells live 33.1 and 25.3.
+    // Not where the link is what the fetch waits for, and the HBM tier's loads stand in the way of the host's (2 000 blocks, 3 % of them on
+    // the host, 77.4 and 78.2 us; 1 %: 47.2 and 45.9), so not before a report is there.  Several layers 36.5 and 36.0 at 25 600 tiles of
+    // 4 KiB, 68.3 and 68.6 at 51 200.
+    const bool unrolled = nthr == WG && total * tpc * c.cfg.n_planes * n_layers <= (n_layers > 1 ? UNROLLED_TILES / 2 : UNROLLED_TILES) &&
+                          (!c.cfg.n_host_slots || (reported && !is_link_bound(latest.hbm, latest.host)));
+    const uint32_t unroll = unrolled ? 2 : 1;
+    const uint64_t dead_tiles = dead_cells * tiles_per_chunk(c.cfg.chunk_bytes, TILE_4K * unroll) * c.cfg.n_planes * n_layers;
     if (!ctx->general_fetch && !c.n_lossy && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
-        total * tpc * n_layers <= (1ull << 31) && dead_tiles <= DEAD_TILES) {
+        total * tpc * n_layers <= (1ull << 31) && dead_tiles <= (unrolled ? DEAD_TILES_2 : DEAD_TILES)) {
         SmallArgs ga{};
         SmallWalk gw{};
         const ClassDev cd = class_dev(c);
@@ -1794,8 +1810,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
             gw.snap = ss->snap;
             if ((rc = launch(ss->s, snap_edit, dim3(1), dim3(1), (const uint32_t *)c.d_done, ss->snap))) return rc;
         }
-        const uint32_t nthr = total <= 64 * ROUND ? 64 : WG;
-        ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16);
+        ga.tiles_per_chunk = tiles_per_chunk(c.cfg.chunk_bytes, nthr * 16 * unroll);
         // Unless the caller has said how wide, a third more reads of the host in flight than in the general path: the tile workgroups
         // keep the host's waiting at the compute units, and members of a group whose number divides the pieces of a cell have even shares.
         // 24 / 32 / 40 workgroups of 256 threads: 256 cells, 102 on the host 124.5 / 123.1 / 124.2 us; 2 000 of 2 x 16 KiB, 300 184.9 /
@@ -1819,8 +1834,9 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
         const dim3 grid(n_layers > 1 ? std::max(ga.hbm_wgs, head) : ga.hbm_wgs + head, c.cfg.n_planes, n_layers > 1 ? n_layers + 1 : 1);
         auto run = [&](auto with_hm, const auto &h) {
             constexpr bool HM = decltype(with_hm)::value;
-            auto kernel = c.cfg.n_planes == 2 ? (nthr == 64 ? fetch_kv_small<2, 64, HM> : fetch_kv_small<2, WG, HM>)
-                                              : (nthr == 64 ? fetch_kv_small<1, 64, HM> : fetch_kv_small<1, WG, HM>);
+            auto of = [&](auto k64, auto k256, auto k256_2) { return nthr == 64 ? k64 : unrolled ? k256_2 : k256; };
+            auto kernel = c.cfg.n_planes == 2 ? of(fetch_kv_small<2, 64, HM>, fetch_kv_small<2, WG, HM>, fetch_kv_small<2, WG, HM, 2>)
+                                              : of(fetch_kv_small<1, 64, HM>, fetch_kv_small<1, WG, HM>, fetch_kv_small<1, WG, HM, 2>);
             return launch_last(ctx, ss, recording, kernel, grid, dim3(nthr), d_block_table, d_n_blocks, d_seq_dst_block, ga, gw, h);
         };
         SmallHm<true> h;

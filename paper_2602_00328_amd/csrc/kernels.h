@@ -816,8 +816,8 @@ struct HmArgs {
 //                     on the host, take 37.1-37.8 us in two groups and took 39.6-40.9 when every workgroup walked all six rounds.
 //   the next one      walks the table too and keeps the books: counters, and the miss list in request order.  No atomics on
 //                     shared counters (a thousand of them on one address take longer than the copy), nothing to zero.
-//   the others        copy a tile of 16 bytes a thread if their cell's block is in HBM: nothing is compacted, so the grid covers the padded
-//                     table - which is why this is for small tables only.  Resolving the cell in every workgroup costs
+//   the others        copy a tile of 16 bytes a thread, or twice that (U), if their cell's block is in HBM: nothing is compacted, so the grid
+//                     covers the padded table - which is why this is for small tables only.  Resolving the cell in every workgroup costs
 //                     little bandwidth (1 750 blocks of 2 x 16 KiB: 5.77 TB/s against 6.00 from a list, whose making
 //                     takes longer than that saves).  Non-temporal accesses: on blocks that are in no cache 1 000 take 23.4 us
 //                     against 27.1 for plain ones, 2 000 43.7 against 51.3.
@@ -915,7 +915,7 @@ inline void deal_out_host_pieces(SmallArgs &a, SmallWalk &w, uint32_t n_planes, 
     w.host_step = in_runs ? w.host_pieces : 1;
 }
 
-template <int PLANES, int NTHR, bool HM>
+template <int PLANES, int NTHR, bool HM, int U = 1>
 __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restrict__ table, const int32_t *__restrict__ n_blocks,
                                                         const uint64_t *__restrict__ seq_dst_block, SmallArgs a, SmallWalk, SmallHm<HM> h)
 {
@@ -941,7 +941,7 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restr
         const uint64_t cache = plane ? a.cache.base[1] : a.cache.base[0], local = plane ? a.local.base[1] : a.local.base[0];
         in_registers(cache, local, a.cache.slot_stride, a.n_cache_slots);
         const int tier = (int)entry_tier(e);
-        const uint64_t off = (uint64_t)k * (NTHR * 16);
+        const uint64_t off = (uint64_t)k * (NTHR * 16 * U);
         const uint64_t slot = entry_slot(e);
         uint64_t src;
         if (tier == T_CACHE || tier == T_LOCAL) {
@@ -954,14 +954,23 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restr
             src = (plane ? w.host.base[1] : w.host.base[0]) + slot * w.host.slot_stride + z * w.host.layer_stride;
         }
         if constexpr (HM) {
+            const uint64_t dst = dst_plane + first * a.chunk_bytes + (uint64_t)j * h.ups * 16;
             if (off + tid * 16 >= a.chunk_bytes) return;
-            uint32_t unit;
-            uint64_t to;
-            h.by_destination(k * NTHR + tid, cap, unit, to);
-            const uint64_t dst = dst_plane + first * a.chunk_bytes + (uint64_t)j * h.ups * 16 + to;
-            st16<true>(reinterpret_cast<u32x4 *>(dst), ld16<true>(reinterpret_cast<const u32x4 *>(src) + unit));
+            u32x4 v[U];
+            uint64_t to[U];
+            bool there[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) {                          // (a load of every turn, so that they are on their way together)
+                const uint32_t u = (k * U + i) * NTHR + tid;
+                uint32_t unit;
+                there[i] = i == 0 || (uint64_t)u * 16 < a.chunk_bytes;
+                h.by_destination(there[i] ? u : k * U * NTHR + tid, cap, unit, to[i]);
+                v[i] = ld16<true>(reinterpret_cast<const u32x4 *>(src) + unit);
+            }
+#pragma unroll
+            for (int i = 0; i < U; ++i) if (there[i]) st16<true>(reinterpret_cast<u32x4 *>(dst + to[i]), v[i]);
         } else {
-            copy_tile<NTHR, 1, true>(src + off, dst_plane + dst_chunk * a.chunk_bytes + off, a.chunk_bytes - off, tid);
+            copy_tile<NTHR, U, true>(src + off, dst_plane + dst_chunk * a.chunk_bytes + off, a.chunk_bytes - off, tid);
         }
         return;
     }

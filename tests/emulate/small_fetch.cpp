@@ -111,6 +111,7 @@ uint32_t read_lane(uint32_t x, uint32_t k)
 extern "C" {
 struct Fetch {
     uint32_t n_planes, nthr, head_major, n_layers, n_objects, n_seq, max_blocks, n_host, lg_groups, seen, n_versions, n_heads, block_tokens, n_slots;
+    uint32_t unrolled, pad;                      // two loads a thread in the tiles' workgroups
     uint64_t chunk_bytes, dst_cap, dst_step;
     uint64_t pool[3][2], dst[2];                 // [tier][plane]: pools [layer][slot][chunk]; destinations [layer][dst_cap][chunk]
     const int32_t *table, *n_blocks;
@@ -134,7 +135,8 @@ int run_fetch(const Fetch *f)
     SmallWalk &w = arguments.w;
     a.dst_cap = f->dst_cap; a.dir = dir.data(); a.chunk_bytes = f->chunk_bytes;
     a.max_blocks = f->max_blocks; a.n_objects = f->n_objects; a.n_rep = f->n_layers;
-    a.tiles_per_chunk = (uint32_t)((f->chunk_bytes + f->nthr * 16 - 1) / (f->nthr * 16));
+    const uint32_t tile = f->nthr * 16 * (f->unrolled ? 2 : 1);
+    a.tiles_per_chunk = (uint32_t)((f->chunk_bytes + tile - 1) / tile);
     a.hbm_wgs = total * a.tiles_per_chunk;
     a.dst_base[0] = f->dst[0]; a.dst_base[1] = f->dst[1]; a.dst_step = f->dst_step;
     auto tier = [&](int t) { return SmallTier{ { f->pool[t][0], f->pool[t][1] }, f->n_slots * f->chunk_bytes, f->chunk_bytes }; };
@@ -156,7 +158,9 @@ int run_fetch(const Fetch *f)
         if (f->head_major) g_kernel = [&, with_hm] { with_hm(f->table, f->n_blocks, f->seq_dst, a, w, h); };
         else g_kernel = [&, plain] { plain(f->table, f->n_blocks, f->seq_dst, a, w, SmallHm<false>{}); };
     };
-    if (f->n_planes == 2 && f->nthr == 64) call(fetch_kv_small<2, 64, false>, fetch_kv_small<2, 64, true>);
+    if (f->unrolled && f->n_planes == 2) call(fetch_kv_small<2, 256, false, 2>, fetch_kv_small<2, 256, true, 2>);
+    else if (f->unrolled) call(fetch_kv_small<1, 256, false, 2>, fetch_kv_small<1, 256, true, 2>);
+    else if (f->n_planes == 2 && f->nthr == 64) call(fetch_kv_small<2, 64, false>, fetch_kv_small<2, 64, true>);
     else if (f->n_planes == 2) call(fetch_kv_small<2, 256, false>, fetch_kv_small<2, 256, true>);
     else if (f->nthr == 64) call(fetch_kv_small<1, 64, false>, fetch_kv_small<1, 64, true>);
     else call(fetch_kv_small<1, 256, false>, fetch_kv_small<1, 256, true>);

@@ -704,3 +704,37 @@ def test_the_segments_of_a_resolve(n_seq, width, revoked):
         want[dst[good]] = rig.payload[1][0][rig.order[t[good]]]
         assert np.array_equal(v.cpu().numpy()[:max(cap, 1) * chunk].reshape(-1, chunk), want)
     rig.h.close()
+
+
+@pytest.mark.parametrize("n_host", [0, 1])
+@pytest.mark.parametrize("n_planes,chunk,heads", [(2, 16, None), (2, 4112, None), (1, 8192, None), (2, 8208, None), (2, 32768 + 48, None), (1, 16384, (8, 16)), (2, 8880, (5, 3))])
+@pytest.mark.parametrize("lens,width", [([129], 129), ([100, 64, 0, 40], 101), ([600, 3], 600)])
+def test_one_kernel_fetch_with_two_loads_a_thread(n_planes, chunk, heads, lens, width, n_host):
+    """From the second call on, which knows from a report that the link is not what the fetch waits for; tiles of 8 KiB."""
+    rig = Rig(chunk, 400, n_planes=n_planes, host_every=100)
+    t, dt, dn, df, cap = rig.tables(lens, width)
+    hosts = np.flatnonzero(rig.on_host)
+    t[np.isin(t, hosts)] = 0                                # a block of the cache tier
+    t[0, 7:7 + n_host] = hosts[:n_host]
+    t[0, 90] = -4
+    dt.copy_(torch.from_numpy(t))
+    for turn in range(3):
+        k, v = rig.buffers(cap)
+        if heads:
+            rig.h.fetch_kv_head_major(0, dt, dn, k, v if n_planes == 2 else None, df, dn, cap, *heads)
+        else:
+            rig.h.fetch_kv(0, dt, dn, k, v if n_planes == 2 else None, df, cap)
+        counts, miss, _ = rig.h.fetch_info(miss_cap=t.size)
+        assert miss.tolist() == rig.misses(np.where(t >= 0, t, rig.n), lens) and len(miss) == n_host and counts["n_invalid"] == 1
+        for p, buf in enumerate([k, v][:n_planes]):
+            got = buf.cpu().numpy()
+            assert (got[cap * chunk:] == 0xEE).all()
+            at = 0
+            for s, n in enumerate(lens):
+                want = rig.payload[p][0][rig.order[t[s, :n]]]
+                want[t[s, :n] < 0] = 0xEE
+                if heads:
+                    want = want.reshape(n * heads[1], heads[0], chunk // (heads[0] * heads[1])).transpose(1, 0, 2)
+                assert np.array_equal(got[at:at + n * chunk], want.reshape(-1)), (turn, p, s)
+                at += n * chunk
+    rig.h.close()

@@ -19,7 +19,7 @@ u32, u64, vp = ctypes.c_uint32, ctypes.c_uint64, ctypes.c_void_p
 
 class Fetch(ctypes.Structure):
     _fields_ = [(n, u32) for n in ("n_planes", "nthr", "head_major", "n_layers", "n_objects", "n_seq", "max_blocks", "n_host", "lg_groups", "seen",
-                                   "n_versions", "n_heads", "block_tokens", "n_slots")]
+                                   "n_versions", "n_heads", "block_tokens", "n_slots", "unrolled", "pad")]
     _fields_ += [("chunk_bytes", u64), ("dst_cap", u64), ("dst_step", u64), ("pool", u64 * 2 * 3), ("dst", u64 * 2)]
     _fields_ += [(n, vp) for n in ("table", "n_blocks", "seq_dst", "seq_cap", "versions", "when", "cnt", "miss")]
 
@@ -170,3 +170,17 @@ def test_head_major_cells_beyond_a_sequences_room_are_invalid(emulated, n_planes
     asked = tier[c.table[c.cells]]
     assert cnt[:6].tolist() == [129, (asked == LOCAL).sum(), (asked == CACHE).sum(), (asked == HOST).sum(), 0, 2]
     assert miss[:(asked == HOST).sum()].tolist() == c.cells[asked == HOST].tolist()
+
+
+@pytest.mark.parametrize("edit", ["revoked", "placed"])
+@pytest.mark.parametrize("n_planes,n_layers,chunk,lens,width,heads", [(2, 1, 16384, [140, 60], 150, None), (1, 1, 8192 + 16, [200], 200, None), (2, 3, 4096 + 16, [70, 71], 71, None),
+                                                                      (2, 1, 16, [129], 129, None), (2, 1, 8 * 16 * 64, [90, 50], 90, (8, 16)), (1, 1, 5 * 3 * 592, [140], 140, (5, 3))])
+def test_blocks_are_whole_with_two_loads_a_thread(emulated, edit, n_planes, n_layers, chunk, lens, width, heads):
+    """Tiles of 8 KiB: chunks of some of them, of one and a bit, of less than half of one."""
+    rng = np.random.default_rng(chunk)
+    c = Case(emulated, rng, lens, width, chunk, n_planes, 256, head_major=heads is not None, n_layers=n_layers, n_host=9, heads=heads or (2, 1))
+    c.f.unrolled = 1
+    tier = rng.choice([HOST, CACHE, LOCAL], c.n_objects, p=[0.2, 0.7, 0.1])
+    after = tier.copy()
+    after[rng.permutation(np.flatnonzero(tier == (CACHE if edit == "revoked" else HOST)))[:9]] = HOST if edit == "revoked" else CACHE
+    c.run([tier, after])
