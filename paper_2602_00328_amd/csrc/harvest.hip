@@ -686,6 +686,9 @@ constexpr uint64_t SMALL_FETCH_TILES = 1u << 22;      // and never more workgrou
 constexpr uint64_t DEAD_TILES = 20000;                // nor with more workgroups than this (8 us) for cells that ask for nothing ...
 constexpr uint64_t DEAD_TILES_2 = 10000;              // ... where they make two loads a thread and no read of the host hides them (4 us)
 constexpr uint64_t UNROLLED_TILES = 65536;            // up to this many tiles of 4 KiB a one-kernel fetch may make two loads a thread
+// Chunks from which both planes of a request are taken in one pass: what longer source runs gain at 32 KiB, destinations that take
+// turns lose at 16 KiB (4 096 blocks of 2 x 32 KiB 91.4 us plane after plane and 88.8 in one pass, 16 384 of 2 x 16 KiB 178.4 and 182.2).
+constexpr uint64_t FOLD_FROM = 32768;
 constexpr uint32_t MARKED_BATCH_IDS = 32768;      // routing-id batches beyond this take the two-kernel resolve
 
 uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t)((chunk_bytes + tile - 1) / tile); }
@@ -891,7 +894,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
     const bool host_tier = c.cfg.n_host_slots != 0;
     // one pass over both planes of each request where the cache tier keeps them side by side (see gather; not the
     // head-major gather, see gather_hm)
-    const bool fold = !hm && c.cache_planes_adjacent() && !ctx->gather_grid;
+    const bool fold = !hm && c.cache_planes_adjacent() && c.cfg.chunk_bytes >= FOLD_FROM && !ctx->gather_grid;
     // Grid of the HBM tier: about one workgroup per tile.  The request count lives on the device, so the grid is
     // sized from what the previous gather of this class on this stream reported, never below a floor that still fills the
     // chip, never above the bound; the kernel loops where the grid is short, so any size is correct.  For experts, whose

@@ -738,3 +738,22 @@ def test_one_kernel_fetch_with_two_loads_a_thread(n_planes, chunk, heads, lens, 
                 assert np.array_equal(got[at:at + n * chunk], want.reshape(-1)), (turn, p, s)
                 at += n * chunk
     rig.h.close()
+
+
+@pytest.mark.parametrize("layout", [0, B.FLAG_CACHE_PLANES_ADJACENT])
+@pytest.mark.parametrize("chunk", [32752, 32768, 32768 + 48, 65536 + 16])
+@pytest.mark.parametrize("threads", [64, 256])
+def test_chunks_around_the_size_from_which_planes_side_by_side_are_taken_in_one_pass(layout, chunk, threads):
+    rig = Rig(chunk, 41, n_layers=2, host_every=5, flags=B.FLAG_GENERAL_FETCH | layout, gather_threads=threads)
+    lens = [13, 0, 22]
+    t, dt, dn, df, cap = rig.tables(lens, 23)
+    for _ in range(2):
+        k, v = rig.buffers(cap)
+        rig.h.fetch_kv_layers(0, 2, dt, dn, k, v, cap * chunk, df, cap)
+        assert rig.h.fetch_info(miss_cap=t.size)[1].tolist() == rig.misses(t, lens)
+        for p, buf in enumerate([k, v]):
+            got = buf.cpu().numpy()
+            for layer in range(2):
+                assert np.array_equal(got[layer * cap * chunk:(layer + 1) * cap * chunk], rig.expected(t, lens, p, layer)), (p, layer)
+            assert (got[2 * cap * chunk:] == 0xEE).all()
+    rig.h.close()
