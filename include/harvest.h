@@ -111,8 +111,8 @@ enum harvest_flags {
     HARVEST_FLAG_PROFILE = 4,    /* bracket the gather kernels with events; read them with harvest_profile
                                     (launches recorded into a graph are not timed, nor are KV fetches in their one-kernel
                                     form, whose tiers are not apart: HARVEST_FLAG_GENERAL_FETCH) */
-    HARVEST_FLAG_GENERAL_FETCH = 8, /* KV fetches never take their one-kernel form for small block tables (up to
-                                    4096 cells): every fetch runs resolve, compaction and the gather - for
+    HARVEST_FLAG_GENERAL_FETCH = 8, /* fetches never take their one-kernel form - for small block tables (up to 4096
+                                    cells), for a few routing ids -: every fetch runs resolve and gather - for
                                     measurements and tests of that path; results are the same either way */
     HARVEST_FLAG_CACHE_PLANES_ADJACENT = 16 /* two-plane classes with cache slots of their own keep them in ONE buffer,
                                     d_cache_pool[0], laid out [layer][slot][plane][chunk_bytes] (d_cache_pool[1] is ignored):

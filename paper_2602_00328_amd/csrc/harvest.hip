@@ -689,6 +689,7 @@ constexpr uint64_t UNROLLED_TILES = 65536;            // up to this many tiles o
 // Chunks from which both planes of a request are taken in one pass: what longer source runs gain at 32 KiB, destinations that take
 // turns lose at 16 KiB (4 096 blocks of 2 x 32 KiB 91.4 us plane after plane and 88.8 in one pass, 16 384 of 2 x 16 KiB 178.4 and 182.2).
 constexpr uint64_t FOLD_FROM = 32768;
+constexpr uint64_t ROUTED_BYTES = 256u << 20;         // experts up to this many bytes are fetched by one kernel
 constexpr uint32_t MARKED_BATCH_IDS = 32768;      // routing-id batches beyond this take the two-kernel resolve
 
 uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t)((chunk_bytes + tile - 1) / tile); }
@@ -797,8 +798,8 @@ int publish(harvest_ctx *ctx, ClassState &c, const std::vector<uint32_t> &ids, h
 // copies on another stream), and until its entry is seen the older one names the host copy, which holds the same bytes.
 // Nothing to do either when the latest edit ran on this very stream: the chain put every earlier one before it.
 //
-// seen_seq is also what a one-kernel fetch goes by (see fetch_kv_small), so placements that another stream has finished are
-// noticed here.
+// seen_seq is also what a one-kernel fetch goes by (see fetch_kv_small, fetch_experts_small), so placements that another stream has
+// finished are noticed here.
 int order_after_directory_edits(harvest_ctx *ctx, StreamState *ss, int cls)
 {
     const ClassState &c = ctx->cls[cls];
@@ -806,7 +807,7 @@ int order_after_directory_edits(harvest_ctx *ctx, StreamState *ss, int cls)
     if (seen == c.edit_seq || is_capturing(ss->s)) return HARVEST_OK;
     if (c.edit_stream != ss->s) {
         if (seen < c.must_seq) HIP_TRY(hipStreamWaitEvent(ss->s, c.edit_evt, 0));
-        else if (cls != HARVEST_KV || event_status(c.edit_evt) != hipSuccess) return HARVEST_OK;
+        else if (event_status(c.edit_evt) != hipSuccess) return HARVEST_OK;
     }
     seen = c.edit_seq;
     return HARVEST_OK;
@@ -1984,6 +1985,38 @@ int harvest_fetch_experts(harvest_ctx *ctx, uint32_t layer, const int32_t *d_top
     if ((rc = order_after_directory_edits(ctx, ss, HARVEST_EXPERT))) return rc;
     const Lists &lists = ss->lists[HARVEST_EXPERT];
     uint32_t *cnt = lists.cnt;
+    const bool recording = is_capturing(ss->s);
+    // A few ids: the whole fetch is one kernel, see fetch_experts_small.  Its workgroups resolve for themselves, so the rank of an expert has to
+    // follow from the ids alone (no expert that is local or may have lost its bytes), and every edit that the fetch comes after has to be
+    // known by number (not while another stream's placement is under way, and not in a recorded graph).  Up to ROUTED_BYTES - 242 MB 71.4 us
+    // against 73.0, 520 MB 129.6 and 128.6 - and where the latest report says that HBM is what the fetch waits for; timed by tier it is two
+    // launches.
+    const volatile Report &latest = ss->h_feedback[HARVEST_EXPERT];
+    const uint32_t n_max = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(n_ids, E), n_staging_slots);
+    const uint64_t seen_hbm = latest.hbm, guess = std::min<uint64_t>(n_max, std::max<uint64_t>(1, seen_hbm - seen_hbm / 8));
+    if (n_ids && n_max && n_ids <= ROUTED_IDS && E <= ROUTED_EXPERTS && !ctx->general_fetch && !ctx->profile && !recording && !c.n_lossy &&
+        c.local_free.size() == c.cfg.n_local_slots && ss->seen_seq[HARVEST_EXPERT] == c.edit_seq && ss->feedback_valid[HARVEST_EXPERT] &&
+        !is_link_bound(seen_hbm, latest.host) && seen_hbm * c.cfg.chunk_bytes <= ROUTED_BYTES) {
+        const ClassDev cd = class_dev(c);
+        RoutedArgs a{};
+        a.topk = d_topk_ids;
+        a.dir = (k_entry *)(uint64_t)(cd.dir + (uint64_t)layer * E);
+        a.chunk_bytes = cd.chunk_bytes; a.staging = (uint64_t)d_staging;
+        a.cache_base = cd.pool[T_CACHE][0]; a.cache_stride = cd.slot_stride[T_CACHE]; a.n_cache_slots = cd.n_slots[T_CACHE];
+        a.host_base = cd.pool[T_HOST][0]; a.host_stride = cd.slot_stride[T_HOST]; a.n_host_slots = cd.n_slots[T_HOST];
+        a.n_experts = E;
+        a.n_known = (uint32_t)std::min<uint64_t>(E, c.n_objects - std::min<uint64_t>(c.n_objects, (uint64_t)layer * E));
+        a.n_ids = (uint32_t)n_ids; a.n_staging = n_staging_slots;
+        a.tiles_per_chunk = tiles_per_chunk(cd.chunk_bytes, TILE_4K * 2);
+        a.n_host = host_workgroups(ctx, WG);
+        a.seen = (uint32_t)ss->seen_seq[HARVEST_EXPERT];
+        // a little short of the last count's tiles, as in launch_gathers
+        a.hbm_wgs = grid_for(std::min<uint64_t>((uint64_t)n_max * a.tiles_per_chunk, std::max<uint64_t>(guess * a.tiles_per_chunk, 8ull * ctx->n_cu)), MAX_GRID - a.n_host - 1);
+        const RoutedBooks b{ cd, (uint64_t *)d_expert_ptr, lists.miss, cnt, ctx->d_totals + HARVEST_EXPERT * C_N, ctx->d_lease, ss->d_feedback + HARVEST_EXPERT, layer, 0 };
+        if ((rc = launch_last(ctx, ss, false, fetch_experts_small<WG, 2>, dim3(a.n_host + 1 + a.hbm_wgs), dim3(WG), a, b))) return rc;
+        ss->last_cls = HARVEST_EXPERT; ss->counted[HARVEST_EXPERT] = true;
+        return HARVEST_OK;
+    }
     // a large batch of routing ids is marked by many workgroups first; the single resolving workgroup reads the bitmap
     const bool marked = n_ids > MARKED_BATCH_IDS;
     if (marked) {
@@ -1998,7 +2031,7 @@ int harvest_fetch_experts(harvest_ctx *ctx, uint32_t layer, const int32_t *d_top
                        marked ? ss->mark + MAX_EXPERTS / 32 : (uint32_t *)nullptr);
     HIP_TRY(hipGetLastError());
     ss->last_cls = HARVEST_EXPERT; ss->counted[HARVEST_EXPERT] = true;
-    return launch_gathers(ctx, ss, is_capturing(ss->s), c, HARVEST_EXPERT, lists, std::min<uint64_t>(E, n_staging_slots), (uint64_t)d_staging, 0);
+    return launch_gathers(ctx, ss, recording, c, HARVEST_EXPERT, lists, std::min<uint64_t>(E, n_staging_slots), (uint64_t)d_staging, 0);
 }
 
 int harvest_prefetcher_create(harvest_ctx *ctx, void *const d_staging[2], uint32_t n_staging_slots,

@@ -177,11 +177,11 @@ template <typename A, typename B, typename C, typename D> __device__ inline void
 }
 
 // Selects instead of indexing: a variable index into a kernel-argument struct would send it to scratch memory.
-__device__ inline uint32_t slots_of(const ClassDev &c, int tier)
+template <typename C> __device__ inline uint32_t slots_of(const C &c, int tier)
 {
     return tier == T_HOST ? c.n_slots[T_HOST] : (tier == T_CACHE ? c.n_slots[T_CACHE] : c.n_slots[T_LOCAL]);
 }
-__device__ inline uint64_t chunk_offset(const ClassDev &c, int tier, uint32_t layer, uint32_t slot)
+template <typename C> __device__ inline uint64_t chunk_offset(const C &c, int tier, uint32_t layer, uint32_t slot)
 {
     uint64_t ls = tier == T_HOST ? c.layer_stride[T_HOST] : (tier == T_CACHE ? c.layer_stride[T_CACHE] : c.layer_stride[T_LOCAL]);
     uint64_t ss = tier == T_HOST ? c.slot_stride[T_HOST] : (tier == T_CACHE ? c.slot_stride[T_CACHE] : c.slot_stride[T_LOCAL]);
@@ -211,6 +211,23 @@ __device__ inline uint32_t wave_rank(bool pred, uint32_t &total)
 // The value that lane k of the wavefront has, k the same in all of them.
 __device__ inline uint32_t lane_value(uint32_t x, uint32_t k) { return __builtin_amdgcn_readlane(x, k); }
 __device__ inline uint64_t lane_value(uint64_t x, uint32_t k) { return (uint64_t)lane_value((uint32_t)(x >> 32), k) << 32 | lane_value((uint32_t)x, k); }
+// The bits that any lane of the wavefront has, in all of them.
+__device__ inline uint32_t wave_or(uint32_t x)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);      // row_shr:1, 2, 4, 8: lane 15 of each row has the row's
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, true);      // row_bcast:15 into rows 1 and 3, row_bcast:31 into 2 and 3
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, true);
+    return lane_value(x, 63);
+#else
+    uint32_t all = 0;
+    for (uint32_t k = 0; k < 32; ++k) all |= __ballot(x >> k & 1) ? 1u << k : 0u;
+    return all;
+#endif
+}
 template <uint32_t N> struct Count { static constexpr uint32_t value = N; };
 
 __device__ inline uint32_t wave_sum(uint32_t v)
@@ -406,6 +423,35 @@ struct HostList {
     }
 };
 
+// Who gets the PCIe link.  A fetch that reads from the host announces, in a word of device memory, until when it
+// expects to need the link (link_announce: now + its host-tier bytes at the link's rate, on the device's constant 100 MHz
+// clock); the copies that cross the link outside a fetch - placements, write-backs - look at that word before they take
+// their next tile and stand back while the time has not come (yield_link), though never for longer than YIELD_TICKS per
+// 32 KiB, whatever their tiles measure, so that they always get on (12 workgroups: 6.5 GB/s, a ninth of the link, when fetches
+// never pause).  A miss is on the
+// critical path and a placement is best effort (paper Sections 2.2 and 3.1).  An estimate instead of an exact begin /
+// end: nothing has to be counted or taken back, and a word that is stale means no more than "nobody is fetching".  The
+// estimate is on the short side (the rate of an undisturbed fetch, no margin): a copy that follows the fetch on the same
+// stream, which cannot run beside it anyway, must not be kept waiting for a fetch that is already over.
+constexpr uint64_t LINK_BYTES_PER_TICK = 575;      // 57.5 GB/s at 100 MHz
+constexpr uint64_t YIELD_TICKS = 6000;             // 60 us
+__device__ inline void link_announce(unsigned long long *lease, uint64_t host_bytes)
+{
+    if (!lease || !host_bytes) return;
+    atomicMax(lease, (unsigned long long)(wall_clock64() + host_bytes / LINK_BYTES_PER_TICK));
+}
+template <uint32_t TILE>
+__device__ inline void yield_link(const unsigned long long *lease)
+{
+    if (!lease) return;
+    const uint64_t t0 = wall_clock64();
+    for (;;) {
+        const uint64_t now = wall_clock64();
+        if (now - t0 >= YIELD_TICKS * TILE / 32768 || now >= __hip_atomic_load(lease, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+        __builtin_amdgcn_s_sleep(127);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------------------
 // Experts: one workgroup forms the distinct set of the routed expert numbers (bitmap in LDS), then walks the
 // experts in ascending order so that staging ranks are the ranks among the staged members of the set.
@@ -436,14 +482,13 @@ __global__ __launch_bounds__(WG) void mark_experts(const int32_t *__restrict__ t
     if (tid == 0 && inval) atomicAdd(g_invalid, inval);
 }
 
-__global__ __launch_bounds__(WG) void resolve_experts(ClassDev c, uint32_t layer, uint32_t n_experts,
-                                                      const int32_t *__restrict__ topk, uint32_t n_ids,
-                                                      uint64_t staging, uint32_t n_staging,
-                                                      uint64_t *__restrict__ expert_ptr, Rec *__restrict__ hbm_recs,
-                                                      Rec *__restrict__ host_recs, uint32_t *__restrict__ miss_idx,
-                                                      uint32_t *cnt, unsigned long long *totals, uint32_t *g_bitmap,
-                                                      uint32_t *g_invalid)
+template <typename C>              // ClassDev, as an argument or where the arguments are
+__device__ inline void resolve_routed(const C &c, uint32_t layer, uint32_t n_experts, const int32_t *__restrict__ topk, uint32_t n_ids,
+                                      uint64_t staging, uint32_t n_staging, uint64_t *__restrict__ expert_ptr, Rec *__restrict__ hbm_recs,
+                                      Rec *__restrict__ host_recs, uint32_t *__restrict__ miss_idx, uint32_t *cnt, unsigned long long *totals,
+                                      uint32_t *g_bitmap, uint32_t *g_invalid, Report *report, unsigned long long *lease)
 {
+    // hbm_recs == nullptr: the caller has no use for the lists, but for a report and the lease (see link_announce).
     // g_bitmap != nullptr: mark_experts has already formed the routed set; it is taken from there (and cleared).
     __shared__ uint32_t bitmap[MAX_EXPERTS / 32];
     __shared__ uint32_t s_cnt[C_N];
@@ -505,11 +550,11 @@ __global__ __launch_bounds__(WG) void resolve_experts(ClassDev c, uint32_t layer
                     Rec it;                 // few, large objects: their order in the lists does not matter
                     it.src = chunk_offset(c, tier, 0, slot) | (uint64_t)tier;
                     it.dst = (uint64_t)rank * c.chunk_bytes;
+                    const uint32_t at = atomicAdd(&s_cnt[tier == T_CACHE ? C_HBM_REQ : C_HOST_REQ], 1u);
+                    if (hbm_recs) (tier == T_CACHE ? hbm_recs : host_recs)[at] = it;
                     if (tier == T_CACHE) {
-                        hbm_recs[atomicAdd(&s_cnt[C_HBM_REQ], 1u)] = it;
                         atomicAdd(&s_cnt[C_CACHE], 1u);
                     } else {
-                        host_recs[atomicAdd(&s_cnt[C_HOST_REQ], 1u)] = it;
                         miss_idx[atomicAdd(&s_cnt[C_MISS], 1u)] = e;
                         atomicAdd(&s_cnt[C_HOST], 1u);
                     }
@@ -534,6 +579,19 @@ __global__ __launch_bounds__(WG) void resolve_experts(ClassDev c, uint32_t layer
         cnt[tid] = s_cnt[tid == C_LIST ? C_HBM_REQ : tid];
         if (tid <= C_INVALID && s_cnt[tid]) atomicAdd(&totals[tid], (unsigned long long)s_cnt[tid]);
     }
+    if (hbm_recs || tid) return;
+    const u32x4 r = { s_cnt[C_HBM_REQ], s_cnt[C_HOST_REQ], 0, 0 };
+    *reinterpret_cast<u32x4 *>(report) = r;
+    link_announce(lease, (uint64_t)s_cnt[C_HOST_REQ] * c.chunk_bytes);
+}
+
+__global__ __launch_bounds__(WG) void resolve_experts(ClassDev c, uint32_t layer, uint32_t n_experts, const int32_t *__restrict__ topk, uint32_t n_ids,
+                                                      uint64_t staging, uint32_t n_staging, uint64_t *__restrict__ expert_ptr, Rec *__restrict__ hbm_recs,
+                                                      Rec *__restrict__ host_recs, uint32_t *__restrict__ miss_idx, uint32_t *cnt,
+                                                      unsigned long long *totals, uint32_t *g_bitmap, uint32_t *g_invalid)
+{
+    resolve_routed(c, layer, n_experts, topk, n_ids, staging, n_staging, expert_ptr, hbm_recs, host_recs, miss_idx, cnt, totals, g_bitmap, g_invalid,
+                   nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -574,35 +632,6 @@ __device__ inline void copy_tile(uint64_t src, uint64_t dst, uint64_t len, uint3
     } else {
         uint32_t n_vec = (uint32_t)(len >> 4);
         for (uint32_t i = tid; i < n_vec; i += NTHR) st16<NT>(d + i, ld16<NT>(s + i));
-    }
-}
-
-// Who gets the PCIe link.  A fetch that reads from the host announces, in a word of device memory, until when it
-// expects to need the link (link_announce: now + its host-tier bytes at the link's rate, on the device's constant 100 MHz
-// clock); the copies that cross the link outside a fetch - placements, write-backs - look at that word before they take
-// their next tile and stand back while the time has not come (yield_link), though never for longer than YIELD_TICKS per
-// 32 KiB, whatever their tiles measure, so that they always get on (12 workgroups: 6.5 GB/s, a ninth of the link, when fetches
-// never pause).  A miss is on the
-// critical path and a placement is best effort (paper Sections 2.2 and 3.1).  An estimate instead of an exact begin /
-// end: nothing has to be counted or taken back, and a word that is stale means no more than "nobody is fetching".  The
-// estimate is on the short side (the rate of an undisturbed fetch, no margin): a copy that follows the fetch on the same
-// stream, which cannot run beside it anyway, must not be kept waiting for a fetch that is already over.
-constexpr uint64_t LINK_BYTES_PER_TICK = 575;      // 57.5 GB/s at 100 MHz
-constexpr uint64_t YIELD_TICKS = 6000;             // 60 us
-__device__ inline void link_announce(unsigned long long *lease, uint64_t host_bytes)
-{
-    if (!lease || !host_bytes) return;
-    atomicMax(lease, (unsigned long long)(wall_clock64() + host_bytes / LINK_BYTES_PER_TICK));
-}
-template <uint32_t TILE>
-__device__ inline void yield_link(const unsigned long long *lease)
-{
-    if (!lease) return;
-    const uint64_t t0 = wall_clock64();
-    for (;;) {
-        const uint64_t now = wall_clock64();
-        if (now - t0 >= YIELD_TICKS * TILE / 32768 || now >= __hip_atomic_load(lease, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-        __builtin_amdgcn_s_sleep(127);
     }
 }
 
@@ -1140,6 +1169,107 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restr
         const u32x4 r = { hbm, host, w.n_seq, max_blocks };        // one store
         *reinterpret_cast<u32x4 *>(w.report) = r;
         link_announce(w.lease, (uint64_t)host * a.chunk_bytes * PLANES * a.n_rep);
+    }
+}
+
+// A whole expert fetch in one kernel, for a few routing ids: what resolve_experts and the gather do in two launches, the first of which
+// is a chain of latencies and a boundary between kernels.  Every workgroup forms the routed set for itself: a wavefront loads the ids at once and
+// ors their bits together (by LDS atomics instead, 240 ids of 16 experts took 57 us against 42; by scalar loads and instructions the scalar unit,
+// one for 32 wavefronts, becomes the bound).  11 experts of 17.3 MB take 60.5 us (62.7 in two launches), 4 of them 24.4 (27.4), 2 of
+// 4.3 MB 6.0 (11.7), 14 of 17.3 MB 71.4 (73.0).  Two loads a thread, in 256 threads: with one load the way to it takes too much of a
+// workgroup's life (65.5), four are more bytes in flight than the memory takes (63.2); 64 and 128 threads with two: 60.3, 60.5.
+//
+// The rank of an expert, its place in the staging buffer, is its rank in the set, whatever the directory says: the caller sees to it that
+// all registered experts are in the cache tier or on the host.  A directory that changes under the fetch is met as in fetch_kv_small: an entry
+// that is younger than `seen` is copied by whoever reads it, and which of the host's readers reads which tile of an expert follows from
+// its rank alone.
+//
+// The first n_host workgroups read the host's experts (24 of them, 192 KiB in flight, see host_tier), the next one keeps the books, the others
+// copy a tile each, or several of them where the grid is short.
+constexpr uint32_t ROUTED_IDS = 64, ROUTED_EXPERTS = 128;      // routing ids and experts that the one kernel takes
+typedef const __attribute__((address_space(4))) uint64_t k_entry;      // (by scalar loads)
+struct RoutedArgs {
+    const int32_t *topk;
+    k_entry *dir;                        // of the layer
+    uint64_t chunk_bytes, staging;
+    uint64_t cache_base, cache_stride, host_base, host_stride;
+    uint32_t n_experts, n_known;         // known: registered
+    uint32_t n_cache_slots, n_host_slots;
+    uint32_t n_ids, n_staging, tiles_per_chunk, n_host, hbm_wgs, seen;
+};
+struct RoutedBooks {
+    ClassDev c;
+    uint64_t *expert_ptr;
+    uint32_t *miss_idx, *cnt;
+    unsigned long long *totals, *lease;
+    Report *report;
+    uint32_t layer, pad;
+};
+typedef const __attribute__((address_space(4))) RoutedBooks k_RoutedBooks;
+// The set of the routed experts, the same in all lanes.
+struct Routed { uint64_t lo, hi; };      // experts 0 to 63, 64 to 127
+__device__ inline Routed routed_set(const RoutedArgs &a)
+{
+    const uint32_t n = a.n_known < a.n_experts ? a.n_known : a.n_experts, lane = lane_id();
+    const uint32_t id = (uint32_t)a.topk[lane < a.n_ids ? lane : 0];
+    auto word = [&](uint32_t k) { return wave_or(id < n && id >> 5 == k ? 1u << (id & 31) : 0u); };
+    Routed set = { (uint64_t)word(1) << 32 | word(0), 0 };
+    if (a.n_experts > 64) set.hi = (uint64_t)word(3) << 32 | word(2);
+    return set;
+}
+// Number r of the set, or ~0.
+__device__ inline uint32_t routed_expert(const Routed &set, uint32_t r)
+{
+    const uint32_t n_lo = (uint32_t)__popcll(set.lo);
+    const bool low = r < n_lo;
+    const uint64_t m = low ? set.lo : set.hi;
+    if (!low) r -= n_lo;
+    // lane i: is expert i in the set, and the r-th of it
+    const uint64_t it = __ballot((m >> lane_id() & 1) && (uint32_t)__popcll(m & ((1ull << lane_id()) - 1)) == r);
+    if (!it) return ~0u;
+    return (uint32_t)__builtin_ctzll(it) + (low ? 0 : 64);
+}
+template <int NTHR, int U>
+__global__ __launch_bounds__(NTHR) void fetch_experts_small(RoutedArgs a, RoutedBooks)
+{
+    constexpr uint32_t TILE = NTHR * 16 * U;
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x == a.n_host) {
+        k_RoutedBooks &b = *(k_RoutedBooks *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + sizeof(RoutedArgs));
+        resolve_routed(b.c, b.layer, a.n_experts, a.topk, a.n_ids, a.staging, a.n_staging, b.expert_ptr, nullptr, nullptr, b.miss_idx,
+                       b.cnt, b.totals, nullptr, nullptr, b.report, b.lease);
+        return;
+    }
+    const Routed set = routed_set(a);
+    if (blockIdx.x < a.n_host) {
+        // tiles are numbered through the set, and every n_host-th one is this workgroup's
+        const uint32_t tpc = a.tiles_per_chunk;
+        uint32_t piece = blockIdx.x;     // of expert number r
+        for (uint32_t r = 0; r < a.n_staging; ++r) {
+            const uint32_t x = routed_expert(set, r);
+            if (x == ~0u) return;
+            const uint64_t e = a.dir[x], slot = entry_slot(e), dst = a.staging + (uint64_t)r * a.chunk_bytes;
+            const bool host = entry_tier(e) == T_HOST, young = entry_tier(e) == T_CACHE && entry_young(e, a.seen);
+            if ((host && slot < a.n_host_slots) || (young && slot < a.n_cache_slots)) {
+                const uint64_t src = host ? a.host_base + slot * a.host_stride : a.cache_base + slot * a.cache_stride;
+                for (; piece < tpc; piece += a.n_host)
+                    copy_tile<NTHR, U, false>(src + (uint64_t)piece * TILE, dst + (uint64_t)piece * TILE, a.chunk_bytes - (uint64_t)piece * TILE, tid);
+            } else if (piece < tpc) piece += (tpc - piece + a.n_host - 1) / a.n_host * a.n_host;
+            piece -= tpc;
+        }
+        return;
+    }
+    for (uint32_t t = blockIdx.x - a.n_host - 1;; t += a.hbm_wgs) {
+        const uint32_t r = t / a.tiles_per_chunk;
+        if (r >= a.n_staging) return;
+        const uint32_t x = routed_expert(set, r);
+        if (x == ~0u) return;
+        const uint64_t e = a.dir[x], slot = entry_slot(e), off = (uint64_t)(t - r * a.tiles_per_chunk) * TILE;
+        const bool cached = entry_tier(e) == T_CACHE;
+        if (cached ? slot < a.n_cache_slots : entry_tier(e) == T_HOST && entry_young(e, a.seen) && slot < a.n_host_slots) {
+            const uint64_t src = cached ? a.cache_base + slot * a.cache_stride : a.host_base + slot * a.host_stride;
+            copy_tile<NTHR, U, true>(src + off, a.staging + (uint64_t)r * a.chunk_bytes + off, a.chunk_bytes - off, tid);
+        }
     }
 }
 

@@ -193,4 +193,46 @@ int run_fetch(const Fetch *f)
             }
     return 0;
 }
+
+struct Experts {
+    uint32_t n_experts, n_known, n_ids, n_staging, n_host, hbm_wgs, seen, n_versions, n_slots, pad;
+    uint64_t chunk_bytes, pool[2], staging;      // [tier]: host, cache
+    const int32_t *topk;
+    const uint64_t *versions;                    // [n_versions][n_experts]
+    const uint32_t *when;                        // [workgroup][n_versions - 1]: at which of its ballots or barriers
+    uint64_t *expert_ptr;
+    uint32_t *cnt, *miss;
+};
+int run_experts(const Experts *f)
+{
+    using namespace hv;
+    std::vector<uint64_t> dir(f->versions, f->versions + f->n_experts);
+    struct { RoutedArgs a; RoutedBooks b; } arguments{};
+    kernel_arguments = (const char *)&arguments;
+    RoutedArgs &a = arguments.a;
+    RoutedBooks &b = arguments.b;
+    a.topk = f->topk; a.dir = (k_entry *)dir.data(); a.chunk_bytes = f->chunk_bytes; a.staging = f->staging;
+    a.cache_base = f->pool[1]; a.host_base = f->pool[0]; a.cache_stride = a.host_stride = f->chunk_bytes;
+    a.n_experts = f->n_experts; a.n_known = f->n_known; a.n_cache_slots = a.n_host_slots = f->n_slots;
+    a.n_ids = f->n_ids; a.n_staging = f->n_staging; a.n_host = f->n_host; a.hbm_wgs = f->hbm_wgs; a.seen = f->seen;
+    a.tiles_per_chunk = (uint32_t)((f->chunk_bytes + WG * 32 - 1) / (WG * 32));
+    std::vector<unsigned long long> totals(C_N);
+    alignas(16) Report report;
+    b.c.dir = dir.data(); b.c.n_objects = f->n_known; b.c.chunk_bytes = f->chunk_bytes;
+    b.c.n_slots[T_HOST] = b.c.n_slots[T_CACHE] = f->n_slots;
+    b.expert_ptr = f->expert_ptr; b.miss_idx = f->miss; b.cnt = f->cnt; b.totals = totals.data(); b.report = &report;
+    g_kernel = [&] { fetch_experts_small<WG, 2>(a, b); };
+    gridDim = { f->n_host + 1 + f->hbm_wgs, 1, 1 };
+    const uint32_t *when = f->when;
+    for (uint32_t x = 0; x < gridDim.x; ++x, when += f->n_versions - 1) {
+        blockIdx = { x, 0, 0 };
+        auto versions_at = [&](uint32_t met) {
+            uint32_t v = 0;
+            while (v + 1 < f->n_versions && when[v] <= met) v++;
+            memcpy(dir.data(), f->versions + (uint64_t)v * f->n_experts, f->n_experts * 8);
+        };
+        run_workgroup(WG, versions_at);
+    }
+    return (int)report.hbm;
+}
 }  // extern "C"

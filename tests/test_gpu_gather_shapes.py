@@ -757,3 +757,86 @@ def test_chunks_around_the_size_from_which_planes_side_by_side_are_taken_in_one_
                 assert np.array_equal(got[layer * cap * chunk:(layer + 1) * cap * chunk], rig.expected(t, lens, p, layer)), (p, layer)
             assert (got[2 * cap * chunk:] == 0xEE).all()
     rig.h.close()
+
+
+class ExpertRig:
+    def __init__(self, e, chunk, known=None, on_host=(), **kw):
+        rng = np.random.default_rng(e + chunk)
+        self.e, self.chunk, self.known = e, chunk, e if known is None else known
+        self.weights = rng.integers(0, 256, (e, chunk), dtype=np.uint8)
+        slots = rng.permutation(e).astype(np.int64)
+        self.h = B.Harvest(expert=B.ClassSpec(n_layers=1, n_planes=1, chunk_bytes=chunk, max_objects=e, n_host_slots=e, n_cache_slots=e, n_local_slots=0,
+                                              n_experts=e), **kw)
+        self.h.host_plane(B.EXPERT, 0)[0, slots] = self.weights
+        self.h.register(B.EXPERT, self.known, slots[:self.known])
+        self.on_host = np.zeros(e, dtype=bool)
+        self.on_host[list(on_host)] = True
+        cached = rng.permutation(np.flatnonzero(~self.on_host[:self.known]))
+        if len(cached):
+            self.h.place(B.EXPERT, cached)
+        torch.cuda.synchronize()
+
+    def fetch(self, ids, n_staging, stream=None):
+        staging = torch.full((n_staging * self.chunk + 64,), 0xEE, dtype=torch.uint8, device="cuda")
+        ptrs = torch.full((self.e,), 7, dtype=torch.int64, device="cuda")
+        self.h.fetch_experts(0, torch.from_numpy(np.ascontiguousarray(ids[None])).cuda(), staging, n_staging, ptrs, stream=stream)
+        counts, miss, _ = self.h.fetch_info(miss_cap=self.e)
+        return staging.cpu().numpy(), ptrs.cpu().numpy() - staging.data_ptr(), counts, sorted(miss.tolist())
+
+
+@pytest.mark.parametrize("e,known,chunk,n_ids,n_staging", [(1, 1, 16, 1, 1), (60, 60, 8192 * 3 + 48, 16, 60), (64, 64, 4096, 64, 64), (65, 65, 8208, 64, 65), (128, 128, 1 << 18, 64, 128),
+                                                           (128, 100, 8192, 50, 128), (90, 90, 12288, 40, 5), (120, 120, 1040, 33, 120)])
+@pytest.mark.parametrize("n_host", [0, 1])
+def test_one_kernel_expert_fetch(e, known, chunk, n_ids, n_staging, n_host):
+    """From the second fetch on, against numpy: repeated ids and ids that are out of range, experts that nobody has registered, less staging
+    than experts; the grid is sized by the fetch before, which had fewer or more."""
+    rig = ExpertRig(e, chunk, known, on_host=range(n_host))
+    rng = np.random.default_rng(n_ids)
+    totals = {}
+    for turn in range(5):
+        ids = rng.integers(-1 if n_ids > 4 else 0, e + (n_ids > 4), n_ids if turn % 2 else max(1, n_ids // 3)).astype(np.int32)
+        if turn < 2:
+            ids[ids < n_host] = n_host % e               # the first reports say that HBM is what the fetch waits for
+        got, ptrs, counts, miss = rig.fetch(ids, n_staging)
+        routed = [i for i in sorted(set(ids.tolist())) if 0 <= i < e]
+        staged = [i for i in routed if i < known][:n_staging]
+        assert np.array_equal(got[:len(staged) * chunk].reshape(-1, chunk), rig.weights[staged]) and (got[len(staged) * chunk:] == 0xEE).all(), turn
+        at = np.zeros(e, dtype=np.int64)
+        at[staged] = np.arange(len(staged)) * chunk
+        there = np.isin(np.arange(e), staged)
+        assert np.array_equal(ptrs[there], at[there]) and (ptrs[~there] < 0).all()
+        assert miss == [i for i in staged if rig.on_host[i]] and counts["n_requests"] == len(routed)
+        assert counts["n_invalid"] == int(((ids < 0) | (ids >= e)).sum()) + len(routed) - len(staged) and counts["n_cache"] == len(staged) - len(miss)
+        for name, x in counts.items():
+            totals[name] = totals.get(name, 0) + x
+        assert rig.h.stats().fetch[B.EXPERT].as_dict() == totals
+    rig.h.close()
+
+
+@pytest.mark.parametrize("edit", ["revoked", "placed"])
+def test_a_one_kernel_expert_fetch_is_whole_when_the_directory_changes_under_it(edit):
+    e, chunk = 96, 1 << 20
+    rig = ExpertRig(e, chunk, on_host=[0])
+    for i in range(e):
+        rig.h.register_cb(B.EXPERT, i, enabled=False)
+    side = torch.cuda.Stream()
+    every = np.arange(e, dtype=np.int32)
+    staging, ptrs = torch.zeros(e * chunk, dtype=torch.uint8, device="cuda"), torch.zeros(e, dtype=torch.int64, device="cuda")
+    d_ids = torch.from_numpy(every[None, :60].copy()).cuda()
+    want = torch.from_numpy(rig.weights[:60].reshape(-1)).cuda()
+    for turn in range(6):
+        rig.fetch(every[30:62] if edit == "placed" else every[:60], e)          # reports about HBM
+        if edit == "placed":
+            rig.h.revoke(B.EXPERT, every[10:12])
+        staging.zero_()
+        torch.cuda.synchronize()
+        rig.h.fetch_experts(0, d_ids, staging, e, ptrs)
+        if edit == "revoked":
+            rig.h.revoke(B.EXPERT, every[5 * turn + 1:5 * turn + 6])
+        else:
+            rig.h.place(B.EXPERT, every[10:12], stream=side)
+        torch.cuda.synchronize()
+        assert torch.equal(staging[:60 * chunk], want), (turn, int((staging[:60 * chunk] != want).reshape(60, -1).any(1).sum()))
+        if edit == "revoked":
+            rig.h.place(B.EXPERT, every[5 * turn + 1:5 * turn + 6])
+    rig.h.close()

@@ -386,3 +386,70 @@ def test_a_callers_numbers_of_workgroups_are_taken_as_they_are(fake, tuning, rea
     assert c.evict(np.arange(150)) == B.OK
     assert grid("move_pcie") == writers
     c.close()
+
+
+def expert_context(lib, n=60, n_local=0, local=(), flags=0):
+    """n experts of 1 MiB, the last n_local of them registered as local; `local`: those without a host copy."""
+    cfg = B.harvest_config()
+    cfg.flags = flags
+    ex = cfg.cls[B.EXPERT]
+    ex.n_layers, ex.n_planes, ex.chunk_bytes, ex.max_objects, ex.n_experts = 1, 1, 1 << 20, n, n
+    ex.n_host_slots, ex.n_cache_slots, ex.n_local_slots = n, n, 4
+    ex.host_pool[0], ex.d_cache_pool[0], ex.d_local_pool[0] = POOL, POOL * 2, POOL * 3
+    h, out = ctypes.c_void_p(), np.empty(n, dtype=np.uint32)
+    assert lib.harvest_create(ctypes.byref(cfg), ctypes.byref(h)) == B.OK
+    slots = np.arange(n, dtype=np.int64)
+    assert lib.harvest_register(h, B.EXPERT, n - n_local, slots.ctypes.data, B.HOST, B.REVOKE_CB(), None, out.ctypes.data) == B.OK
+    if n_local:
+        assert lib.harvest_register(h, B.EXPERT, n_local, None if local == "lossy" else slots[n - n_local:].ctypes.data, B.LOCAL, B.REVOKE_CB(), None, out.ctypes.data) == B.OK
+    return h
+
+
+def test_a_few_routing_ids_are_fetched_by_one_kernel_when_ranks_and_edits_are_known(fake):
+    """The rank of an expert has to follow from the ids alone, and the latest report to say that HBM is what the fetch waits for."""
+    lib = fake
+
+    def path(h, stream, n_ids=16, staging=60):
+        lib.fake_log()
+        assert lib.harvest_fetch_experts(h, 0, POOL * 4, n_ids, 1, POOL * 5, staging, POOL * 6, stream) == B.OK
+        log = lib.fake_log().decode().splitlines()
+        small = bool(launches(log, "fetch_experts_small"))
+        assert small != bool(launches(log, "resolve_experts")), log
+        return "one kernel" if small else "general"
+
+    def report(hbm, host):
+        words = (ctypes.c_uint32 * 16).from_address(lib.fake_pinned(64, lib.fake_pinned_count(64) - 1))
+        words[4:8] = [hbm, host, 0, 0]
+
+    h, s = expert_context(lib), lib.fake_stream()
+    assert path(h, s) == "general"                        # nothing is known yet
+    report(11, 0)
+    assert path(h, s) == path(h, s, n_ids=64) == path(h, s, staging=1) == "one kernel"
+    assert path(h, s, n_ids=65) == path(h, s, n_ids=0) == path(h, s, staging=0) == "general"
+    report(11, 1)                                         # the link is what it waits for
+    assert path(h, s) == "general"
+    report(300, 0)                                        # 300 MiB
+    assert path(h, s) == "general"
+    report(11, 0)
+    lib.fake_capture(s)
+    assert path(h, s) == "general"
+    lib.fake_capture(None)
+    assert path(h, s) == "one kernel"
+    other = lib.fake_stream()                             # another stream places: until its edit is seen
+    assert path(h, other) == "general"
+    report(11, 0)
+    assert path(h, other) == "one kernel"
+    ids = np.array([3], dtype=np.uint32)
+    lib.fake_not_ready(True)
+    assert lib.harvest_place(h, B.EXPERT, ids.ctypes.data, 1, s, None) == B.OK
+    assert path(h, other) == "general"
+    lib.fake_not_ready(False)
+    assert path(h, other) == "one kernel"
+    assert lib.harvest_destroy(h) == B.OK
+    for kw, expected in (({}, "one kernel"), (dict(n_local=2), "general"), (dict(n_local=2, local="lossy"), "general"), (dict(n=129), "general"),
+                         (dict(flags=B.FLAG_GENERAL_FETCH), "general"), (dict(flags=B.FLAG_PROFILE), "general")):
+        h, s = expert_context(lib, **kw), lib.fake_stream()
+        assert path(h, s) == "general"
+        report(11, 0)
+        assert path(h, s) == expected, kw
+        assert lib.harvest_destroy(h) == B.OK

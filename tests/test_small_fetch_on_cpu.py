@@ -184,3 +184,60 @@ def test_blocks_are_whole_with_two_loads_a_thread(emulated, edit, n_planes, n_la
     after = tier.copy()
     after[rng.permutation(np.flatnonzero(tier == (CACHE if edit == "revoked" else HOST)))[:9]] = HOST if edit == "revoked" else CACHE
     c.run([tier, after])
+
+
+class Experts(ctypes.Structure):
+    _fields_ = [(n, u32) for n in ("n_experts", "n_known", "n_ids", "n_staging", "n_host", "hbm_wgs", "seen", "n_versions", "n_slots", "pad")]
+    _fields_ += [("chunk_bytes", u64), ("pool", u64 * 2), ("staging", u64)] + [(n, vp) for n in ("topk", "versions", "when", "expert_ptr", "cnt", "miss")]
+
+
+@pytest.mark.parametrize("edit", [None, "revoked", "placed", "placed and revoked"])
+@pytest.mark.parametrize("n_experts,n_known,n_ids,n_staging,n_host,short,chunk", [(60, 60, 16, 60, 5, 1, 24576 + 16), (64, 64, 50, 64, 3, 0.4, 8192), (128, 128, 64, 128, 7, 0.7, 4096),
+                                                                                  (65, 50, 30, 65, 1, 1, 16), (100, 100, 40, 9, 24, 1, 8192 + 4112), (1, 1, 1, 1, 2, 1, 40960), (33, 33, 5, 33, 0, 1, 8208)])
+def test_routed_experts_are_whole_when_entries_change_under_the_fetch(emulated, edit, n_experts, n_known, n_ids, n_staging, n_host, short, chunk):
+    """A grid of a tile each and shorter ones, ids that are out of range, experts that nobody has registered, less staging than experts."""
+    rng = np.random.default_rng(n_experts + n_ids)
+    ids = rng.integers(0, n_experts, n_ids).astype(np.int32)
+    if n_ids > 4:
+        ids[1], ids[3] = -1, n_experts
+    weights = aligned((n_experts, chunk))
+    weights[:] = rng.integers(0, 256, weights.shape, dtype=np.uint8)
+    pools = [aligned(weights.shape) for _ in range(2)]
+    for x in pools:
+        x[:] = weights
+    inside = sorted({int(i) for i in ids if 0 <= i < n_experts})
+    routed = [i for i in inside if i < n_known]
+    staged = routed[:n_staging]
+    tier = rng.choice([HOST, CACHE], n_experts, p=[0.3, 0.7]) if n_host else np.full(n_experts, CACHE)
+    tiers = [tier]
+    if edit and n_host:
+        moved = rng.permutation(np.flatnonzero(tier == (CACHE if edit == "revoked" else HOST)))[:7]
+        tiers.append(tier.copy())
+        tiers[1][moved] = HOST if edit == "revoked" else CACHE
+        if edit == "placed and revoked":
+            tiers.append(tiers[1].copy())
+            tiers[2][moved[::2]] = HOST
+    versions = np.empty((len(tiers), n_experts), dtype=np.uint64)
+    for v, t in enumerate(tiers):
+        for i in range(n_experts):
+            versions[v, i] = entry(t[i], i, 3) if v == 0 else (versions[v - 1, i] if t[i] == tiers[v - 1][i] else entry(t[i], i, 7 + v))
+    versions[:, n_known:] = np.uint64(0xFFFFFFFFFFFFFFFF)
+    tiles = -(-chunk // 8192)
+    wgs = max(1, int(short * len(staged) * tiles))
+    when = np.sort(rng.choice([0, NEVER], (n_host + 1 + wgs, len(tiers) - 1)), axis=1).astype(np.uint32)
+    staging, ptr = aligned((n_staging, chunk)), np.full(n_experts, 7, dtype=np.uint64)
+    staging[:] = 0xEE
+    cnt, miss = np.zeros(16, dtype=np.uint32), np.zeros(n_experts, dtype=np.uint32)
+    f = Experts(n_experts=n_experts, n_known=n_known, n_ids=n_ids, n_staging=n_staging, n_host=n_host, hbm_wgs=wgs, seen=7, n_versions=len(tiers),
+                n_slots=n_experts, chunk_bytes=chunk, staging=staging.ctypes.data, topk=ids.ctypes.data, versions=versions.ctypes.data,
+                when=when.ctypes.data, expert_ptr=ptr.ctypes.data, cnt=cnt.ctypes.data, miss=miss.ctypes.data)
+    f.pool[0], f.pool[1] = pools[0].ctypes.data, pools[1].ctypes.data
+    hbm = emulated.run_experts(ctypes.byref(f))
+    assert np.array_equal(staging[:len(staged)], weights[staged]) and (staging[len(staged):] == 0xEE).all()
+    want = np.zeros(n_experts, dtype=np.uint64)
+    want[staged] = staging.ctypes.data + np.arange(len(staged), dtype=np.uint64) * chunk
+    assert np.array_equal(ptr, want)
+    assert cnt[0] == len(inside) and cnt[2] + cnt[3] == len(staged) and hbm == cnt[2]
+    assert cnt[5] == len(inside) - len(staged) + (2 if n_ids > 4 else 0)
+    if len(tiers) == 1:
+        assert cnt[3] == sum(tier[i] == HOST for i in staged) and sorted(miss[:cnt[3]]) == [i for i in staged if tier[i] == HOST]
