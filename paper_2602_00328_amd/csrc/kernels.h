@@ -697,13 +697,14 @@ __device__ inline void host_tier(const HostList &recs, const GatherArgs &a, uint
 {
     const uint32_t ppc = a.pages_per_chunk, n_pages = recs.sums.total * ppc;      // (fits: the host bounds requests times 1 KiB tiles)
     if (!n_pages) return;
-    uint32_t rep = 0, g = b0, step_reps = 0, step = a.n_host;
+    uint32_t rep = 0, g = b0, step_reps = 0, step = a.n_host, at = ~0u;
+    Rec x = { 0, 0 };
     if (a.n_rep > 1) { step_reps = step / n_pages; step -= step_reps * n_pages; rep = g / n_pages; g %= n_pages; }
     for (;; rep += step_reps, g += step) {
         if (g >= n_pages) { g -= n_pages; rep++; }
         if (rep >= a.n_rep) return;
         const uint32_t idx = g / ppc, page = g - idx * ppc;
-        const Rec x = recs[idx];
+        if (idx != at) { at = idx; x = recs[idx]; }            // (a whole expert has thousands of pages: 2 727 us, 2 725 this way)
         host_page<NTHR, PLANES, LOADS>(a, (x.src & 0x0000FFFFFFFFFFFCull) + rep * a.layer_stride[T_HOST], x.dst + rep * a.dst_step, page,
                                        threadIdx.x);
     }
