@@ -1391,7 +1391,9 @@ __device__ inline MoveChunk move_chunk(const MoveArgs &a, uint32_t item)
 // counted out one at a time from a.next: when something else is using the link as well, the
 // workgroups of one launch progress at very different rates (a 3.4-fold spread was measured), and with fixed shares
 // the launch ends with a few workgroups working off their backlog alone - a 906 MB placement beside a stream of
-// fetches took 106 ms that way.  The counter is zero at launch and again at the end: every workgroup draws one number
+// fetches took 106 ms that way.  Only the first tile is the workgroup's own, without a draw - nothing has run at any rate yet, and lists of
+// no more tiles than workgroups draw none at all (8 MiB to the host 78.3 us with a draw in front, 77.8 without, 1 MiB 23.0 and 22.8, 0.5 MiB
+// in tiles of 16 KiB 13.9 and 13.4).  The counter is zero at launch and again at the end: every workgroup draws one number
 // beyond the tiles, and the one that draws the last puts it back.  The next number is drawn while the tile is on its way; whether
 // a fetch needs the link is asked last, right before the next tile's loads go out - asked along with the draw, the answer was a tile
 // old, and a fetch of 200 blocks beside a placement of 32 workgroups took 1.56 ms instead of 0.98 (alone 0.25).
@@ -1414,9 +1416,10 @@ __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
     constexpr int WAY1 = WAY == PLAIN_STORES ? PLAIN_STORES : NT_STORES;        // of the copy that stays in HBM
     __shared__ unsigned long long s_tile[2];
     const uint32_t tid = threadIdx.x;
-    if (tid == 0) { yield_link<TILE>(a.lease); s_tile[0] = atomicAdd(a.next, 1ull); }
+    const bool drawn = a.n_tiles > gridDim.x;            // otherwise every workgroup has the one tile that it starts with
+    if (tid == 0) yield_link<TILE>(a.lease);
     __syncthreads();
-    uint64_t t = s_tile[0];
+    uint64_t t = blockIdx.x;
     for (uint32_t turn = 1; t < a.n_tiles; turn ^= 1) {
         const uint32_t item = (uint32_t)t / a.tiles_per_chunk;
         const uint64_t off = (uint64_t)((uint32_t)t - item * a.tiles_per_chunk) * TILE;
@@ -1428,7 +1431,7 @@ __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
             u32x4 v[U];
 #pragma unroll
             for (int i = 0; i < U; ++i) v[i] = ld16<false>(s + tid + i * WG);
-            if (tid == 0) s_tile[turn] = atomicAdd(a.next, 1ull);
+            if (drawn && tid == 0) s_tile[turn] = gridDim.x + atomicAdd(a.next, 1ull);
             if (m.dst0) {
 #pragma unroll
                 for (int i = 0; i < U; ++i) st16_to<WAY>(d0 + tid + i * WG, v[i]);
@@ -1438,7 +1441,7 @@ __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
                 for (int i = 0; i < U; ++i) st16_to<WAY1>(d1 + tid + i * WG, v[i]);
             }
         } else {
-            if (tid == 0) s_tile[turn] = atomicAdd(a.next, 1ull);
+            if (drawn && tid == 0) s_tile[turn] = gridDim.x + atomicAdd(a.next, 1ull);
             const uint32_t n_vec = (uint32_t)(len >> 4);
             for (uint32_t i = tid; i < n_vec; i += WG) {
                 u32x4 v = ld16<false>(s + i);
@@ -1446,6 +1449,7 @@ __global__ __launch_bounds__(WG) void move_pcie(MoveArgs a, MoveList)
                 if (m.dst1) st16_to<WAY1>(d1 + i, v);
             }
         }
+        if (!drawn) return;
         if (tid == 0) yield_link<TILE>(a.lease);
         __syncthreads();                         // two words in turn: nobody reads the one that is written next
         t = s_tile[turn];

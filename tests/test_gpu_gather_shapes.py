@@ -840,3 +840,26 @@ def test_a_one_kernel_expert_fetch_is_whole_when_the_directory_changes_under_it(
         if edit == "revoked":
             rig.h.place(B.EXPERT, every[5 * turn + 1:5 * turn + 6])
     rig.h.close()
+
+
+@pytest.mark.parametrize("pcie_wgs", [0, 1, 4])
+@pytest.mark.parametrize("n", [1, 2, 3, 6, 7, 10, 11, 30])
+def test_moves_of_fewer_and_of_more_tiles_than_workgroups(n, pcie_wgs):
+    """Two tiles a block, against 12 workgroups from the host, 20 to it, or 1 and 4; three calls in a row on the same tile counter."""
+    chunk = 32768
+    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n, n_host_slots=n, n_cache_slots=n, n_local_slots=0), pcie_wgs=pcie_wgs)
+    rng = np.random.default_rng(n)
+    slots = rng.permutation(n).astype(np.int64)
+    ids = h.register(B.KV, n, slots)
+    at = rng.permutation(n).astype(np.uint64)
+    for turn in range(3):
+        src = [torch.from_numpy(rng.integers(0, 256, (n, chunk), dtype=np.uint8)).cuda() for _ in range(2)]
+        h.evict(B.KV, -1, ids, src[0], src[1], at, n)
+        h.place(B.KV, ids)
+        torch.cuda.synchronize()
+        for p in range(2):
+            want = src[p].cpu().numpy()[at.astype(np.int64)]
+            assert np.array_equal(h.host_plane(B.KV, p)[0][slots], want), (turn, p)
+            assert np.array_equal(h.dev_plane(B.KV, B.CACHE, p)[0].cpu().numpy(), want), (turn, p)
+        h.revoke(B.KV, ids)
+    h.close()
