@@ -1178,7 +1178,9 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restr
 // ors their bits together (by LDS atomics instead, 240 ids of 16 experts took 57 us against 42; by scalar loads and instructions the scalar unit,
 // one for 32 wavefronts, becomes the bound).  11 experts of 17.3 MB take 60.5 us (62.7 in two launches), 4 of them 24.4 (27.4), 2 of
 // 4.3 MB 6.0 (11.7), 14 of 17.3 MB 71.4 (73.0).  Two loads a thread, in 256 threads: with one load the way to it takes too much of a
-// workgroup's life (65.5), four are more bytes in flight than the memory takes (63.2); 64 and 128 threads with two: 60.3, 60.5.
+// workgroup's life (65.5), four are more bytes in flight than the memory takes (63.2); 64 and 128 threads with two: 60.3, 60.5.  256 ids of 16
+// experts of 4.3 MB 27.1 in two launches and 24.7; with room for 512 ids 24.9, and 512 of them 25.0, but 32 ids 45.3 instead of 45.1 and 11
+// experts 60.6 instead of 60.4.
 //
 // The rank of an expert, its place in the staging buffer, is its rank in the set, whatever the directory says: the caller sees to it that
 // all registered experts are in the cache tier or on the host.  A directory that changes under the fetch is met as in fetch_kv_small: an entry
@@ -1187,7 +1189,7 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restr
 //
 // The first n_host workgroups read the host's experts (24 of them, 192 KiB in flight, see host_tier), the next one keeps the books, the others
 // copy a tile each, or several of them where the grid is short.
-constexpr uint32_t ROUTED_IDS = 64, ROUTED_EXPERTS = 128;      // routing ids and experts that the one kernel takes
+constexpr uint32_t ROUTED_IDS = 256, ROUTED_EXPERTS = 128;      // routing ids and experts that the one kernel takes
 typedef const __attribute__((address_space(4))) uint64_t k_entry;      // (by scalar loads)
 struct RoutedArgs {
     const int32_t *topk;
@@ -1212,10 +1214,18 @@ struct Routed { uint64_t lo, hi; };      // experts 0 to 63, 64 to 127
 __device__ inline Routed routed_set(const RoutedArgs &a)
 {
     const uint32_t n = a.n_known < a.n_experts ? a.n_known : a.n_experts, lane = lane_id();
-    const uint32_t id = (uint32_t)a.topk[lane < a.n_ids ? lane : 0];
-    auto word = [&](uint32_t k) { return wave_or(id < n && id >> 5 == k ? 1u << (id & 31) : 0u); };
-    Routed set = { (uint64_t)word(1) << 32 | word(0), 0 };
-    if (a.n_experts > 64) set.hi = (uint64_t)word(3) << 32 | word(2);
+    uint32_t id[ROUTED_IDS / 64], bits[ROUTED_EXPERTS / 32] = { 0, 0, 0, 0 };
+#pragma unroll
+    for (uint32_t i = 0; i < ROUTED_IDS / 64; ++i) {
+        id[i] = ~0u;
+        if (i * 64 < a.n_ids) id[i] = (uint32_t)a.topk[i * 64 + lane < a.n_ids ? i * 64 + lane : 0];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < ROUTED_IDS / 64; ++i)
+#pragma unroll
+        for (uint32_t k = 0; k < ROUTED_EXPERTS / 32; ++k) bits[k] |= id[i] < n && id[i] >> 5 == k ? 1u << (id[i] & 31) : 0u;
+    Routed set = { (uint64_t)wave_or(bits[1]) << 32 | wave_or(bits[0]), 0 };
+    if (a.n_experts > 64) set.hi = (uint64_t)wave_or(bits[3]) << 32 | wave_or(bits[2]);
     return set;
 }
 // Number r of the set, or ~0.

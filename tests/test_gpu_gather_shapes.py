@@ -784,7 +784,7 @@ class ExpertRig:
         return staging.cpu().numpy(), ptrs.cpu().numpy() - staging.data_ptr(), counts, sorted(miss.tolist())
 
 
-@pytest.mark.parametrize("e,known,chunk,n_ids,n_staging", [(1, 1, 16, 1, 1), (60, 60, 8192 * 3 + 48, 16, 60), (64, 64, 4096, 64, 64), (65, 65, 8208, 64, 65), (128, 128, 1 << 18, 64, 128),
+@pytest.mark.parametrize("e,known,chunk,n_ids,n_staging", [(1, 1, 16, 1, 1), (60, 60, 8192 * 3 + 48, 16, 60), (64, 64, 4096, 64, 64), (16, 16, 4096, 256, 16), (127, 127, 2048, 193, 127), (65, 65, 8208, 65, 65), (128, 128, 1 << 18, 64, 128),
                                                            (128, 100, 8192, 50, 128), (90, 90, 12288, 40, 5), (120, 120, 1040, 33, 120)])
 @pytest.mark.parametrize("n_host", [0, 1])
 def test_one_kernel_expert_fetch(e, known, chunk, n_ids, n_staging, n_host):

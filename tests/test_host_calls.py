@@ -424,8 +424,8 @@ def test_a_few_routing_ids_are_fetched_by_one_kernel_when_ranks_and_edits_are_kn
     h, s = expert_context(lib), lib.fake_stream()
     assert path(h, s) == "general"                        # nothing is known yet
     report(11, 0)
-    assert path(h, s) == path(h, s, n_ids=64) == path(h, s, staging=1) == "one kernel"
-    assert path(h, s, n_ids=65) == path(h, s, n_ids=0) == path(h, s, staging=0) == "general"
+    assert path(h, s) == path(h, s, n_ids=256) == path(h, s, staging=1) == "one kernel"
+    assert path(h, s, n_ids=257) == path(h, s, n_ids=0) == path(h, s, staging=0) == "general"
     report(11, 1)                                         # the link is what it waits for
     assert path(h, s) == "general"
     report(300, 0)                                        # 300 MiB

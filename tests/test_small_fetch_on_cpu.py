@@ -193,7 +193,8 @@ class Experts(ctypes.Structure):
 
 @pytest.mark.parametrize("edit", [None, "revoked", "placed", "placed and revoked"])
 @pytest.mark.parametrize("n_experts,n_known,n_ids,n_staging,n_host,short,chunk", [(60, 60, 16, 60, 5, 1, 24576 + 16), (64, 64, 50, 64, 3, 0.4, 8192), (128, 128, 64, 128, 7, 0.7, 4096),
-                                                                                  (65, 50, 30, 65, 1, 1, 16), (100, 100, 40, 9, 24, 1, 8192 + 4112), (1, 1, 1, 1, 2, 1, 40960), (33, 33, 5, 33, 0, 1, 8208)])
+                                                                                  (65, 50, 30, 65, 1, 1, 16), (100, 100, 40, 9, 24, 1, 8192 + 4112), (1, 1, 1, 1, 2, 1, 40960), (33, 33, 5, 33, 0, 1, 8208), (16, 16, 256, 16, 3, 1, 8192),
+                                                                                  (128, 128, 129, 128, 5, 1, 2048)])
 def test_routed_experts_are_whole_when_entries_change_under_the_fetch(emulated, edit, n_experts, n_known, n_ids, n_staging, n_host, short, chunk):
     """A grid of a tile each and shorter ones, ids that are out of range, experts that nobody has registered, less staging than experts."""
     rng = np.random.default_rng(n_experts + n_ids)
