@@ -355,7 +355,7 @@ struct StreamState {
                                             // state of a stream that harvest_fetch_kv_static serves
     // the latest single-layer KV fetch, for harvest_fetch_kv_again
     struct {
-        bool valid = false, lists = false;  // lists: the general path ran, so the compacted lists describe it
+        bool valid = false, lists = false;  // lists: the general path ran, so the lists describe it
         uint32_t layer = 0, n_seq = 0, max_blocks = 0, n_heads = 0, block_tokens = 0;
         const int32_t *table = nullptr, *n_blocks = nullptr;
         const uint64_t *seq_dst_block = nullptr;
@@ -1764,10 +1764,11 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     const bool recording = is_capturing(ss->s);
     if (recording) ss->recorded = true;
     const uint32_t tpc = tiles_per_chunk(c.cfg.chunk_bytes, TILE_4K);
-    // A small table: the whole fetch is one kernel (no compaction) - see fetch_kv_small.  Unless most of it is padding: the
+    // A small table: the whole fetch is one kernel (no lists) - see fetch_kv_small.  Unless most of it is padding: the
     // one kernel has a workgroup for every tile of every cell, and one whose cell asks for nothing still costs 0.2 to 0.5 ns
-    // (4 096 cells, 64 of them live: 27 us with one load a thread), where the general path spends about 5 us more on a small kernel and
-    // none on cells that are not there (2 048 cells, two loads a thread: 1 024 live 25.3 us against 27.6, 512 live 19.4 and 17.3).  How many are live is known when the latest report on this stream came from a table of these
+    // (4 096 cells, 64 of them live: 27 us with one load a thread), where the general path spends about 5 us more on a small
+    // kernel and none on cells that are not there (2 048 cells, two loads a thread: 1 024 live 25.3 us against 27.6, 512 live 19.4
+    // and 17.3).  How many are live is known when the latest report on this stream came from a table of these
     // rows and columns - a step's table keeps its shape from layer to layer and mostly from step to step; of any other table
     // (two that take turns, say) they are taken to be live, for a wrong guess costs those 5 us.  So they are for a
     // fetch that is being recorded: its replays may meet any number of live cells.

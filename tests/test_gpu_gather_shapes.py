@@ -863,3 +863,18 @@ def test_moves_of_fewer_and_of_more_tiles_than_workgroups(n, pcie_wgs):
             assert np.array_equal(h.dev_plane(B.KV, B.CACHE, p)[0].cpu().numpy(), want), (turn, p)
         h.revoke(B.KV, ids)
     h.close()
+
+
+@pytest.mark.parametrize("flags", [0, B.FLAG_GENERAL_FETCH])
+@pytest.mark.parametrize("e,n_ids", [(5, 255), (40, 256), (40, 257), (300, 511), (300, 2047), (33, 2048), (33, 2049), (2000, 4100), (64, 32768)])
+def test_routing_ids_around_what_a_workgroup_loads_at_once(e, n_ids, flags):
+    rig = ExpertRig(e, 64, on_host=range(0, e, 3), flags=flags)
+    ids = np.random.default_rng(e).integers(0, e, n_ids).astype(np.int32)
+    ids[[0, n_ids // 2, n_ids - 1]] = -5, e, 1 << 30
+    for _ in range(2):
+        got, ptrs, counts, miss = rig.fetch(ids, e)
+        routed = [i for i in sorted(set(ids.tolist())) if 0 <= i < e]
+        assert np.array_equal(got[:len(routed) * 64].reshape(-1, 64), rig.weights[routed]) and (got[len(routed) * 64:] == 0xEE).all()
+        assert np.array_equal(ptrs[routed], np.arange(len(routed)) * 64) and (np.delete(ptrs, routed) < 0).all()
+        assert counts["n_requests"] == len(routed) and counts["n_invalid"] == 3 and miss == [i for i in routed if i % 3 == 0]
+    rig.h.close()
