@@ -301,7 +301,7 @@ int harvest_fetch_kv_layers(harvest_ctx *ctx, uint32_t layer_first, uint32_t n_l
  * layers (Section 5.2: the table says where every block of the step is; it does not change from layer to layer).  The
  * caller vouches that the table arrays of that call have not changed and are still valid device memory.  When no directory
  * edit has happened since that call, its request lists are used again (an object occupies the same slot in every layer),
- * which saves resolving and compacting the table; otherwise, for the small tables that are fetched without lists, and on a
+ * which saves resolving the table; otherwise, for the small tables that are fetched without lists, and on a
  * stream on which a KV fetch has been recorded into a graph (a replay writes the stream's lists), the table is resolved
  * again - the result is the same either way.  Counters and miss list are those of a fetch of this
  * layer; the running totals count the requests again.  EINVAL: no such earlier fetch on this stream (a multi-layer call
@@ -324,7 +324,7 @@ int harvest_fetch_kv_head_major(harvest_ctx *ctx, uint32_t layer, const int32_t 
  * serving loops, harnesses that forbid hipMalloc.  Same requests, same bytes in d_dst_k / d_dst_v, but this call never
  * allocates (no hipMalloc / hipFree / hipHostMalloc, no event or stream creation, on any call including the first):
  * everything it needs beyond its arguments - the arrays of the resolve, the two request lists, the counters - lives in
- * a statically allocated device array of about 3.4 MiB, which every GPU the library has created a context on holds
+ * a statically allocated device array of about 2.5 MiB, which every GPU the library has created a context on holds
  * until the process ends.  The limit that follows: n_seq * max_blocks <= HARVEST_STATIC_MAX_CELLS table cells,
  * HARVEST_E2BIG (and a message on stderr, nothing enqueued) beyond.  The fetch may be recorded into a HIP graph without
  * any earlier call.
