@@ -388,12 +388,12 @@ def test_a_callers_numbers_of_workgroups_are_taken_as_they_are(fake, tuning, rea
     c.close()
 
 
-def expert_context(lib, n=60, n_local=0, local=(), flags=0):
+def expert_context(lib, n=60, n_local=0, local=(), flags=0, chunk=1 << 20):
     """n experts of 1 MiB, the last n_local of them registered as local; `local`: those without a host copy."""
     cfg = B.harvest_config()
     cfg.flags = flags
     ex = cfg.cls[B.EXPERT]
-    ex.n_layers, ex.n_planes, ex.chunk_bytes, ex.max_objects, ex.n_experts = 1, 1, 1 << 20, n, n
+    ex.n_layers, ex.n_planes, ex.chunk_bytes, ex.max_objects, ex.n_experts = 1, 1, chunk, n, n
     ex.n_host_slots, ex.n_cache_slots, ex.n_local_slots = n, n, 4
     ex.host_pool[0], ex.d_cache_pool[0], ex.d_local_pool[0] = POOL, POOL * 2, POOL * 3
     h, out = ctypes.c_void_p(), np.empty(n, dtype=np.uint32)
@@ -445,6 +445,11 @@ def test_a_few_routing_ids_are_fetched_by_one_kernel_when_ranks_and_edits_are_kn
     assert path(h, other) == "general"
     lib.fake_not_ready(False)
     assert path(h, other) == "one kernel"
+    assert lib.harvest_destroy(h) == B.OK
+    h, s = expert_context(lib, chunk=16 << 20), lib.fake_stream()
+    assert path(h, s) == "general"
+    report(11, 0)                                         # 176 MiB; 32 different ids would be 512 MiB, twice the limit
+    assert path(h, s, n_ids=32) == "one kernel" and path(h, s, n_ids=33) == "general" and path(h, s, n_ids=33, staging=32) == "one kernel"
     assert lib.harvest_destroy(h) == B.OK
     for kw, expected in (({}, "one kernel"), (dict(n_local=2), "general"), (dict(n_local=2, local="lossy"), "general"), (dict(n=129), "general"),
                          (dict(flags=B.FLAG_GENERAL_FETCH), "general"), (dict(flags=B.FLAG_PROFILE), "general")):
