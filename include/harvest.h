@@ -110,7 +110,8 @@ enum harvest_flags {
     HARVEST_FLAG_POISON = 2,     /* revoke overwrites the freed cache slot with 0xA5 after the drain */
     HARVEST_FLAG_PROFILE = 4,    /* bracket the gather kernels with events; read them with harvest_profile
                                     (launches recorded into a graph are not timed, nor are KV fetches in their one-kernel
-                                    form, whose tiers are not apart: HARVEST_FLAG_GENERAL_FETCH) */
+                                    form, whose tiers are not apart: HARVEST_FLAG_GENERAL_FETCH; expert fetches never take
+                                    theirs with this flag) */
     HARVEST_FLAG_GENERAL_FETCH = 8, /* fetches never take their one-kernel form - for small block tables (up to 4096
                                     cells), for a few routing ids -: every fetch runs resolve and gather - for
                                     measurements and tests of that path; results are the same either way */
@@ -147,7 +148,9 @@ typedef struct harvest_config {
     harvest_class_config cls[HARVEST_N_CLASSES];
     uint32_t gather_wg_per_cu;      /* tuning: cap the HBM-tier gather at this many workgroups per CU (they then loop
                                        over tiles, and take a request's planes one after the other); 0 = default, one workgroup
-                                       per tile of gather_threads * 16 bytes */
+                                       per tile of gather_threads * 16 bytes.  One-kernel fetches have no such gather: an expert
+                                       fetch never takes that form once this or gather_threads is set, a KV fetch by
+                                       small_fetch_cells */
     uint32_t host_wgs;              /* tuning: 8 KiB of host-tier (PCIe) reads in flight per unit; 0 = default (24; the
                                        one-kernel form of small KV fetches 32) */
     uint32_t shared_granule;        /* segment granule of the shared cache pool in bytes: a power of two >= 256;
@@ -157,7 +160,7 @@ typedef struct harvest_config {
                                        registered without a host copy: a revocation can then leave a fetch in flight nothing
                                        to copy from, and only the general path resolves a block in one place */
     uint32_t gather_threads;        /* tuning: threads per workgroup of the HBM-tier gather, 64, 128 or 256; 0 = default
-                                       (64: one wavefront per workgroup, 1 KiB tiles) */
+                                       (64: one wavefront per workgroup, 1 KiB tiles); see gather_wg_per_cu */
     uint32_t pcie_wgs;              /* tuning: persistent workgroups of the copies that cross PCIe outside a fetch (place,
                                        write-back), each with one 32 KiB tile in flight (16 KiB for
                                        write-backs of chunks below 32 KiB); 0 = default (12: enough to fill the link

@@ -1992,10 +1992,12 @@ int harvest_fetch_experts(harvest_ctx *ctx, uint32_t layer, const int32_t *d_top
     // known by number (not while another stream's placement is under way, and not in a recorded graph).  Up to ROUTED_BYTES - 242 MB 71.4 us
     // against 73.0, 520 MB 129.6 and 128.6 - by the latest report, and twice that if every id is another expert (a report of a smaller batch
     // must not send a large one this way), and where the report says that HBM is what the fetch waits for; timed by tier it is two launches.
+    // A caller's own gather (gather_threads, gather_wg_per_cu) is what every fetch of the context then runs.
     const volatile Report &latest = ss->h_feedback[HARVEST_EXPERT];
     const uint32_t n_max = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(n_ids, E), n_staging_slots);
     const uint64_t seen_hbm = latest.hbm, guess = std::min<uint64_t>(n_max, std::max<uint64_t>(1, seen_hbm - seen_hbm / 8));
     if (n_ids && n_max && n_ids <= ROUTED_IDS && E <= ROUTED_EXPERTS && !ctx->general_fetch && !ctx->profile && !recording && !c.n_lossy &&
+        !ctx->gather_grid && !ctx->cfg.gather_threads &&
         c.local_free.size() == c.cfg.n_local_slots && ss->seen_seq[HARVEST_EXPERT] == c.edit_seq && ss->feedback_valid[HARVEST_EXPERT] &&
         !is_link_bound(seen_hbm, latest.host) && seen_hbm * c.cfg.chunk_bytes <= ROUTED_BYTES && n_max * c.cfg.chunk_bytes <= 2 * ROUTED_BYTES) {
         const ClassDev cd = class_dev(c);

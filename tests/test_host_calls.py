@@ -388,10 +388,12 @@ def test_a_callers_numbers_of_workgroups_are_taken_as_they_are(fake, tuning, rea
     c.close()
 
 
-def expert_context(lib, n=60, n_local=0, local=(), flags=0, chunk=1 << 20):
+def expert_context(lib, n=60, n_local=0, local=(), flags=0, chunk=1 << 20, **tuning):
     """n experts of 1 MiB, the last n_local of them registered as local; `local`: those without a host copy."""
     cfg = B.harvest_config()
     cfg.flags = flags
+    for name, value in tuning.items():
+        setattr(cfg, name, value)
     ex = cfg.cls[B.EXPERT]
     ex.n_layers, ex.n_planes, ex.chunk_bytes, ex.max_objects, ex.n_experts = 1, 1, chunk, n, n
     ex.n_host_slots, ex.n_cache_slots, ex.n_local_slots = n, n, 4
@@ -458,3 +460,23 @@ def test_a_few_routing_ids_are_fetched_by_one_kernel_when_ranks_and_edits_are_kn
         report(11, 0)
         assert path(h, s) == expected, kw
         assert lib.harvest_destroy(h) == B.OK
+
+
+@pytest.mark.parametrize("tuning,threads,cap", [(dict(gather_wg_per_cu=2), 64, 2), (dict(gather_threads=64), 64, None), (dict(gather_threads=256), 256, None),
+                                                (dict(gather_wg_per_cu=1, gather_threads=128), 128, 1)])
+def test_a_callers_gather_serves_every_expert_fetch(fake, tuning, threads, cap):
+    """Workgroups per compute unit and threads of the HBM-tier gather hold for a few routing ids too, whatever is known from earlier fetches."""
+    h, s = expert_context(fake, **tuning), fake.fake_stream()
+    for turn in range(3):
+        fake.fake_log()
+        assert fake.harvest_fetch_experts(h, 0, POOL * 4, 16, 1, POOL * 5, 60, POOL * 6, s) == B.OK
+        log = fake.fake_log().decode().splitlines()
+        assert not launches(log, "fetch_experts_small"), log
+        (at,) = launches(log, "gather")
+        grid, block = (int(re.search(rf"{word} (\d+)", log[at]).group(1)) for word in ("grid", "block"))
+        assert block == threads, log
+        if cap:                                           # 256 compute units, and at most 192 KiB of reads of the host
+            assert grid <= cap * 256 + 24 * 256 // threads, log
+        words = (ctypes.c_uint32 * 16).from_address(fake.fake_pinned(64, fake.fake_pinned_count(64) - 1))
+        words[4:8] = [11, 0, 0, 0]
+    assert fake.harvest_destroy(h) == B.OK
