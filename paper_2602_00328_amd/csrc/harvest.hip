@@ -689,7 +689,7 @@ constexpr uint64_t UNROLLED_TILES = 65536;            // up to this many tiles o
 // Chunks from which both planes of a request are taken in one pass: what longer source runs gain at 32 KiB, destinations that take
 // turns lose at 16 KiB (4 096 blocks of 2 x 32 KiB 91.4 us plane after plane and 88.8 in one pass, 16 384 of 2 x 16 KiB 178.4 and 182.2).
 constexpr uint64_t FOLD_FROM = 32768;
-constexpr uint64_t ROUTED_BYTES = 256u << 20;         // experts up to this many bytes are fetched by one kernel
+constexpr uint64_t ROUTED_BYTES = 256u << 20;         // experts up to this many bytes, by the latest report, are fetched by one kernel
 constexpr uint32_t MARKED_BATCH_IDS = 32768;      // routing-id batches beyond this take the two-kernel resolve
 
 uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t)((chunk_bytes + tile - 1) / tile); }
@@ -1989,9 +1989,11 @@ int harvest_fetch_experts(harvest_ctx *ctx, uint32_t layer, const int32_t *d_top
     const bool recording = is_capturing(ss->s);
     // A few ids: the whole fetch is one kernel, see fetch_experts_small.  Its workgroups resolve for themselves, so the rank of an expert has to
     // follow from the ids alone (no expert that is local or may have lost its bytes), and every edit that the fetch comes after has to be
-    // known by number (not while another stream's placement is under way, and not in a recorded graph).  Up to ROUTED_BYTES - 242 MB 71.4 us
-    // against 73.0, 520 MB 129.6 and 128.6 - by the latest report, and twice that if every id is another expert (a report of a smaller batch
-    // must not send a large one this way), and where the report says that HBM is what the fetch waits for; timed by tier it is two launches.
+    // known by number (not while another stream's placement is under way, and not in a recorded graph), and the report has to say that HBM is
+    // what the fetch waits for; timed by tier it is two launches.  What it gains shrinks with the bytes: experts of 17.3 MB that no cache
+    // holds, one kernel and two launches, 190 MB 59.7 and 62.1 us, 242 MB 74.8 and 77.1, 381 MB 115.7 and 117.4, 519 MB 156.8 and 157.5,
+    // 692 MB 209.2 and 207.0.  So no fetch of more than 2 * ROUTED_BYTES, if every id is another expert, and none after a report of more
+    // than half of that.
     // A caller's own gather (gather_threads, gather_wg_per_cu) is what every fetch of the context then runs.
     const volatile Report &latest = ss->h_feedback[HARVEST_EXPERT];
     const uint32_t n_max = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(n_ids, E), n_staging_slots);

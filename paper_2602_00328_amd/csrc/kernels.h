@@ -1187,9 +1187,10 @@ __global__ __launch_bounds__(NTHR, 8) void fetch_kv_small(const int32_t *__restr
 // A whole expert fetch in one kernel, for a few routing ids: what resolve_experts and the gather do in two launches, the first of which
 // is a chain of latencies and a boundary between kernels.  Every workgroup forms the routed set for itself: a wavefront loads the ids at once and
 // ors their bits together (by LDS atomics instead, 240 ids of 16 experts took 57 us against 42; by scalar loads and instructions the scalar unit,
-// one for 32 wavefronts, becomes the bound).  11 experts of 17.3 MB take 60.5 us (62.7 in two launches), 4 of them 24.4 (27.4), 2 of
-// 4.3 MB 6.0 (11.7), 14 of 17.3 MB 71.4 (73.0).  Two loads a thread, in 256 threads: with one load the way to it takes too much of a
-// workgroup's life (65.5), four are more bytes in flight than the memory takes (63.2); 64 and 128 threads with two: 60.3, 60.5.  256 ids of 16
+// one for 32 wavefronts, becomes the bound).  Of experts that no cache holds, 4 of 17.3 MB take 25.4 us (27.6 in two launches), 11 59.7 (62.1), 14 74.8 (77.1), 8 of
+// 4.3 MB 15.3 (19.3), 64 87.8 (97.8).  Two loads a thread, in 256 threads: 11 experts fetched again and again 60.5, and with one load, when the
+// way to it takes too much of a workgroup's life, 65.5; four are more bytes in flight than the memory takes (63.2); 64 and 128 threads with
+// two: 60.3, 60.5.  256 ids of 16
 // experts of 4.3 MB 27.1 in two launches and 24.7; with room for 512 ids 24.9, and 512 of them 25.0, but 32 ids 45.3 instead of 45.1 and 11
 // experts 60.6 instead of 60.4.
 //
