@@ -148,7 +148,7 @@ struct GatherRest {
     uint32_t n_seq, max_blocks;          // for the report
     unsigned long long *lease;           // see link_announce
     Report *report;
-    // Books, by the first BOOK_WGS workgroups of the HBM tier once they have copied their tiles.  BOOKS_COUNTED: *cnt is there, report it.
+    // Books, by the first BOOK_WGS workgroups of the HBM tier (a segment's misses each) once they have copied their tiles.  BOOKS_COUNTED: *cnt is there, report it.
     // BOOKS_AGAIN: and add it to the running totals, for a fetch repeated from older lists.  BOOKS_RESOLVED: the segments' counts make
     // up *cnt, the running totals and the caller's copy (info, may be null), and their misses one list.
     uint32_t books, pad;
@@ -156,7 +156,7 @@ struct GatherRest {
     const uint32_t *seg_miss;
     unsigned long long *totals;
 };
-constexpr uint32_t BOOK_WGS = 16;
+constexpr uint32_t BOOK_WGS = SEGS;
 typedef const __attribute__((address_space(4))) GatherRest k_GatherRest;
 template <uint32_t AT> __device__ inline k_GatherRest &gather_rest()       // AT: where it is among the kernel's arguments
 {
@@ -720,7 +720,8 @@ __device__ inline void host_tier(const HostList &recs, const GatherArgs &a, uint
     }
 }
 
-// The books of a fetch, see GatherRest: by workgroup bx of the HBM tier's n_wgs in a plane.
+// The books of a fetch, see GatherRest: by workgroup bx of the HBM tier's n_wgs in a plane.  (Long lists of misses that no transfer hides
+// are a chain of latencies: 500 224 lost blocks 197.6 us with 16 workgroups and a load at a time, 88.5 this way.)
 template <int NTHR>
 __device__ inline void keep_books(k_GatherRest &r, uint32_t bx, uint32_t n_wgs)
 {
@@ -749,7 +750,15 @@ __device__ inline void keep_books(k_GatherRest &r, uint32_t bx, uint32_t n_wgs)
         const uint32_t lane_of = seg >> 2, i = seg & 3;
         const uint32_t before = lane_value(i == 0 ? missed.before : i == 1 ? missed.upto[0] : i == 2 ? missed.upto[1] : missed.upto[2], lane_of);
         const uint32_t n = lane_value(i == 0 ? missed.upto[0] : i == 1 ? missed.upto[1] : i == 2 ? missed.upto[2] : missed.upto[3], lane_of) - before;
-        for (uint32_t k = tid; k < n; k += NTHR) r.miss_idx[before + k] = r.seg_miss[(uint64_t)seg * r.seg_cells + k];
+        const uint32_t *from = r.seg_miss + (uint64_t)seg * r.seg_cells;
+        constexpr uint32_t AT_ONCE = 4;
+        for (uint32_t k0 = tid; k0 < n; k0 += NTHR * AT_ONCE) {
+            uint32_t cell[AT_ONCE];
+#pragma unroll
+            for (uint32_t k = 0; k < AT_ONCE; ++k) cell[k] = from[k0 + k * NTHR < n ? k0 + k * NTHR : k0];
+#pragma unroll
+            for (uint32_t k = 0; k < AT_ONCE; ++k) if (k0 + k * NTHR < n) r.miss_idx[before + k0 + k * NTHR] = cell[k];
+        }
     }
 }
 

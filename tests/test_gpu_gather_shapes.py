@@ -878,3 +878,54 @@ def test_routing_ids_around_what_a_workgroup_loads_at_once(e, n_ids, flags):
         assert np.array_equal(ptrs[routed], np.arange(len(routed)) * 64) and (np.delete(ptrs, routed) < 0).all()
         assert counts["n_requests"] == len(routed) and counts["n_invalid"] == 3 and miss == [i for i in routed if i % 3 == 0]
     rig.h.close()
+
+
+def with_a_lost_object(chunk, n, flags=B.FLAG_GENERAL_FETCH):
+    """n objects in the cache tier, number n lost; every object's bytes are its number modulo 251."""
+    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n + 1, n_host_slots=n, n_cache_slots=n + 1, n_local_slots=1), flags=flags)
+    for p in range(2):
+        h.host_plane(B.KV, p)[0] = (np.arange(n) % 251).astype(np.uint8)[:, None]
+    h.register(B.KV, n, np.arange(n))
+    h.place(B.KV, np.arange(n))
+    h.register(B.KV, 1, None, tier=B.LOCAL)
+    h.evict(B.KV, -1, [n], h.dev_plane(B.KV, B.LOCAL, 0), h.dev_plane(B.KV, B.LOCAL, 1), np.zeros(1, dtype=np.uint64), 1, B.EVICT_DEMOTE)
+    torch.cuda.synchronize()
+    h.revoke(B.KV, [n])
+    return h
+
+
+@pytest.mark.parametrize("n_seq,width,live,chunk,most", [(256, 2048, 500224, 512, 0.55)])
+def test_a_fetch_of_lost_blocks_takes_a_fraction_of_the_fetch_that_finds_them(n_seq, width, live, chunk, most):
+    """It moves no payload; the misses are long lists that no transfer hides (500 224 blocks: 245 us found, 17 lost; 198 with the misses put
+    together by 16 wavefronts, a load at a time)."""
+    n = 4096
+    h = with_a_lost_object(chunk, n)
+    lens = np.full(n_seq, live // n_seq, dtype=np.int32)
+    found = np.random.default_rng(0).integers(0, n, (n_seq, width), dtype=np.int32)
+    dn, df = torch.from_numpy(lens).cuda(), torch.from_numpy((np.cumsum(lens) - lens).astype(np.int64)).cuda()
+    k, v = (torch.zeros(live * chunk, dtype=torch.uint8, device="cuda") for _ in range(2))
+    us = {}
+    for what, table in (("found", found), ("lost", np.full_like(found, n))):
+        dt = torch.from_numpy(table).cuda()
+        fetch = lambda: h.fetch_kv(0, dt, dn, k, v, df, live)
+        for _ in range(3):
+            fetch()
+        times = []
+        for _ in range(7):
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            for _ in range(10):
+                fetch()
+            end.record()
+            end.synchronize()
+            times.append(begin.elapsed_time(end) * 100)
+        us[what] = np.median(times)
+        counts, miss, n_miss = h.fetch_info(miss_cap=found.size)
+        if what == "lost":
+            cells = np.flatnonzero((np.arange(width)[None] < lens[:, None]).reshape(-1))
+            assert counts["n_lost"] == n_miss == live and np.array_equal(miss, cells)
+        else:
+            assert counts["n_cache"] == live and n_miss == 0
+    print({x: round(float(y), 1) for x, y in us.items()}, flush=True)
+    assert us["lost"] < most * us["found"], us
+    h.close()
