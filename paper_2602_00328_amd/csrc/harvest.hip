@@ -690,6 +690,7 @@ constexpr uint64_t UNROLLED_TILES = 65536;            // up to this many tiles o
 // turns lose at 16 KiB (4 096 blocks of 2 x 32 KiB 91.4 us plane after plane and 88.8 in one pass, 16 384 of 2 x 16 KiB 178.4 and 182.2).
 constexpr uint64_t FOLD_FROM = 32768;
 constexpr uint64_t ROUTED_BYTES = 256u << 20;         // experts up to this many bytes, by the latest report, are fetched by one kernel
+constexpr uint64_t SHORT_GRID = 4;                    // a grid that has to go round more often than this looks ahead in its list, see gather_hm
 constexpr uint32_t MARKED_BATCH_IDS = 32768;      // routing-id batches beyond this take the two-kernel resolve
 
 uint32_t tiles_per_chunk(uint64_t chunk_bytes, uint32_t tile) { return (uint32_t)((chunk_bytes + tile - 1) / tile); }
@@ -906,8 +907,10 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
     uint64_t max_tiles = max_req * tpc;
     uint64_t want = max_tiles;
     bool link_bound = host_tier, serial = !host_tier;
+    uint64_t listed = 0;                           // entries of the list that the report is about (KV)
     if (ss->feedback_valid[cls]) {
         const volatile Report &r = ss->h_feedback[cls];
+        listed = *(const volatile uint32_t *)(ss->h_feedback + HARVEST_N_CLASSES);
         const uint64_t seen = r.hbm, seen_host = r.host;
         uint64_t guess = std::max<uint64_t>(1, cls == HARVEST_KV ? seen : seen - seen / 8) * tpc;
         want = std::min(max_tiles, std::max<uint64_t>(guess, 16ull * ctx->n_cu));
@@ -928,6 +931,7 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
     rest.n_seq = n_seq; rest.max_blocks = max_blocks;
     rest.lease = ctx->d_lease;
     rest.report = ss->d_feedback + cls;
+    rest.listed = kv ? (uint32_t *)(ss->d_feedback + HARVEST_N_CLASSES) : nullptr;
     rest.books = books;
     rest.cnt = lists.cnt; rest.info = info; rest.miss_idx = lists.miss; rest.seg_miss = ss->work.seg_miss;
     rest.totals = ctx->d_totals + cls * C_N;
@@ -938,7 +942,8 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
         const Rec *l_hbm = lists.hbm;
         const uint32_t *cnt = lists.cnt;
         if (hm) {
-            auto kernel = planes == 2 ? gather_hm<2> : gather_hm<1>;
+            const bool skip = n_hbm && std::min(listed, max_req) * tpc > SHORT_GRID * (uint64_t)n_hbm;
+            auto kernel = planes == 2 ? (skip ? gather_hm<2, true> : gather_hm<2, false>) : (skip ? gather_hm<1, true> : gather_hm<1, false>);
             if (!begin) return launch_last(ctx, ss, recording, kernel, g, dim3(nthr), l_hbm, cnt, ga, *hm, rest);
             hipExtLaunchKernelGGL(kernel, g, dim3(nthr), 0, s, begin, end, 0, l_hbm, cnt, ga, *hm, rest);
         } else {

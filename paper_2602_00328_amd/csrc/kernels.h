@@ -148,6 +148,7 @@ struct GatherRest {
     uint32_t n_seq, max_blocks;          // for the report
     unsigned long long *lease;           // see link_announce
     Report *report;
+    uint32_t *listed;                    // KV, beside the report: how many entries the HBM list had
     // Books, by the first BOOK_WGS workgroups of the HBM tier (a segment's misses each) once they have copied their tiles.  BOOKS_COUNTED: *cnt is there, report it.
     // BOOKS_AGAIN: and add it to the running totals, for a fetch repeated from older lists.  BOOKS_RESOLVED: the segments' counts make
     // up *cnt, the running totals and the caller's copy (info, may be null), and their misses one list.
@@ -740,7 +741,9 @@ __device__ inline void keep_books(k_GatherRest &r, uint32_t bx, uint32_t n_wgs)
         } else if (lane <= C_MISS) v = r.cnt[lane];
         if (r.books != BOOKS_COUNTED && lane <= C_INVALID && v) atomicAdd(&r.totals[lane], (unsigned long long)v);
         const u32x4 report = { lane_value(v, C_HBM_REQ), lane_value(v, C_HOST_REQ), r.n_seq, r.max_blocks };
+        const uint32_t listed = lane_value(v, C_REQ);
         if (lane == 0) *reinterpret_cast<u32x4 *>(r.report) = report;
+        if (lane == 0 && r.listed) *r.listed = listed;
     }
     if (r.books != BOOKS_RESOLVED) return;
     const uint32_t n_books = n_wgs < BOOK_WGS ? n_wgs : BOOK_WGS;
@@ -760,6 +763,19 @@ __device__ inline void keep_books(k_GatherRest &r, uint32_t bx, uint32_t n_wgs)
             for (uint32_t k = 0; k < AT_ONCE; ++k) if (k0 + k * NTHR < n) r.miss_idx[before + k0 + k * NTHR] = cell[k];
         }
     }
+}
+
+// The next of the tiles t, t + gx, t + 2 gx, ... whose request HBM serves, or one beyond the last tile.  Where a grid is short most of the list
+// may be of other tiers, lost or invalid, and to look at them one by one is a memory latency each: after two in a row 64 are looked at
+// together (12 000 lost blocks of 2 x 32 KiB 53.2 us one by one, 12.5 this way).
+__device__ inline uint64_t next_in_hbm(const Rec *__restrict__ recs, uint64_t t, uint32_t gx, uint64_t n_tiles, uint32_t tpr)
+{
+    for (; t < n_tiles; t += 64 * (uint64_t)gx) {
+        const uint64_t mine = t + lane_id() * (uint64_t)gx;
+        const uint64_t there = __ballot(mine < n_tiles && in_hbm((uint32_t)recs[mine < n_tiles ? (uint32_t)mine / tpr : 0].src & 3));
+        if (there) return t + (uint32_t)__builtin_ctzll(there) * (uint64_t)gx;
+    }
+    return t;
 }
 
 // HBM tier.  NTHR threads per workgroup, one 16-byte load and store each: a tile is NTHR * 16 bytes, and the launch has about
@@ -824,6 +840,12 @@ __global__ __launch_bounds__(NTHR) void gather(const Rec *__restrict__ hbm_recs,
         if (t >= n_tiles) break;
         idx = (uint32_t)t / tpr;
         x = hbm_recs[idx];
+        if (!in_hbm(tier) && !in_hbm((uint32_t)x.src & 3)) {
+            t = next_in_hbm(hbm_recs, t + gx, gx, n_tiles, tpr);
+            if (t >= n_tiles) break;
+            idx = (uint32_t)t / tpr;
+            x = hbm_recs[idx];
+        }
     }
     if (bx < BOOK_WGS && plane_y == 0 && rep == 0) keep_books<NTHR>(gather_rest<REST>(), bx, gx);
 }
@@ -1338,7 +1360,7 @@ __device__ inline void host_tier_hm(const HostList &recs, const GatherArgs &a, c
 // instruction a contiguous kilobyte on both sides) 5.91 in isolation but 5.85 against 5.94 once inside the library's
 // looping, feedback-sized launch.  One-wavefront workgroups (1 KiB tiles), the token-major gather's shape, are a
 // wash here: 5.95 against 5.90 TB/s alone, 5.32 against 5.35 inside the step.
-template <int PLANES>
+template <int PLANES, bool SKIP>
 __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs, const uint32_t *__restrict__ cnt, GatherArgs a, HmArgs h,
                                                 GatherRest)
 {
@@ -1351,6 +1373,8 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
         host_tier_hm<PLANES>(recs, a, h, blockIdx.x);
         return;
     }
+    // SKIP: next_in_hbm, for grids that are known to be far too short.  With that code in its loop, though it does not run, the usual fetch
+    // takes longer (12 000 blocks 271.7 and 274.0 us).
     // plane after plane: taking both planes of a request in one pass, as gather does for a cache tier that keeps
     // them side by side, was measured to lose here (5.60 against 5.98 TB/s alone): the stores are 4 KiB strips, and with
     // two planes' strips interleaved they no longer follow each other
@@ -1368,9 +1392,10 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
         uint64_t dst_plane = plane ? a.dst_base[1] : a.dst_base[0];
         uint32_t u = k * WG + threadIdx.x;
         uint64_t cap = x.src >> 48;
-        uint64_t src = src_base_of(a, (uint32_t)(x.src & 3), plane) + (x.src & 0x0000FFFFFFFFFFFCull);
+        uint32_t tier = (uint32_t)(x.src & 3);
+        uint64_t src = src_base_of(a, tier, plane) + (x.src & 0x0000FFFFFFFFFFFCull);
         uint64_t dst = dst_plane + x.dst;
-        if (in_hbm((uint32_t)(x.src & 3)) && u < chunk_units) {
+        if (in_hbm(tier) && u < chunk_units) {
             uint32_t s_unit;
             uint64_t d_off;
             h.by_destination(u, cap, s_unit, d_off);
@@ -1380,6 +1405,12 @@ __global__ __launch_bounds__(WG) void gather_hm(const Rec *__restrict__ hbm_recs
         if (t >= n_tiles) break;
         idx = (uint32_t)t / tpr;
         x = hbm_recs[idx];
+        if (SKIP && !in_hbm(tier) && !in_hbm((uint32_t)x.src & 3)) {
+            t = next_in_hbm(hbm_recs, t + gx, gx, n_tiles, tpr);
+            if (t >= n_tiles) break;
+            idx = (uint32_t)t / tpr;
+            x = hbm_recs[idx];
+        }
     }
     if (bx < BOOK_WGS && plane == 0) keep_books<WG>(gather_rest<REST>(), bx, gx);
 }

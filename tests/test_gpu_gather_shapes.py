@@ -880,9 +880,10 @@ def test_routing_ids_around_what_a_workgroup_loads_at_once(e, n_ids, flags):
     rig.h.close()
 
 
-def with_a_lost_object(chunk, n, flags=B.FLAG_GENERAL_FETCH):
+def with_a_lost_object(chunk, n, layout=0, **kw):
     """n objects in the cache tier, number n lost; every object's bytes are its number modulo 251."""
-    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n + 1, n_host_slots=n, n_cache_slots=n + 1, n_local_slots=1), flags=flags)
+    h = B.Harvest(kv=B.ClassSpec(n_layers=1, n_planes=2, chunk_bytes=chunk, max_objects=n + 1, n_host_slots=n, n_cache_slots=n + 1, n_local_slots=1),
+                  flags=B.FLAG_GENERAL_FETCH | layout, **kw)
     for p in range(2):
         h.host_plane(B.KV, p)[0] = (np.arange(n) % 251).astype(np.uint8)[:, None]
     h.register(B.KV, n, np.arange(n))
@@ -894,10 +895,11 @@ def with_a_lost_object(chunk, n, flags=B.FLAG_GENERAL_FETCH):
     return h
 
 
-@pytest.mark.parametrize("n_seq,width,live,chunk,most", [(256, 2048, 500224, 512, 0.55)])
-def test_a_fetch_of_lost_blocks_takes_a_fraction_of_the_fetch_that_finds_them(n_seq, width, live, chunk, most):
+@pytest.mark.parametrize("n_seq,width,live,chunk,heads,most", [(256, 2048, 500224, 512, None, 0.55), (4, 4096, 12000, 32768, None, 0.12), (4, 4096, 12000, 32768, (8, 16), 0.12)])
+def test_a_fetch_of_lost_blocks_takes_a_fraction_of_the_fetch_that_finds_them(n_seq, width, live, chunk, heads, most):
     """It moves no payload; the misses are long lists that no transfer hides (500 224 blocks: 245 us found, 17 lost; 198 with the misses put
-    together by 16 wavefronts, a load at a time)."""
+    together by 16 wavefronts, a load at a time), and so is the list of what HBM might serve (12 000 blocks: 250 us found, 12.5 lost; 53 with
+    a tile of it looked at at a time)."""
     n = 4096
     h = with_a_lost_object(chunk, n)
     lens = np.full(n_seq, live // n_seq, dtype=np.int32)
@@ -907,7 +909,10 @@ def test_a_fetch_of_lost_blocks_takes_a_fraction_of_the_fetch_that_finds_them(n_
     us = {}
     for what, table in (("found", found), ("lost", np.full_like(found, n))):
         dt = torch.from_numpy(table).cuda()
-        fetch = lambda: h.fetch_kv(0, dt, dn, k, v, df, live)
+        if heads:
+            fetch = lambda: h.fetch_kv_head_major(0, dt, dn, k, v, df, dn, live, *heads)
+        else:
+            fetch = lambda: h.fetch_kv(0, dt, dn, k, v, df, live)
         for _ in range(3):
             fetch()
         times = []
@@ -928,4 +933,44 @@ def test_a_fetch_of_lost_blocks_takes_a_fraction_of_the_fetch_that_finds_them(n_
             assert counts["n_cache"] == live and n_miss == 0
     print({x: round(float(y), 1) for x, y in us.items()}, flush=True)
     assert us["lost"] < most * us["found"], us
+    h.close()
+
+
+@pytest.mark.parametrize("chunk,heads,threads,layout", [(1024, None, 0, 0), (2064, None, 128, 0), (32768, None, 0, B.FLAG_CACHE_PLANES_ADJACENT), (4096, (8, 16), 0, 0),
+                                                        (8256, (3, 4), 0, 0)])
+@pytest.mark.parametrize("where", [0.0, 0.001, 0.02, 0.3, 0.7, "runs", "first and last"])
+def test_a_few_live_blocks_among_lost_ones(where, chunk, heads, threads, layout):
+    """From the second call on the grid is sized by the live ones, far shorter than the list, and passes over the others."""
+    n, n_seq = 1000, 3
+    h = with_a_lost_object(chunk, n, layout, gather_threads=threads)
+    live = 90000 if chunk < 2000 else 12000
+    lens = np.array([live // 2, live // 3, live // 6], dtype=np.int32)
+    cap, width = int(lens.sum()), int(lens.max())
+    rng = np.random.default_rng(chunk)
+    at = np.arange(cap)
+    there = at // 1700 % 3 == 1 if where == "runs" else (at == 0) | (at == cap - 1) if where == "first and last" else rng.random(cap) < where
+    asked = np.where(there, rng.integers(0, n, cap), n).astype(np.int32)
+    first = np.cumsum(lens) - lens
+    table = np.full((n_seq, width), -1, dtype=np.int32)
+    for s in range(n_seq):
+        table[s, :lens[s]] = asked[first[s]:first[s] + lens[s]]
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    dt, dn, df = dev(table), dev(lens), dev(first.astype(np.int64))
+    want = dev(np.where(there, asked % 251, 0xEE).astype(np.uint8))
+    k, v = (torch.empty(cap * chunk, dtype=torch.uint8, device="cuda") for _ in range(2))
+    for turn in range(3):
+        k.fill_(0xEE), v.fill_(0xEE)
+        if heads:
+            h.fetch_kv_head_major(0, dt, dn, k, v, df, dn, cap, *heads)
+        else:
+            h.fetch_kv(0, dt, dn, k, v, df, cap)
+        counts, miss, n_miss = h.fetch_info(miss_cap=table.size)
+        cells = np.flatnonzero((np.arange(width)[None] < lens[:, None]).reshape(-1))
+        assert counts["n_cache"] == there.sum() and counts["n_lost"] == n_miss == cap - there.sum() and np.array_equal(miss, cells[~there])
+        for buf in (k, v):
+            for s in range(n_seq):
+                a, b = int(first[s]), int(first[s] + lens[s])
+                got = buf[a * chunk:b * chunk]
+                got = got.view(heads[0], b - a, -1) if heads else got.view(1, b - a, chunk)
+                assert torch.equal(got, want[a:b][None, :, None].expand_as(got)), (turn, s)
     h.close()
