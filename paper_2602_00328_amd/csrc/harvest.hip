@@ -903,7 +903,11 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
     // number changes from layer to layer, the guess is biased low on purpose: surplus workgroups at the end of the grid cost
     // time (6 % of them 1 %, 23 % of them 3.5 %), a grid 10 to 25 % short costs less (the first workgroups take a
     // second tile while the rest still run).  A KV table grows by a block now and then: its last count is the best guess
-    // (15 000 blocks with the planes side by side: 302.8 us on an exact grid, 307.2 us on one 1/8 short).
+    // (15 000 blocks with the planes side by side: 302.8 us on an exact grid, 307.2 us on one 1/8 short).  Its list has an entry for every
+    // request, so the count is that of the list: a workgroup whose entry HBM does not serve takes 0.22 ns to start, 2 KiB of
+    // payload 0.33, so up to half as many of them again are hidden (of 12 000 blocks 20 / 30 % invalid: 209.0 / 184.9 us, 211.0 / 188.3 on
+    // a grid for the others alone, head-major 30 % 198.0 and 203.0).  With more of them they are what the launch waits for (50 % lost: 170 us,
+    // 138 on the short grid), and where the link is, the grid is left short.
     uint64_t max_tiles = max_req * tpc;
     uint64_t want = max_tiles;
     bool link_bound = host_tier, serial = !host_tier;
@@ -912,9 +916,10 @@ int launch_gathers(harvest_ctx *ctx, StreamState *ss, bool recording, ClassState
         const volatile Report &r = ss->h_feedback[cls];
         listed = *(const volatile uint32_t *)(ss->h_feedback + HARVEST_N_CLASSES);
         const uint64_t seen = r.hbm, seen_host = r.host;
-        uint64_t guess = std::max<uint64_t>(1, cls == HARVEST_KV ? seen : seen - seen / 8) * tpc;
-        want = std::min(max_tiles, std::max<uint64_t>(guess, 16ull * ctx->n_cu));
         link_bound = host_tier && is_link_bound(seen, seen_host);
+        const uint64_t entries = !link_bound && listed > seen && 2 * listed <= 3 * seen ? listed : seen;
+        uint64_t guess = std::max<uint64_t>(1, cls == HARVEST_KV ? entries : seen - seen / 8) * tpc;
+        want = std::min(max_tiles, std::max<uint64_t>(guess, 16ull * ctx->n_cu));
         double bytes = (double)planes * c.cfg.chunk_bytes * n_rep;
         double us_hbm = 2.0 * seen * bytes / 6.0e6, us_host = seen_host * bytes / 57.0e3;     // at 6 TB/s and 57 GB/s
         serial = serial || std::max(us_hbm, us_host) < 35.0 || std::min(us_hbm, us_host) < 8.0;

@@ -325,6 +325,48 @@ def test_the_host_tier_is_spread_wider_when_the_link_is_what_a_fetch_waits_for(f
     c.close()
 
 
+@pytest.mark.parametrize("head_major", [False, True])
+def test_the_gathers_grid_covers_the_list_where_that_is_not_much_longer_than_what_hbm_serves(fake, head_major):
+    """Word 8 of the report: entries of the list, those of lost and invalid requests and of the host's among them.  Not beyond half as
+    many again, and not where the link is what the fetch waits for."""
+    c = Ctx(fake, flags=B.FLAG_GENERAL_FETCH)
+
+    def hbm_tiles(at_host):
+        c.log()
+        if head_major:
+            assert fake.harvest_fetch_kv_head_major(c.h, 0, POOL, POOL, 1, 10000, POOL, POOL, POOL, POOL, 8, 8, 16, c.stream) == B.OK
+        else:
+            assert fake.harvest_fetch_kv(c.h, 0, POOL, POOL, 1, 10000, POOL, POOL, POOL, 8, c.stream) == B.OK
+        log = c.log()
+        return int(re.search(r"grid (\d+),", log[launches(log, "gather")[0]]).group(1)) - (24 if head_major else at_host)
+
+    tiles = 8 if head_major else 32
+    assert hbm_tiles(96) == 10000 * tiles
+    words = (ctypes.c_uint32 * 16).from_address(fake.fake_pinned(64, fake.fake_pinned_count(64) - 1))
+    for hbm, host, listed, entries, at_host in ((7000, 0, 8000, 8000, 48), (7000, 100, 9000, 9000, 48), (6000, 0, 9000, 9000, 48), (6000, 0, 9001, 6000, 48), (6000, 3000, 9000, 6000, 96),
+                                                (7000, 0, 0, 7000, 48), (9000, 0, 12000, 10000, 48)):
+        words[:4], words[8] = [hbm, host, 1, 10000], listed
+        assert hbm_tiles(at_host) == entries * tiles, (hbm, host, listed)
+    c.close()
+
+
+def test_a_head_major_gather_looks_ahead_in_its_list_where_its_grid_is_far_too_short(fake):
+    c = Ctx(fake, flags=B.FLAG_GENERAL_FETCH)
+
+    def looks_ahead():
+        c.log()
+        assert fake.harvest_fetch_kv_head_major(c.h, 0, POOL, POOL, 1, 10000, POOL, POOL, POOL, POOL, 8, 8, 16, c.stream) == B.OK
+        log = c.log()
+        return "gather_hmILi2ELb1E" in log[launches(log, "gather")[0]]
+
+    assert not looks_ahead()
+    words = (ctypes.c_uint32 * 16).from_address(fake.fake_pinned(64, fake.fake_pinned_count(64) - 1))
+    for hbm, listed, expected in ((0, 2048, False), (0, 2049, True), (600, 2400, False), (600, 2401, True), (9000, 10000, False), (3000, 1 << 30, False)):
+        words[:4], words[8] = [hbm, 0, 1, 10000], listed                # (never fewer than 16 workgroups of a tile on each of 256 compute units)
+        assert looks_ahead() == expected, (hbm, listed)
+    c.close()
+
+
 def test_the_one_kernel_fetch_knows_the_edits_it_comes_after(fake):
     """One that is being recorded learns them from a kernel in front of it.  With an object around that a revocation can leave
     nothing to copy from, every fetch resolves in one place."""
