@@ -15,7 +15,6 @@
 dim3 threadIdx, blockIdx, gridDim;
 const char *kernel_arguments;
 uint32_t __shfl_xor(uint32_t, int) { abort(); }
-uint32_t __shfl_up(uint32_t, int) { abort(); }
 void __threadfence_system() {}
 
 namespace {
@@ -108,7 +107,35 @@ uint32_t read_lane(uint32_t x, uint32_t k)
     return got;
 }
 
+uint32_t __shfl_up(uint32_t x, int o)
+{
+    g_lanes[g_current].value = x;
+    wait(AT_BALLOT);
+    const uint32_t got = (g_current & 63u) >= (uint32_t)o ? g_lanes[g_current - o].value : x;
+    wait(AT_BALLOT);
+    return got;
+}
+
 extern "C" {
+// The entries idx[0 .. n) of the host's list, one after the other, by one wavefront: counts[n_seg] of its segments, recs[n_seg][seg_cells].
+int host_list(const uint32_t *counts, uint32_t n_seg, uint32_t seg_cells, const hv::Rec *recs, const uint32_t *idx, uint32_t n, hv::Rec *out)
+{
+    using namespace hv;
+    GatherRest rest{};
+    rest.host_recs = recs; rest.counts = counts; rest.n_seg = n_seg; rest.seg_cells = seg_cells;
+    uint32_t total = 0;
+    g_kernel = [&] {
+        HostList list(*(k_GatherRest *)(const __attribute__((address_space(4))) char *)(const char *)&rest);
+        if (threadIdx.x == 0) total = list.sums.total;
+        for (uint32_t i = 0; i < n; ++i) {
+            const Rec x = list[idx[i]];
+            if (threadIdx.x == 0 || (x.src != out[i].src || x.dst != out[i].dst)) out[i] = x;      // (lane 0 runs first: another's answer would show)
+        }
+    };
+    run_workgroup(64, [](uint32_t) {});
+    return (int)total;
+}
+
 struct Fetch {
     uint32_t n_planes, nthr, head_major, n_layers, n_objects, n_seq, max_blocks, n_host, lg_groups, seen, n_versions, n_heads, block_tokens, n_slots;
     uint32_t unrolled, pad;                      // two loads a thread in the tiles' workgroups

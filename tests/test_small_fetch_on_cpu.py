@@ -242,3 +242,27 @@ def test_routed_experts_are_whole_when_entries_change_under_the_fetch(emulated, 
     assert cnt[5] == len(inside) - len(staged) + (2 if n_ids > 4 else 0)
     if len(tiers) == 1:
         assert cnt[3] == sum(tier[i] == HOST for i in staged) and sorted(miss[:cnt[3]]) == [i for i in staged if tier[i] == HOST]
+
+
+@pytest.mark.parametrize("n_seg,seg_cells,fill", [(1, 0, 7), (1, 256, 256), (2, 256, 3), (5, 256, 0.3), (64, 256, 0.02), (255, 1024, 0.01), (256, 1024, 0.1), (256, 256, "last")])
+@pytest.mark.parametrize("step", [1, 3, 24, 96, 300, "back", "any"])
+def test_the_hosts_list_over_its_segments(emulated, n_seg, seg_cells, fill, step):
+    """Entries in the order in which a workgroup asks for them, and in others: segments of none, of one, of all their cells."""
+    rng = np.random.default_rng(n_seg)
+    if isinstance(fill, int):
+        counts = np.full(n_seg, fill)
+    elif fill == "last":
+        counts = np.where(np.arange(n_seg) == n_seg - 1, 200, 0)
+    else:
+        counts = rng.binomial(seg_cells, fill, n_seg) * (rng.random(n_seg) < 0.8)
+        counts[rng.integers(n_seg)] = seg_cells
+    recs = rng.integers(0, 1 << 60, (n_seg, max(seg_cells, 7), 2), dtype=np.uint64)
+    want = np.concatenate([recs[s, :k] for s, k in enumerate(counts)])
+    total = len(want)
+    order = np.arange(total)[::-1] if step == "back" else rng.integers(0, total, 100) if step == "any" else np.arange(step % 7, total, step)
+    order = order[:300] if step != 1 else order[-300:]
+    padded = np.zeros(256, dtype=np.uint32)
+    padded[:n_seg] = counts
+    idx, out = np.ascontiguousarray(order, dtype=np.uint32), np.zeros((len(order), 2), dtype=np.uint64)
+    got = emulated.host_list(padded.ctypes.data_as(vp), u32(n_seg), u32(seg_cells), recs.ctypes.data_as(vp), idx.ctypes.data_as(vp), u32(len(idx)), out.ctypes.data_as(vp))
+    assert got == total and np.array_equal(out, want[order])
