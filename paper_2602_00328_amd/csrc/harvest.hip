@@ -683,8 +683,8 @@ int release_after(harvest_ctx *ctx, Staging *st, hipStream_t s)
 constexpr uint64_t SMALL_FETCH_CELLS = 4096;      // block tables up to this many cells are fetched by one kernel (measured:
                                                   // it wins up to 4 096 cells and loses from 8 192 on)
 constexpr uint64_t SMALL_FETCH_TILES = 1u << 22;      // and never more workgroups than this in x
-constexpr uint64_t DEAD_TILES = 20000;                // nor with more workgroups than this (8 us) for cells that ask for nothing ...
-constexpr uint64_t DEAD_TILES_2 = 10000;              // ... where they make two loads a thread and no read of the host hides them (4 us)
+constexpr uint64_t DEAD_TILES = 20000;                // nor with more workgroups than this (4 to 8 us) for cells that ask for nothing, or half as many
+                                                      // where they make two loads a thread: for chunks of whole 8 KiB the same cells
 constexpr uint64_t UNROLLED_TILES = 65536;            // up to this many tiles of 4 KiB a one-kernel fetch may make two loads a thread
 // Chunks from which both planes of a request are taken in one pass: what longer source runs gain at 32 KiB, destinations that take
 // turns lose at 16 KiB (4 096 blocks of 2 x 32 KiB 91.4 us plane after plane and 88.8 in one pass, 16 384 of 2 x 16 KiB 178.4 and 182.2).
@@ -1801,7 +1801,7 @@ static int fetch_kv_locked(harvest_ctx *ctx, uint32_t layer, const int32_t *d_bl
     const uint32_t unroll = unrolled ? 2 : 1;
     const uint64_t dead_tiles = dead_cells * tiles_per_chunk(c.cfg.chunk_bytes, TILE_4K * unroll) * c.cfg.n_planes * n_layers;
     if (!ctx->general_fetch && !c.n_lossy && n_layers < MAX_GRID_Z && total <= ctx->small_cells && total * tpc <= SMALL_FETCH_TILES &&
-        total * tpc * n_layers <= (1ull << 31) && dead_tiles <= (unrolled ? DEAD_TILES_2 : DEAD_TILES)) {
+        total * tpc * n_layers <= (1ull << 31) && dead_tiles <= DEAD_TILES / unroll) {
         SmallArgs ga{};
         SmallWalk gw{};
         const ClassDev cd = class_dev(c);

@@ -367,6 +367,48 @@ def test_a_head_major_gather_looks_ahead_in_its_list_where_its_grid_is_far_too_s
     c.close()
 
 
+def test_which_one_kernel_fetches_make_two_loads_a_thread(fake):
+    """Their tiles are 8 KiB, not 4: more than 128 cells, up to 256 MiB (128 of several layers), once a report says that the link is not
+    what the fetch waits for.  Both sides of each line, of that for tables that are mostly padding too."""
+    c = Ctx(fake, n=16, n_layers=4, chunk=65536)
+
+    def tiles(width, layers=1):
+        """Of 64 KiB, by the grid: 16, or 8 with two loads a thread; 0: the general path."""
+        c.log()
+        assert fake.harvest_fetch_kv_layers(c.h, 0, layers, POOL, POOL, 1, width, POOL, POOL, 16 * 65536, POOL, 16, c.stream) == B.OK
+        log = c.log()
+        small = launches(log, "fetch_kv_small")
+        if not small:
+            return 0
+        grid, block = (int(re.search(rf"{word} (\d+)", log[small[0]]).group(1)) for word in ("grid", "block"))
+        hbm = grid if layers > 1 else grid - 1 - (32 if block == 256 else 64)
+        assert hbm % width == 0, log
+        return hbm // width * block // 256
+
+    def report(hbm, host, width):
+        words[:4] = [hbm, host, 1, width]
+
+    assert tiles(600) == 16                               # nothing is known yet
+    words = (ctypes.c_uint32 * 16).from_address(fake.fake_pinned(64, fake.fake_pinned_count(64) - 1))
+    report(500, 0, 1)
+    assert tiles(128) == 16 and tiles(129) == 8 and tiles(2048) == 8 and tiles(2049) == 16
+    assert tiles(512, 2) == 8 and tiles(513, 2) == 16 and tiles(256, 4) == 8 and tiles(257, 4) == 16
+    report(550, 10, 1)
+    assert tiles(600) == 8
+    report(549, 10, 1)                                    # the link
+    assert tiles(600) == 16
+    fake.fake_capture(c.stream)
+    report(500, 0, 1)
+    assert tiles(600) == 16
+    fake.fake_capture(None)
+    for loads, width, host in ((8, 2000, 0), (16, 2100, 0), (16, 2000, 50)):
+        report(width - 625 - host, host, width)           # 625 cells that ask for nothing: 20 000 tiles of 4 KiB, 10 000 of 8
+        assert tiles(width) == loads
+        report(width - 626 - host, host, width)
+        assert tiles(width) == 0
+    c.close()
+
+
 def test_the_one_kernel_fetch_knows_the_edits_it_comes_after(fake):
     """One that is being recorded learns them from a kernel in front of it.  With an object around that a revocation can leave
     nothing to copy from, every fetch resolves in one place."""
