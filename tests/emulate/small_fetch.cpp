@@ -42,7 +42,8 @@ void lane_main()
     swapcontext(&g_lanes[g_current].ctx, &g_scheduler);
 }
 // Runs the workgroup blockIdx of n threads; at_barrier(k) is called when all have met for the k-th time, and with 0 before they start.
-void run_workgroup(uint32_t n, const std::function<void(uint32_t)> &at_barrier)
+// ballots: the ballots of any of its wavefronts count as well.
+void run_workgroup(uint32_t n, const std::function<void(uint32_t)> &at_barrier, bool ballots = false)
 {
     g_fibers = true;
     for (uint32_t i = 0; i < n; ++i) {
@@ -76,8 +77,10 @@ void run_workgroup(uint32_t n, const std::function<void(uint32_t)> &at_barrier)
                 done += l.state == DONE;
                 met += l.state == AT_BARRIER;
             }
-            if (there == 64)
+            if (there == 64) {
                 for (uint32_t i = w; i < w + 64; ++i) { g_lanes[i].mask = mask; g_lanes[i].state = READY; progress = true; }
+                if (ballots) at_barrier(++barriers);
+            }
         }
         if (done == n) return;
         if (met && met + done == n) {
@@ -258,7 +261,7 @@ int run_experts(const Experts *f)
             while (v + 1 < f->n_versions && when[v] <= met) v++;
             memcpy(dir.data(), f->versions + (uint64_t)v * f->n_experts, f->n_experts * 8);
         };
-        run_workgroup(WG, versions_at);
+        run_workgroup(WG, versions_at, true);
     }
     return (int)report.hbm;
 }

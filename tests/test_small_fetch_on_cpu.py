@@ -196,7 +196,8 @@ class Experts(ctypes.Structure):
                                                                                   (65, 50, 30, 65, 1, 1, 16), (100, 100, 40, 9, 24, 1, 8192 + 4112), (1, 1, 1, 1, 2, 1, 40960), (33, 33, 5, 33, 0, 1, 8208), (16, 16, 256, 16, 3, 1, 8192),
                                                                                   (128, 128, 129, 128, 5, 1, 2048)])
 def test_routed_experts_are_whole_when_entries_change_under_the_fetch(emulated, edit, n_experts, n_known, n_ids, n_staging, n_host, short, chunk):
-    """A grid of a tile each and shorter ones, ids that are out of range, experts that nobody has registered, less staging than experts."""
+    """A grid of a tile each and shorter ones, ids that are out of range, experts that nobody has registered, less staging than experts; entries
+    change between two experts of a reader's walk and between two tiles of a workgroup too."""
     rng = np.random.default_rng(n_experts + n_ids)
     ids = rng.integers(0, n_experts, n_ids).astype(np.int32)
     if n_ids > 4:
@@ -225,7 +226,10 @@ def test_routed_experts_are_whole_when_entries_change_under_the_fetch(emulated, 
     versions[:, n_known:] = np.uint64(0xFFFFFFFFFFFFFFFF)
     tiles = -(-chunk // 8192)
     wgs = max(1, int(short * len(staged) * tiles))
-    when = np.sort(rng.choice([0, NEVER], (n_host + 1 + wgs, len(tiers) - 1)), axis=1).astype(np.uint32)
+    # before a workgroup's first look, never, or at one of its meetings: four wavefronts have 32 for every 32 experts, then each one an expert
+    walk = 4 * 32 * (2 if n_experts <= 64 else 4) + np.arange(-4, 4 * len(staged) + 8)
+    times = np.concatenate([np.repeat([0, NEVER], len(walk) // 2), np.repeat([1, 2, 3, 5, 8], len(walk) // 8 + 1), walk])
+    when = np.sort(rng.choice(times, (n_host + 1 + wgs, len(tiers) - 1)), axis=1).astype(np.uint32)
     staging, ptr = aligned((n_staging, chunk)), np.full(n_experts, 7, dtype=np.uint64)
     staging[:] = 0xEE
     cnt, miss = np.zeros(16, dtype=np.uint32), np.zeros(n_experts, dtype=np.uint32)
