@@ -131,9 +131,9 @@ def test_fetch_sizes_that_jump_between_calls():
         eh.close(); eo.close()
 
 
-def test_block_table_large_enough_for_the_grouped_compaction():
-    """More than 262 144 table cells: the compaction takes its three-kernel form (workgroup totals are grouped before they
-    are added up).  Sparse rows, empty rows, one full row, invalid ids and a row that runs past the destination."""
+def test_block_table_of_several_rounds_a_segment():
+    """More than 262 144 table cells: the 256 segments of the resolve take more than a round of 1 024 each.  Sparse rows, empty rows,
+    one full row, invalid ids and a row that runs past the destination."""
     say("large block table")
     wl = W.kv_decode(seed=35, n_layers=2, n_seq=3, min_len=3000, max_len=6000, p_cache=0.6, n_steps=1)
     eo, eh = P.make_engines(wl)
@@ -141,7 +141,7 @@ def test_block_table_large_enough_for_the_grouped_compaction():
         ro, rh = S.KVRun(eo, wl), S.KVRun(eh, wl)
         g = W.rng(35, 9)
         n_seq, max_blocks = 41, 8192
-        assert n_seq * max_blocks > 1024 * 256
+        assert n_seq * max_blocks > 256 * 1024
         table = g.integers(0, wl.n_closed, size=(n_seq, max_blocks)).astype(np.int32)
         table[g.random(table.shape) < 0.001] = -7                                # unknown ids here and there
         table[5, 17] = wl.n_objects + 100

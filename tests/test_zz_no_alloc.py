@@ -77,7 +77,7 @@ def _compare_one(eh, eo, layer, args, cap, what, stream=None):
 @pytest.mark.parametrize("general", [False, True], ids=["one-kernel", "general"])
 def test_static_fetch_matches_fetch_kv_on_two_calls_in_a_row(general):
     say(f"fetch without allocation, general path {general}")
-    # 3 sequences of 900-2600 blocks: more than 4096 cells, so the first call takes resolve + compaction + two gathers
+    # 3 sequences of 900-2600 blocks: more than 4096 cells, so the first call takes resolve and gather
     wl = W.kv_decode(seed=61, n_layers=2, n_seq=3, min_len=16000, max_len=42000, p_cache=0.65, n_steps=4)
     eo, eh = P.make_engines(wl, poison=True, hip_kwargs=dict(general_fetch=general))
     try:
