@@ -895,11 +895,11 @@ def with_a_lost_object(chunk, n, layout=0, **kw):
     return h
 
 
-@pytest.mark.parametrize("n_seq,width,live,chunk,heads,most", [(256, 2048, 500224, 512, None, 0.55), (4, 4096, 12000, 32768, None, 0.12), (4, 4096, 12000, 32768, (8, 16), 0.12)])
+@pytest.mark.parametrize("n_seq,width,live,chunk,heads,most", [(256, 2048, 500224, 512, None, 0.55), (4, 4096, 12000, 32768, None, 0.16), (4, 4096, 12000, 32768, (8, 16), 0.16)])
 def test_a_fetch_of_lost_blocks_takes_a_fraction_of_the_fetch_that_finds_them(n_seq, width, live, chunk, heads, most):
     """It moves no payload; the misses are long lists that no transfer hides (500 224 blocks: 245 us found, 17 lost; 198 with the misses put
     together by 16 wavefronts, a load at a time), and so is the list of what HBM might serve (12 000 blocks: 250 us found, 12.5 lost; 53 with
-    a tile of it looked at at a time)."""
+    one tile of it looked at after the other: 0.21 of the time, 0.19 head-major; the limit leaves a slow host 39 us for two launches)."""
     n = 4096
     h = with_a_lost_object(chunk, n)
     lens = np.full(n_seq, live // n_seq, dtype=np.int32)
