@@ -149,7 +149,7 @@ typedef struct harvest_config {
     uint32_t gather_wg_per_cu;      /* tuning: cap the HBM-tier gather at this many workgroups per CU (they then loop
                                        over tiles, and take a request's planes one after the other); 0 = default, one workgroup
                                        per tile of gather_threads * 16 bytes.  One-kernel fetches have no such gather: an expert
-                                       fetch never takes that form once this or gather_threads is set, a KV fetch by
+                                       fetch never takes that form once this or gather_threads is set, a KV fetch goes by
                                        small_fetch_cells */
     uint32_t host_wgs;              /* tuning: 8 KiB of host-tier (PCIe) reads in flight per unit; 0 = default (24; the
                                        one-kernel form of small KV fetches 32) */
